@@ -11,11 +11,12 @@
 // n_sink and the last `window`, and the key tiles in between are never touched.
 //
 // Mapping to the machine
-//  * Work unit = (32 consecutive chunk rows, one query head).  A wavefront owns QB units, a
-//    workgroup 4 wavefronts; all units of a workgroup share one KV head, so a K/V tile staged in
-//    LDS is reused across the grouped-query heads, and with QB = 2 every K/V fragment read from
-//    LDS feeds two MFMAs.  Units are ordered token-block-major, head-minor, so the wavefronts of a
-//    workgroup see (almost) the same key range and only the last tiles need the causal mask.
+//  * Work unit = 32 consecutive packed rows of a KV head: its (token, head of the group) pairs,
+//    token-major.  A wavefront owns QB units, a workgroup 4 wavefronts; all units of a workgroup
+//    share one KV head, so a K/V tile staged in LDS is reused across the grouped-query heads, and
+//    with QB = 2 every K/V fragment read from LDS feeds two MFMAs.  Units ascend with the tokens,
+//    so the wavefronts of a workgroup see (almost) the same key range and only the last tiles need
+//    the causal mask; a chunk of C tokens fills ceil(C G / 32) units, whatever C is.
 //  * 64-key K/V tiles travel HBM/L2 -> LDS with global_load_lds_dwordx4 (no registers), several
 //    tiles ahead, into rings of NV+1 (K) and NV (V) slots; the XOR swizzle that makes the later
 //    LDS reads conflict-free is applied by choosing which 16-byte chunk each lane fetches.
@@ -46,7 +47,11 @@
 //  * Start and end of a workgroup are kept short (they are 4 % of a short-prefix launch): the ring is
 //    filled before the Q rows are fetched, all Q loads are in flight together, the first reference is
 //    set without touching the still-zero O, and the finished O^T is turned in the dead ring space so
-//    that every store instruction writes whole rows.
+//    that every store instruction writes whole rows.  Code a launch runs once is fetched at about 3 bytes
+//    per ns, so what is outside the main loop is kept small rather than unrolled, and a piece of the
+//    prefix stays in the main loop to its last tile.  Measured inside the kernel, entry to first tile:
+//    two-unit kernel 9.2 -> 7.0 us, one-unit kernel 4.9 -> 3.9 us; the last four tiles of a prefix piece
+//    8.0 -> 5.9 us (two-unit, against the copy of the loop with clamped rows that they took before).
 #include <type_traits>
 
 #include "kvfold_internal.h"
@@ -195,11 +200,11 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
 
   // ---- which workgroup am I (XCD-aware: a KV head stays on its XCDs, see logical_workgroup())
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
-  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p.n_q_heads / p.group, wgs_per_kvh);
+  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
   if (lid >= p.n_wgs) return;
-  const int g = lid / wgs_per_kvh;
+  const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int rem = lid - g * wgs_per_kvh;
-  const int split = rem / p.wgs_per_head;
+  const int split = (int)quot((unsigned)rem, p.by_wgs_per_head);
   // Later token blocks see more keys.  Default order: heaviest first (longest-processing-time
   // first over several rounds of workgroups).  With pair_order the grid is resident at once, two
   // workgroups per CU, dispatched in id order: the first half descends from the heaviest, the second
@@ -218,8 +223,9 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   const float sc = p.scale_log2e;
 
   // ---- my units
-  int tok[QB], head[QB], tokc[QB];
-  bool store_ok[QB], unit_valid[QB];
+  int tok[QB], head[QB];  // of this lane's row (the chunk's last row where the unit runs past it)
+  int unit_of[QB];        // the units themselves, wave-uniform
+  bool unit_valid[QB];
   int my_vis[QB];     // keys visible to this lane's query row
   int vis_first[QB];  // keys visible to the unit's first row (key blocks entirely below need no mask)
   int vis_last0 = 0;  // keys visible to the last row of unit 0: tiles entirely beyond are dead for it
@@ -239,22 +245,22 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     const int u = !pair_units ? n * QB + qb : (qb == 0 ? n : p.units_per_head - 1 - n);
     const bool valid = !pair_units ? u < p.units_per_head : (qb == 0 ? 2 * n <= p.units_per_head - 1 : 2 * n < p.units_per_head - 1);
     const int uc = u < 0 ? 0 : (u < p.units_per_head ? u : p.units_per_head - 1);
-    const int tb = uc / G, hg = uc - tb * G;
-    head[qb] = g * G + hg;
-    tok[qb] = tb * kRowsPerUnit + m;
-    tokc[qb] = tok[qb] < C ? tok[qb] : C - 1;
+    const UnitRows ur(uc, p);
+    const bool inside = ur.tok(m) < C;
+    tok[qb] = inside ? ur.tok(m) : C - 1;
+    head[qb] = g * G + (inside ? ur.head(m) : G - 1);
+    unit_of[qb] = uc;
     unit_valid[qb] = valid;
-    store_ok[qb] = valid && (tok[qb] < C);
     {
-      const int last = tb * kRowsPerUnit + kRowsPerUnit - 1;
-      const int vis_last = (int)p.len_prev + (last < C ? last : C - 1) + 1;
+      const int vis_last = (int)p.len_prev + unit_last_token(uc, p.by_group, C) + 1;
       if (qb == 0) vis_last0 = vis_last;
       if (win && vis_last - p.window > lb_last) lb_last = vis_last - p.window;
     }
-    my_vis[qb] = (int)p.len_prev + tokc[qb] + 1;
-    vis_first[qb] = (int)p.len_prev + tb * kRowsPerUnit + 1;
+    my_vis[qb] = (int)p.len_prev + tok[qb] + 1;
+    vis_first[qb] = (int)p.len_prev + ur.tok0 + 1;
   }
-  const int vis_min = vis_first[0];  // units are ordered by token block, so unit 0 has the nearest horizon
+  const bool idle = !unit_valid[0];  // (then the second unit does not exist either)
+  const int vis_min = vis_first[0];  // units ascend with the tokens, so unit 0 has the nearest horizon
 
   // ---- tile range of this workgroup / split
   int nkeys_wg;
@@ -263,15 +269,13 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     int ulast = pair_units ? p.units_per_head - 1 - ug * kUnitsPerWg : ug * UPW + UPW - 1;
     if (ulast > p.units_per_head - 1) ulast = p.units_per_head - 1;
     if (ulast < 0) ulast = 0;
-    int row_hi = (ulast / G) * kRowsPerUnit + kRowsPerUnit - 1;
-    if (row_hi > C - 1) row_hi = C - 1;
-    nkeys_wg = (int)p.len_prev + row_hi + 1;
+    nkeys_wg = (int)p.len_prev + unit_last_token(ulast, p.by_group, C) + 1;
   }
   // logical tiles 0 .. ntiles-1 of this workgroup; under a window the tiles between the sinks and the window
   // are left out: logical tile t is physical tile t + (t >= ns_t ? skip : 0)
   TileMap tm;
   if (win) {
-    const RowRange rr = workgroup_rows(ug, UPW, p.units_per_head, G, C);
+    const RowRange rr = workgroup_rows(ug, UPW, p.units_per_head, p.by_group, C);
     tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, n_sink, p.window);
   } else {
     tm.ns_t = 0;
@@ -288,6 +292,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   // this workgroup's piece of them, and what its DMA may touch (shared with the host-side model of this walk)
   const KeyRange kr = key_range(tm, split, p.tiles_per_split, p.len_prev, C, p.k_new != nullptr);
   const int t_begin = kr.t_begin, t_end = kr.t_end;
+  const int t_new = kr.t_straddle >= 0 ? kr.t_straddle : kr.t_new;  // first physical tile with rows of the chunk
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
   const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
@@ -299,13 +304,16 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);  // bytes from one token's row to the next
   const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
   const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
-  // This workgroup's share of the copy: rows [r0, r1) of K and of V, 16 bytes per lane and access.  The first
-  // kCopyFirst vectors per lane are only loaded here and stored once the ring refill and the Q loads are on
-  // their way, so that their latency is not paid on its own; whatever is left (few workgroups, long chunks)
-  // is copied on the spot.
-  constexpr int kCopyFirst = 8;
-  uintx4 copy_v[kCopyFirst];
+  // This workgroup's share of the copy: rows [r0, r1) of K and of V, 16 bytes per lane and access, loaded once the
+  // ring refill and the Q loads are on their way and stored while the Q rows are scaled, so that its latency is not
+  // paid on its own.
+  constexpr int kCopyBatch = 4;
   int copy_r0 = 0, copy_nvec = 0;
+  if (fused) {
+    copy_r0 = rem * p.copy_rows;
+    const int r1 = copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C;
+    copy_nvec = (r1 > copy_r0 ? r1 - copy_r0 : 0) * CH;  // 16-byte vectors per tensor
+  }
   auto copy_src = [&](int idx) __attribute__((always_inline)) -> const uintx4* {
     const bool is_v = idx >= copy_nvec;
     const int e = is_v ? idx - copy_nvec : idx, r = copy_r0 + e / CH, c = e % CH;
@@ -316,97 +324,99 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     const int e = is_v ? idx - copy_nvec : idx, r = copy_r0 + e / CH, c = e % CH;
     return reinterpret_cast<uintx4*>(const_cast<unsigned char*>(is_v ? vbase : kbase) + (p.len_prev + r) * ROWB + c * 16);
   };
-  if (fused) {
-    const int per = (C + wgs_per_kvh - 1) / wgs_per_kvh;  // rows of this workgroup
-    const int r1 = rem * per + per < C ? rem * per + per : C;
-    copy_r0 = rem * per;
-    copy_nvec = (r1 > copy_r0 ? r1 - copy_r0 : 0) * CH;  // 16-byte vectors per tensor
+  uintx4 copy_v[kCopyBatch] = {};
+  auto copy_load = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kCopyFirst; ++u)
-      if (tid + u * 256 < 2 * copy_nvec) copy_v[u] = *copy_src(tid + u * 256);
-    for (int idx = tid + kCopyFirst * 256; idx < 2 * copy_nvec; idx += 256) __builtin_nontemporal_store(*copy_src(idx), copy_dst(idx));
-  }
+    for (int u = 0; u < kCopyBatch; ++u)
+      if (i0 + u * 256 < 2 * copy_nvec && tid + i0 + u * 256 < 2 * copy_nvec) copy_v[u] = *copy_src(tid + i0 + u * 256);
+  };
+  auto copy_store = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kCopyBatch; ++u)
+      if (i0 + u * 256 < 2 * copy_nvec && tid + i0 + u * 256 < 2 * copy_nvec)
+        __builtin_nontemporal_store(copy_v[u], copy_dst(tid + i0 + u * 256));
+    // the loads end here on every path: one that the compiler took to be pending would be waited for in the main loop,
+    // together with the whole ring
+#pragma unroll
+    for (int u = 0; u < kCopyBatch; ++u) asm volatile("" ::"v"(copy_v[u]));
+  };
 
   // ---- DMA addressing: wavefront w moves slabs w, w+4, ...; lane l lands at chunk (l % CH) of row
-  // slab*RPS + l / CH and therefore fetches the chunk that the swizzle maps there.  Offsets from
-  // the head's base are 32-bit (the host checks capacity * row bytes < 2^32).
+  // slab*RPS + l / CH and therefore fetches the chunk that the swizzle maps there.  Lane offsets are 32-bit (the host
+  // checks capacity * row bytes < 2^32, and the fused append's chunk the same).
   const int dma_row0 = w * RPS + l / CH;  // + i * 4 * RPS for slab i
   const unsigned dma_kc = (unsigned)(((l % CH) ^ (dma_row0 % KSW)) * 16);
   const unsigned dma_vc = (unsigned)(((l % CH) ^ ((dma_row0 & 3) * VSW)) * 16);
-  const unsigned dma_koff = (unsigned)dma_row0 * ROWB + dma_kc;  // lane part of an unclamped offset
+  const unsigned dma_koff = (unsigned)dma_row0 * ROWB + dma_kc;  // lane part of an offset into the cache
   const unsigned dma_voff = (unsigned)dma_row0 * ROWB + dma_vc;
-  // slab i of tile t of K (is_v = false) or V; CLAMP redirects rows past the cache end, or past this
-  // workgroup's key range (the ring runs NV + 1 tiles ahead and knows no end), to the last row inside:
-  // they are never used, and so are never fetched from HBM either
-  // (kr.row_lim).  Fused append: tiles from kr.t_new on lie in the chunk -- unless this workgroup's key range ends
-  // before the chunk begins: then every row past the range is redirected to row_lim, a cache row, whatever its tile.
-  const int t_new = kr.t_straddle >= 0 ? kr.t_straddle : kr.t_new;  // first physical tile with rows of the chunk
-  auto issue_slab = [&](bool is_v, int t_log, int slot, int i, auto clamp_tag, unsigned extra = 0) __attribute__((always_inline)) {
-    constexpr bool CLAMP = decltype(clamp_tag)::value;
-    const int t = tphys(t_log);
+  const int t_last = t_end - 1;
+  // Slab i of a tile, in the main loop over plain cache tiles (64 rows that are all there).  The ring runs NV + 1 tiles
+  // ahead and knows no end: past the piece its last tile is fetched again (an L2 hit), so that pieces of the prefix
+  // never leave the main loop.
+  auto issue_slab = [&](bool is_v, int t_log, int slot, int i) __attribute__((always_inline)) {
+    const int t = tphys(t_log < t_last ? t_log : t_last);
     const unsigned lds = lds0 + (unsigned)(((is_v ? NK : 0) + slot) * TILEB + (w + 4 * i) * 1024);
-    unsigned off;
-    if (CLAMP) {
-      int row0_here = dma_row0;  // opaque copy: what is derived from it is computed here, not once ahead of all
-      asm volatile("" : "+v"(row0_here));  // loops and then held in registers through the main loop
-      const DmaRow src = dma_row(kr, t, row0_here + i * 4 * RPS);
-      if (__builtin_expect(t != kr.t_straddle, 1)) {
-        // (wave-uniform choice, scalar selects) a tile of the chunk itself comes from the rows as handed in
-        const bool nw = t >= kr.t_new;
-        const unsigned char* base = nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase);
-        const unsigned stride = nw ? new_stride : (unsigned)ROWB;
-        off = src.row * stride + (is_v ? dma_vc : dma_kc) + extra;
+    const unsigned off = (is_v ? dma_voff : dma_koff) + (unsigned)(t * BN + i * 4 * RPS) * ROWB;
+    dma16(is_v ? vbase : kbase, off, lds);
+  };
+  // A whole tile, plain or not, outside the slot schedule; nothing past the piece.  A plain tile -- 64 rows that all
+  // exist and lie on one side of the old cache's end -- has a uniform base that moves from slab to slab.  Else rows
+  // past the piece's last row are redirected to that row (never used, and so never fetched from HBM either).  The one
+  // tile with rows on both sides of the cache's end (cache length not a multiple of the tile): each lane fetches from
+  // its own side, two DMA instructions with complementary lanes fill a slab.
+  auto issue_tile = [&](bool is_v, int t_log, int slot) __attribute__((always_inline)) {
+    if (t_log >= t_end) return;
+    const int t = tphys(t_log);
+    unsigned lds = lds0 + (unsigned)(((is_v ? NK : 0) + slot) * TILEB + w * 1024);
+    if (__builtin_expect(t != kr.t_straddle && (unsigned)(t * BN + BN - 1) <= kr.row_lim, 1)) {
+      const bool nw = t >= kr.t_new;  // rows of the chunk as handed in (fused append)
+      const unsigned stride = nw ? new_stride : (unsigned)ROWB;
+      const unsigned row = (unsigned)(t * BN) - (nw ? (unsigned)p.len_prev : 0u);
+      const unsigned char* base = (nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase)) + (uint64_t)(row * stride);
+      unsigned off = (unsigned)dma_row0 * stride + (is_v ? dma_vc : dma_kc);
+#pragma unroll
+      for (int i = 0; i < SLABS; ++i) {
         dma16(base, off, lds);
-      } else if (src.from_chunk) {
-        // the one tile with rows on both sides of the cache's end (cache length not a multiple of the tile): each
-        // lane fetches from its own side, two DMA instructions with complementary lanes fill the slab
-        dma16(is_v ? vnew : knew, src.row * new_stride + (is_v ? dma_vc : dma_kc) + extra, lds);
-      } else {
-        dma16(is_v ? vbase : kbase, src.row * (unsigned)ROWB + (is_v ? dma_vc : dma_kc) + extra, lds);
+        off += stride * (unsigned)(4 * RPS);
+        lds += 4096u;
       }
     } else {
-      off = (is_v ? dma_voff : dma_koff) + (unsigned)(t * BN + i * 4 * RPS) * ROWB;
-      dma16(is_v ? vbase : kbase, off, lds);
+#pragma unroll 1
+      for (int i = 0; i < SLABS; ++i) {
+        const DmaRow src = dma_row(kr, t, dma_row0 + i * 4 * RPS);
+        if (src.from_chunk)
+          dma16(is_v ? vnew : knew, src.row * new_stride + (is_v ? dma_vc : dma_kc), lds);
+        else
+          dma16(is_v ? vbase : kbase, src.row * (unsigned)ROWB + (is_v ? dma_vc : dma_kc), lds);
+        lds += 4096u;
+      }
     }
-  };
-  auto issue_k = [&](int t, unsigned extra) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < SLABS; ++i) issue_slab(false, t, t % NK, i, std::true_type{}, extra);
-  };
-  auto issue_v = [&](int t, unsigned extra) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < SLABS; ++i) issue_slab(true, t, t % NV, i, std::true_type{}, extra);
   };
 
   // ---- the ring is filled first (only addresses are needed), then the Q fragments are fetched: the two
   // latencies overlap.  Q, pre-multiplied by scale*log2(e), stays in registers for the whole kernel.
-  auto prefill = [&](unsigned extra) __attribute__((always_inline)) {
+  // Code that a launch runs once is fetched at about 3 bytes per ns (measured: an unrolled fill of 6 KB took 2.3 us of
+  // a workgroup's start), so the fill is a loop.
+  auto prefill = [&]() __attribute__((always_inline)) {
     // Steady state at the top of the even step of tile t: K[t], K[t+1], V[t] are in LDS and visible, the
-    // groups {K[t+1+j], V[t+j]}, j = 1 .. NV-1, are in flight.
-    issue_k(t_begin, extra);
-    issue_k(t_begin + 1, extra);
-    issue_v(t_begin, extra);
-#pragma unroll
-    for (int j = 1; j < NV; ++j) {
-      issue_k(t_begin + 1 + j, extra);
-      issue_v(t_begin + j, extra);
+    // groups {K[t+1+j], V[t+j]}, j = 1 .. NV-1, are in flight.  Tile t_begin + j takes ring slot j.
+#pragma unroll 1
+    for (int j = 0; j <= NV; ++j) {
+      issue_tile(false, t_begin + j, j);
+      if (j > 0) issue_tile(true, t_begin + j - 1, j - 1);
     }
   };
-  if (t_begin < t_end) prefill(0u);
+  if (t_begin < t_end) prefill();
   bf16x8 qf[QB][KS];
   {
     bf16x8 raw[QB][KS];  // every load in flight before the first is waited for
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + ((int64_t)tokc[qb] * Hq + head[qb]) * D;
+      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + ((int64_t)tok[qb] * Hq + head[qb]) * D;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) raw[qb][ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16 + hi * 8);
     }
-    if (fused) {
-#pragma unroll
-      for (int u = 0; u < kCopyFirst; ++u)
-        if (tid + u * 256 < 2 * copy_nvec) __builtin_nontemporal_store(copy_v[u], copy_dst(tid + u * 256));
-    }
+    copy_load(0);
     if (p.rope_cos) {
       // Rotary embedding at the row's absolute position (Sec. 2), half-split pairs (j, j + D/2), fp32 with
       // the sine product rounded first, result rounded to bf16: bit for bit what a caller that rotates q
@@ -415,8 +425,8 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
         for (int ks = 0; ks < KS / 2; ++ks) {
-          const float* cs = p.rope_cos + (int64_t)tokc[qb] * (D / 2) + ks * 16 + hi * 8;
-          const float* sn = p.rope_sin + (int64_t)tokc[qb] * (D / 2) + ks * 16 + hi * 8;
+          const float* cs = p.rope_cos + (int64_t)tok[qb] * (D / 2) + ks * 16 + hi * 8;
+          const float* sn = p.rope_sin + (int64_t)tok[qb] * (D / 2) + ks * 16 + hi * 8;
           const bf16x8 lo = raw[qb][ks], up = raw[qb][ks + KS / 2];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
@@ -437,6 +447,12 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       }
   }
 
+  copy_store(0);
+  for (int i0 = kCopyBatch * 256; i0 < 2 * copy_nvec; i0 += kCopyBatch * 256) {
+    copy_load(i0);
+    copy_store(i0);
+  }
+
   // ---- LDS read offsets (per lane) of the tile currently being read, ring slot included; moved
   // from slot to slot once per tile
   // K fragment (A operand of S^T): row kb*32+m, chunk ks*2+hi, swizzled by row % KSW = m % KSW
@@ -450,8 +466,8 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   float m_run[QB], l_run[QB];
   int overflowed = 0;   // wave-uniform: a row sum left the range the sum-driven rescale can repair
   auto reset_state = [&]() __attribute__((always_inline)) {
-    kslot = t_begin % NK;
-    vslot = t_begin % NV;
+    kslot = 0;
+    vslot = 0;
     // derived from an opaque copy of the lane id, so that nothing computed here is kept in registers
     // across the main loop for the sake of a restart that almost never happens
     int l2 = l;
@@ -691,12 +707,15 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   // tiles of halves hh+1 / hh.  ODD steps (second half of a tile) end with the workgroup barrier
   // and the ring refill for the tiles after next; MASKED selects the variant for halves hh+1 that
   // reach past the causal horizon, and for every half once a row sum has overflowed (mask, then the
-  // exact row max, after the matrix work); CLAMP the variant whose refill may run past the end of
-  // the cache.  q0_tag = 1 (two-unit kernel only): unit 0 has passed its causal horizon for good and
-  // only unit 1 is worked on, with the schedule of a one-unit step; a masked step of both units that
-  // is followed by such a step (next_unit1_only) leaves the early events in that step's numbering.
-  auto step = [&](floatx16 (&s_cur)[QB], floatx16 (&s_next)[QB], int hh, auto odd_tag, auto masked_tag,
-                  auto clamp_tag, auto q0_tag, bool next_unit1_only = false) __attribute__((always_inline)) {
+  // exact row max, after the matrix work); PLAIN the variant whose refill consists of cache tiles only, slab by slab in
+  // the slot schedule, where the others refill whole tiles after the matrix work.  q0_tag = 1 (two-unit kernel only):
+  // unit 0 has passed its causal horizon for good and only unit 1 is worked on, with the schedule of a one-unit step; a
+  // masked step of both units that is followed by such a step (next_unit1_only) leaves the early events in that step's
+  // numbering.  Past the piece's last tile the ring need not hold keys: the last step forms an S^T of stale LDS
+  // contents, on which nothing may be decided.
+  auto step = [&](floatx16 (&s_cur)[QB], floatx16 (&s_next)[QB], int hh, auto odd_tag, auto masked_tag, auto plain_tag,
+                  auto q0_tag, bool next_unit1_only = false) __attribute__((always_inline)) {
+    constexpr bool PLAIN = decltype(plain_tag)::value;
     constexpr bool ODD = decltype(odd_tag)::value;
     constexpr bool MASKED = decltype(masked_tag)::value;
     constexpr int Q0 = decltype(q0_tag)::value, QA = QB - Q0;
@@ -716,6 +735,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     bool need_rescale = false;
     int sum_flag = 0;      // per lane: a row sum of this half passed 2^20 (or is not a number)
     int kslot_prev = 0, vslot_prev = 0;
+    const bool more = (SUM_MODE && PLAIN) || hh + 1 < 2 * t_end;  // half hh + 1 is there (or nothing is decided on it)
 
     wait_lds<0>();  // kg[0] (fetched at the end of the previous step) has landed
 #pragma unroll
@@ -727,7 +747,10 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (ODD && i == EW) {
         // Every read of K[t] and V[t] by this wave has returned.  K[t+2] and V[t+1] were issued
         // NV-1 tiles ago: they are the oldest group in flight.
-        wait_vm<(NV - 2) * LPG>();
+        if (PLAIN || (NV > 2 && t + NV < t_end))
+          wait_vm<(NV - 2) * LPG>();
+        else
+          wait_vm<0>();  // the group issued last is not whole
         __builtin_amdgcn_s_barrier();  // ... and this holds for every wave of the workgroup
         kslot_prev = kslot == 0 ? NK - 1 : kslot - 1;  // K[t]'s slot (kslot already names K[t+1]) takes K[t+1+NV]
         vslot_prev = vslot;                            // V[t]'s slot takes V[t+NV]
@@ -797,13 +820,15 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
         }
       }
       if (!SUM_MODE && !MASKED && i >= RM1 && i < RM1 + QA) dm[Q0 + i - RM1] = pair_max(mx[Q0 + i - RM1]);
-      if (!SUM_MODE && !MASKED && i == RM1 + QA) need_rescale = rescale_need(dm, Q0);
+      if (!SUM_MODE && !MASKED && i == RM1 + QA) need_rescale = rescale_need(dm, Q0) && more;
       // ring refill and the V address of the next tile (odd steps, after the barrier)
       if (ODD && i >= EW) {
+        if (PLAIN) {
 #pragma unroll
-        for (int d = ((i - EW) * LPG) / (M - EW); d < ((i - EW + 1) * LPG) / (M - EW); ++d) {
-          if (d < SLABS) issue_slab(false, t + 1 + NV, kslot_prev, d, clamp_tag);
-          else issue_slab(true, t + NV, vslot_prev, d - SLABS, clamp_tag);
+          for (int d = ((i - EW) * LPG) / (M - EW); d < ((i - EW + 1) * LPG) / (M - EW); ++d) {
+            if (d < SLABS) issue_slab(false, t + 1 + NV, kslot_prev, d);
+            else issue_slab(true, t + NV, vslot_prev, d - SLABS);
+          }
         }
         if (i == M - 1) {
           const int vn = vslot + 1 == NV ? 0 : vslot + 1;
@@ -824,11 +849,15 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (__builtin_expect(__any(sum_flag), 0)) {
 #pragma unroll
         for (int qb = Q0; qb < QB; ++qb) mfma_settle_v(s_next[qb]);
-        rescale_from_sum(lsum, s_next, Q0);
+        rescale_from_sum(lsum, s_next, Q0);  // (past the last half s_next is stale, and merely moved)
         if (!MASKED) early_events(s_next, q0_tag);  // they were formed against the old reference: once more
       }
     }
-    if (MASKED) {
+    if (!PLAIN && ODD) {
+      issue_tile(false, t + 1 + NV, kslot_prev);
+      issue_tile(true, t + NV, vslot_prev);
+    }
+    if (MASKED && more) {
 #pragma unroll
       for (int qb = Q0; qb < QB; ++qb) mfma_settle_v(s_next[qb]);
       mask_half(s_next, hh + 1, Q0);
@@ -857,12 +886,8 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       // (tile bounds are worked out on physical tiles, i.e. on keys, and then turned into logical tile numbers)
       int t_fast = tlogical((vis_min - 96) / BN + 1);  // first tile that is not fast (vis_min >= 1)
       if (vis_min < 96 || exact) t_fast = 0;
+      if (!exact && tphys(t_end - 1) * BN + BN <= vis_min) t_fast = t_end;  // the piece ends below every horizon
       if (t_fast > t_end) t_fast = t_end;
-      // ... and tiles whose refill (tile t + 1 + NV) lies entirely inside the cache and the key range need no row
-      // clamp (inside the cache proper when the append is fused)
-      int t_nc = tlogical((Lm1 + 1) / BN < t_new ? (Lm1 + 1) / BN : t_new) - NV - 1;
-      if (t_nc > t_end - NV - 1) t_nc = t_end - NV - 1;
-      if (t_nc > t_fast) t_nc = t_fast;
       // Under a window the first tiles (the sinks, and the tiles that begin below the window of the wavefront's
       // last row) are masked on the left: tiles [t_begin, t_lead) take the masked variant
       int t_lead = win ? tlogical((lb_last + BN - 1) / BN) : 0;
@@ -875,17 +900,34 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (QB == 1 || exact || t_dead > t_end) t_dead = t_end;
       int t_fast1 = tlogical((vis_first[QB - 1] - 96) / BN + 1);
       if (vis_first[QB - 1] < 96 || exact) t_fast1 = 0;
-      if (t_fast1 < t_dead) t_fast1 = t_dead;
       if (t_fast1 > t_end) t_fast1 = t_end;
+      // ... and tiles whose refill (tile t + 1 + NV) is a plain tile of the cache take the main loop (every tile of a
+      // piece that holds nothing else).
+      int t_plain = tlogical((Lm1 + 1) / BN < t_new ? (Lm1 + 1) / BN : t_new);
+      t_plain = t_plain >= t_end ? t_end : t_plain - NV - 1;
+      if (t_plain > t_fast) t_plain = t_fast;
       // Prologue.  The first pass finds the ring filled ahead of the Q loads; a second pass fills it again.
-      if (exact) {
-        unsigned again_zero = 0;  // opaque zero: keeps these addresses from being computed once and held in
-        asm volatile("" : "+v"(again_zero));  // registers across the main loop for the sake of a second pass
-        prefill(again_zero);
-      }
-      wait_vm<(NV - 1) * LPG>();
+      if (exact) prefill();
+      if (t_begin + NV < t_end)  // every group of the fill is whole
+        wait_vm<(NV - 1) * LPG>();
+      else
+        wait_vm<0>();
       __builtin_amdgcn_s_barrier();
-      {
+      if (idle) {
+        // no rows of its own: this wavefront only moves its share of the tiles (the LDS bandwidth and the power of
+        // computing on rows that do not exist would be taken from the wavefronts that have some)
+        for (int t = t_begin, ks = 0, vs = 0; t < t_end; ++t) {
+          if (NV > 2 && t + NV < t_end)
+            wait_vm<(NV - 2) * LPG>();
+          else
+            wait_vm<0>();
+          __builtin_amdgcn_s_barrier();
+          issue_tile(false, t + 1 + NV, ks);
+          issue_tile(true, t + NV, vs);
+          ks = ks + 1 == NK ? 0 : ks + 1;
+          vs = vs + 1 == NV ? 0 : vs + 1;
+        }
+      } else {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) kg[ks / GK][ks % GK] = k_frag(ks, 0);
         wait_lds<0>();
@@ -912,35 +954,37 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
         // first K batch of the first step: second half of tile t_begin
 #pragma unroll
         for (int j = 0; j < GK; ++j) kg[0][j] = k_frag(j, HALFB);
-      }
-      int t = t_begin;
-      constexpr std::integral_constant<int, 0> both{};
-      for (; t < t_lead; ++t) {
-        step(sA, sB, 2 * t, std::false_type{}, std::true_type{}, std::true_type{}, both);
-        step(sB, sA, 2 * t + 1, std::true_type{}, std::true_type{}, std::true_type{}, both, t + 1 == t_dead && t_dead < t_end);
-      }
-      for (; t < t_nc; ++t) {
-        step(sA, sB, 2 * t, std::false_type{}, std::false_type{}, std::false_type{}, both);
-        step(sB, sA, 2 * t + 1, std::true_type{}, std::false_type{}, std::false_type{}, both);
-      }
-      for (; t < t_fast; ++t) {
-        step(sA, sB, 2 * t, std::false_type{}, std::false_type{}, std::true_type{}, both);
-        step(sB, sA, 2 * t + 1, std::true_type{}, std::false_type{}, std::true_type{}, both);
-      }
-      for (; t < t_dead; ++t) {
-        step(sA, sB, 2 * t, std::false_type{}, std::true_type{}, std::true_type{}, both);
-        step(sB, sA, 2 * t + 1, std::true_type{}, std::true_type{}, std::true_type{}, both, t + 1 == t_dead && t_dead < t_end);
-      }
-      if constexpr (QB == 2) {
-        // unit 0 is done for good (every further key is beyond its last row): unit 1 alone
-        constexpr std::integral_constant<int, 1> second{};
-        for (; t < t_fast1; ++t) {
-          step(sA, sB, 2 * t, std::false_type{}, std::false_type{}, std::true_type{}, second);
-          step(sB, sA, 2 * t + 1, std::true_type{}, std::false_type{}, std::true_type{}, second);
+        constexpr std::integral_constant<int, 0> both{};
+        constexpr std::false_type even{}, unmasked{}, mixed{};
+        constexpr std::true_type odd{}, masked{}, plain{};
+        int t = t_begin;
+        for (; t < t_lead; ++t) {
+          step(sA, sB, 2 * t, even, masked, mixed, both);
+          step(sB, sA, 2 * t + 1, odd, masked, mixed, both, t + 1 == t_dead && t_dead < t_end);
         }
-        for (; t < t_end; ++t) {
-          step(sA, sB, 2 * t, std::false_type{}, std::true_type{}, std::true_type{}, second);
-          step(sB, sA, 2 * t + 1, std::true_type{}, std::true_type{}, std::true_type{}, second);
+        for (; t < t_plain; ++t) {
+          step(sA, sB, 2 * t, even, unmasked, plain, both);
+          step(sB, sA, 2 * t + 1, odd, unmasked, plain, both);
+        }
+        for (; t < t_fast; ++t) {
+          step(sA, sB, 2 * t, even, unmasked, mixed, both);
+          step(sB, sA, 2 * t + 1, odd, unmasked, mixed, both);
+        }
+        for (; t < t_dead; ++t) {
+          step(sA, sB, 2 * t, even, masked, mixed, both);
+          step(sB, sA, 2 * t + 1, odd, masked, mixed, both, t + 1 == t_dead && t_dead < t_end);
+        }
+        if constexpr (QB == 2) {
+          // unit 0 is done for good (every further key is beyond its last row): unit 1 alone
+          constexpr std::integral_constant<int, 1> second{};
+          for (; t < t_fast1; ++t) {
+            step(sA, sB, 2 * t, even, unmasked, mixed, second);
+            step(sB, sA, 2 * t + 1, odd, unmasked, mixed, second);
+          }
+          for (; t < t_end; ++t) {
+            step(sA, sB, 2 * t, even, masked, mixed, second);
+            step(sB, sA, 2 * t + 1, odd, masked, mixed, second);
+          }
         }
       }
       wait_vm<0>();  // nothing of ours may still be writing LDS when the workgroup retires or starts over
@@ -973,13 +1017,19 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   // instruction; turned in LDS, every store instruction writes whole rows, 16 bytes per lane.
   __builtin_amdgcn_s_barrier();  // every wavefront of the workgroup is through with the rings
   const int64_t n_rows = (int64_t)C * Hq;
+  // (the lane's place and its row's token and head are formed anew: nothing is held for them through the main loop)
+  const int le = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), hie = le >> 5, me = le & 31;
   constexpr int OROWF = D * 4 + 16;  // padded LDS row: fp32 partials
   constexpr int OROWH = D * 2 + 16;  // padded LDS row: bf16 output
   const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROWF);  // this wavefront's staging area, reused by its units
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const float l_tot = pair_sum(l_run[qb]);
-    const int tok0 = tok[qb] - m;  // first token of the unit
+    const UnitRows ur(unit_of[qb], p);
+    const int tok_e = ur.tok(me), head_e = g * G + ur.head(me);
+    const bool store_row = unit_valid[qb] && hie == 0 && tok_e < C;
+    // offset of row r of the unit in [token][query head] rows
+    auto out_row = [&](int r) __attribute__((always_inline)) -> int64_t { return (int64_t)ur.tok(r) * Hq + g * G + ur.head(r); };
     if (p.n_splits == 1) {
       const float inv = 1.f / l_tot;
 #pragma unroll
@@ -989,18 +1039,18 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[qb][db][rg * 4 + e] * inv);
-          *LDS_PTR(bf16x4, obase + (unsigned)(m * OROWH + (db * 32 + 8 * rg + 4 * hi) * 2)) = v;
+          *LDS_PTR(bf16x4, obase + (unsigned)(me * OROWH + (db * 32 + 8 * rg + 4 * hie) * 2)) = v;
         }
-      if (p.lse && hi == 0 && store_ok[qb])
-        p.lse[(int64_t)head[qb] * C + tok[qb]] = (m_run[qb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
+      if (p.lse && store_row)
+        p.lse[(int64_t)head_e * C + tok_e] = (m_run[qb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
       constexpr int CPR = D / 8;        // 16-byte chunks per row
       constexpr int RPI = 64 / CPR;     // rows per store instruction
 #pragma unroll
       for (int i = 0; i < kRowsPerUnit / RPI; ++i) {
-        const int r = i * RPI + l / CPR, c = l % CPR;
+        const int r = i * RPI + le / CPR, c = le % CPR;
         const uintx4 x = *LDS_PTR(const uintx4, obase + (unsigned)(r * OROWH + c * 16));
-        if (unit_valid[qb] && tok0 + r < C)
-          __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(reinterpret_cast<__bf16*>(p.out) + ((int64_t)(tok0 + r) * Hq + head[qb]) * D + c * 8));
+        if (unit_valid[qb] && ur.tok(r) < C)
+          __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(reinterpret_cast<__bf16*>(p.out) + out_row(r) * D + c * 8));
       }
     } else {
 #pragma unroll
@@ -1010,20 +1060,20 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
           floatx4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = o[qb][db][rg * 4 + e];
-          *LDS_PTR(floatx4, obase + (unsigned)(m * OROWF + (db * 32 + 8 * rg + 4 * hi) * 4)) = v;
+          *LDS_PTR(floatx4, obase + (unsigned)(me * OROWF + (db * 32 + 8 * rg + 4 * hie) * 4)) = v;
         }
-      if (hi == 0 && store_ok[qb]) {
+      if (store_row) {
         float2 ml = make_float2(m_run[qb], l_tot);
-        *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + (int64_t)tok[qb] * Hq + head[qb]) * 2) = ml;
+        *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + (int64_t)tok_e * Hq + head_e) * 2) = ml;
       }
       constexpr int CPR = D / 4;        // 16-byte chunks per row
       constexpr int RPI = 64 / CPR;     // rows per store instruction
 #pragma unroll
       for (int i = 0; i < kRowsPerUnit / RPI; ++i) {
-        const int r = i * RPI + l / CPR, c = l % CPR;
+        const int r = i * RPI + le / CPR, c = le % CPR;
         const floatx4 x = *LDS_PTR(const floatx4, obase + (unsigned)(r * OROWF + c * 16));
-        if (unit_valid[qb] && tok0 + r < C)
-          __builtin_nontemporal_store(x, reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + (int64_t)(tok0 + r) * Hq + head[qb]) * D + c * 4));
+        if (unit_valid[qb] && ur.tok(r) < C)
+          __builtin_nontemporal_store(x, reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + out_row(r)) * D + c * 4));
       }
     }
   }

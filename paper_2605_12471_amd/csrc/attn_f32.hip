@@ -1,6 +1,6 @@
 // Chunk-prefix attention of the fold step in fp32 throughout (the precision-ablation mode of the
 // paper's Sec. 3; here the 1e-5 correctness mode).  Same decomposition as the bf16 kernel: a
-// wavefront owns one (32 chunk rows, one query head) unit, 4 wavefronts of one KV head share
+// wavefront owns one unit of 32 packed (token, head of the group) rows, 4 wavefronts of one KV head share
 // each 64-key K/V tile through LDS, logits are formed transposed (S^T = K Q^T, keys as MFMA rows)
 // with v_mfma_f32_32x32x2_f32 so a lane holds 32 logits of one query, and the accumulator layout
 // of S^T feeds O^T = V^T P^T directly: register r of S^T pairs the two keys 8*(r/4) + r%4 and
@@ -34,11 +34,11 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
   unsigned char* sV = smem + BN * ROWB;
 
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
-  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p.n_q_heads / p.group, wgs_per_kvh);
+  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
   if (lid >= p.n_wgs) return;
-  const int g = lid / wgs_per_kvh;
+  const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int rem = lid - g * wgs_per_kvh;
-  const int split = rem / p.wgs_per_head;
+  const int split = (int)quot((unsigned)rem, p.by_wgs_per_head);
   // Later token blocks see more keys.  Default order: heaviest first (longest-processing-time
   // first over several rounds of workgroups).  With pair_order the grid is resident at once, two
   // workgroups per CU, dispatched in id order: the first half descends from the heaviest, the second
@@ -56,26 +56,22 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
 
   const int u = ug * kUnitsPerWg + w;
   const int uc = u < p.units_per_head ? u : p.units_per_head - 1;
-  const int tb = uc / G, hg = uc - tb * G;
-  const int head = g * G + hg;
-  const int tok = tb * kRowsPerUnit + m;
-  const int tokc = tok < C ? tok : C - 1;
-  const bool store_ok = (u < p.units_per_head) && (tok < C);
-  const int my_vis = (int)p.len_prev + tokc + 1;
-  const int vis_first = (int)p.len_prev + tb * kRowsPerUnit + 1;
+  const UnitRows ur(uc, p);
+  const bool inside = ur.tok(m) < C;
+  const int tok = inside ? ur.tok(m) : C - 1;  // of this lane's row (the chunk's last row where the unit runs past it)
+  const int head = g * G + (inside ? ur.head(m) : G - 1);
+  const bool store_ok = (u < p.units_per_head) && inside;
+  const int my_vis = (int)p.len_prev + tok + 1;
+  const int vis_first = (int)p.len_prev + ur.tok0 + 1;
   // Sink + sliding-window step (Sec. 6 of the paper, the streaming baseline's mask): of the keys [0, vis) a row
   // sees only j < n_sink and j >= vis - window; lb_last is the largest such lower bound among the unit's rows
   constexpr bool win = WIN;
-  int lb_last;
-  {
-    const int last = tb * kRowsPerUnit + kRowsPerUnit - 1;
-    lb_last = (int)p.len_prev + (last < C ? last : C - 1) + 1 - p.window;
-  }
+  const int lb_last = (int)p.len_prev + unit_last_token(uc, p.by_group, C) + 1 - p.window;
 
   // Q: lane (m, hi) keeps q[m][8*s + 4*hi + j], j = 0..3, s = 0..D/8-1 (contraction slot hi of MFMA (s,j))
   float4 qf[D / 8];
   {
-    const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)tokc * Hq + head) * D;
+    const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)tok * Hq + head) * D;
 #pragma unroll
     for (int s8 = 0; s8 < D / 8; ++s8) {
       float4 v = *reinterpret_cast<const float4*>(qrow + s8 * 8 + hi * 4);
@@ -85,8 +81,8 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
         const bool lower = s8 < D / 16;
         const int j0 = (lower ? s8 : s8 - D / 16) * 8 + hi * 4;  // index of the pair's angle
         const float4 o = *reinterpret_cast<const float4*>(qrow + (lower ? D / 2 : 0) + j0);
-        const float4 cs = *reinterpret_cast<const float4*>(p.rope_cos + (int64_t)tokc * (D / 2) + j0);
-        const float4 sn = *reinterpret_cast<const float4*>(p.rope_sin + (int64_t)tokc * (D / 2) + j0);
+        const float4 cs = *reinterpret_cast<const float4*>(p.rope_cos + (int64_t)tok * (D / 2) + j0);
+        const float4 sn = *reinterpret_cast<const float4*>(p.rope_sin + (int64_t)tok * (D / 2) + j0);
         const float tx = o.x * sn.x, ty = o.y * sn.y, tz = o.z * sn.z, tw = o.w * sn.w;
         v.x = __builtin_fmaf(v.x, cs.x, lower ? -tx : tx);
         v.y = __builtin_fmaf(v.y, cs.y, lower ? -ty : ty);
@@ -101,15 +97,13 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
   {
     int ulast = ug * kUnitsPerWg + kUnitsPerWg - 1;
     if (ulast > p.units_per_head - 1) ulast = p.units_per_head - 1;
-    int row_hi = (ulast / G) * kRowsPerUnit + kRowsPerUnit - 1;
-    if (row_hi > C - 1) row_hi = C - 1;
-    nkeys_wg = (int)p.len_prev + row_hi + 1;
+    nkeys_wg = (int)p.len_prev + unit_last_token(ulast, p.by_group, C) + 1;
   }
   // logical tiles 0 .. ntiles-1; under a window the tiles between the sinks and the window are left out:
   // logical tile t is physical tile t + (t >= ns_t ? skip : 0)
   TileMap tm;
   if (win) {
-    const RowRange rr = workgroup_rows(ug, kUnitsPerWg, p.units_per_head, G, C);
+    const RowRange rr = workgroup_rows(ug, kUnitsPerWg, p.units_per_head, p.by_group, C);
     tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, p.n_sink, p.window);
   } else {
     tm.ns_t = 0;

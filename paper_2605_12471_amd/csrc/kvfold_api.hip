@@ -264,6 +264,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   const bool fused_append = fused_append_applies(pc, n_tokens, len_prev, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
+  finish_attn_params(at);
   if (pl.n_splits > 1 && ((int64_t)pl.n_splits * n_tokens * f.n_q_heads > pc.ws_rows || !part_o))
     return KVFOLD_ERR_HIP;  // planner bug guard
 

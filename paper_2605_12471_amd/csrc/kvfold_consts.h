@@ -4,7 +4,8 @@
 
 namespace kvfold {
 
-// Rows of one (query head, 32-token block) pair are the unit of work of one wavefront.
+// Rows of a unit, the work of one wavefront: 32 consecutive rows of a KV head's (token, query head of the group)
+// rows, token-major -- packed row r of the KV head is token r / G, head r % G of its group.
 constexpr int kRowsPerUnit = 32;
 // Wavefronts (units) per workgroup of the attention kernels.
 constexpr int kUnitsPerWg = 4;
@@ -20,21 +21,52 @@ constexpr int kNumXcd = 8;
 #define KVFOLD_HD inline
 #endif
 
-// Chunk rows [row_lo, row_hi] owned by workgroup `ug` of a KV head: its `upw_wg` consecutive units, ordered
-// token-block-major, head-minor (unit u = token block u / G, head u % G of the group of G query heads).
+// Quotients by a divisor that the host knows: n / d = (n * mul) >> shift for every n < 2^31.  With l = ceil(log2 d),
+// mul = ceil(2^(31+l) / d) < 2^32 overshoots by e = mul * d - 2^(31+l) < 2^l, and n * e < 2^(31+l).  Integer division
+// has no instruction on the GPU; the half dozen that a workgroup needs to find its place took 1 us of its start.
+struct FastDiv {
+  unsigned mul;
+  int shift;
+};
+inline FastDiv fast_div(int d) {
+  int l = 0;
+  while ((1ll << l) < d) ++l;
+  FastDiv f;
+  f.shift = 31 + l;
+  f.mul = (unsigned)(((1ull << f.shift) + (unsigned)d - 1) / (unsigned)d);
+  return f;
+}
+KVFOLD_HD unsigned quot(unsigned n, int d) { return n / (unsigned)d; }
+KVFOLD_HD unsigned quot(unsigned n, const FastDiv& d) { return (unsigned)(((unsigned long long)n * d.mul) >> d.shift); }
+
+// 32-row units of one KV head: its n_tokens * G packed rows, the last unit filled up.
+KVFOLD_HD int units_of_head(int n_tokens, int G) { return (int)(((long long)n_tokens * G + kRowsPerUnit - 1) / kRowsPerUnit); }
+// First and last token (of the chunk) with a row in unit u; units are token-major, so they ascend with u.
+// (DIV: the group size G itself, or its FastDiv.)
+template <class DIV>
+KVFOLD_HD int unit_first_token(int u, const DIV& G) {
+  return (int)quot((unsigned)(u * kRowsPerUnit), G);
+}
+template <class DIV>
+KVFOLD_HD int unit_last_token(int u, const DIV& G, int n_tokens) {
+  const int t = (int)quot((unsigned)(u * kRowsPerUnit + kRowsPerUnit - 1), G);
+  return t < n_tokens - 1 ? t : n_tokens - 1;
+}
+
+// Tokens [row_lo, row_hi] of the chunk with rows in workgroup `ug` of a KV head: its `upw_wg` consecutive units.
 struct RowRange {
   int row_lo, row_hi;
 };
-KVFOLD_HD RowRange workgroup_rows(int ug, int upw_wg, int units_per_head, int G, int n_tokens) {
+template <class DIV>
+KVFOLD_HD RowRange workgroup_rows(int ug, int upw_wg, int units_per_head, const DIV& G, int n_tokens) {
   int ufirst = ug * upw_wg, ulast = ufirst + upw_wg - 1;
   if (ulast > units_per_head - 1) ulast = units_per_head - 1;
   if (ufirst > ulast) ufirst = ulast;
   if (ufirst < 0) ufirst = 0;
   if (ulast < 0) ulast = 0;
   RowRange r;
-  r.row_lo = (ufirst / G) * kRowsPerUnit;
-  r.row_hi = (ulast / G) * kRowsPerUnit + kRowsPerUnit - 1;
-  if (r.row_hi > n_tokens - 1) r.row_hi = n_tokens - 1;
+  r.row_lo = unit_first_token(ufirst, G);
+  r.row_hi = unit_last_token(ulast, G, n_tokens);
   if (r.row_lo > r.row_hi) r.row_lo = r.row_hi;
   return r;
 }

@@ -41,7 +41,7 @@ struct AttnParams {
   int64_t len_prev;      // cache length before this chunk
   int32_t n_splits;      // S >= 1; S == 1 writes out/lse directly
   int32_t tiles_per_split;
-  int32_t units_per_head;  // G * ceil(C / 32)
+  int32_t units_per_head;  // ceil(C * G / 32): units of 32 packed rows
   int32_t wgs_per_head;    // ceil(units_per_head / units per workgroup)
   int32_t n_wgs;           // Hkv * wgs_per_head * S (the grid is padded to a multiple of 8)
   int32_t pair_order;      // 1: every workgroup is resident at once, two per CU; order them heaviest-first for the
@@ -53,9 +53,8 @@ struct AttnParams {
   const float* rope_cos;
   const float* rope_sin;
   // Append fused into the bf16 attention kernel (nullptr: the cache already holds the chunk's rows): the
-  // chunk's K / V rows as handed in, [C][Hkv][d].  Requires len_prev to be a multiple of the 64-key tile, so
-  // that a tile lies entirely in the cache or entirely in the chunk.  Tiles of the chunk are then streamed
-  // from here, and every workgroup copies its share of the rows into the cache for the steps to come.
+  // chunk's K / V rows as handed in, [C][Hkv][d].  Tiles of the chunk are then streamed from here, and every
+  // workgroup copies its share of the rows into the cache for the steps to come.
   const void* k_new;
   const void* v_new;
   // Sink + sliding-window step (window > 0; 0: every key up to the row's own position is visible): the row at
@@ -63,7 +62,27 @@ struct AttnParams {
   // window are skipped (see tile_map()).
   int32_t n_sink;
   int32_t window;
+  // Quotients the workgroups need, prepared by finish_attn_params()
+  FastDiv by_group, by_wgs_per_head, by_wgs_per_kvh;
+  int32_t group_inv16;      // floor(2^16 / G) + 1
+  int32_t copy_rows;        // fused append: chunk rows that one workgroup copies, ceil(C / (wgs_per_head * S))
+  int32_t xcd_share_log2;   // log2 of the XCDs that share one KV head, -1: contiguous runs (see logical_workgroup())
 };
+
+// Fills in what follows from the launch geometry.
+inline void finish_attn_params(AttnParams& p) {
+  const int per_kvh = p.wgs_per_head * p.n_splits;
+  p.by_group = fast_div(p.group);
+  p.by_wgs_per_head = fast_div(p.wgs_per_head);
+  p.by_wgs_per_kvh = fast_div(per_kvh);
+  p.group_inv16 = 65536 / p.group + 1;
+  p.copy_rows = (p.n_tokens + per_kvh - 1) / per_kvh;
+  p.xcd_share_log2 = -1;
+  if (p.n_kv_heads < kNumXcd && kNumXcd % p.n_kv_heads == 0 && per_kvh % (kNumXcd / p.n_kv_heads) == 0) {
+    p.xcd_share_log2 = 0;
+    while ((p.n_kv_heads << p.xcd_share_log2) < kNumXcd) ++p.xcd_share_log2;
+  }
+}
 
 struct CombineParams {
   const float* part_o;
@@ -96,13 +115,28 @@ inline int padded_grid(int n_wgs) { return (n_wgs + kNumXcd - 1) / kNumXcd * kNu
 // A KV head that spans k = 8 / Hkv XCDs has its workgroups dealt to those XCDs in turn, not in k contiguous
 // runs: every XCD then gets the same mix of heavy and light workgroups and of prefix splits (a contiguous
 // run would put all late token blocks, or a whole split, on one XCD and the light rest on its neighbour).
-__device__ __forceinline__ int logical_workgroup(int b, int grid, int n_kv_heads, int wgs_per_kvh) {
-  const int x = b % kNumXcd, j = b / kNumXcd;
-  if (n_kv_heads < kNumXcd && kNumXcd % n_kv_heads == 0) {
-    const int k = kNumXcd / n_kv_heads;
-    if (wgs_per_kvh % k == 0) return (x / k) * wgs_per_kvh + j * k + x % k;  // grid = Hkv * wgs_per_kvh, a multiple of 8
-  }
+__device__ __forceinline__ int logical_workgroup(int b, int grid, const AttnParams& p) {
+  const int x = b % kNumXcd, j = b / kNumXcd, lk = p.xcd_share_log2;
+  if (lk >= 0) return (x >> lk) * (p.wgs_per_head * p.n_splits) + (j << lk) + (x & ((1 << lk) - 1));  // grid = Hkv * wgs per head
   return x * (grid / kNumXcd) + j;
 }
+
+// Packed rows of one unit (row j of unit u: packed row 32 u + j of the KV head, j < 32): token and head of the group.
+// One scalar quotient per unit; the lanes add rem0 + j < G + 32, whose quotient by G is a multiplication for G < 32
+// (x < 64 and inv * G - 2^16 <= G, so x * inv / 2^16 never reaches the next whole number) and 0 or 1 above.
+struct UnitRows {
+  int tok0, rem0, G, inv;
+  __device__ __forceinline__ UnitRows(int u, const AttnParams& p) : G(p.group), inv(p.group_inv16) {
+    const unsigned r0 = (unsigned)u * kRowsPerUnit;
+    tok0 = (int)quot(r0, p.by_group);
+    rem0 = (int)(r0 - (unsigned)tok0 * (unsigned)G);
+  }
+  __device__ __forceinline__ int step(int j) const {
+    const int x = rem0 + j;
+    return G < kRowsPerUnit ? (x * inv) >> 16 : (int)(x >= G);
+  }
+  __device__ __forceinline__ int tok(int j) const { return tok0 + step(j); }
+  __device__ __forceinline__ int head(int j) const { return rem0 + j - step(j) * G; }
+};
 
 }  // namespace kvfold

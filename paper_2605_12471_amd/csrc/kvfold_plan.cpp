@@ -63,7 +63,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   Plan pl;
   pl.pair_order = 0;
   pl.pair_units = 0;
-  pl.units_per_head = G * ((n_tokens + kRowsPerUnit - 1) / kRowsPerUnit);
+  pl.units_per_head = units_of_head(n_tokens, G);
   pl.units_per_wave = upw;
   const int per_wg = kUnitsPerWg * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
