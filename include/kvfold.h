@@ -237,7 +237,8 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_SPLITS         number of prefix splits of the attention kernel; 0 = automatic.
  *                              Clamped to what the split workspace and the key range allow.
  *   KVFOLD_TUNE_UNITS_PER_WAVE 32-row query blocks owned by one wavefront of the bf16 kernel:
- *                              1 or 2; 0 = automatic.
+ *                              1 or 2; 0 = automatic.  fp32 kernel (always one block per wavefront): 1 or 2 for
+ *                              workgroups of four or eight wavefronts.
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
  *                              round of workgroups), 1 = never, 2 = always.

@@ -1,15 +1,34 @@
-// Chunk-prefix attention of the fold step in fp32 throughout (the precision-ablation mode of the
-// paper's Sec. 3; here the 1e-5 correctness mode).  Same decomposition as the bf16 kernel: a
-// wavefront owns one unit of 32 packed (token, head of the group) rows, 4 wavefronts of one KV head share
-// each 64-key K/V tile through LDS, logits are formed transposed (S^T = K Q^T, keys as MFMA rows)
-// with v_mfma_f32_32x32x2_f32 so a lane holds 32 logits of one query, and the accumulator layout
-// of S^T feeds O^T = V^T P^T directly: register r of S^T pairs the two keys 8*(r/4) + r%4 and
-// that + 4 held by the two half-waves, which are exactly the K=2 contraction slots of the MFMA.
+// Chunk-prefix attention of the fold step in fp32 (the precision-ablation mode of the paper's Sec. 3; here the 1e-5
+// correctness mode).  Same decomposition as the bf16 kernel: a wavefront owns one unit of 32 packed (token, head of the
+// group) rows, the wavefronts of a workgroup share the K/V tiles of one KV head through LDS, logits are formed transposed
+// (S^T = K Q^T, keys as MFMA rows) so that a lane holds logits of one query only, and S^T feeds O^T = V^T P^T directly.
+//
+// The products run on the bf16 matrix instructions, on operands split into three bf16 terms: x = x0 + x1 + x2 exactly (x0
+// the upper half of x's bits, x1 the next 8 bits rounded, x2 the rest, which fits), and
+//     x y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + two terms below 2^-23 of x y and one below 2^-31,
+// summed in fp32 like the fp32 instruction's own products.  Six 32x32x16 bf16 instructions take 192 cycles where the eight
+// 32x32x2 fp32 ones that they replace take 512, and round the sum less often: against 64 bits the outputs are off by
+// 0.4 to 0.9 of what the fp32 instructions left (relative 2-norm, N(0,1) inputs: 1.9e-7 ... 6.8e-7, before 2.8e-7 ...
+// 7.3e-7; queries 8 times larger: 4.1e-7 ... 9.4e-7, before 8.7e-7 ... 2.7e-6).
+// 512 tokens on 16K keys, 28 heads: 1160 us before (106 TFLOP/s), 575 us now (212; the fp32 instructions' peak is 157).
+// What bounds it: the matrix pipe is busy half of the time; the split and the softmax take a third of the issue slots, and
+// the two wavefronts of a SIMD do not overlap them perfectly.
+// K and V are split once per workgroup, on their way into LDS, where a tile's terms lie in the order in which the matrix
+// instructions read their fragments: V is transposed by the split (a lane gathers 8 keys of one column), so that all
+// fragment reads are 16 bytes per lane.  P is split in registers.
+//
+// The terms of an infinity would be NaN.  A workgroup that met a key or value row with a number that is not finite, and a
+// wavefront with such a query, does its work once more with the fp32 instructions, operands straight from memory.
+#include <type_traits>
+
 #include "kvfold_internal.h"
 
 namespace kvfold {
 
 typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
 
 __device__ __forceinline__ float pair_max_f(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -20,18 +39,44 @@ __device__ __forceinline__ float pair_sum_f(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <int D, bool WIN>  // WIN: the sink + sliding-window step
-__global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
-  constexpr int CH = D / 4;    // 16-byte chunks per row
-  constexpr int ROWB = D * 4;  // bytes per row
-  constexpr int BN = kTileKeys;
-  constexpr int DB = D / 32;
-  constexpr int LD_IT = BN * CH / 256;
+constexpr int kTerms = 3;
+// Eight values as three fragments of bf16 terms.  (A value that is not finite leaves NaN in the lower terms.)
+__device__ __forceinline__ void split8(const float (&x)[8], uintx4 (&t)[kTerms]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const unsigned a = __float_as_uint(x[2 * j]), b = __float_as_uint(x[2 * j + 1]);
+    t[0][j] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // upper halves: rounded towards zero, so never to infinity
+    const float ra = x[2 * j] - __uint_as_float(a & 0xffff0000u), rb = x[2 * j + 1] - __uint_as_float(b & 0xffff0000u);
+    bf16x2 h;
+    h[0] = (__bf16)ra;
+    h[1] = (__bf16)rb;
+    const unsigned h2 = __builtin_bit_cast(unsigned, h);
+    t[1][j] = h2;
+    const float qa = ra - __uint_as_float(h2 << 16), qb = rb - __uint_as_float(h2 & 0xffff0000u);  // exact, at most 8 bits
+    t[2][j] = __builtin_amdgcn_perm(__float_as_uint(qb), __float_as_uint(qa), 0x07060302u);
+  }
+}
+__device__ __forceinline__ floatx16 mfma16(const uintx4& a, const uintx4& b, const floatx16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// NW wavefronts per workgroup, one workgroup per CU at D = 128 (96 KB of LDS).  Eight (two per SIMD) share the split of a
+// tile among twice the rows and have one wavefront's vector work behind the other's matrix work; four are for chunks that
+// leave half of the eight without rows.  WIN: the sink + sliding-window step.
+template <int D, bool WIN, int NW>
+__global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p) {
+  constexpr int NT = NW * 64;
+  constexpr int ROWB = D * 4;       // bytes per row of the cache
+  constexpr int BN = 32;            // keys per step; the planner's tiles hold two
+  constexpr int KS = D / 16, DB = D / 32;
+  constexpr int TERMB = BN * D * 2;          // one term of a K or V tile
+  constexpr int BUFB = 2 * kTerms * TERMB;   // a K tile, a V tile
+  constexpr int ITEMS = BN * D / 8;          // vectors of 8 values per tensor and tile
+  constexpr int PER = ITEMS >= NT ? ITEMS / NT : 1;
   constexpr float kThresh = 8.0f;
 
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BN * ROWB];
-  unsigned char* sK = smem;
-  unsigned char* sV = smem + BN * ROWB;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUFB];
+  __shared__ int odd_value;  // a tile holds a value that is not finite
 
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
   const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
@@ -39,63 +84,33 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
   const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int rem = lid - g * wgs_per_kvh;
   const int split = (int)quot((unsigned)rem, p.by_wgs_per_head);
-  // Later token blocks see more keys.  Default order: heaviest first (longest-processing-time
-  // first over several rounds of workgroups).  With pair_order the grid is resident at once, two
-  // workgroups per CU, dispatched in id order: the first half descends from the heaviest, the second
-  // half ascends from the lightest, so the two workgroups that share a CU add up to the same work.
-  int ug;
-  {
-    const int idx = rem - split * p.wgs_per_head, W = p.wgs_per_head, half = (W + 1) / 2;
-    ug = (!p.pair_order || idx < half) ? W - 1 - idx : idx - half;
-  }
+  // Later token blocks see more keys: heaviest first (longest-processing-time first over several rounds of workgroups).
+  const int ug = p.wgs_per_head - 1 - (rem - split * p.wgs_per_head);
 
   const int tid = threadIdx.x, l = tid & 63, hi = l >> 5, m = l & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: what depends on it alone stays in scalar registers
   const int C = p.n_tokens, Hq = p.n_q_heads, G = p.group;
   const int L = (int)p.len_prev + C;  // (row counts fit 32 bits: the host limits the capacity to 2^30 rows)
 
-  const int u = ug * kUnitsPerWg + w;
+  const int u = ug * NW + w;
   const int uc = u < p.units_per_head ? u : p.units_per_head - 1;
+  const bool idle = u >= p.units_per_head;  // no rows: this wavefront only moves its share of the tiles
   const UnitRows ur(uc, p);
   const bool inside = ur.tok(m) < C;
   const int tok = inside ? ur.tok(m) : C - 1;  // of this lane's row (the chunk's last row where the unit runs past it)
   const int head = g * G + (inside ? ur.head(m) : G - 1);
-  const bool store_ok = (u < p.units_per_head) && inside;
+  const bool store_ok = !idle && inside;
   const int my_vis = (int)p.len_prev + tok + 1;
   const int vis_first = (int)p.len_prev + ur.tok0 + 1;
   // Sink + sliding-window step (Sec. 6 of the paper, the streaming baseline's mask): of the keys [0, vis) a row
   // sees only j < n_sink and j >= vis - window; lb_last is the largest such lower bound among the unit's rows
   constexpr bool win = WIN;
-  const int lb_last = (int)p.len_prev + unit_last_token(uc, p.by_group, C) + 1 - p.window;
-
-  // Q: lane (m, hi) keeps q[m][8*s + 4*hi + j], j = 0..3, s = 0..D/8-1 (contraction slot hi of MFMA (s,j))
-  float4 qf[D / 8];
-  {
-    const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)tok * Hq + head) * D;
-#pragma unroll
-    for (int s8 = 0; s8 < D / 8; ++s8) {
-      float4 v = *reinterpret_cast<const float4*>(qrow + s8 * 8 + hi * 4);
-      if (p.rope_cos) {
-        // Rotary embedding at the row's absolute position (Sec. 2), half-split pairs (j, j + D/2): the sine
-        // product rounded first, then one fused multiply-add
-        const bool lower = s8 < D / 16;
-        const int j0 = (lower ? s8 : s8 - D / 16) * 8 + hi * 4;  // index of the pair's angle
-        const float4 o = *reinterpret_cast<const float4*>(qrow + (lower ? D / 2 : 0) + j0);
-        const float4 cs = *reinterpret_cast<const float4*>(p.rope_cos + (int64_t)tok * (D / 2) + j0);
-        const float4 sn = *reinterpret_cast<const float4*>(p.rope_sin + (int64_t)tok * (D / 2) + j0);
-        const float tx = o.x * sn.x, ty = o.y * sn.y, tz = o.z * sn.z, tw = o.w * sn.w;
-        v.x = __builtin_fmaf(v.x, cs.x, lower ? -tx : tx);
-        v.y = __builtin_fmaf(v.y, cs.y, lower ? -ty : ty);
-        v.z = __builtin_fmaf(v.z, cs.z, lower ? -tz : tz);
-        v.w = __builtin_fmaf(v.w, cs.w, lower ? -tw : tw);
-      }
-      qf[s8] = v;
-    }
-  }
+  const int vis_last = (int)p.len_prev + unit_last_token(uc, p.by_group, C) + 1;
+  const int lb_last = vis_last - p.window;
 
   int nkeys_wg;
   {
-    int ulast = ug * kUnitsPerWg + kUnitsPerWg - 1;
+    int ulast = ug * NW + NW - 1;
     if (ulast > p.units_per_head - 1) ulast = p.units_per_head - 1;
     nkeys_wg = (int)p.len_prev + unit_last_token(ulast, p.by_group, C) + 1;
   }
@@ -103,90 +118,228 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
   // logical tile t is physical tile t + (t >= ns_t ? skip : 0)
   TileMap tm;
   if (win) {
-    const RowRange rr = workgroup_rows(ug, kUnitsPerWg, p.units_per_head, p.by_group, C);
+    const RowRange rr = workgroup_rows(ug, NW, p.units_per_head, p.by_group, C);
     tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, p.n_sink, p.window);
   } else {
     tm.ns_t = 0;
     tm.skip = 0;
-    tm.ntiles = (nkeys_wg + BN - 1) / BN;
+    tm.ntiles = (nkeys_wg + kTileKeys - 1) / kTileKeys;
   }
-  const int ntiles = tm.ntiles;
   const int t_begin = split * p.tiles_per_split;
   int t_end = t_begin + p.tiles_per_split;
-  if (t_end > ntiles) t_end = ntiles;
+  if (t_end > tm.ntiles) t_end = tm.ntiles;
+  const int h_begin = 2 * t_begin;
+  int h_end = 2 * t_end;  // steps: half tiles
+  auto first_key = [&](int h) __attribute__((always_inline)) -> int {
+    const int t = h >> 1;
+    return (2 * (t + (t >= tm.ns_t ? tm.skip : 0)) + (h & 1)) * BN;
+  };
+  if (h_end > h_begin && first_key(h_end - 1) >= nkeys_wg) --h_end;  // the piece's last half lies beyond every row
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
   const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
 
-  // K tile: chunk c of row r stored at chunk c ^ (r % 16)  (16 lanes with consecutive rows, one column -> 16 banksets)
-  // V tile: chunk c of row r stored at chunk c ^ (8 * ((r >> 2) & 1))  (rows r and r+4 read together by the half-waves)
-  floatx16 o[DB];
+  // ---- split of a tile on its way into LDS.  K: thread = (row, 8 columns), read as it lies; the fragment of contraction
+  // step ks, lane (m, hi), goes to slot m ^ (2 ks + hi) % 8 of its 32, so that neighbouring threads, which hold neighbouring
+  // columns of one row, write different banks.  V: thread = (column, the 8 keys that registers 8 tt .. 8 tt + 7 of S^T stand
+  // for in its half-wave).  Rows past the last one are read as the last one (and masked).  With fewer vectors than
+  // threads (D = 64, eight wavefronts) the first half of the wavefronts splits K, the second V.
+  const bool k_mine = ITEMS >= NT || tid < ITEMS, v_mine = ITEMS >= NT || tid >= NT - ITEMS;
+  float stage[PER][8];
+  auto load_k = [&](int h) __attribute__((always_inline)) {
+    const int key0 = first_key(h);
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float sc = p.scale_log2e;
-
-  for (int t_log = t_begin; t_log < t_end; ++t_log) {
-    const int t = t_log + (t_log >= tm.ns_t ? tm.skip : 0);
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < LD_IT; ++it) {
-      const int ci = it * 256 + tid;
-      const int row = ci / CH, c = ci % CH;
-      int grow = t * BN + row;
-      if (grow > L - 1) grow = L - 1;
-      const uint4 kv = *reinterpret_cast<const uint4*>(kbase + (int64_t)grow * ROWB + c * 16);
-      const uint4 vv = *reinterpret_cast<const uint4*>(vbase + (int64_t)grow * ROWB + c * 16);
-      *reinterpret_cast<uint4*>(sK + row * ROWB + ((c ^ (row & 15)) * 16)) = kv;
-      *reinterpret_cast<uint4*>(sV + row * ROWB + ((c ^ (8 * ((row >> 2) & 1))) * 16)) = vv;
-    }
-    __syncthreads();
-
-    // ---- S^T = K Q^T
-    floatx16 s[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-      const int row = kb * 32 + m;
-#pragma unroll
-      for (int s8 = 0; s8 < D / 8; ++s8) {
-        const int c = s8 * 2 + hi;
-        const float4 a = *reinterpret_cast<const float4*>(sK + row * ROWB + ((c ^ (row & 15)) * 16));
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, qf[s8].x, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, qf[s8].y, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, qf[s8].z, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, qf[s8].w, s[kb], 0, 0, 0);
+    for (int it = 0; it < PER; ++it) {
+      const int ci = it * NT + tid;
+      int row = key0 + ci / (D / 8);
+      if (row > L - 1) row = L - 1;
+      const float4* src = reinterpret_cast<const float4*>(kbase + (unsigned)row * (unsigned)ROWB + (ci % (D / 8)) * 32);
+      if (k_mine) {
+        const float4 a = src[0], b = src[1];
+        stage[it][0] = a.x; stage[it][1] = a.y; stage[it][2] = a.z; stage[it][3] = a.w;
+        stage[it][4] = b.x; stage[it][5] = b.y; stage[it][6] = b.z; stage[it][7] = b.w;
       }
     }
+  };
+  auto load_v = [&](int h) __attribute__((always_inline)) {
+    const int key0 = first_key(h);
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int vi = it * NT + tid - (ITEMS >= NT ? 0 : NT - ITEMS);
+      const int grp = __builtin_amdgcn_readfirstlane(vi / D);  // 2 tt + half-wave; 64 consecutive threads share it
+      const int key = key0 + 16 * (grp >> 1) + 4 * (grp & 1);
+      if (v_mine) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          int row = key + 8 * (j >> 2) + (j & 3);
+          if (row > L - 1) row = L - 1;
+          stage[it][j] = *reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB + (vi % D) * 4);
+        }
+      }
+    }
+  };
+  auto put = [&](int h, bool is_v) __attribute__((always_inline)) {
+    unsigned char* buf = smem + (h & 1) * BUFB + (is_v ? kTerms * TERMB : 0);
+    if (is_v ? v_mine : k_mine) {
+      float probe = 0.f;
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        uintx4 t[kTerms];
+        split8(stage[it], t);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) probe = __builtin_fmaf(stage[it][j], 0.f, probe);  // NaN from the first value that is not finite
+        int at;
+        if (is_v) {
+          const int vi = it * NT + tid - (ITEMS >= NT ? 0 : NT - ITEMS);
+          const int col = vi % D, grp = vi / D;
+          at = (((grp >> 1) * DB + col / 32) * 64 + (grp & 1) * 32 + col % 32) * 16;
+        } else {
+          const int ci = it * NT + tid, row = ci / (D / 8), c = ci % (D / 8);
+          at = (c * 32 + (row ^ (c & 7))) * 16;
+        }
+#pragma unroll
+        for (int i = 0; i < kTerms; ++i) *reinterpret_cast<uintx4*>(buf + i * TERMB + at) = t[i];
+      }
+      if (!(probe == 0.f)) odd_value = 1;
+    }
+  };
 
-    // ---- online softmax
-    const int tile_key0 = t * BN;
-    const bool left = WIN && tile_key0 < lb_last && tile_key0 + BN > p.n_sink;  // keys between the sinks and the window
-    if (tile_key0 + BN > vis_first || left) {
+  // ---- Q: lane (m, hi) keeps q[m][16 ks + 8 hi + j], j = 0..7, as terms
+  uintx4 qt[KS][kTerms];
+  bool odd_q = false;
+  if (tid == 0) odd_value = 0;
+  if (h_begin < h_end) load_k(h_begin);
+  {
+    float raw[KS][8];
+    const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)tok * Hq + head) * D + hi * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const float4 a = *reinterpret_cast<const float4*>(qrow + ks * 16), b = *reinterpret_cast<const float4*>(qrow + ks * 16 + 4);
+      raw[ks][0] = a.x; raw[ks][1] = a.y; raw[ks][2] = a.z; raw[ks][3] = a.w;
+      raw[ks][4] = b.x; raw[ks][5] = b.y; raw[ks][6] = b.z; raw[ks][7] = b.w;
+    }
+    if (p.rope_cos) {
+      // Rotary embedding at the row's absolute position (Sec. 2), half-split pairs (j, j + D/2): the sine
+      // product rounded first, then one fused multiply-add
+#pragma unroll
+      for (int ks = 0; ks < KS / 2; ++ks) {
+        const float* cs = p.rope_cos + (int64_t)tok * (D / 2) + ks * 16 + hi * 8;
+        const float* sn = p.rope_sin + (int64_t)tok * (D / 2) + ks * 16 + hi * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float lo = raw[ks][e], up = raw[ks + KS / 2][e];
+          const float tl = up * sn[e], tu = lo * sn[e];
+          raw[ks][e] = __builtin_fmaf(lo, cs[e], -tl);
+          raw[ks + KS / 2][e] = __builtin_fmaf(up, cs[e], tu);
+        }
+      }
+    }
+    float probe = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      split8(raw[ks], qt[ks]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) probe = __builtin_fmaf(raw[ks][e], 0.f, probe);
+    }
+    odd_q = __any(!(probe == 0.f));
+  }
+
+  floatx16 o[DB];
+  float m_run, l_run;
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+    m_run = -INFINITY;
+    l_run = 0.f;
+  };
+  clear();
+  const float sc = p.scale_log2e;
+
+  // lane part of the LDS addresses
+  unsigned k_at[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) k_at[i] = (unsigned)((2 * i + hi) * 32 + (m ^ ((2 * i + hi) & 7))) * 16u;
+
+  if (h_begin < h_end) {
+    __syncthreads();  // the flag is clear
+    put(h_begin, false);
+    load_v(h_begin);
+    put(h_begin, true);
+  }
+  floatx16 s;
+  auto logits = [&](int h, auto split_tag) __attribute__((always_inline)) {
+    const int key0 = first_key(h);
+    if constexpr (decltype(split_tag)::value) {
+      // the leading products in one sum, the small ones in another
+      const unsigned char* buf = smem + (h & 1) * BUFB;
+      floatx16 sm;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = sm[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        uintx4 a[kTerms];
+#pragma unroll
+        for (int i = 0; i < kTerms; ++i)
+          a[i] = *reinterpret_cast<const uintx4*>(buf + k_at[ks & 3] + (ks >> 2) * 4096 + i * TERMB);
+        sm = mfma16(a[2], qt[ks][0], sm);
+        sm = mfma16(a[1], qt[ks][1], sm);
+        sm = mfma16(a[0], qt[ks][2], sm);
+        sm = mfma16(a[1], qt[ks][0], sm);
+        sm = mfma16(a[0], qt[ks][1], sm);
+        s = mfma16(a[0], qt[ks][0], s);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] += sm[r];
+    } else {
+      // fp32 instructions, operands from memory: contraction slot hi of step (ks, j) is column 16 ks + 8 hi + j
+      // (formed from an opaque lane id, so that nothing is held for this through the loop over the tiles)
+      int l2 = l;
+      asm volatile("" : "+v"(l2));
+      const int hi2 = l2 >> 5, m2 = l2 & 31;
+      int row = key0 + m2, t2 = ur.tok(m2), h2 = ur.head(m2);
+      if (row > L - 1) row = L - 1;
+      if (t2 > C - 1) t2 = C - 1, h2 = G - 1;
+      const float* krow = reinterpret_cast<const float*>(kbase + (unsigned)row * (unsigned)ROWB) + hi2 * 8;
+      const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)t2 * Hq + g * G + h2) * D;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll 1
+      for (int c = 0; c < 8 * KS; ++c) {
+        const int col = 16 * (c >> 3) + (c & 7) + 8 * hi2;
+        float q = qrow[col];
+        if (p.rope_cos) {
+          const bool lower = col < D / 2;
+          const int j = lower ? col : col - D / 2;
+          const float t = qrow[lower ? col + D / 2 : j] * p.rope_sin[(int64_t)t2 * (D / 2) + j];
+          q = __builtin_fmaf(q, p.rope_cos[(int64_t)t2 * (D / 2) + j], lower ? -t : t);
+        }
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(krow[16 * (c >> 3) + (c & 7)], q, s, 0, 0, 0);
+      }
+    }
+  };
+  auto softmax = [&](int h) __attribute__((always_inline)) {
+    const int key0 = first_key(h);
+    const bool left = WIN && key0 < lb_last && key0 + BN > p.n_sink;  // keys between the sinks and the window
+    if (key0 + BN > vis_first || left) {
       // visible inside the tile: keys below rel, and of those (window step) the ones below rel_sink or from rel_lb
       // on; all three are counted from the lane's own first key, 4 * hi
-      // (opaque copy of the lane's half: the 32 key offsets below are formed here, not once ahead of the tile loop
+      // (opaque copy of the lane's half: the key offsets below are formed here, not once ahead of the tile loop
       // and then held in registers through it)
       int hi_here = hi;
       asm volatile("" : "+v"(hi_here));
-      const int rel = my_vis - tile_key0 - 4 * hi_here;
-      const int rel_lb = WIN ? rel - p.window : -1, rel_sink = WIN ? p.n_sink - tile_key0 - 4 * hi_here : 0;
+      const int rel = my_vis - key0 - 4 * hi_here;
+      const int rel_lb = WIN ? rel - p.window : -1, rel_sink = WIN ? p.n_sink - key0 - 4 * hi_here : 0;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kk = kb * 32 + 8 * (r >> 2) + (r & 3);  // key offset in the tile, less the lane's 4 * hi
-          if (kk >= rel || (WIN && kk < rel_lb && kk >= rel_sink)) s[kb][r] = -INFINITY;
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int kk = 8 * (r >> 2) + (r & 3);  // key offset in the tile, less the lane's 4 * hi
+        if (kk >= rel || (WIN && kk < rel_lb && kk >= rel_sink)) s[r] = -INFINITY;
+      }
     }
-    float mx = s[0][0];
+    float mx = s[0];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     mx = pair_max_f(mx) * sc;
     if (__any(mx > m_run + kThresh)) {
       // only rows that asked for it move, so a row's arithmetic never depends on its wave neighbours
@@ -201,28 +354,80 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
     }
     const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], sc, -m_use));
+      l_run += s[r];
+    }
+  };
+  // registers 8 tt .. 8 tt + 7 of P^T contract keys 16 tt + 4 hi + {0..3, 8..11}
+  auto add_values = [&](int h, auto split_tag) __attribute__((always_inline)) {
+    if constexpr (decltype(split_tag)::value) {
+      const unsigned char* buf = smem + (h & 1) * BUFB + kTerms * TERMB + l * 16;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[kb][r] = exp2f(fmaf(s[kb][r], sc, -m_use));
-        l_run += s[kb][r];
-      }
-
-    // ---- O^T += V^T P^T : register r of block kb contracts keys kb*32 + 8*(r/4) + r%4 (+4 for hi = 1)
+      for (int tt = 0; tt < 2; ++tt) {
+        float px[8];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+        for (int j = 0; j < 8; ++j) px[j] = s[8 * tt + j];
+        uintx4 pt[kTerms];
+        split8(px, pt);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = kb * 32 + 8 * (r >> 2) + (r & 3) + 4 * hi;
-        const int sw = 8 * ((row >> 2) & 1);
+        for (int db = 0; db < DB; db += 2) {
+          uintx4 a[2][kTerms];
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int col = db * 32 + m;  // float column
-          const int c = (col >> 2) ^ sw;
-          const float a = *reinterpret_cast<const float*>(sV + row * ROWB + c * 16 + (col & 3) * 4);
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, s[kb][r], o[db], 0, 0, 0);
+          for (int i = kTerms - 1; i >= 0; --i)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) a[e][i] = *reinterpret_cast<const uintx4*>(buf + (tt * DB + db + e) * 1024 + i * TERMB);
+#pragma unroll
+          for (int i = kTerms - 1; i >= 0; --i)
+#pragma unroll
+            for (int j = kTerms - 1 - i; j >= 0; --j)
+#pragma unroll
+              for (int e = 0; e < 2; ++e) o[db + e] = mfma16(a[e][i], pt[j], o[db + e]);
         }
       }
+    } else {
+      const int key0 = first_key(h);
+      int l2 = l;
+      asm volatile("" : "+v"(l2));
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        int row = key0 + 8 * (r >> 2) + (r & 3) + 4 * (l2 >> 5);
+        if (row > L - 1) row = L - 1;
+        const float* vrow = reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB) + (l2 & 31);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vrow[db * 32], s[r], o[db], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  constexpr std::true_type by_terms{};
+  constexpr std::false_type in_fp32{};
+  // (A second wavefront per SIMD that does its O^T one step later, so that the two are never in the softmax together, was
+  // 4 % slower; a priority for one of the two changed nothing.)
+  for (int h = h_begin; h < h_end; ++h) {
+    __syncthreads();  // tile h is in LDS, and nobody reads tile h - 1 any more
+    const int hn = h + 1 < h_end ? h + 1 : h;  // (past the last tile it is fetched again, for nobody)
+    const bool work = !idle && first_key(h) < vis_last;  // (else every row is masked)
+    load_k(hn);
+    if (work) logits(h, by_terms);
+    put(h + 1, false);
+    load_v(hn);
+    if (work) {
+      softmax(h);
+      add_values(h, by_terms);
+    }
+    put(h + 1, true);
+  }
+  __syncthreads();
+  if (__builtin_expect((odd_q || __builtin_amdgcn_readfirstlane(odd_value)) && !idle, 0)) {
+    // once more, with the fp32 instructions
+    clear();
+#pragma unroll 1
+    for (int h = h_begin; h < h_end && first_key(h) < vis_last; ++h) {
+      logits(h, in_fp32);
+      softmax(h);
+      add_values(h, in_fp32);
+    }
   }
 
   // ---- epilogue
@@ -252,16 +457,24 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnParams p) {
   }
 }
 
-hipError_t launch_attn_f32(const AttnParams& p, int head_dim, hipStream_t s) {
+template <int D>
+static void launch_f32(const AttnParams& p, int waves_per_wg, hipStream_t s) {
   const dim3 grid(padded_grid(p.n_wgs));
-  if (head_dim == 128 && p.window > 0)
-    hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, dim3(256), 0, s, p);
-  else if (head_dim == 128)
-    hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, dim3(256), 0, s, p);
-  else if (head_dim == 64 && p.window > 0)
-    hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, dim3(256), 0, s, p);
+  if (waves_per_wg == 8 && p.window > 0)
+    hipLaunchKernelGGL((attn_f32_kernel<D, true, 8>), grid, dim3(512), 0, s, p);
+  else if (waves_per_wg == 8)
+    hipLaunchKernelGGL((attn_f32_kernel<D, false, 8>), grid, dim3(512), 0, s, p);
+  else if (p.window > 0)
+    hipLaunchKernelGGL((attn_f32_kernel<D, true, 4>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((attn_f32_kernel<D, false, 4>), grid, dim3(256), 0, s, p);
+}
+
+hipError_t launch_attn_f32(const AttnParams& p, int head_dim, int waves_per_wg, hipStream_t s) {
+  if (head_dim == 128)
+    launch_f32<128>(p, waves_per_wg, s);
   else if (head_dim == 64)
-    hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, dim3(256), 0, s, p);
+    launch_f32<64>(p, waves_per_wg, s);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -285,7 +285,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   }
   const bool own_append = !fused_append || pc.storage_bits;  // something ran between ev[0] and the attention kernel
   if (ev && own_append) (void)hipEventRecord(ev[1], s);
-  e = (f.dtype == KVFOLD_BF16) ? launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s) : launch_attn_f32(at, f.head_dim, s);
+  e = (f.dtype == KVFOLD_BF16) ? launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s) : launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
   if (e != hipSuccess) return hip_fail(e);
   if (ev) (void)hipEventRecord(ev[2], s);
   if (pl.n_splits > 1) {

@@ -57,7 +57,8 @@ namespace {
 
 // Launch geometry for `upw` units per wavefront: enough prefix splits to put at least `target`
 // workgroups on the chip when the unsplit grid has fewer (a forced split count overrides that).
-Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window) {
+Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
+               int waves = kUnitsPerWg) {
   const kvfold_config_t& f = c.cfg;
   const int G = f.n_q_heads / f.n_kv_heads;
   Plan pl;
@@ -65,7 +66,8 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.pair_units = 0;
   pl.units_per_head = units_of_head(n_tokens, G);
   pl.units_per_wave = upw;
-  const int per_wg = kUnitsPerWg * upw;
+  pl.waves_per_wg = waves;
+  const int per_wg = waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
   // tiles of the longest key range of any workgroup (the kernels cut exactly this many into pieces), and the
@@ -148,7 +150,11 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
 
 Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, int64_t window) {
   const kvfold_config_t& f = c.cfg;
-  if (f.dtype != KVFOLD_BF16) return plan_with(c, n_tokens, len_after, 1, n_sink, window);
+  if (f.dtype != KVFOLD_BF16) {
+    const Plan w4 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 4), w8 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 8);
+    if (c.tune_units_per_wave) return c.tune_units_per_wave == 2 ? w8 : w4;
+    return w4.units_per_head <= 4 ? w4 : w8;  // one workgroup of four wavefronts, or eight
+  }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
   Plan p1 = plan_with(c, n_tokens, len_after, 1, n_sink, window);
   // Prefix shorter than the chunk: the causal part makes late token blocks several times as long as early

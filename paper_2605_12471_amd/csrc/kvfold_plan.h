@@ -23,6 +23,7 @@ struct PlanCtx {
 };
 
 struct Plan {
+  int waves_per_wg;  // 4, or 8 in the fp32 kernel's large form
   int units_per_wave, units_per_head, wgs_per_head, n_splits, tiles_per_split, n_wgs, pair_order, pair_units;
   double est_seconds;  // the planner's time estimate of the step (0 when the split count was forced)
 };

@@ -1,0 +1,97 @@
+"""fp32 mode on operands split into three bf16 terms: both workgroup sizes around the edges of the 32-key tile, values over
+many powers of two, and rows that are not finite (which take the fp32 instructions)."""
+import math
+
+import pytest
+import torch
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import inputs as I
+from test_gpu_parity_small import H, _run_case  # noqa: F401  (H: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("waves", [1, 2])  # four or eight wavefronts
+@pytest.mark.parametrize("chunks", [[1, 31, 1, 31], [33, 63, 32, 65], [300, 17, 64]])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_tile_edges(H, oracle, d, waves, chunks, splits):
+    cfg = I.FoldConfig("f32_edges", 63, 1, 6, 2, d, max(chunks), 0, "f32")
+    _run_case(H, oracle, cfg, chunks, splits=splits, upw=waves)
+
+
+def _step(q, k, v, waves, splits):
+    n, hq, d = q.shape
+    hkv = k.shape[1]
+    cache = kv.KvFoldCache(1, hq, hkv, d, n, n, "f32")
+    cache.set_tuning(0, splits)
+    cache.set_tuning(1, waves)
+    out = torch.empty_like(q)
+    cache.step(0, q, k, v, out, pos_offset=0)
+    torch.cuda.synchronize()
+    cache.close()
+    return out
+
+
+def _reference(q, k, v):
+    n, hq, d = q.shape
+    g = hq // k.shape[1]
+    qd = q.cpu().double().transpose(0, 1)
+    kd, vd = (t.cpu().double().repeat_interleave(g, dim=1).transpose(0, 1) for t in (k, v))
+    s = qd @ kd.transpose(1, 2) / math.sqrt(d)
+    s = s.masked_fill(torch.ones(n, n).triu(1).bool(), -math.inf)
+    return (torch.softmax(s, -1) @ vd).transpose(0, 1)
+
+
+def _random(n, h, d, seed):
+    return torch.randn(n, h, d, generator=torch.Generator("cuda").manual_seed(seed), device="cuda")
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_over_many_powers_of_two(d, waves):
+    """Columns scaled by 2^-40 ... 2^40 (queries the other way round, so that the logits stay of ordinary size).  Every
+    operand keeps its 24 bits; each product and sum has the fp32 bound d 2^-24 of its terms, here twice that for the two
+    products, on logits below 8 (weights move by as much as their logits), and relative to the column's largest value."""
+    n, hq, hkv = 200, 4, 1
+    scale = 2.0 ** torch.linspace(-40, 40, d, device="cuda").round()
+    q, k, v = _random(n, hq, d, 1) / scale, _random(n, hkv, d, 2) * scale, _random(n, hkv, d, 3) * scale
+    out = _step(q, k, v, waves, 1)
+    err = (out.cpu().double() - _reference(q, k, v)).abs() / scale.cpu().double() / 4.0
+    assert err.max() <= 2 * 8 * d * 2.0 ** -24
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_that_are_not_finite(d, waves, splits):
+    """An infinite value, a key that hides itself (logit -inf), a key that wins alone (+inf: NaN), a NaN query."""
+    n, hq, hkv = 150, 4, 2
+    q, k, v = _random(n, hq, d, 4), _random(n, hkv, d, 5), _random(n, hkv, d, 6)
+    q[:, :2, 3] = -q[:, :2, 3].abs()  # KV head 0: every query sees key 20 at -inf
+    k[20, 0, 3] = math.inf
+    v[0, 1, 7] = math.inf             # KV head 1: a value that every row sees
+    q[99, 1] = math.nan
+    out, ref = _step(q, k, v, waves, splits).cpu().double(), _reference(q, k, v)
+    finite = torch.isfinite(ref)
+    assert torch.isnan(out[99, 1]).all() and (out[:, 2:, 7] == math.inf).all()
+    finite[99, 1] = False
+    assert torch.equal(torch.isfinite(out), finite)
+    assert (out - ref)[finite].abs().max() <= 1e-5
+    # a query of the other sign sees the same key at +inf: NaN from there on, as inf - inf
+    q[140, 0, 3] = 1.0
+    out = _step(q, k, v, waves, splits).cpu()
+    assert torch.isnan(out[140, 0]).all() and torch.isfinite(out[139, 0]).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_largest_finite_values(d):
+    """The largest floats are split without overflow (the leading term is rounded towards zero)."""
+    n, big = 40, 3.4028234663852886e38
+    q = torch.zeros(n, 1, d, device="cuda")
+    k, v = _random(n, 1, d, 7), torch.zeros(n, 1, d, device="cuda")
+    v[0, 0, 5] = big
+    out = _step(q, k, v, 1, 1).cpu().double()[:, 0, 5]
+    ref = big / torch.arange(1, n + 1, dtype=torch.float64)
+    assert ((out - ref).abs() <= 8 * 2.0 ** -24 * ref).all()
