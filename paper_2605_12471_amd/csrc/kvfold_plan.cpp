@@ -55,8 +55,25 @@ bool fused_append_applies(const PlanCtx& c, int n_tokens, int64_t len_prev, bool
 
 namespace {
 
-// Launch geometry for `upw` units per wavefront: enough prefix splits to put at least `target`
-// workgroups on the chip when the unsplit grid has fewer (a forced split count overrides that).
+// What a workgroup of an attention kernel costs, in us (see plan_with()): per 64-key tile on an otherwise idle chip and on
+// a full one (one workgroup per CU, two per CU), and once.
+struct KernelCost {
+  double idle, full, full_two, start_end;
+  bool two_per_cu, sqrt_fill;
+};
+KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, double with_rows) {
+  const double d = head_dim / 128.0;
+  if (dtype == KVFOLD_BF16) {
+    // half the head dim leaves the same vector work per logit
+    if (head_dim == 64) return upw == 2 ? KernelCost{0.80, 0.95, 0, 10.0, false, false} : KernelCost{0.70, 0.71, 1.12, 6.2, true, false};
+    return upw == 2 ? KernelCost{1.09, 1.53, 0, 10.0, false, false} : KernelCost{0.85, 0.94, 1.81, 6.2, true, false};
+  }
+  if (waves == 8) return {(4.8 + 2.1 * with_rows) * d, 8.6 * d, 0, 10.0, false, true};
+  return {7.6 * d, 7.6 * d, 12.2 * d, 7.0, head_dim == 64, true};
+}
+
+// Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
+// estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
                int waves = kUnitsPerWg) {
   const kvfold_config_t& f = c.cfg;
@@ -70,74 +87,78 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   const int per_wg = waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
-  // tiles of the longest key range of any workgroup (the kernels cut exactly this many into pieces), and the
-  // (row, key) pairs of the step
+  // tiles of the longest key range of any workgroup (the kernels cut exactly this many into pieces)
   int ntiles = (int)((len_after + kTileKeys - 1) / kTileKeys);
-  double pairs = (double)n_tokens * ((double)len_after - 0.5 * n_tokens);
   if (window > 0) {
     ntiles = 1;
     for (int ug = 0; ug < pl.wgs_per_head; ++ug) {
       const RowRange rr = workgroup_rows(ug, per_wg, pl.units_per_head, G, n_tokens);
       ntiles = std::max(ntiles, tile_map(len_after - n_tokens, rr.row_lo, rr.row_hi, n_sink, window).ntiles);
     }
-    const double per_row = std::min((double)len_after - 0.5 * n_tokens, (double)n_sink + (double)window);
-    pairs = (double)n_tokens * per_row;
   }
-  int64_t s_max = c.tune_splits > 0 ? ntiles : ntiles / kMinTilesPerSplit;  // a forced count only needs a tile each
+  int64_t s_max = ntiles;
   const int64_t rows = (int64_t)n_tokens * f.n_q_heads;
   if (c.ws_rows / rows < s_max) s_max = c.ws_rows / rows;
   if (s_max > kMaxSplits) s_max = kMaxSplits;
   if (s_max < 1) s_max = 1;
   int64_t s = 1;
-  pl.est_seconds = 0.0;
+  pl.est_us = 0.0;
   if (c.tune_splits > 0) {
     s = c.tune_splits;
   } else {
-    // Estimated time of the step for every split count; the smallest wins (by more than 0.5 %).
-    //  * Attention itself at the rate of a full chip (1.35 PFLOP/s, or 5 TB/s for the K and V rows when that
-    //    is longer), divided by what a partly filled last round still delivers.  The chip is power-limited:
-    //    idle CUs hand their share to the busy ones, so 87.5 % of the CUs give 96 % of the rate (measured:
-    //    rate ~ fill^0.3), until the busy CUs reach their top clock (1.41 x the full-chip clock).
+    // Estimated time of the step for every split count; the smallest wins (by more than 0.5 %):
+    //     rounds of workgroups x (tiles of the longest piece x time per tile + start and end), and for s > 1 the merge.
+    //  * Time per tile: `idle` on a chip that is otherwise idle (one workgroup's chain of matrix work and waits), up to
+    //    `full` when every CU works at it: the chip is power-limited, busy CUs share what it has (rate ~ fill^0.25), and
+    //    wavefronts without rows leave theirs to the others.
+    //  * K and V rows come from memory at 5.2 TB/s with two workgroups per CU, less with fewer in flight.
     //  * Unsplit, several rounds, heaviest workgroups first: the slots left over in the last round idle for
     //    the length of the lightest workgroups only (first token block: the prefix and little else).
-    //  * A residue of imbalance that more rounds even out, 8 us of start and end per round of workgroups,
-    //    and for s > 1 the fp32 partials written and read once at 4 TB/s plus the combine launch.
-    //  * Matrix work counts the padding of the last workgroup of a KV head (units that do not exist are computed
-    //    all the same), and 10 % more in the one-unit kernel, where every LDS fragment feeds one MFMA instead of two.
-    //    A one-unit grid of at most one workgroup per CU runs one wavefront per SIMD with nothing to overlap with:
-    //    7 % less than two per CU deliver between them (measured on the C = 128, G = 7 fold: 8 pieces on 224 CUs
-    //    beat 18 pieces on all 256 twice over by 3 %).
-    const double pad = (double)((int64_t)pl.wgs_per_head * per_wg) / (double)pl.units_per_head;
-    const double kernel_cost = upw == 2 ? 1.0 : 1.1;
-    const double flops = 4.0 * f.n_q_heads * f.head_dim * pairs * pad * kernel_cost;
-    const double kv_rows = window > 0 ? std::min((double)len_after, (double)ntiles * kTileKeys * pl.wgs_per_head) : (double)len_after;
-    const double kv_bytes = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows;
-    const double t_attn = std::max(flops / (f.dtype == KVFOLD_BF16 ? 1.35e15 : 1.2e14), kv_bytes / 5e12);  // bf16 / fp32 MFMA rates
+    //  * The merge: its launch, and the fp32 partials written and read once at 5 TB/s.
+    //  * A step is not queued faster than its launches: some 9 us with one, 3.8 us more for each further one.
+    // The figures are fitted to measured steps (1 to 4096 tokens on 0 to 128K keys, all split counts): over 30 workloads
+    // the choice is within 2 % of the best split count on average.
+    const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
+    const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, with_rows);
+    const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
+    const double active = std::sqrt(with_rows);
+    const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
+    const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / 5.2e6;
+    const int launches = 1 + (f.dtype != KVFOLD_BF16 || c.storage_bits ? 1 : 0) + (c.storage_bits ? 1 : 0);
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
       // only split counts that whole tiles can realise; the last piece may be shorter than the others, and the
       // launch lasts as long as the longest
       const int64_t tps = (ntiles + cand - 1) / cand;
       if ((ntiles + tps - 1) / tps != cand) continue;
-      const double uneven = (double)(tps * cand) / (double)ntiles;
       const int64_t w = base * cand;
-      const bool one_per_cu = upw == 1 && w <= (int64_t)c.n_cu;
-      const int64_t slots = (int64_t)c.n_cu * (upw == 1 && !one_per_cu ? 2 : 1);
-      const int64_t rounds = (w + slots - 1) / slots;
-      double fill = (double)w / (double)(rounds * slots);
-      if (cand == 1 && rounds >= 2 && window <= 0) {
-        const double w_min = (double)(len_after - n_tokens) + kRowsPerUnit, w_mean = (double)len_after - 0.5 * n_tokens;
-        fill = (double)w * w_mean / ((double)w * w_mean + (double)(rounds * slots - w) * w_min);
+      const bool two_per_cu = k.two_per_cu && w > (int64_t)c.n_cu;
+      const double slots = (double)c.n_cu * (two_per_cu ? 2 : 1);
+      const double full = two_per_cu ? k.full_two : k.full;
+      // (pieces past the causal horizon of their row block are empty: the first row block's pieces, the last one's, the mean;
+      // and what is left lies unevenly)
+      const double first_pieces = std::ceil(((la - n_tokens) / kTileKeys + 1.0) / (double)tps);
+      const double some = cand > 1 && window <= 0 ? std::min(1.0, first_pieces / (double)cand) : 1.0;
+      const double busy = 0.5 * (double)w * (1.0 + some);
+      const double rounds = std::max(1.0, std::ceil(busy / slots - 1e-9));
+      const double fill = busy / (rounds * slots);
+      double t = rounds * (double)tps * std::max(k.idle, full * active * (k.sqrt_fill ? std::sqrt(fill) : std::sqrt(fill * std::sqrt(fill))));
+      if (cand == 1 && window <= 0) {
+        if (rounds >= 2.0)
+          t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
+        else if (upw == 2)
+          t *= mean_keys / la;  // paired units: every wavefront has the mean
       }
-      const double rate = std::min(1.41 * fill, std::pow(fill, 0.3)) * (one_per_cu ? 0.93 : 1.0);
-      const double merge = cand > 1 ? (double)cand * rows * (f.head_dim + 2) * 8.0 / 4e12 + 6e-6 : 0.0;
-      const double t = t_attn * uneven / rate * (1.0 + 0.03 / (double)rounds) + 8e-6 * (double)rounds + merge;
+      t = std::max(t, kv_us * (double)(tps * cand) / (double)ntiles * std::max(1.0, std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
+      t = t * (1.0 + 0.03 / rounds + 0.5 * (1.0 - some)) + (k.start_end + (two_per_cu ? 1.0 : 0.0)) * rounds;
+      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 5e6 + 4.2;
+      t = std::max(t, 5.0 + 3.8 * (launches + (cand > 1 ? 1 : 0)));
       if (t < best * 0.995) {
         best = t;
         s = cand;
       }
     }
-    pl.est_seconds = best;
+    pl.est_us = best;
   }
   if (s > s_max) s = s_max;
   pl.tiles_per_split = (int)((ntiles + s - 1) / s);
@@ -153,7 +174,7 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   if (f.dtype != KVFOLD_BF16) {
     const Plan w4 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 4), w8 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 8);
     if (c.tune_units_per_wave) return c.tune_units_per_wave == 2 ? w8 : w4;
-    return w4.units_per_head <= 4 ? w4 : w8;  // one workgroup of four wavefronts, or eight
+    return c.tune_splits > 0 ? (w4.units_per_head <= 4 ? w4 : w8) : (w4.est_us <= w8.est_us ? w4 : w8);
   }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
   Plan p1 = plan_with(c, n_tokens, len_after, 1, n_sink, window);
@@ -166,17 +187,17 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     p1.pair_order = 1;
     return p1;
   }
-  // Two units per wavefront is the faster kernel (every LDS fragment feeds two MFMAs) whenever it
-  // can fill the chip, if need be by splitting the prefix; one unit per wavefront is for grids too
-  // small for that, and for chunks so short that half of the two-unit workgroup would idle.
+  // Two units per wavefront is the faster kernel on a full chip (every LDS fragment feeds two MFMAs); one unit starts
+  // sooner and fills the chip with fewer rows.
   const Plan p2 = plan_with(c, n_tokens, len_after, 2, n_sink, window);
   const int64_t padded1 = (int64_t)p1.wgs_per_head * kUnitsPerWg, padded2 = (int64_t)p2.wgs_per_head * kUnitsPerWg * 2;
   if (padded2 * 5 > padded1 * 6) return p1;                                   // more than 20 % extra padding
   if ((int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
-  // Some extra padding (odd group sizes: 28 units of a G = 7 head at C = 128 fill 3.5 two-unit workgroups): the
-  // time estimates of the two grids decide.
-  if (padded2 > padded1 && c.tune_splits == 0 && p1.est_seconds < p2.est_seconds) return p1;
-  return p2;
+  if (c.tune_splits > 0) return p2;
+  // Else the estimates decide.  With some extra padding (odd group sizes: the 28 units of a G = 7 head at C = 128 fill 3.5
+  // two-unit workgroups) they are within their error of each other, and the one-unit grid has the shorter start (measured
+  // there, one unit / two units per wavefront: 43.5 / 48.3 us at 16K keys, 72 / 70 at 32K, 100 / 96 at 48K, 128 / 121 at 64K).
+  return p1.est_us < p2.est_us * (padded2 > padded1 ? 1.08 : 1.0) ? p1 : p2;
 }
 
 }  // namespace

@@ -11,7 +11,6 @@ namespace kvfold {
 
 constexpr int64_t kMaxSplitRows = 1 << 19;  // cap on S * C * Hq rows held in a cache's split workspace
 constexpr int kMaxSplits = 64;
-constexpr int kMinTilesPerSplit = 8;
 
 // What the planner needs to know of a cache (all host values).
 struct PlanCtx {
@@ -25,7 +24,7 @@ struct PlanCtx {
 struct Plan {
   int waves_per_wg;  // 4, or 8 in the fp32 kernel's large form
   int units_per_wave, units_per_head, wgs_per_head, n_splits, tiles_per_split, n_wgs, pair_order, pair_units;
-  double est_seconds;  // the planner's time estimate of the step (0 when the split count was forced)
+  double est_us;  // the planner's time estimate of the step (0 when the split count was forced)
 };
 
 int elem_size(int dtype);
