@@ -258,9 +258,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.rope_sin = opt.rope_sin;
   at.n_sink = opt.n_sink;
   at.window = (int32_t)opt.window;
-  // The bf16 attention kernel appends by itself when the cache length is a whole number of key tiles (every
-  // chunk length that is a multiple of 64), nothing has to happen to the rows on their way in, and the chunk's
-  // rows can be addressed with 32-bit byte offsets.
+  // The bf16 attention kernel appends by itself when nothing has to happen to the rows on their way in and the
+  // chunk's rows can be addressed with 32-bit byte offsets.
   const bool fused_append = fused_append_applies(pc, n_tokens, len_prev, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
@@ -276,14 +275,10 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     if (e != hipSuccess) return hip_fail(e);
   }
   if (!fused_append) {
-    e = launch_append(ap, s);
+    e = launch_append(ap, pc.storage_bits, s);  // (a storage round trip rules the fused append out)
     if (e != hipSuccess) return hip_fail(e);
   }
-  if (pc.storage_bits) {
-    e = launch_storage_roundtrip(ap, pc.storage_bits, s);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  const bool own_append = !fused_append || pc.storage_bits;  // something ran between ev[0] and the attention kernel
+  const bool own_append = !fused_append;  // something ran between ev[0] and the attention kernel
   if (ev && own_append) (void)hipEventRecord(ev[1], s);
   e = (f.dtype == KVFOLD_BF16) ? launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s) : launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
   if (e != hipSuccess) return hip_fail(e);

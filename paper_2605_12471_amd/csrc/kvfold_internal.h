@@ -97,9 +97,8 @@ struct CombineParams {
   int32_t out_is_bf16;
 };
 
-hipError_t launch_append(const AppendParams& p, hipStream_t s);
-// In-place storage round trip bf16 -> intN -> bf16 (n_bits = 4 or 8) of cache rows [len_prev, len_prev + C) of K and V.
-hipError_t launch_storage_roundtrip(const AppendParams& p, int n_bits, hipStream_t s);
+// storage_bits 4 or 8 (bf16 only): the rows take the storage round trip bf16 -> intN -> bf16 on their way; 0: they do not.
+hipError_t launch_append(const AppendParams& p, int storage_bits, hipStream_t s);
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int units_per_wave, hipStream_t s);
 // Sets the LDS size attribute of every bf16 attention kernel variant of this head dimension on the current
 // device (once per device; launches then have nothing left that could fail for a valid configuration).

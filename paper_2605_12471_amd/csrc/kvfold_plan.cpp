@@ -124,7 +124,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     const double active = std::sqrt(with_rows);
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
     const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / 5.2e6;
-    const int launches = 1 + (f.dtype != KVFOLD_BF16 || c.storage_bits ? 1 : 0) + (c.storage_bits ? 1 : 0);
+    const int launches = f.dtype != KVFOLD_BF16 || c.storage_bits ? 2 : 1;
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
       // only split counts that whole tiles can realise; the last piece may be shorter than the others, and the

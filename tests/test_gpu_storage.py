@@ -99,3 +99,27 @@ def test_roundtrip_switch_and_errors(H):
     finally:
         g.close()
         f32.close()
+
+
+@pytest.mark.parametrize("n_bits", [8, 4])
+@pytest.mark.parametrize("d,Hkv,n", [(64, 3, 1), (64, 1, 37), (128, 2, 130), (128, 1, 17000)])
+def test_rotation_and_round_trip_in_one_pass(H, oracle, d, Hkv, n, n_bits):
+    """Rows that are rotated and quantised on their way into the cache: the rotation's bf16 bits go through the round trip.
+    From one row to more rows than the launch has threads for in one go; cache bits against the oracle, output against the
+    step on queries and keys rotated beforehand."""
+    cfg = I.FoldConfig("store_rope", 64, 1, Hkv, Hkv, d, n, 0, "bf16")
+    q, k, v = I.chunk_qkv(cfg, 0, 0, n_tokens=n, token_base=0)
+    cos, sin = I.rope_tables(d, 5, n)
+    q_rot, k_rot = (torch.from_numpy(oracle.rope(t.float().numpy(), cos.numpy(), sin.numpy())).bfloat16() for t in (q, k))
+    results = []
+    for args, rope in (((q, k, v), (cos, sin)), ((q_rot, k_rot, v), None)):
+        gpu = H.GpuFold(cfg, capacity=n)
+        gpu.cache.set_storage_roundtrip(n_bits)
+        out = gpu.step(0, *args, rope=rope)
+        torch.cuda.synchronize()
+        results.append([H.bits(t[:, :n]) for t in gpu.cache.view(0)] + [H.bits(out)])
+        gpu.close()
+    for one, other in zip(*results):
+        assert np.array_equal(one, other)
+    for got, rows in zip(results[0], (k_rot, v)):
+        assert np.array_equal(got, oracle.storage_roundtrip(H.bits(rows), n_bits).transpose(1, 0, 2))
