@@ -1,0 +1,349 @@
+// Chunk-prefix attention for few rows: steps whose rows of a KV head fit one unit (C G <= 32: decoding, one token or a few
+// at a time), bf16, every key visible up to the row's own position.  The arithmetic and its rounding points are the general
+// bf16 kernel's (attn_bf16.hip): queries scaled by scale * log2(e) and rounded once more, P = 2^(S - m) rounded to bf16 for
+// P V, row sums in fp32 from the unrounded P, the reference m stale by at most 2^16.
+//
+// Such a step reads every key once and computes next to nothing: it is bound by memory when the cache is long and by what a
+// launch does once when it is short.  The general kernel gives the unit to one wavefront of four, behind a software pipeline
+// whose start and code cost more than a short step's work; here
+//  * the keys of a workgroup's piece are dealt to its four wavefronts in blocks of 32, and each runs alone: its K and V block
+//    come into LDS of its own (16 KB at D = 128, two workgroups per CU), so there is no barrier until the four results are
+//    merged through LDS;
+//  * the next K block is fetched as soon as S^T is formed, the next V block after O^T: eight wavefronts per CU, each with up
+//    to 16 KB in flight, are more than memory can deliver;
+//  * the loop is not unrolled or pipelined: code that runs once is fetched at about 3 bytes per ns.
+// One token, 32 heads on 8, D = 128, whole step, general kernel -> this one: 1K keys 12.5 -> 11.8 us (unsplit, one launch
+// instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
+// read gets 5.8 to 6.2).  Below about 8K keys a step is bound by the rate at which its launches are queued.
+#include "kvfold_internal.h"
+
+namespace kvfold {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) short short4_;
+typedef __attribute__((ext_vector_type(8))) short short8_;
+typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
+typedef __attribute__((ext_vector_type(2))) float floatx2;
+
+#define LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(uintptr_t)(p))
+
+namespace {
+
+__device__ __forceinline__ float few_pair_max(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float few_pair_sum(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// One wavefront-wide 1 KiB copy global -> LDS (see attn_bf16.hip): lane l's 16 bytes from base + off land at lds + 16 l.
+__device__ __forceinline__ void few_dma16(const unsigned char* base_uniform, unsigned off, unsigned lds_uniform) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base_uniform), "s"(lds_uniform)
+               : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void few_wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+}  // namespace
+
+template <int D>
+constexpr int few_lds_bytes() {
+  const int rings = 4 * 2 * 32 * D * 2, results = 4 * kRowsPerUnit * (D * 4 + 16) + 4 * kRowsPerUnit * 8;
+  return rings > results ? rings : results;
+}
+
+template <int D>
+__global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const unsigned lds0 = (unsigned)(uintptr_t)((unsigned char __attribute__((address_space(3)))*)smem);
+  constexpr int CH = D / 8, ROWB = D * 2, KS = D / 16, DB = D / 32;
+  constexpr int BLOCKB = 32 * ROWB;         // a K or V block
+  constexpr int RPS = 64 / CH;              // rows of a 1 KiB copy
+  constexpr int SLABS = 32 / RPS;           // copies per block
+  constexpr int KSW = CH < 16 ? CH : 16;    // K swizzle: chunk ^= row % KSW
+  constexpr int VSW = CH / 4;               // V swizzle: chunk ^= (row & 3) * VSW
+  constexpr float kStale = 16.0f;           // log2 units
+
+  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
+  if (lid >= p.n_wgs) return;
+  const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
+  const int split = lid - g * p.n_splits;   // one workgroup per KV head and piece
+
+  const int tid = threadIdx.x, l = tid & 63, hi = l >> 5, m = l & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int C = p.n_tokens, Hq = p.n_q_heads, G = p.group;
+  const int rows = C * G;                   // packed rows: row j is token j / G, head j % G of the group
+  const int row = m < rows ? m : rows - 1;
+  const int tok = (int)quot((unsigned)row, p.by_group), head = g * G + row - tok * G;
+  const int my_vis = (int)p.len_prev + tok + 1;
+
+  TileMap tm;
+  tm.ns_t = 0;
+  tm.skip = 0;
+  tm.ntiles = (int)((p.len_prev + C + kTileKeys - 1) / kTileKeys);
+  const bool fused = p.k_new != nullptr;
+  const KeyRange kr = key_range(tm, split, p.tiles_per_split, p.len_prev, C, fused);
+  const int b_all = (int)((p.len_prev + C + 31) / 32);
+  const int b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;  // blocks of 32 keys
+
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
+  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
+  const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);
+  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
+  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
+
+  // Blocks of cache rows that all exist are plain; else each row comes from the cache or the chunk, or is redirected to the
+  // piece's last row (and masked).
+  auto plain = [&](int b) __attribute__((always_inline)) -> bool {
+    const unsigned last = (unsigned)(b * 32 + 31);
+    return last <= kr.row_lim && last < kr.chunk_row0;
+  };
+  const unsigned my_lds = lds0 + (unsigned)(w * 2 * BLOCKB);
+  const int lrow = l / CH;  // + i * RPS for copy i
+  auto fetch = [&](bool is_v, int b) __attribute__((always_inline)) {
+    const unsigned lds = my_lds + (is_v ? BLOCKB : 0);
+    const unsigned char* base = is_v ? vbase : kbase;
+    const unsigned chunk = is_v ? (unsigned)((l % CH) ^ ((lrow & 3) * VSW)) : (unsigned)((l % CH) ^ (lrow % KSW));
+    if (__builtin_expect(plain(b), 1)) {
+      const unsigned off = (unsigned)(b * 32 + lrow) * ROWB;
+#pragma unroll
+      for (int i = 0; i < SLABS; ++i)
+        few_dma16(base, off + (unsigned)(i * RPS * ROWB) + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
+    } else {
+#pragma unroll 1
+      for (int i = 0; i < SLABS; ++i) {
+        const DmaRow src = dma_row(kr, b >> 1, (b & 1) * 32 + lrow + i * RPS);
+        const unsigned c16 = (is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16;
+        if (src.from_chunk)
+          few_dma16(is_v ? vnew : knew, src.row * new_stride + c16, lds + (unsigned)(i * 1024));
+        else
+          few_dma16(base, src.row * (unsigned)ROWB + c16, lds + (unsigned)(i * 1024));
+      }
+    }
+  };
+
+  // The wavefront's blocks, every fourth of the piece's, in cyclic order from a place that differs from piece to piece and
+  // head to head: pieces and heads lie powers of two apart, and workgroups in step would ask the same few memory channels
+  // for their rows.
+  const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + 3) / 4 : 0;
+  int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
+  if (n_blocks > 0) {
+    fetch(false, b);
+    fetch(true, b);
+  }
+
+  // ---- Q, scaled; lane (m, hi) holds q[m][16 ks + 8 hi + j]
+  bf16x8 qf[KS];
+  {
+    const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + ((int64_t)tok * Hq + head) * D + hi * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+    if (p.rope_cos) {
+      // rotary embedding, bit for bit that of a caller who rotates and stores bf16 (see attn_bf16.hip)
+#pragma unroll
+      for (int ks = 0; ks < KS / 2; ++ks) {
+        const float* cs = p.rope_cos + (int64_t)tok * (D / 2) + ks * 16 + hi * 8;
+        const float* sn = p.rope_sin + (int64_t)tok * (D / 2) + ks * 16 + hi * 8;
+        const bf16x8 lo = qf[ks], up = qf[ks + KS / 2];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float tl = (float)up[e] * sn[e], tu = (float)lo[e] * sn[e];
+          qf[ks][e] = (__bf16)__builtin_fmaf((float)lo[e], cs[e], -tl);
+          qf[ks + KS / 2][e] = (__bf16)__builtin_fmaf((float)up[e], cs[e], tu);
+        }
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * p.scale_log2e);
+  }
+
+  // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes per thread and turn
+  if (fused) {
+    const int r0 = split * p.copy_rows, r1 = r0 + p.copy_rows < C ? r0 + p.copy_rows : C;
+    const int nvec = (r1 > r0 ? r1 - r0 : 0) * CH;
+    for (int i = tid; i < 2 * nvec; i += 256) {
+      const bool is_v = i >= nvec;
+      const int e = is_v ? i - nvec : i, r = r0 + e / CH, c = e % CH;
+      const uintx4 x = *reinterpret_cast<const uintx4*>((is_v ? vnew : knew) + (int64_t)r * new_stride + c * 16);
+      __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(const_cast<unsigned char*>(is_v ? vbase : kbase) + (p.len_prev + r) * ROWB + c * 16));
+    }
+  }
+
+  // ---- LDS read offsets (general kernel's layouts): K fragment ks, row m, chunk 2 ks + hi; V^T by the transpose read, lane i
+  // of a 16-lane group supplies row i / 4 of a 4-row group and 4 columns
+  unsigned kaddr[KS], vaddr[DB];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) kaddr[ks] = my_lds + (unsigned)(m * ROWB + (((ks * 2 + hi) ^ (m % KSW)) * 16));
+  {
+    const int i16 = l & 15, b2 = (l >> 4) & 1, v_row = 4 * hi + (i16 >> 2);
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      vaddr[db] = my_lds + (unsigned)(BLOCKB + v_row * ROWB + (((4 * db + 2 * b2 + ((i16 & 3) >> 1)) ^ ((v_row & 3) * VSW)) * 16) + 8 * (i16 & 1));
+  }
+
+  floatx16 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+#pragma unroll 1
+  for (int i = 0; i < n_blocks; ++i) {
+    const int nb = b + 4 < b_end ? b + 4 : b_first;
+    const bool more = i + 1 < n_blocks;
+    // copies complete in order; a block that is not plain may have taken more of them than SLABS
+    if (plain(b))
+      few_wait_vm<SLABS>();
+    else
+      few_wait_vm<0>();
+    floatx16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 a = *LDS_PTR(const bf16x8, kaddr[ks]);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s, 0, 0, 0);
+    }
+    asm volatile("" : "+v"(s)::"memory");  // every read of the K block has returned
+    if (more) fetch(false, nb);
+
+    const int key0 = b * 32;
+    if (key0 + 32 > (int)p.len_prev + 1) {  // wave-uniform: some row does not see the whole block
+      const int rel = my_vis - key0 - 4 * hi;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r >> 2) + (r & 3) >= rel) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = few_pair_max(mx);
+    // only rows that ask for it move, so a row's arithmetic never depends on its wave neighbours
+    const bool mine = mx > m_run + kStale || (m_run == -INFINITY && mx > -INFINITY);
+    if (__any(mine)) {
+      const float m2 = mine ? mx : m_run;
+      const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m2);  // (without history: l = 0, O = 0)
+      m_run = m2;
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+    const float ref = m_run == -INFINITY ? 0.f : m_run;
+    uintx4 pb[2];  // P^T fragments: 8 bf16 per 16-key slab
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float a = __builtin_amdgcn_exp2f(s[2 * k] - ref), c = __builtin_amdgcn_exp2f(s[2 * k + 1] - ref);
+      l_run += a;
+      l_run += c;
+      bf16x2 pk;
+      pk[0] = (__bf16)a;
+      pk[1] = (__bf16)c;
+      pb[k >> 2][k & 3] = __builtin_bit_cast(unsigned, pk);
+    }
+
+    if (more && plain(nb))
+      few_wait_vm<SLABS>();
+    else
+      few_wait_vm<0>();
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const unsigned at = vaddr[db] + (unsigned)(16 * tt * ROWB);
+        const short4_ lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4_, at));
+        const short4_ up = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4_, at + 8 * ROWB));
+        const short8_ a8 = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a8), __builtin_bit_cast(bf16x8, pb[tt]), o[db], 0, 0, 0);
+      }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(o[db])::"memory");  // every read of the V block has returned
+    if (more) fetch(true, nb);
+    b = nb;
+  }
+
+  // ---- the four results meet in LDS: [wavefront][row][D] and [wavefront][row] (m, l)
+  few_wait_vm<0>();
+  __syncthreads();
+  constexpr int OROW = D * 4 + 16;
+  const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROW), mlbase = lds0 + (unsigned)(4 * kRowsPerUnit * OROW);
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+      floatx4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = o[db][rg * 4 + e];
+      *LDS_PTR(floatx4, obase + (unsigned)(m * OROW + (db * 32 + 8 * rg + 4 * hi) * 4)) = v;
+    }
+  const float l_tot = few_pair_sum(l_run);
+  if (hi == 0) *LDS_PTR(floatx2, mlbase + (unsigned)((w * kRowsPerUnit + m) * 8)) = floatx2{m_run, l_tot};
+  __syncthreads();
+
+  constexpr int V = D / 4;  // 16-byte column vectors of a row
+  const int c = tid % V;
+  const int64_t n_rows = (int64_t)C * Hq;
+#pragma unroll 1
+  for (int r = tid / V; r < rows; r += 256 / V) {
+    floatx2 ml[4];
+    float M = -INFINITY;
+#pragma unroll
+    for (int ww = 0; ww < 4; ++ww) {
+      ml[ww] = *LDS_PTR(const floatx2, mlbase + (unsigned)((ww * kRowsPerUnit + r) * 8));
+      M = fmaxf(M, ml[ww].x);
+    }
+    float L = 0.f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ww = 0; ww < 4; ++ww) {
+      const floatx4 x = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
+      const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);  // (0: it saw no visible key)
+      L += f * ml[ww].y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += f * x[e];
+    }
+    const int t = (int)quot((unsigned)r, p.by_group), h = g * G + r - t * G;
+    const int64_t at = (int64_t)t * Hq + h;
+    if (p.n_splits == 1) {
+      const float inv = 1.f / L;
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[e] * inv);
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at * D + c * 4) = v;
+      if (p.lse && c == 0) p.lse[(int64_t)h * C + t] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+    } else {
+      *reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + at) * D + c * 4) = acc;
+      if (c == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + at) * 2) = make_float2(M, L);
+    }
+  }
+}
+
+template <int D>
+static hipError_t prepare_few_one() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D>());
+}
+hipError_t prepare_attn_few(int head_dim) { return head_dim == 128 ? prepare_few_one<128>() : prepare_few_one<64>(); }
+
+hipError_t launch_attn_few(const AttnParams& p, int head_dim, hipStream_t s) {
+  const dim3 grid(padded_grid(p.n_wgs)), block(256);
+  if (head_dim == 128)
+    hipLaunchKernelGGL(attn_few_kernel<128>, grid, block, few_lds_bytes<128>(), s, p);
+  else if (head_dim == 64)
+    hipLaunchKernelGGL(attn_few_kernel<64>, grid, block, few_lds_bytes<64>(), s, p);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace kvfold

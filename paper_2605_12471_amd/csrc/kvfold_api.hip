@@ -129,6 +129,7 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
   // whatever a launch could still refuse (the attention kernels' LDS size) is settled here, so that a step
   // never fails with part of its work already on the stream
   if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) e = prepare_attn_bf16(cfg->head_dim);
+  if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) e = prepare_attn_few(cfg->head_dim);
   unsigned char* scratch_ptr = nullptr;
   if (e == hipSuccess && static_scratch(cfg->device, &scratch_ptr) != KVFOLD_OK) e = hipErrorInvalidSymbol;
   if (e != hipSuccess) {
@@ -280,7 +281,12 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   }
   const bool own_append = !fused_append;  // something ran between ev[0] and the attention kernel
   if (ev && own_append) (void)hipEventRecord(ev[1], s);
-  e = (f.dtype == KVFOLD_BF16) ? launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s) : launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
+  if (f.dtype != KVFOLD_BF16)
+    e = launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
+  else if (pl.few_rows)
+    e = launch_attn_few(at, f.head_dim, s);
+  else
+    e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s);
   if (e != hipSuccess) return hip_fail(e);
   if (ev) (void)hipEventRecord(ev[2], s);
   if (pl.n_splits > 1) {

@@ -75,7 +75,7 @@ KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, double with_
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
 // estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
-               int waves = kUnitsPerWg) {
+               int waves = kUnitsPerWg, bool few_rows = false) {
   const kvfold_config_t& f = c.cfg;
   const int G = f.n_q_heads / f.n_kv_heads;
   Plan pl;
@@ -84,6 +84,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.units_per_head = units_of_head(n_tokens, G);
   pl.units_per_wave = upw;
   pl.waves_per_wg = waves;
+  pl.few_rows = few_rows;
   const int per_wg = waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
@@ -119,7 +120,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     // The figures are fitted to measured steps (1 to 4096 tokens on 0 to 128K keys, all split counts): over 30 workloads
     // the choice is within 2 % of the best split count on average.
     const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
-    const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, with_rows);
+    const KernelCost k = few_rows ? KernelCost{0.54, 0.54, 0.54, 3.0, true, false} : kernel_cost(f.dtype, f.head_dim, upw, waves, with_rows);
     const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
     const double active = std::sqrt(with_rows);
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
@@ -149,11 +150,19 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
         else if (upw == 2)
           t *= mean_keys / la;  // paired units: every wavefront has the mean
       }
-      t = std::max(t, kv_us * (double)(tps * cand) / (double)ntiles * std::max(1.0, std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
-      t = t * (1.0 + 0.03 / rounds + 0.5 * (1.0 - some)) + (k.start_end + (two_per_cu ? 1.0 : 0.0)) * rounds;
+      const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;
+      if (few_rows) {
+        // 5.9 TB/s from one workgroup per CU on, less where some CUs have two and some one; near that rate both times count
+        // (measured, one token on 128K keys: 121 us with 12 pieces, 101 with 16, 93.5 with 28, 110 with 40, 95 with 64)
+        const double mem = kv_piece * (5.2 / 5.9) * (two_per_cu ? std::sqrt(slots / (double)w) : 1.0);
+        t = std::sqrt(std::sqrt(t * t * t * t + mem * mem * mem * mem));
+      } else {
+        t = std::max(t, kv_piece * std::max(1.0, std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
+      }
+      t = t * (1.0 + 0.03 / rounds + 0.5 * (1.0 - some)) + (k.start_end + (two_per_cu && !few_rows ? 1.0 : 0.0)) * rounds;
       if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 5e6 + 4.2;
-      t = std::max(t, 5.0 + 3.8 * (launches + (cand > 1 ? 1 : 0)));
-      if (t < best * 0.995) {
+      t = std::max(t, 5.0 + 3.8 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
+      if (t < best * (few_rows ? 1.0 : 0.995)) {
         best = t;
         s = cand;
       }
@@ -177,6 +186,8 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return c.tune_splits > 0 ? (w4.units_per_head <= 4 ? w4 : w8) : (w4.est_us <= w8.est_us ? w4 : w8);
   }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
+  if (window <= 0 && units_of_head(n_tokens, f.n_q_heads / f.n_kv_heads) == 1)
+    return plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, true);
   Plan p1 = plan_with(c, n_tokens, len_after, 1, n_sink, window);
   // Prefix shorter than the chunk: the causal part makes late token blocks several times as long as early
   // ones.  If the one-unit-per-wavefront grid is resident at once (two workgroups per CU), pair heavy with

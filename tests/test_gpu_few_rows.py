@@ -1,0 +1,108 @@
+"""Steps of at most 32 packed rows per KV head (decoding): every row against the oracle around the 32-key block and the
+64-key tile, with and without a split, and against the general kernel where the oracle has no answer."""
+import math
+
+import pytest
+import torch
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import inputs as I
+from test_gpu_parity_small import H, _run_case  # noqa: F401  (H: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,Hkv", [(1, 3), (3, 2), (4, 2), (7, 1), (32, 1)])
+@pytest.mark.parametrize("splits", [0, 1, 2, 5])
+def test_edges_of_blocks_tiles_and_rows(H, oracle, d, G, Hkv, splits):
+    """From an empty cache on: lengths that straddle, meet and pass the edges of blocks and tiles, one row to 32."""
+    n = 32 // G
+    cfg = I.FoldConfig("few", 65, 1, G * Hkv, Hkv, d, 200, 0, "bf16")
+    _run_case(H, oracle, cfg, [1, n, 31, 1, n, 61 - n, 1, 1, 200, n, 1, max(1, n - 1), 1], splits=splits)
+
+
+@pytest.mark.parametrize("profile", sorted(I.LOGIT_PROFILES))
+def test_logit_jumps(H, oracle, profile):
+    cfg = I.FoldConfig("few_jump", 66, 1, 4, 1, 128, 400, 0, "bf16")
+    _run_case(H, oracle, cfg, [400, 8, 1, 7], profile=profile, check_lse=False)
+
+
+def _filled(Hq, Hkv, d, n, L):
+    g = torch.Generator("cuda").manual_seed(L)
+    cache = kv.KvFoldCache(1, Hq, Hkv, d, n, L + n, "bf16")
+    for rows in cache.view(0):
+        rows[:, :L].normal_(generator=g)
+    cache.set_length(-1, L)
+    return cache, [torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv)]
+
+
+def _step(cache, L, args, **kw):
+    out = torch.full_like(args[0], 7.0)
+    cache.set_length(0, L)
+    cache.step(0, *args, out, pos_offset=L, **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("splits", [1, 4])
+def test_append_inside_or_before(splits):
+    """The same bits, outputs and cache rows, whether the kernel appends by itself or reads rows appended before."""
+    L, n = 1000 + 13, 8
+    cache, args = _filled(8, 2, 128, n, L)
+    cache.set_tuning(kv.TUNE_SPLITS, splits)
+    one = _step(cache, L, args)
+    rows = [t[:, L:L + n].clone() for t in cache.view(0)]
+    for t in cache.view(0):
+        t[:, L:L + n] = 0
+    cache.set_tuning(kv.TUNE_FUSED_APPEND, 1)
+    assert torch.equal(one, _step(cache, L, args))
+    for t, r, new in zip(cache.view(0), rows, args[1:]):
+        assert torch.equal(t[:, L:L + n], r) and torch.equal(r, new.transpose(0, 1))
+    cache.close()
+
+
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_that_are_not_finite(d, splits):
+    """Not a number where the general kernel has none, infinite where it is, equal to rounding elsewhere: an infinite and a
+    NaN value, a key at -inf, a NaN key, a NaN query."""
+    L, n = 700, 4
+    cache, args = _filled(16, 4, d, n, L)
+    K, V = cache.view(0)
+    args[0][:, :4, 3] = -args[0][:, :4, 3].abs() - 0.1  # KV head 0: its queries see key 40 at -inf
+    K[0, 40, 3] = math.inf
+    V[1, 300, 5] = math.inf
+    V[1, 301, 6] = math.nan
+    K[2, 500, 0] = math.nan
+    args[0][2, 13] = math.nan
+    cache.set_tuning(kv.TUNE_SPLITS, splits)
+    got = _step(cache, L, args).float()
+    cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, 1)
+    want = _step(cache, L, args).float()
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    assert torch.isnan(got[:, 8:12]).all() and torch.isinf(got[:, 4:8, 5]).all() and torch.isfinite(got[:, :4]).all()
+    ok = torch.isfinite(want)
+    # each is a sum of values below 5 with weights rounded to 2^-9 and an output rounded to 2^-9 of its size
+    assert (got - want)[ok].abs().max() <= 2e-2
+    cache.close()
+
+
+def test_graph_replays():
+    L = 5000
+    cache, args = _filled(32, 8, 128, 1, L)
+    want = _step(cache, L, args)
+    out = torch.empty_like(want)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    cache.set_length(0, L)
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            cache.step(0, *args, out, pos_offset=L)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(_step(cache, L, args), want)
+    cache.close()
