@@ -65,8 +65,8 @@ KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, double with_
   const double d = head_dim / 128.0;
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
-    if (head_dim == 64) return upw == 2 ? KernelCost{0.80, 0.95, 0, 10.0, false, false} : KernelCost{0.70, 0.71, 1.12, 6.2, true, false};
-    return upw == 2 ? KernelCost{1.09, 1.53, 0, 10.0, false, false} : KernelCost{0.85, 0.94, 1.81, 6.2, true, false};
+    if (head_dim == 64) return upw == 2 ? KernelCost{0.80, 0.95, 0, 10.0, false, false} : KernelCost{0.70, 0.71, 1.25, 6.2, true, false};
+    return upw == 2 ? KernelCost{1.09, 1.53, 0, 10.0, false, false} : KernelCost{0.85, 0.94, 1.92, 6.2, true, false};
   }
   if (waves == 8) return {(4.8 + 2.1 * with_rows) * d, 8.6 * d, 0, 10.0, false, true};
   return {7.6 * d, 7.6 * d, 12.2 * d, 7.0, head_dim == 64, true};
@@ -203,12 +203,13 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   const Plan p2 = plan_with(c, n_tokens, len_after, 2, n_sink, window);
   const int64_t padded1 = (int64_t)p1.wgs_per_head * kUnitsPerWg, padded2 = (int64_t)p2.wgs_per_head * kUnitsPerWg * 2;
   if (padded2 * 5 > padded1 * 6) return p1;                                   // more than 20 % extra padding
-  if ((int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
+  if (p2.n_splits == 1 && (int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
   if (c.tune_splits > 0) return p2;
-  // Else the estimates decide.  With some extra padding (odd group sizes: the 28 units of a G = 7 head at C = 128 fill 3.5
-  // two-unit workgroups) they are within their error of each other, and the one-unit grid has the shorter start (measured
-  // there, one unit / two units per wavefront: 43.5 / 48.3 us at 16K keys, 72 / 70 at 32K, 100 / 96 at 48K, 128 / 121 at 64K).
-  return p1.est_us < p2.est_us * (padded2 > padded1 ? 1.08 : 1.0) ? p1 : p2;
+  // Else the estimates decide.  Where units straddle tokens and the two-unit grid pads more (the 28 units of a G = 7 head at
+  // C = 128 fill 3.5 two-unit workgroups) they are within their error of each other, and the one-unit grid has the shorter
+  // start (measured there, one unit / two units per wavefront: 71 / 75 us at 32K keys, 100 / 96 at 48K, 126 / 121 at 64K).
+  const bool close = padded2 > padded1 && kRowsPerUnit % (f.n_q_heads / f.n_kv_heads) != 0;
+  return p1.est_us < p2.est_us * (close ? 1.06 : 1.0) ? p1 : p2;
 }
 
 }  // namespace
