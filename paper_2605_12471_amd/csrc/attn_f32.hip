@@ -11,8 +11,8 @@
 // 0.4 to 0.9 of what the fp32 instructions left (relative 2-norm, N(0,1) inputs: 1.9e-7 ... 6.8e-7, before 2.8e-7 ...
 // 7.3e-7; queries 8 times larger: 4.1e-7 ... 9.4e-7, before 8.7e-7 ... 2.7e-6).
 // 512 tokens on 16K keys, 28 heads: 1160 us before (106 TFLOP/s), 575 us now (212; the fp32 instructions' peak is 157).
-// What bounds it: the matrix pipe is busy half of the time; the split and the softmax take a third of the issue slots, and
-// the two wavefronts of a SIMD do not overlap them perfectly.
+// What bounds it: 212 TFLOP/s are 1.27 PFLOP/s of bf16 products, near the 1.4 that the bf16 kernel reaches on the
+// power-limited chip; the split and the softmax take a third of the issue slots.
 // K and V are split once per workgroup, on their way into LDS, where a tile's terms lie in the order in which the matrix
 // instructions read their fragments: V is transposed by the split (a lane gathers 8 keys of one column), so that all
 // fragment reads are 16 bytes per lane.  P is split in registers.
