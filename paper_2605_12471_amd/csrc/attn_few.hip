@@ -331,7 +331,15 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
 
 template <int D>
 static hipError_t prepare_few_one() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D>());
+  // once per device (idempotent; a benign race at worst sets it twice)
+  static bool attr_done[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (attr_done[dev]) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D>());
+  if (e == hipSuccess) attr_done[dev] = true;
+  return e;
 }
 hipError_t prepare_attn_few(int head_dim) { return head_dim == 128 ? prepare_few_one<128>() : prepare_few_one<64>(); }
 
