@@ -37,7 +37,7 @@ PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA (256 CU x 4096 FLOP/clk x 2
 PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 
-KERNEL_SOURCES = ("attn_bf16.hip", "kvfold_internal.h", "kvfold_consts.h")
+KERNEL_SOURCES = ("attn_bf16.hip", "wave_ops.h", "kvfold_internal.h", "kvfold_consts.h")
 
 
 def kernel_source_hash():

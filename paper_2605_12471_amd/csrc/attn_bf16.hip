@@ -55,6 +55,7 @@
 #include <type_traits>
 
 #include "kvfold_internal.h"
+#include "wave_ops.h"
 
 namespace kvfold {
 
@@ -66,34 +67,11 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 
-#define LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(uintptr_t)(p))
-
-__device__ __forceinline__ float pair_max(float x) {
-  // lanes l and l^32 exchange x; both end with the maximum
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float pair_sum(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// One wavefront-wide 1 KiB copy global -> LDS: lane l's 16 bytes, read from base + off, land at
-// lds_base + 16*l.  The compiler is not told about the LDS write; ordering is done by hand with
-// wait_vm<> + barrier.
-__device__ __forceinline__ void dma16(const unsigned char* base_uniform, unsigned off, unsigned lds_base_uniform) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base_uniform), "s"(lds_base_uniform)
-               : "memory", "m0");
-}
 // Wait until at most N LDS reads are outstanding (compiler-visible, so that it adds none of its own
 // for fragments covered by this wait).  gfx9 encoding: vmcnt and expcnt left at their maxima.
 template <int N>
 __device__ __forceinline__ void wait_lds() {
   __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // MFMA issued by hand so that the register files are under control: S^T accumulates in VGPRs

@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "kvfold_internal.h"
+#include "wave_ops.h"
 
 namespace kvfold {
 
@@ -29,15 +30,6 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
-
-__device__ __forceinline__ float pair_max_f(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float pair_sum_f(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 constexpr int kTerms = 3;
 // Eight values as three fragments of bf16 terms.  (A value that is not finite leaves NaN in the lower terms.)
@@ -340,7 +332,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
     float mx = s[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    mx = pair_max_f(mx) * sc;
+    mx = pair_max(mx) * sc;
     if (__any(mx > m_run + kThresh)) {
       // only rows that asked for it move, so a row's arithmetic never depends on its wave neighbours
       const float m2 = (mx > m_run + kThresh) ? mx : m_run;
@@ -431,7 +423,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   }
 
   // ---- epilogue
-  const float l_tot = pair_sum_f(l_run);
+  const float l_tot = pair_sum(l_run);
   if (!store_ok) return;
   const int64_t n_rows = (int64_t)C * Hq;
   const int64_t row = (int64_t)tok * Hq + head;

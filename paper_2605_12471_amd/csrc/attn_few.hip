@@ -16,6 +16,7 @@
 // instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
 // read gets 5.8 to 6.2).  Below about 8K keys a step is bound by the rate at which its launches are queued.
 #include "kvfold_internal.h"
+#include "wave_ops.h"
 
 namespace kvfold {
 
@@ -28,30 +29,6 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(2))) float floatx2;
-
-#define LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(uintptr_t)(p))
-
-namespace {
-
-__device__ __forceinline__ float few_pair_max(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float few_pair_sum(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// One wavefront-wide 1 KiB copy global -> LDS (see attn_bf16.hip): lane l's 16 bytes from base + off land at lds + 16 l.
-__device__ __forceinline__ void few_dma16(const unsigned char* base_uniform, unsigned off, unsigned lds_uniform) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base_uniform), "s"(lds_uniform)
-               : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void few_wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-}  // namespace
 
 template <int D>
 constexpr int few_lds_bytes() {
@@ -115,16 +92,16 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
       const unsigned off = (unsigned)(b * 32 + lrow) * ROWB;
 #pragma unroll
       for (int i = 0; i < SLABS; ++i)
-        few_dma16(base, off + (unsigned)(i * RPS * ROWB) + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
+        dma16(base, off + (unsigned)(i * RPS * ROWB) + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
     } else {
 #pragma unroll 1
       for (int i = 0; i < SLABS; ++i) {
         const DmaRow src = dma_row(kr, b >> 1, (b & 1) * 32 + lrow + i * RPS);
         const unsigned c16 = (is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16;
         if (src.from_chunk)
-          few_dma16(is_v ? vnew : knew, src.row * new_stride + c16, lds + (unsigned)(i * 1024));
+          dma16(is_v ? vnew : knew, src.row * new_stride + c16, lds + (unsigned)(i * 1024));
         else
-          few_dma16(base, src.row * (unsigned)ROWB + c16, lds + (unsigned)(i * 1024));
+          dma16(base, src.row * (unsigned)ROWB + c16, lds + (unsigned)(i * 1024));
       }
     }
   };
@@ -203,9 +180,9 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     const bool more = i + 1 < n_blocks;
     // copies complete in order; a block that is not plain may have taken more of them than SLABS
     if (plain(b))
-      few_wait_vm<SLABS>();
+      wait_vm<SLABS>();
     else
-      few_wait_vm<0>();
+      wait_vm<0>();
     floatx16 s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -227,7 +204,7 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     float mx = s[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    mx = few_pair_max(mx);
+    mx = pair_max(mx);
     // only rows that ask for it move, so a row's arithmetic never depends on its wave neighbours
     const bool mine = mx > m_run + kStale || (m_run == -INFINITY && mx > -INFINITY);
     if (__any(mine)) {
@@ -254,9 +231,9 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     }
 
     if (more && plain(nb))
-      few_wait_vm<SLABS>();
+      wait_vm<SLABS>();
     else
-      few_wait_vm<0>();
+      wait_vm<0>();
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
@@ -274,7 +251,7 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   }
 
   // ---- the four results meet in LDS: [wavefront][row][D] and [wavefront][row] (m, l)
-  few_wait_vm<0>();
+  wait_vm<0>();
   __syncthreads();
   constexpr int OROW = D * 4 + 16;
   const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROW), mlbase = lds0 + (unsigned)(4 * kRowsPerUnit * OROW);
@@ -287,7 +264,7 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
       for (int e = 0; e < 4; ++e) v[e] = o[db][rg * 4 + e];
       *LDS_PTR(floatx4, obase + (unsigned)(m * OROW + (db * 32 + 8 * rg + 4 * hi) * 4)) = v;
     }
-  const float l_tot = few_pair_sum(l_run);
+  const float l_tot = pair_sum(l_run);
   if (hi == 0) *LDS_PTR(floatx2, mlbase + (unsigned)((w * kRowsPerUnit + m) * 8)) = floatx2{m_run, l_tot};
   __syncthreads();
 
