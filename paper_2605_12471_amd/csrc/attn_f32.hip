@@ -17,8 +17,9 @@
 // instructions read their fragments: V is transposed by the split (a lane gathers 8 keys of one column), so that all
 // fragment reads are 16 bytes per lane.  P is split in registers.
 //
-// The terms of an infinity would be NaN.  A workgroup that met a key or value row with a number that is not finite, and a
-// wavefront with such a query, does its work once more with the fp32 instructions, operands straight from memory.
+// The terms of an infinity would be NaN, and sums of terms of values above 2^60 could overflow.  A workgroup that met a key or
+// value row with such a number, and a wavefront with such a query, does its work once more with the fp32 instructions,
+// operands straight from memory.
 #include <type_traits>
 
 #include "kvfold_internal.h"
@@ -32,6 +33,11 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
 
 constexpr int kTerms = 3;
+// What the terms can hold: magnitudes below 2^60 (and a softmax scale below 2^20).  The products of a row's terms then stay
+// below 2^127 and no partial sum overflows that the fp32 instructions' own sum would not; above, terms of opposite sign could
+// meet as inf - inf where the product is infinite and the weight 0.  A sum of values times kProbe stays finite
+// exactly if none of them reaches 2^60 (several that come within a factor of 128 may pass for one that does).
+constexpr float kProbe = 0x1p68f, kMaxScale = 0x1p20f;
 // Eight values as three fragments of bf16 terms.  (A value that is not finite leaves NaN in the lower terms.)
 __device__ __forceinline__ void split8(const float (&x)[8], uintx4 (&t)[kTerms]) {
 #pragma unroll
@@ -68,7 +74,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   constexpr float kThresh = 8.0f;
 
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUFB];
-  __shared__ int odd_value;  // a tile holds a value that is not finite
+  __shared__ int odd_value;  // a tile holds a value that the terms cannot
 
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
   const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
@@ -179,7 +185,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
         uintx4 t[kTerms];
         split8(stage[it], t);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) probe = __builtin_fmaf(stage[it][j], 0.f, probe);  // NaN from the first value that is not finite
+        for (int j = 0; j < 8; ++j) probe = __builtin_fmaf(stage[it][j], kProbe, probe);
         int at;
         if (is_v) {
           const int vi = it * NT + tid - (ITEMS >= NT ? 0 : NT - ITEMS);
@@ -192,7 +198,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
         for (int i = 0; i < kTerms; ++i) *reinterpret_cast<uintx4*>(buf + i * TERMB + at) = t[i];
       }
-      if (!(probe == 0.f)) odd_value = 1;
+      if (!(fabsf(probe) < INFINITY)) odd_value = 1;
     }
   };
 
@@ -231,9 +237,9 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
     for (int ks = 0; ks < KS; ++ks) {
       split8(raw[ks], qt[ks]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) probe = __builtin_fmaf(raw[ks][e], 0.f, probe);
+      for (int e = 0; e < 8; ++e) probe = __builtin_fmaf(raw[ks][e], kProbe, probe);
     }
-    odd_q = __any(!(probe == 0.f));
+    odd_q = __any(!(fabsf(probe) < INFINITY)) || !(p.scale_log2e < kMaxScale);
   }
 
   floatx16 o[DB];

@@ -21,17 +21,18 @@ def test_tile_edges(H, oracle, d, waves, chunks, splits):
     _run_case(H, oracle, cfg, chunks, splits=splits, upw=waves)
 
 
-def _step(q, k, v, waves, splits):
+def _step(q, k, v, waves, splits, want_lse=False):
     n, hq, d = q.shape
     hkv = k.shape[1]
     cache = kv.KvFoldCache(1, hq, hkv, d, n, n, "f32")
     cache.set_tuning(0, splits)
     cache.set_tuning(1, waves)
     out = torch.empty_like(q)
-    cache.step(0, q, k, v, out, pos_offset=0)
+    lse = torch.empty((hq, n), device="cuda") if want_lse else None
+    cache.step(0, q, k, v, out, pos_offset=0, lse=lse)
     torch.cuda.synchronize()
     cache.close()
-    return out
+    return (out, lse) if want_lse else out
 
 
 def _reference(q, k, v):
@@ -95,3 +96,18 @@ def test_largest_finite_values(d):
     out = _step(q, k, v, 1, 1).cpu().double()[:, 0, 5]
     ref = big / torch.arange(1, n + 1, dtype=torch.float64)
     assert ((out - ref).abs() <= 8 * 2.0 ** -24 * ref).all()
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_finite_values_whose_product_overflows(d, waves):
+    """Key 20 is -FLT_MAX in one column and the queries 2^24 there: its logit is -infinity in 32 bits, its weight 0, and
+    every row keeps the finite result of the other keys (an error of the other logits is one of 128 products: 1e-5)."""
+    n, hq, hkv = 70, 4, 2
+    q, k, v = _random(n, hq, d, 8), _random(n, hkv, d, 9), _random(n, hkv, d, 10)
+    k[:, :, 3] = 0.0
+    k[20, :, 3] = -3.4028234663852886e38
+    q[:, :, 3] = 2.0 ** 24
+    out, ref = _step(q, k, v, waves, 1).cpu().double(), _reference(q, k, v)
+    assert torch.isfinite(out).all()
+    assert (out - ref).abs().max() <= 1e-5
