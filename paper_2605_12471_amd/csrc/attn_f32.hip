@@ -3,7 +3,7 @@
 // group) rows, the wavefronts of a workgroup share the K/V tiles of one KV head through LDS, logits are formed transposed
 // (S^T = K Q^T, keys as MFMA rows) so that a lane holds logits of one query only, and S^T feeds O^T = V^T P^T directly.
 //
-// The products run on the bf16 matrix instructions, on operands split into three bf16 terms: x = x0 + x1 + x2 exactly (x0
+// The products run on the bf16 matrix instructions, on operands split into three bf16 terms: x = x0 + x1 + x2 (x0
 // the upper half of x's bits, x1 the next 8 bits rounded, x2 the rest, which fits), and
 //     x y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + two terms below 2^-23 of x y and one below 2^-31,
 // summed in fp32 like the fp32 instruction's own products.  Six 32x32x16 bf16 instructions take 192 cycles where the eight
@@ -13,6 +13,7 @@
 // 512 tokens on 16K keys, 28 heads: 1160 us before (106 TFLOP/s), 575 us now (212; the fp32 instructions' peak is 157).
 // What bounds it: 212 TFLOP/s are 1.27 PFLOP/s of bf16 products, near the 1.4 that the bf16 kernel reaches on the
 // power-limited chip; the split and the softmax take a third of the issue slots.
+// The terms are exact for every value that fp32 holds below 2^60 (see kProbe and kValueScale).
 // K and V are split once per workgroup, on their way into LDS, where a tile's terms lie in the order in which the matrix
 // instructions read their fragments: V is transposed by the split (a lane gathers 8 keys of one column), so that all
 // fragment reads are 16 bytes per lane.  P is split in registers.
@@ -38,6 +39,11 @@ constexpr int kTerms = 3;
 // meet as inf - inf where the product is infinite and the weight 0.  A sum of values times kProbe stays finite
 // exactly if none of them reaches 2^60 (several that come within a factor of 128 may pass for one that does).
 constexpr float kProbe = 0x1p68f, kMaxScale = 0x1p20f;
+// Values are split 2^23 times as large, so that their last bit, 2^-149 at the least, lies in the range of bf16; the sums of
+// weights (at most 2^8) times values stay below 2^(8 + 83 + 24).  Queries and keys need no such factor: what a tiny one of
+// them loses, at most 2^-126, moves a logit by less than 2^-38.  Nor do weights: one below 2^-103 loses at most
+// 2^-126 of a sum of weights that is at least 1 (below 2^-126 it is 0).
+constexpr float kValueScale = 0x1p23f, kValueUnscale = 0x1p-23f;
 // Eight values as three fragments of bf16 terms.  (A value that is not finite leaves NaN in the lower terms.)
 __device__ __forceinline__ void split8(const float (&x)[8], uintx4 (&t)[kTerms]) {
 #pragma unroll
@@ -182,10 +188,14 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       float probe = 0.f;
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
-        uintx4 t[kTerms];
-        split8(stage[it], t);
 #pragma unroll
         for (int j = 0; j < 8; ++j) probe = __builtin_fmaf(stage[it][j], kProbe, probe);
+        if (is_v) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) stage[it][j] *= kValueScale;
+        }
+        uintx4 t[kTerms];
+        split8(stage[it], t);
         int at;
         if (is_v) {
           const int vi = it * NT + tid - (ITEMS >= NT ? 0 : NT - ITEMS);
@@ -417,9 +427,11 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
     put(h + 1, true);
   }
   __syncthreads();
+  float unscale = kValueUnscale;
   if (__builtin_expect((odd_q || __builtin_amdgcn_readfirstlane(odd_value)) && !idle, 0)) {
     // once more, with the fp32 instructions
     clear();
+    unscale = 1.f;
 #pragma unroll 1
     for (int h = h_begin; h < h_end && first_key(h) < vis_last; ++h) {
       logits(h, in_fp32);
@@ -434,7 +446,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   const int64_t n_rows = (int64_t)C * Hq;
   const int64_t row = (int64_t)tok * Hq + head;
   if (p.n_splits == 1) {
-    const float inv = 1.f / l_tot;
+    const float inv = unscale / l_tot;
     float* orow = reinterpret_cast<float*>(p.out) + row * D;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -450,7 +462,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg)
         *reinterpret_cast<float4*>(prow + db * 32 + 8 * rg + 4 * hi) =
-            make_float4(o[db][rg * 4 + 0], o[db][rg * 4 + 1], o[db][rg * 4 + 2], o[db][rg * 4 + 3]);
+            make_float4(o[db][rg * 4 + 0] * unscale, o[db][rg * 4 + 1] * unscale, o[db][rg * 4 + 2] * unscale, o[db][rg * 4 + 3] * unscale);
     if (hi == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + row) * 2) = make_float2(m_run, l_tot);
   }
 }

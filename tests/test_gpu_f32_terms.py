@@ -111,3 +111,17 @@ def test_finite_values_whose_product_overflows(d, waves):
     out, ref = _step(q, k, v, waves, 1).cpu().double(), _reference(q, k, v)
     assert torch.isfinite(out).all()
     assert (out - ref).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_smallest_values_keep_their_bits(d, waves):
+    """Values of 2^-120 come out as the same values of ordinary size do, 2^-120 smaller: both are sums of the same numbers,
+    which differ by roundings of 2^-24 of the largest (here allowed sixteen).  A third term below the smallest bf16 number
+    would leave 2^-14 of a value."""
+    n, hq, hkv = 100, 4, 2
+    q, k = _random(n, hq, d, 11), _random(n, hkv, d, 12)
+    v = _random(n, hkv, d, 13)
+    v = torch.copysign(1.0 + torch.frac(v.abs()), v)
+    small, plain = (_step(q, k, v * s, waves, 1).cpu().double() / s for s in (2.0 ** -120, 1.0))
+    assert (small - plain).abs().max() <= 2.0 ** -20
