@@ -3,15 +3,20 @@
 // group) rows, the wavefronts of a workgroup share the K/V tiles of one KV head through LDS, logits are formed transposed
 // (S^T = K Q^T, keys as MFMA rows) so that a lane holds logits of one query only, and S^T feeds O^T = V^T P^T directly.
 //
-// The products run on the bf16 matrix instructions, on operands split into three bf16 terms: x = x0 + x1 + x2 (x0
-// the upper half of x's bits, x1 the next 8 bits rounded, x2 the rest, which fits), and
-//     x y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + two terms below 2^-23 of x y and one below 2^-31,
-// summed in fp32 like the fp32 instruction's own products.  Six 32x32x16 bf16 instructions take 192 cycles where the eight
-// 32x32x2 fp32 ones that they replace take 512, and round the sum less often: against 64 bits the outputs are off by
-// 0.4 to 0.9 of what the fp32 instructions left (relative 2-norm, N(0,1) inputs: 1.9e-7 ... 6.8e-7, before 2.8e-7 ...
-// 7.3e-7; queries 8 times larger: 4.1e-7 ... 9.4e-7, before 8.7e-7 ... 2.7e-6).
-// 512 tokens on 16K keys, 28 heads: 1160 us before (106 TFLOP/s), 575 us now (212; the fp32 instructions' peak is 157).
-// What bounds it: 212 TFLOP/s are 1.27 PFLOP/s of bf16 products, near the 1.4 that the bf16 kernel reaches on the
+// The products run on the bf16 matrix instructions, on operands split into three bf16 terms: x = x0 + x1 + x2, each term what
+// is left of x rounded to nearest (sums of shorter floats: Dekker 1971; of bf16 numbers: Henry, Tang and Heinecke 2019), so that
+// |x1| <= 2^-8 |x| and |x2| <= 2^-17 |x|, and
+//     x y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + (x1 y2 + x2 y1, each at most 2^-25) + x2 y2 (2^-34),
+// summed in fp32 like the fp32 instruction's own products.  Logits take all but the last: an error of a logit is one of its
+// weight, and a logit may be a single large product.  P V takes the first six: what the others add is less than the row sums'
+// rounding.  Seven bf16 32x32x16 instructions on average take 224 cycles where the eight 32x32x2 fp32 ones that they replace
+// take 512, and round the sums less often.  Error against 64 bits, relative to what the fp32 instructions left (60 pairs of
+// shape and distribution, N(0,1), larger, sparse and tiny values, geometric means): outputs 0.57 (2-norm) and 0.56 (largest),
+// log-sum-exp 0.79; log-sum-exp of a single product 3.76e-8 against 3.76e-8 (with six products 3.80e-8, and with terms rounded
+// towards zero 4.32e-8), output of a single product 7.5e-8 against 13.3e-8.
+// 512 tokens on 16K keys, 28 heads: 1145 us with the fp32 instructions (108 TFLOP/s, of 157), 663 us now (187); six
+// products everywhere would take 585, eight 730.
+// What bounds it: 187 TFLOP/s are 1.31 PFLOP/s of bf16 products, near the 1.4 that the bf16 kernel reaches on the
 // power-limited chip; the split and the softmax take a third of the issue slots.
 // The terms are exact for every value that fp32 holds below 2^60 (see kProbe and kValueScale).
 // K and V are split once per workgroup, on their way into LDS, where a tile's terms lie in the order in which the matrix
@@ -44,20 +49,24 @@ constexpr float kProbe = 0x1p68f, kMaxScale = 0x1p20f;
 // them loses, at most 2^-126, moves a logit by less than 2^-38.  Nor do weights: one below 2^-103 loses at most
 // 2^-126 of a sum of weights that is at least 1 (below 2^-126 it is 0).
 constexpr float kValueScale = 0x1p23f, kValueUnscale = 0x1p-23f;
-// Eight values as three fragments of bf16 terms.  (A value that is not finite leaves NaN in the lower terms.)
+// Eight values as three fragments of bf16 terms, each rounded to nearest, so that the second is at most 2^-8 and the third at
+// most 2^-17 of the value.  (A value that is not finite leaves NaN in the lower terms.)
 __device__ __forceinline__ void split8(const float (&x)[8], uintx4 (&t)[kTerms]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const unsigned a = __float_as_uint(x[2 * j]), b = __float_as_uint(x[2 * j + 1]);
-    t[0][j] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // upper halves: rounded towards zero, so never to infinity
-    const float ra = x[2 * j] - __uint_as_float(a & 0xffff0000u), rb = x[2 * j + 1] - __uint_as_float(b & 0xffff0000u);
-    bf16x2 h;
-    h[0] = (__bf16)ra;
-    h[1] = (__bf16)rb;
-    const unsigned h2 = __builtin_bit_cast(unsigned, h);
-    t[1][j] = h2;
-    const float qa = ra - __uint_as_float(h2 << 16), qb = rb - __uint_as_float(h2 & 0xffff0000u);  // exact, at most 8 bits
-    t[2][j] = __builtin_amdgcn_perm(__float_as_uint(qb), __float_as_uint(qa), 0x07060302u);
+    float a = x[2 * j], b = x[2 * j + 1];
+#pragma unroll
+    for (int i = 0; i < kTerms; ++i) {
+      bf16x2 h;
+      h[0] = (__bf16)a;
+      h[1] = (__bf16)b;
+      const unsigned h2 = __builtin_bit_cast(unsigned, h);
+      t[i][j] = h2;
+      if (i + 1 < kTerms) {
+        a -= __uint_as_float(h2 << 16);
+        b -= __uint_as_float(h2 & 0xffff0000u);
+      }
+    }
   }
 }
 __device__ __forceinline__ floatx16 mfma16(const uintx4& a, const uintx4& b, const floatx16& c) {
@@ -291,6 +300,8 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
         for (int i = 0; i < kTerms; ++i)
           a[i] = *reinterpret_cast<const uintx4*>(buf + k_at[ks & 3] + (ks >> 2) * 4096 + i * TERMB);
+        sm = mfma16(a[2], qt[ks][1], sm);
+        sm = mfma16(a[1], qt[ks][2], sm);
         sm = mfma16(a[2], qt[ks][0], sm);
         sm = mfma16(a[1], qt[ks][1], sm);
         sm = mfma16(a[0], qt[ks][2], sm);

@@ -125,3 +125,25 @@ def test_smallest_values_keep_their_bits(d, waves):
     v = torch.copysign(1.0 + torch.frac(v.abs()), v)
     small, plain = (_step(q, k, v * s, waves, 1).cpu().double() / s for s in (2.0 ** -120, 1.0))
     assert (small - plain).abs().max() <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_single_products_are_rounded_once(d, waves):
+    """Row i's query has one column, which only key i has too: its log-sum-exp is one product.  The six roundings on the way
+    (product, scale, its constant, reference + log, ln 2, its constant) are each at most 2^-24 and on average nothing, where
+    products of second and third terms would be missing by 4 x 2^-24 of the product, all of one sign for these numbers:
+    the lower 16 bits of a factor are 2^-7 - 2^-16 - something, as second and third term 2^-7 - 2^-15 and 2^-16 - something."""
+    n, h = 64, 8
+    gen = torch.Generator().manual_seed(14)
+    def factor():
+        return 1.0 + torch.randint(0, 16, (n, h), generator=gen) / 128 + 2.0 ** -7 - 2.0 ** -16 - torch.randint(0, 16, (n, h), generator=gen) * 2.0 ** -23
+    x, y = factor() * 512.0, factor()
+    q, k = torch.zeros(n, h, d), torch.zeros(n, h, d)
+    i = torch.arange(n)
+    q[i, :, i], k[i, :, i] = x, y
+    lse = _step(q.cuda(), k.cuda(), _random(n, h, d, 15), waves, 1, want_lse=True)[1].cpu().double().T
+    exact = x.double() * y.double() / math.sqrt(d)
+    err = lse / exact - 1.0
+    assert err.abs().max() <= 6 * 2.0 ** -24
+    assert err.mean().abs() <= 2.0 ** -24
