@@ -23,9 +23,12 @@
 // instructions read their fragments: V is transposed by the split (a lane gathers 8 keys of one column), so that all
 // fragment reads are 16 bytes per lane.  P is split in registers.
 //
-// The terms of an infinity would be NaN, and sums of terms of values above 2^60 could overflow.  A workgroup that met a key or
-// value row with such a number, and a wavefront with such a query, does its work once more with the fp32 instructions,
-// operands straight from memory.
+// The terms of an infinity would be NaN, and sums of terms of values above 2^60 could overflow.  A key whose K or V row holds
+// such a number is left out of its tile and added after the piece's end with the fp32 instructions, operands straight from
+// memory: rows that do not see it keep their bits.  A workgroup that met more such tiles than it can list, and the rows
+// of a wavefront with such a query, take the whole piece that way.  Measured on 512 tokens on 16K keys (677 us): one NaN key
+// 700 us, 24 infinite values 765, one in every tile 2350 (which the fp32 instructions alone did in 1142), a NaN query 1594;
+// with the whole piece done again for one such key it was 5100.
 #include <type_traits>
 
 #include "kvfold_internal.h"
@@ -43,7 +46,7 @@ constexpr int kTerms = 3;
 // below 2^127 and no partial sum overflows that the fp32 instructions' own sum would not; above, terms of opposite sign could
 // meet as inf - inf where the product is infinite and the weight 0.  A sum of values times kProbe stays finite
 // exactly if none of them reaches 2^60 (several that come within a factor of 128 may pass for one that does).
-constexpr float kProbe = 0x1p68f, kMaxScale = 0x1p20f;
+constexpr float kLargest = 0x1p60f, kProbe = 0x1p68f, kMaxScale = 0x1p20f;
 // Values are split 2^23 times as large, so that their last bit, 2^-149 at the least, lies in the range of bf16; the sums of
 // weights (at most 2^8) times values stay below 2^(8 + 83 + 24).  Queries and keys need no such factor: what a tiny one of
 // them loses, at most 2^-126, moves a logit by less than 2^-38.  Nor do weights: one below 2^-103 loses at most
@@ -89,7 +92,12 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   constexpr float kThresh = 8.0f;
 
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUFB];
-  __shared__ int odd_value;  // a tile holds a value that the terms cannot
+  // keys with a number that the terms cannot hold: by tile, for the two tiles in flight and one being cleared, and the list
+  // of tiles with such keys
+  constexpr int kOddList = 32;
+  __shared__ unsigned odd_keys[3];
+  __shared__ int odd_tiles;
+  __shared__ struct { int h; unsigned keys; } odd_list[kOddList];
 
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
   const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
@@ -196,9 +204,28 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
     if (is_v ? v_mine : k_mine) {
       float probe = 0.f;
 #pragma unroll
-      for (int it = 0; it < PER; ++it) {
+      for (int it = 0; it < PER; ++it)
 #pragma unroll
         for (int j = 0; j < 8; ++j) probe = __builtin_fmaf(stage[it][j], kProbe, probe);
+      if (__builtin_expect(!(fabsf(probe) < INFINITY), 0)) {
+        unsigned keys = 0;
+        int tid_here = tid;
+        asm volatile("" : "+v"(tid_here));
+#pragma unroll
+        for (int it = 0; it < PER; ++it) {
+          const int grp = (it * NT + tid_here - (ITEMS >= NT ? 0 : NT - ITEMS)) / D;
+          const int first = is_v ? 16 * (grp >> 1) + 4 * (grp & 1) : (it * NT + tid_here) / (D / 8);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const bool odd = !(fabsf(stage[it][j]) < kLargest);
+            keys |= odd ? 1u << (first + (is_v ? 8 * (j >> 2) + (j & 3) : 0)) : 0u;
+            if (is_v) stage[it][j] = odd ? 0.f : stage[it][j];  // (its weight will be 0)
+          }
+        }
+        if (keys) atomicOr(&odd_keys[(unsigned)h % 3u], keys);
+      }
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
         if (is_v) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) stage[it][j] *= kValueScale;
@@ -217,14 +244,14 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
         for (int i = 0; i < kTerms; ++i) *reinterpret_cast<uintx4*>(buf + i * TERMB + at) = t[i];
       }
-      if (!(fabsf(probe) < INFINITY)) odd_value = 1;
     }
   };
 
   // ---- Q: lane (m, hi) keeps q[m][16 ks + 8 hi + j], j = 0..7, as terms
   uintx4 qt[KS][kTerms];
-  bool odd_q = false;
-  if (tid == 0) odd_value = 0;
+  bool odd_q = false, odd_row = false;  // some row of the unit, this lane's row
+  if (tid < 3) odd_keys[tid] = 0;
+  if (tid == 3) odd_tiles = 0;
   if (h_begin < h_end) load_k(h_begin);
   {
     float raw[KS][8];
@@ -258,7 +285,8 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
       for (int e = 0; e < 8; ++e) probe = __builtin_fmaf(raw[ks][e], kProbe, probe);
     }
-    odd_q = __any(!(fabsf(probe) < INFINITY)) || !(p.scale_log2e < kMaxScale);
+    odd_row = pair_max(fabsf(probe) < INFINITY && p.scale_log2e < kMaxScale ? 0.f : 1.f) != 0.f;
+    odd_q = !idle && __any(odd_row);
   }
 
   floatx16 o[DB];
@@ -280,7 +308,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   for (int i = 0; i < 4; ++i) k_at[i] = (unsigned)((2 * i + hi) * 32 + (m ^ ((2 * i + hi) & 7))) * 16u;
 
   if (h_begin < h_end) {
-    __syncthreads();  // the flag is clear
+    __syncthreads();  // the words above are clear
     put(h_begin, false);
     load_v(h_begin);
     put(h_begin, true);
@@ -325,21 +353,36 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll 1
-      for (int c = 0; c < 8 * KS; ++c) {
-        const int col = 16 * (c >> 3) + (c & 7) + 8 * hi2;
-        float q = qrow[col];
+      for (int ks = 0; ks < KS; ++ks) {
+        float kv[8], qv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) kv[e] = krow[16 * ks + e], qv[e] = qrow[16 * ks + 8 * hi2 + e];
         if (p.rope_cos) {
-          const bool lower = col < D / 2;
-          const int j = lower ? col : col - D / 2;
-          const float t = qrow[lower ? col + D / 2 : j] * p.rope_sin[(int64_t)t2 * (D / 2) + j];
-          q = __builtin_fmaf(q, p.rope_cos[(int64_t)t2 * (D / 2) + j], lower ? -t : t);
+          const bool lower = ks < KS / 2;
+          const int j0 = 16 * (lower ? ks : ks - KS / 2) + 8 * hi2;
+          const float* cs = p.rope_cos + (int64_t)t2 * (D / 2) + j0;
+          const float* sn = p.rope_sin + (int64_t)t2 * (D / 2) + j0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float t = qrow[(lower ? D / 2 : 0) + j0 + e] * sn[e];
+            qv[e] = __builtin_fmaf(qv[e], cs[e], lower ? -t : t);
+          }
         }
-        s = __builtin_amdgcn_mfma_f32_32x32x2f32(krow[16 * (c >> 3) + (c & 7)], q, s, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e], s, 0, 0, 0);
       }
     }
   };
-  auto softmax = [&](int h) __attribute__((always_inline)) {
+  auto softmax = [&](int h, unsigned hide) __attribute__((always_inline)) {  // hide: keys of the tile to leave out
     const int key0 = first_key(h);
+    if (__builtin_expect(hide != 0, 0)) {
+      int hi_here = hi;  // (opaque copies here and below: what rare code derives from a lane's place is not held through the loop)
+      asm volatile("" : "+v"(hi_here));
+      const unsigned mine = hide >> (4 * hi_here);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (mine & (1u << (8 * (r >> 2) + (r & 3)))) s[r] = -INFINITY;
+    }
     const bool left = WIN && key0 < lb_last && key0 + BN > p.n_sink;  // keys between the sinks and the window
     if (key0 + BN > vis_first || left) {
       // visible inside the tile: keys below rel, and of those (window step) the ones below rel_sink or from rel_lb
@@ -409,12 +452,20 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       int l2 = l;
       asm volatile("" : "+v"(l2));
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int row = key0 + 8 * (r >> 2) + (r & 3) + 4 * (l2 >> 5);
-        if (row > L - 1) row = L - 1;
-        const float* vrow = reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB) + (l2 & 31);
+      for (int r0 = 0; r0 < 16; r0 += 4) {
+        float v[4][DB];
 #pragma unroll
-        for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vrow[db * 32], s[r], o[db], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) {
+          int row = key0 + 2 * r0 + j + 4 * (l2 >> 5);
+          if (row > L - 1) row = L - 1;
+          const float* vrow = reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB) + (l2 & 31);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) v[j][db] = vrow[db * 32];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[j][db], s[r0 + j], o[db], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -423,58 +474,87 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   constexpr std::false_type in_fp32{};
   // (A second wavefront per SIMD that does its O^T one step later, so that the two are never in the softmax together, was
   // 4 % slower; a priority for one of the two changed nothing.)
+  unsigned hide = 0;
   for (int h = h_begin; h < h_end; ++h) {
     __syncthreads();  // tile h is in LDS, and nobody reads tile h - 1 any more
     const int hn = h + 1 < h_end ? h + 1 : h;  // (past the last tile it is fetched again, for nobody)
     const bool work = !idle && first_key(h) < vis_last;  // (else every row is masked)
+    const unsigned hide_before = hide;
+    hide = __builtin_amdgcn_readfirstlane(odd_keys[(unsigned)h % 3u]);
     load_k(hn);
     if (work) logits(h, by_terms);
     put(h + 1, false);
     load_v(hn);
+    if (__builtin_expect((hide | hide_before) != 0, 0)) {
+      if (tid == 0) {
+        if (hide_before) odd_keys[(unsigned)(h + 2) % 3u] = 0;  // tile h - 1's, next used for tile h + 2
+        if (hide) {
+          const int n = odd_tiles;
+          if (n < kOddList) odd_list[n].h = h, odd_list[n].keys = hide;
+          odd_tiles = n + 1;
+        }
+      }
+    }
     if (work) {
-      softmax(h);
+      softmax(h, hide);
       add_values(h, by_terms);
     }
     put(h + 1, true);
   }
   __syncthreads();
-  float unscale = kValueUnscale;
-  if (__builtin_expect((odd_q || __builtin_amdgcn_readfirstlane(odd_value)) && !idle, 0)) {
-    // once more, with the fp32 instructions
-    clear();
-    unscale = 1.f;
-#pragma unroll 1
-    for (int h = h_begin; h < h_end && first_key(h) < vis_last; ++h) {
-      logits(h, in_fp32);
-      softmax(h);
-      add_values(h, in_fp32);
-    }
-  }
 
-  // ---- epilogue
-  const float l_tot = pair_sum(l_run);
-  if (!store_ok) return;
-  const int64_t n_rows = (int64_t)C * Hq;
-  const int64_t row = (int64_t)tok * Hq + head;
-  if (p.n_splits == 1) {
-    const float inv = unscale / l_tot;
-    float* orow = reinterpret_cast<float*>(p.out) + row * D;
+  // ---- keys and rows for the fp32 instructions, and the epilogue: first the rows whose query the terms can hold
+  const int n_odd = __builtin_amdgcn_readfirstlane(odd_tiles);
+  float unscale = kValueUnscale;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    if (__builtin_expect((n_odd > 0 || pass > 0) && !idle, 0)) {
+      const bool whole = pass > 0 || n_odd > kOddList;
+      if (whole)
+        clear();
+      else
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg)
-        *reinterpret_cast<float4*>(orow + db * 32 + 8 * rg + 4 * hi) =
-            make_float4(o[db][rg * 4 + 0] * inv, o[db][rg * 4 + 1] * inv, o[db][rg * 4 + 2] * inv, o[db][rg * 4 + 3] * inv);
-    if (p.lse && hi == 0) p.lse[(int64_t)head * C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
-  } else {
-    float* prow = p.part_o + ((int64_t)split * n_rows + row) * D;
+          for (int r = 0; r < 16; ++r) o[db][r] *= unscale;
+      unscale = 1.f;
+      const int n = whole ? h_end - h_begin : n_odd;
+#pragma unroll 1
+      for (int i = 0; i < n; ++i) {
+        const int h = whole ? h_begin + i : __builtin_amdgcn_readfirstlane(odd_list[i].h);
+        if (first_key(h) >= vis_last) break;  // (tiles ascend)
+        logits(h, in_fp32);
+        softmax(h, whole ? 0u : ~(unsigned)__builtin_amdgcn_readfirstlane(odd_list[i].keys));
+        add_values(h, in_fp32);
+      }
+    }
+
+    const float l_tot = pair_sum(l_run);
+    if (store_ok && odd_row == (pass > 0)) {
+      const int64_t n_rows = (int64_t)C * Hq;
+      const int64_t row = (int64_t)tok * Hq + head;
+      if (p.n_splits == 1) {
+        const float inv = unscale / l_tot;
+        float* orow = reinterpret_cast<float*>(p.out) + row * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg)
-        *reinterpret_cast<float4*>(prow + db * 32 + 8 * rg + 4 * hi) =
-            make_float4(o[db][rg * 4 + 0] * unscale, o[db][rg * 4 + 1] * unscale, o[db][rg * 4 + 2] * unscale, o[db][rg * 4 + 3] * unscale);
-    if (hi == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + row) * 2) = make_float2(m_run, l_tot);
+          for (int rg = 0; rg < 4; ++rg)
+            *reinterpret_cast<float4*>(orow + db * 32 + 8 * rg + 4 * hi) =
+                make_float4(o[db][rg * 4 + 0] * inv, o[db][rg * 4 + 1] * inv, o[db][rg * 4 + 2] * inv, o[db][rg * 4 + 3] * inv);
+        if (p.lse && hi == 0) p.lse[(int64_t)head * C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+      } else {
+        float* prow = p.part_o + ((int64_t)split * n_rows + row) * D;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int rg = 0; rg < 4; ++rg)
+            *reinterpret_cast<float4*>(prow + db * 32 + 8 * rg + 4 * hi) =
+                make_float4(o[db][rg * 4 + 0] * unscale, o[db][rg * 4 + 1] * unscale, o[db][rg * 4 + 2] * unscale, o[db][rg * 4 + 3] * unscale);
+        if (hi == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + row) * 2) = make_float2(m_run, l_tot);
+      }
+    }
+    if (!odd_q) break;
   }
 }
 

@@ -147,3 +147,43 @@ def test_single_products_are_rounded_once(d, waves):
     err = lse / exact - 1.0
     assert err.abs().max() <= 6 * 2.0 ** -24
     assert err.mean().abs() <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_do_not_notice_what_they_do_not_see(d, waves, splits):
+    """A key that is not finite changes no bit of the rows before it, wherever they are computed, and a query that is not
+    finite changes no bit of any other row."""
+    n, hq, hkv = 200, 4, 2
+    q, k, v = _random(n, hq, d, 16), _random(n, hkv, d, 17), _random(n, hkv, d, 18)
+    plain = _step(q, k, v, waves, splits)
+    k2, v2, q2 = k.clone(), v.clone(), q.clone()
+    k2[150, 0, 3] = math.nan
+    v2[160, 1, 7] = math.inf
+    out = _step(q, k2, v2, waves, splits)
+    assert torch.equal(out[:150, :2], plain[:150, :2]) and torch.isnan(out[150:, :2]).all()
+    assert torch.equal(out[:160, 2:], plain[:160, 2:]) and (out[160:, 2:, 7] == math.inf).all()
+    ref = _reference(q, k2, v2)[160:, 2:]
+    assert (out[160:, 2:].cpu().double() - ref)[torch.isfinite(ref)].abs().max() <= 1e-5
+    q2[77, 1, 5] = math.nan
+    out = _step(q2, k, v, waves, splits)
+    assert torch.isnan(out[77, 1]).all()
+    out[77, 1] = plain[77, 1]
+    assert torch.equal(out, plain)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("waves", [1, 2])
+def test_many_keys_that_are_not_finite(waves, splits):
+    """Every tile of 32 keys, more of them than a workgroup takes one by one, holds a value or a key that is not finite: the
+    column with infinite values is not finite from the first such key on, hidden keys (-inf) have no weight, all else is as ever."""
+    n, hq, hkv, d = 1500, 2, 1, 64
+    q, k, v = _random(n, hq, d, 19), _random(n, hkv, d, 20), _random(n, hkv, d, 21)
+    q[:, :, 3] = -q[:, :, 3].abs() - 0.1
+    k[5::37, 0, 3] = math.inf
+    v[7::29, 0, 9] = math.inf
+    out, ref = _step(q, k, v, waves, splits).cpu().double(), _reference(q, k, v)
+    cols = torch.arange(d) != 9
+    assert (out[..., cols] - ref[..., cols]).abs().max() <= 1e-5
+    assert not torch.isfinite(out[7:, :, 9]).any()
