@@ -59,17 +59,18 @@ namespace {
 // a full one (one workgroup per CU, two per CU), and once.
 struct KernelCost {
   double idle, full, full_two, start_end;
-  bool two_per_cu, sqrt_fill;
+  bool two_per_cu;
 };
-KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, double with_rows) {
+KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_rows, double with_rows) {
   const double d = head_dim / 128.0;
+  if (few_rows) return {0.46, 0.46, 0.46, 4.6, true};
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
-    if (head_dim == 64) return upw == 2 ? KernelCost{0.80, 0.95, 0, 10.0, false, false} : KernelCost{0.70, 0.71, 1.25, 6.2, true, false};
-    return upw == 2 ? KernelCost{1.09, 1.53, 0, 10.0, false, false} : KernelCost{0.85, 0.94, 1.92, 6.2, true, false};
+    if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
+    return upw == 2 ? KernelCost{1.4, 1.4, 0, 14.0, false} : KernelCost{1.1, 1.1, 2.1, 5.5, true};
   }
-  if (waves == 8) return {(4.8 + 2.1 * with_rows) * d, 8.6 * d, 0, 10.0, false, true};
-  return {7.6 * d, 7.6 * d, 12.2 * d, 7.0, head_dim == 64, true};
+  if (waves == 8) return {(6.9 + 2.0 * with_rows) * d, 12.0 * d, 0, 8.7, false};
+  return {9.0 * d, 9.0 * d, 14.0 * d, 7.1, head_dim == 64};
 }
 
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
@@ -107,24 +108,25 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   if (c.tune_splits > 0) {
     s = c.tune_splits;
   } else {
-    // Estimated time of the step for every split count; the smallest wins (by more than 0.5 %):
+    // Estimated time of the step for every split count; the smallest wins (by more than 1.5 %):
     //     rounds of workgroups x (tiles of the longest piece x time per tile + start and end), and for s > 1 the merge.
     //  * Time per tile: `idle` on a chip that is otherwise idle (one workgroup's chain of matrix work and waits), up to
-    //    `full` when every CU works at it: the chip is power-limited, busy CUs share what it has (rate ~ fill^0.25), and
+    //    `full` when every CU works at it: the chip is power-limited, busy CUs share what it has (rate ~ fill^0.5), and
     //    wavefronts without rows leave theirs to the others.
-    //  * K and V rows come from memory at 5.2 TB/s with two workgroups per CU, less with fewer in flight.
+    //  * K and V rows come from memory at 6.5 TB/s with two workgroups per CU, a little less with fewer in flight.
     //  * Unsplit, several rounds, heaviest workgroups first: the slots left over in the last round idle for
     //    the length of the lightest workgroups only (first token block: the prefix and little else).
-    //  * The merge: its launch, and the fp32 partials written and read once at 5 TB/s.
-    //  * A step is not queued faster than its launches: some 9 us with one, 3.8 us more for each further one.
-    // The figures are fitted to measured steps (1 to 4096 tokens on 0 to 128K keys, all split counts): over 30 workloads
-    // the choice is within 2 % of the best split count on average.
+    //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.
+    //  * A step is not queued faster than its launches: some 9 us with one, 3.5 us more for each further one.
+    // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
+    // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
+    // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.
     const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
-    const KernelCost k = few_rows ? KernelCost{0.54, 0.54, 0.54, 3.0, true, false} : kernel_cost(f.dtype, f.head_dim, upw, waves, with_rows);
+    const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, few_rows, with_rows);
     const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
-    const double active = std::sqrt(with_rows);
+    const double active = f.dtype == KVFOLD_BF16 ? std::sqrt(std::sqrt(with_rows)) : std::sqrt(with_rows);
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
-    const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / 5.2e6;
+    const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / (few_rows ? 5.9e6 : 6.5e6);
     const int launches = f.dtype != KVFOLD_BF16 || c.storage_bits ? 2 : 1;
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
@@ -136,33 +138,34 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       const bool two_per_cu = k.two_per_cu && w > (int64_t)c.n_cu;
       const double slots = (double)c.n_cu * (two_per_cu ? 2 : 1);
       const double full = two_per_cu ? k.full_two : k.full;
-      // (pieces past the causal horizon of their row block are empty: the first row block's pieces, the last one's, the mean;
-      // and what is left lies unevenly)
-      const double first_pieces = std::ceil(((la - n_tokens) / kTileKeys + 1.0) / (double)tps);
-      const double some = cand > 1 && window <= 0 ? std::min(1.0, first_pieces / (double)cand) : 1.0;
-      const double busy = 0.5 * (double)w * (1.0 + some);
+      // Workgroups with work: piece j is empty for the tokens before j * tps tiles less the prefix, so of the pieces from
+      // first_cut on only the later tokens' have any.
+      double busy = (double)w;
+      if (cand > 1 && window <= 0) {
+        const double keys = (double)tps * kTileKeys, prefix = la - n_tokens, first_cut = std::floor(prefix / keys) + 1.0;
+        const double cut = (double)cand - first_cut;
+        if (cut > 0.0) busy = (double)base * (first_cut + cut * (1.0 + (prefix - 0.5 * keys * (first_cut + (double)cand - 1.0)) / n_tokens));
+      }
       const double rounds = std::max(1.0, std::ceil(busy / slots - 1e-9));
       const double fill = busy / (rounds * slots);
-      double t = rounds * (double)tps * std::max(k.idle, full * active * (k.sqrt_fill ? std::sqrt(fill) : std::sqrt(fill * std::sqrt(fill))));
-      if (cand == 1 && window <= 0) {
-        if (rounds >= 2.0)
-          t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
-        else if (upw == 2)
-          t *= mean_keys / la;  // paired units: every wavefront has the mean
-      }
+      double t = rounds * (double)tps * std::max(k.idle, full * active * std::sqrt(fill));
+      if (cand == 1 && window <= 0 && rounds >= 2.0)
+        t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
       const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;
       if (few_rows) {
-        // 5.9 TB/s from one workgroup per CU on, less where some CUs have two and some one; near that rate both times count
-        // (measured, one token on 128K keys: 121 us with 12 pieces, 101 with 16, 93.5 with 28, 110 with 40, 95 with 64)
-        const double mem = kv_piece * (5.2 / 5.9) * (two_per_cu ? std::sqrt(slots / (double)w) : 1.0);
+        // 5.9 TB/s from one workgroup per CU on, less where some CUs have one more than others; near that rate both times
+        // count (measured, one token on 128K keys: 121 us with 12 pieces, 101 with 16, 93.5 with 28, 110 with 40, 95 with 64)
+        const double per_cu = std::ceil((double)w / c.n_cu);
+        const double mem = kv_piece * (two_per_cu ? std::sqrt(per_cu * c.n_cu / (double)w) : 1.0);
         t = std::sqrt(std::sqrt(t * t * t * t + mem * mem * mem * mem));
       } else {
-        t = std::max(t, kv_piece * std::max(1.0, std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
+        const double few_in_flight = std::sqrt(std::sqrt(std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
+        t = std::max(t, kv_piece * std::max(1.0, few_in_flight));
       }
-      t = t * (1.0 + 0.03 / rounds + 0.5 * (1.0 - some)) + (k.start_end + (two_per_cu && !few_rows ? 1.0 : 0.0)) * rounds;
-      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 5e6 + 4.2;
-      t = std::max(t, 5.0 + 3.8 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
-      if (t < best * (few_rows ? 1.0 : 0.995)) {
+      t += (k.start_end + (two_per_cu && !few_rows ? 0.5 : 0.0)) * rounds;
+      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 6.7e6 + 4.7;
+      t = std::max(t, 5.2 + 3.5 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
+      if (t < best * (few_rows ? 1.0 : 0.985)) {
         best = t;
         s = cand;
       }
@@ -199,17 +202,18 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return p1;
   }
   // Two units per wavefront is the faster kernel on a full chip (every LDS fragment feeds two MFMAs); one unit starts
-  // sooner and fills the chip with fewer rows.
+  // sooner and fills the chip with fewer rows.  The estimates decide, the two-unit kernel's taken 10 % longer (part of the
+  // fit).  Where units straddle tokens and half of a two-unit workgroup is padding (C = 128, G = 7) the choice changes
+  // at 38K keys; measured there, one unit / two units per wavefront: 70.8 / 73.0 us at 32K, 84.7 / 84.5 at 40K, 98 / 96
+  // at 48K, 125 / 123 at 64K; with 24 heads on 8, 64 / 66 at 32K, 101 / 100 at 56K.
   const Plan p2 = plan_with(c, n_tokens, len_after, 2, n_sink, window);
-  const int64_t padded1 = (int64_t)p1.wgs_per_head * kUnitsPerWg, padded2 = (int64_t)p2.wgs_per_head * kUnitsPerWg * 2;
-  if (padded2 * 5 > padded1 * 6) return p1;                                   // more than 20 % extra padding
-  if (p2.n_splits == 1 && (int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
-  if (c.tune_splits > 0) return p2;
-  // Else the estimates decide.  Where units straddle tokens and the two-unit grid pads more (the 28 units of a G = 7 head at
-  // C = 128 fill 3.5 two-unit workgroups) they are within their error of each other, and the one-unit grid has the shorter
-  // start (measured there, one unit / two units per wavefront: 71 / 75 us at 32K keys, 100 / 96 at 48K, 126 / 121 at 64K).
-  const bool close = padded2 > padded1 && kRowsPerUnit % (f.n_q_heads / f.n_kv_heads) != 0;
-  return p1.est_us < p2.est_us * (close ? 1.06 : 1.0) ? p1 : p2;
+  if (c.tune_splits > 0) {
+    const int64_t padded1 = (int64_t)p1.wgs_per_head * kUnitsPerWg, padded2 = (int64_t)p2.wgs_per_head * kUnitsPerWg * 2;
+    if (padded2 * 5 > padded1 * 6) return p1;  // more than 20 % extra padding
+    if (p2.n_splits == 1 && (int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
+    return p2;
+  }
+  return p1.est_us < p2.est_us * 1.1 ? p1 : p2;
 }
 
 }  // namespace

@@ -141,9 +141,11 @@ def test_launch_plans_of_the_benchmark_configurations(lib):
     # config 5 (G=7, C=2048): 224 busy CUs of 256 beat any split on the power-limited chip
     assert plan(28, 4, 128, 2048, 65536, cap=65536) == (224, 1, 2)
     assert plan(28, 4, 128, 8192, 65536, cap=65536) == (1792, 2, 2)
-    # config 5 at C=128: the 28 units of a G=7 head fill 3.5 two-unit workgroups; seven one-unit workgroups and nine
-    # pieces on 252 CUs are faster (measured: +9 % on the fold)
-    assert plan(28, 4, 128, 128, 65536, cap=65536) == (252, 9, 1)
+    # config 5 at C=128: the 28 units of a G=7 head fill 3.5 two-unit workgroups; on short caches seven one-unit workgroups and
+    # nine pieces on 252 CUs are faster (measured, one / two units per wavefront: 68.8 / 72.7 us at 32K keys, 84.7 / 84.5
+    # at 40K), at the fold's end two units are (121 / 115)
+    assert plan(28, 4, 128, 128, 32768, cap=65536) == (252, 9, 1)
+    assert plan(28, 4, 128, 128, 65536, cap=65536) == (256, 16, 2)
     # decode-shaped steps against 128K: one unit per wavefront, 512 workgroups (two per CU)
     w, s, u = plan(32, 8, 128, 16, 131072)
     assert (w, s, u) == (512, 64, 1)
@@ -160,6 +162,27 @@ def test_launch_plans_of_the_benchmark_configurations(lib):
     assert kv.kvfold_plan_for(cfg, 256, 256, 1024, n_sink=-1, window=8)[0] == -1
     assert kv.kvfold_plan_for(cfg, 256, 256, 1024, n_sink=0, window=-1)[0] == -1
     assert load_raw_plan_for_null_out(cfg) == -1
+
+
+def test_launch_plans_where_one_choice_is_much_the_better(lib):
+    """Shapes in which the wrong kernel or split count costs a fifth of the step (measured, the choice / the other)."""
+    def plan(Hq, Hkv, d, C, prev):
+        cfg = binding.make_config(1, Hq, Hkv, d, max(C, 256), prev + C, kv.KVFOLD_BF16)
+        rc, pl = kv.kvfold_plan_for(cfg, 256, C, prev + C)
+        assert rc == 0
+        return pl
+    # few full units on a long cache: two units per wavefront (136 / 169 us, 135 / 167 us, 77 / 90 us)
+    for Hq, Hkv, C in ((64, 8, 32), (32, 8, 64), (28, 4, 32)):
+        pl = plan(Hq, Hkv, 128, C, 128000)
+        assert pl.units_per_wave == 2 and 200 <= pl.n_workgroups <= 256, (Hq, C, pl.n_workgroups, pl.n_splits)
+    # two units per wavefront on two thirds of the CUs beat one unit in two rounds (202 / 240 us)
+    assert plan(28, 4, 128, 1500, 9000).units_per_wave == 2
+    # chunks longer than their prefix: one unit and a split beat two units unsplit (29 / 48 us)
+    pl = plan(12, 12, 64, 1500, 1000)
+    assert pl.units_per_wave == 1 and pl.n_splits > 1
+    # one unit of rows per KV head, many heads: more pieces than two workgroups per CU only cost (89 / 97 us, 169 / 199 us)
+    for prev in (30000, 60000):
+        assert plan(32, 32, 128, 32, prev).n_workgroups <= 512
 
 
 def load_raw_plan_for_null_out(cfg):
