@@ -4,8 +4,10 @@
 //  1. A host model of the attention kernels' key-range walk.  The kernels' tile arithmetic lives in
 //     kvfold_consts.h (workgroup_rows, tile_map, key_range, dma_row) and the launch geometry in the planner;
 //     both are used here exactly as the kernels use them.  For many shapes -- chunk length, cache length, group
-//     size, prefix splits, units per wavefront, fused append or not, plain and sink + sliding-window steps --
-//     every workgroup's pieces are walked, ring run-ahead included, and checked:
+//     size, prefix splits, units per wavefront (fp32: wavefronts per workgroup), fused append or not, plain and
+//     sink + sliding-window steps -- every workgroup's pieces are walked as its kernel walks them -- the general bf16
+//     kernel's ring with its run-ahead and the last tile fetched again past the end, the few-rows kernel's blocks of
+//     32 keys in cyclic order, the fp32 kernel's half tiles -- and checked:
 //       * every DMA source row lies inside what exists (cache rows below len_prev when the chunk's rows are not
 //         in the cache yet, else below len_prev + C; chunk rows below C), with 32-bit offsets that do not wrap;
 //       * a row that a query of the workgroup can see is fetched unclamped, from the right place;
@@ -43,8 +45,83 @@ static long g_checks = 0;
     }                                                        \
   } while (0)
 
-// Ring depth of the bf16 kernels: the refill runs NV + 1 tiles ahead of the tile being read.
-static const int kRunAhead = 4;
+// One row that a kernel reads for `key` (of the piece: the workgroup may need it; else it only has to exist).
+struct Reader {
+  const kvfold_config_t& cfg;
+  int n_tokens;
+  int64_t len_prev, readable_cache, last_key;
+  int row_bytes;
+  bool fused;
+  std::vector<int>& seen;
+  void read(const DmaRow& d, int64_t key, bool of_piece) {
+    if (d.from_chunk) {
+      REQUIRE(fused && (int64_t)d.row < n_tokens, "chunk row %u out of %d", d.row, n_tokens);
+      REQUIRE((uint64_t)d.row * cfg.n_kv_heads * row_bytes + row_bytes <= (1ull << 32), "32-bit chunk offset wraps");
+    } else {
+      REQUIRE((int64_t)d.row < readable_cache, "cache row %u not readable (%lld rows are)", d.row, (long long)readable_cache);
+      REQUIRE((uint64_t)d.row * row_bytes + row_bytes <= (1ull << 32), "32-bit cache offset wraps");
+    }
+    if (of_piece && key <= last_key) {
+      // inside the piece and not beyond the workgroup's last row: must be the key itself
+      const int64_t got = d.from_chunk ? len_prev + d.row : d.row;
+      REQUIRE(got == key, "key %lld is read from the row of key %lld", (long long)key, (long long)got);
+      REQUIRE(d.from_chunk == (fused && key >= len_prev), "wrong source for key %lld", (long long)key);
+      seen[(size_t)key]++;
+    }
+  }
+};
+
+// The general bf16 kernel: every tile of the piece row by row where it is issued as a whole (issue_tile), and the main loop's
+// refills (issue_slab), which run NV + 1 tiles (K) and NV tiles (V) ahead, take every row to be a cache row, and fetch
+// the last tile again past the end.
+static void walk_ring(Reader& rd, const TileMap& tm, const KeyRange& kr, int nv) {
+  auto tphys = [&](int t) { return t + (t >= tm.ns_t ? tm.skip : 0); };
+  auto tlogical = [&](int tp) { return tp < tm.ns_t ? tp : tp - tm.skip > tm.ns_t ? tp - tm.skip : tm.ns_t; };
+  for (int t = kr.t_begin; t < kr.t_end; ++t)
+    for (int row = 0; row < kTileKeys; ++row) rd.read(dma_row(kr, tphys(t), row), (int64_t)tphys(t) * kTileKeys + row, true);
+  const int len_after = (int)rd.len_prev + rd.n_tokens, t_new = kr.t_straddle >= 0 ? kr.t_straddle : kr.t_new;
+  int t_plain = tlogical(len_after / kTileKeys < t_new ? len_after / kTileKeys : t_new);
+  t_plain = t_plain >= kr.t_end ? kr.t_end : t_plain - nv - 1;
+  for (int t = kr.t_begin; t < t_plain; ++t)
+    for (int ahead : {nv, nv + 1}) {
+      const int t_log = t + ahead < kr.t_end - 1 ? t + ahead : kr.t_end - 1, tp = tphys(t_log);
+      for (int row : {0, kTileKeys - 1}) {
+        const DmaRow plain{false, (unsigned)(tp * kTileKeys + row)}, is = dma_row(kr, tp, row);
+        rd.read(plain, -1, false);
+        REQUIRE(is.from_chunk == plain.from_chunk && is.row == plain.row, "refill of tile %d (tile %d) is not plain", t_log, t);
+      }
+    }
+}
+
+// The few-rows kernel: wavefront w takes every fourth block of 32 keys, in cyclic order from a place of its own.
+static void walk_few(Reader& rd, const KeyRange& kr, int split, int g) {
+  const int b_all = (int)((rd.len_prev + rd.n_tokens + 31) / 32), b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
+  for (int w = 0; w < 4; ++w) {
+    const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + 3) / 4 : 0;
+    int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
+    for (int i = 0; i < n_blocks; ++i) {
+      REQUIRE(b >= b_first && b < b_end && (b - b_first) % 4 == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_end, w);
+      const unsigned last = (unsigned)(b * 32 + 31);
+      const bool plain = last <= kr.row_lim && last < kr.chunk_row0;
+      for (int row = 0; row < 32; ++row)
+        rd.read(plain ? DmaRow{false, (unsigned)(b * 32 + row)} : dma_row(kr, b >> 1, (b & 1) * 32 + row), (int64_t)b * 32 + row, true);
+      b = b + 4 < b_end ? b + 4 : b_first;
+    }
+  }
+}
+
+// The fp32 kernel: half tiles, rows past the last one read as the last one; a last half beyond every row is left out.
+static void walk_halves(Reader& rd, const TileMap& tm, const KeyRange& kr, int64_t nkeys_wg) {
+  const int64_t len_after = rd.len_prev + rd.n_tokens;
+  auto first_key = [&](int h) { const int t = h >> 1; return (2 * (int64_t)(t + (t >= tm.ns_t ? tm.skip : 0)) + (h & 1)) * 32; };
+  int h_end = 2 * kr.t_end;
+  if (h_end > 2 * kr.t_begin && first_key(h_end - 1) >= nkeys_wg) --h_end;
+  for (int h = 2 * kr.t_begin; h < h_end; ++h)
+    for (int row = 0; row < 32; ++row) {
+      const int64_t key = first_key(h) + row;
+      rd.read(DmaRow{false, (unsigned)(key < len_after ? key : len_after - 1)}, key, true);
+    }
+}
 
 static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_t len_prev, int n_sink, int64_t window,
                       int force_splits, int force_upw) {
@@ -58,12 +135,16 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   const Plan pl = make_plan(pc, n_tokens, len_after, n_sink, window);
   const bool fused = fused_append_applies(pc, n_tokens, len_prev, false);
   const int G = cfg.n_q_heads / cfg.n_kv_heads;
-  const int upw_wg = kUnitsPerWg * pl.units_per_wave;
+  const int upw_wg = pl.waves_per_wg * pl.units_per_wave;
   const int row_bytes = cfg.head_dim * elem_size(cfg.dtype);
   REQUIRE(pl.n_splits >= 1 && pl.n_splits <= kMaxSplits && pl.tiles_per_split >= 1, "plan");
   REQUIRE(pl.n_splits == 1 || (int64_t)pl.n_splits * n_tokens * cfg.n_q_heads <= pc.ws_rows, "workspace");
   REQUIRE(pl.n_wgs == cfg.n_kv_heads * pl.wgs_per_head * pl.n_splits, "grid");
   if (window > 0) REQUIRE(!pl.pair_units && !pl.pair_order, "pairing under a window");
+  REQUIRE(pl.waves_per_wg == kUnitsPerWg || (pl.waves_per_wg == 8 && cfg.dtype == KVFOLD_F32 && pl.units_per_wave == 1), "wavefronts");
+  REQUIRE(!pl.few_rows || (cfg.dtype == KVFOLD_BF16 && window <= 0 && pl.units_per_head == 1 && pl.wgs_per_head == 1), "few rows");
+  REQUIRE((int64_t)pl.wgs_per_head * upw_wg >= pl.units_per_head && (int64_t)pl.units_per_head * kRowsPerUnit >= (int64_t)n_tokens * G,
+          "%d workgroups of %d units for %d tokens x %d heads", pl.wgs_per_head, upw_wg, n_tokens, G);
 
   std::vector<int> seen((size_t)len_after);
   for (int ug = 0; ug < pl.wgs_per_head; ++ug) {
@@ -72,8 +153,7 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       rr.row_lo = 0;
       int ulast = pl.units_per_head - 1 - ug * kUnitsPerWg;
       if (ulast < 0) ulast = 0;
-      rr.row_hi = (ulast / G) * kRowsPerUnit + kRowsPerUnit - 1;
-      if (rr.row_hi > n_tokens - 1) rr.row_hi = n_tokens - 1;
+      rr.row_hi = unit_last_token(ulast, G, n_tokens);
     } else {
       rr = workgroup_rows(ug, upw_wg, pl.units_per_head, G, n_tokens);
     }
@@ -88,28 +168,13 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       // (a piece that never reads the chunk as handed in ends below len_prev, so the clamp keeps it there too)
       const int64_t readable_cache = fused ? len_prev : len_after;
       REQUIRE((int64_t)kr.row_lim < len_after, "row_lim");
-      for (int t = kr.t_begin; t < kr.t_end + kRunAhead; ++t) {
-        const int tp = t + (t >= tm.ns_t ? tm.skip : 0);
-        for (int row = 0; row < kTileKeys; ++row) {
-          const DmaRow d = dma_row(kr, tp, row);
-          const int64_t key = (int64_t)tp * kTileKeys + row;  // the key this ring row stands for
-          if (d.from_chunk) {
-            REQUIRE(fused && (int64_t)d.row < n_tokens, "chunk row %u out of %d", d.row, n_tokens);
-            REQUIRE((uint64_t)d.row * cfg.n_kv_heads * row_bytes + row_bytes <= (1ull << 32), "32-bit chunk offset wraps");
-          } else {
-            REQUIRE((int64_t)d.row < readable_cache, "cache row %u not readable (%lld rows are)", d.row, (long long)readable_cache);
-            REQUIRE((uint64_t)d.row * row_bytes + row_bytes <= (1ull << 32), "32-bit cache offset wraps");
-          }
-          if (t < kr.t_end && key < len_after && key <= len_prev + rr.row_hi) {
-            // inside the piece and not beyond the workgroup's last row: must be the key itself
-            const int64_t got = d.from_chunk ? len_prev + d.row : d.row;
-            REQUIRE(got == key, "tile %d (physical %d) row %d reads key %lld instead of %lld", t, tp, row, (long long)got,
-                    (long long)key);
-            REQUIRE(d.from_chunk == (fused && key >= len_prev), "wrong source for key %lld", (long long)key);
-            seen[(size_t)key]++;
-          }
-        }
-      }
+      Reader rd{cfg, n_tokens, len_prev, readable_cache, len_prev + rr.row_hi, row_bytes, fused, seen};
+      if (cfg.dtype != KVFOLD_BF16)
+        walk_halves(rd, tm, kr, len_prev + rr.row_hi + 1);
+      else if (pl.few_rows)
+        walk_few(rd, kr, split, (split * 5 + ug) % cfg.n_kv_heads);
+      else
+        walk_ring(rd, tm, kr, pl.units_per_wave == 2 ? 3 : 2);
     }
     // every key some row of the workgroup can see was fetched exactly once
     for (int r = rr.row_lo; r <= rr.row_hi; ++r) {
@@ -137,8 +202,8 @@ static kvfold_config_t make_cfg(int Hq, int Hkv, int d, int C, int64_t cap, int 
 }
 
 static void model_sweep() {
-  const int heads[][2] = {{4, 1}, {7, 1}, {6, 3}, {32, 8}, {2, 2}};
-  const int chunks[] = {1, 16, 33, 64, 100, 256, 1000};
+  const int heads[][2] = {{4, 1}, {7, 1}, {6, 3}, {32, 8}, {2, 2}, {40, 1}};
+  const int chunks[] = {1, 5, 16, 33, 64, 100, 256, 1000};
   const int64_t prefixes[] = {0, 63, 64, 500, 1024, 5000};
   const int64_t windows[][2] = {{0, 0}, {4, 1020}, {0, 1}, {4, 1}, {1, 33}, {70, 50}, {130, 129}, {0, 1 << 20}};
   long steps = 0;
@@ -151,7 +216,6 @@ static void model_sweep() {
             REQUIRE(validate_config(&cfg) == KVFOLD_OK, "config");
             for (int splits : {0, 2, 5})
               for (int upw : {0, 1, 2}) {
-                if (dtype == KVFOLD_F32 && upw == 2) continue;
                 if (splits > 0 && (int64_t)splits * C * h[0] > workspace_rows(&cfg)) continue;
                 walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw);
                 ++steps;
