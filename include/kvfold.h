@@ -222,7 +222,8 @@ int kvfold_cache_set_length(kvfold_cache_t* cache, int layer, int64_t new_len);
  * Storage perturbation of the carried cache (Sec. 8, Discussion: a per-step
  * quantisation round trip bf16 -> intN -> bf16).  n_bits = 8 or 4: from now on
  * every step passes the K and V rows it appends through that integer width and
- * back, in place, before its queries attend to them; 0 switches it off.  The
+ * back on their way into the cache (k_new and v_new are left as they are, and its
+ * queries attend to the rows as stored); 0 switches it off.  The
  * paper names no quantiser; the one used: a group is the head_dim elements of
  * one (token, KV head) row, symmetric, scale = max|x| / (2^(N-1) - 1), code =
  * round-half-even(x / scale) clamped to +-(2^(N-1) - 1), x' = code * scale, in
@@ -237,7 +238,9 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_SPLITS         number of prefix splits of the attention kernel; 0 = automatic.
  *                              Clamped to what the split workspace and the key range allow.
  *   KVFOLD_TUNE_UNITS_PER_WAVE 32-row query blocks owned by one wavefront of the bf16 kernel:
- *                              1 or 2; 0 = automatic.  fp32 kernel (always one block per wavefront): 1 or 2 for
+ *                              1 or 2; 0 = automatic, which also gives bf16 steps without a window of at most 32
+ *                              (token, query head) rows per KV head a kernel of their own: any other value takes the
+ *                              general kernel for these too.  fp32 kernel (always one block per wavefront): 1 or 2 for
  *                              workgroups of four or eight wavefronts.
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
@@ -269,9 +272,10 @@ int kvfold_cache_plan(const kvfold_cache_t* cache, int32_t n_tokens, int64_t len
  * create, and for n_tokens, len_after, n_sink or window outside the configuration, or out == NULL.
  */
 typedef struct {
-  int32_t n_workgroups;    /* workgroups of the attention kernel                                        */
+  int32_t n_workgroups;    /* workgroups of the attention kernel (fp32: of four or eight wavefronts)     */
   int32_t n_splits;        /* pieces the key range is cut into (> 1: a merge kernel follows)            */
-  int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32: 1)                 */
+  int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32, and bf16 steps of at */
+                           /* most 32 rows per KV head, which have a kernel of their own: 1)            */
   int32_t tiles_per_split; /* 64-key tiles per piece                                                    */
   int32_t fused_append;    /* 1: the attention kernel appends the chunk's rows itself (kvfold_step_ex)  */
   int32_t pair_units;      /* 1: every wavefront owns an early and a late row block of the chunk        */
