@@ -142,9 +142,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // first_cut on only the later tokens' have any.
       double busy = (double)w;
       if (cand > 1 && window <= 0) {
-        const double keys = (double)tps * kTileKeys, prefix = la - n_tokens, first_cut = std::floor(prefix / keys) + 1.0;
-        const double cut = (double)cand - first_cut;
-        if (cut > 0.0) busy = (double)base * (first_cut + cut * (1.0 + (prefix - 0.5 * keys * (first_cut + (double)cand - 1.0)) / n_tokens));
+        const int64_t keys = tps * kTileKeys, prefix = len_after - n_tokens, first_cut = prefix / keys + 1, cut = cand - first_cut;
+        if (cut > 0)
+          busy = (double)base * ((double)first_cut + (double)cut * (1.0 + ((double)prefix - 0.5 * (double)(keys * (first_cut + cand - 1))) / n_tokens));
       }
       const double rounds = std::max(1.0, std::ceil(busy / slots - 1e-9));
       const double fill = busy / (rounds * slots);
@@ -158,9 +158,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
         const double per_cu = std::ceil((double)w / c.n_cu);
         const double mem = kv_piece * (two_per_cu ? std::sqrt(per_cu * c.n_cu / (double)w) : 1.0);
         t = std::sqrt(std::sqrt(t * t * t * t + mem * mem * mem * mem));
-      } else {
-        const double few_in_flight = std::sqrt(std::sqrt(std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w))));
-        t = std::max(t, kv_piece * std::max(1.0, few_in_flight));
+      } else if (2.0 * kv_piece > t) {  // (the factor stays below 1.6)
+        const bool few_in_flight = w < 2 * (int64_t)c.n_cu;
+        t = std::max(t, kv_piece * (few_in_flight ? std::sqrt(std::sqrt(std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w)))) : 1.0));
       }
       t += (k.start_end + (two_per_cu && !few_rows ? 0.5 : 0.0)) * rounds;
       if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 6.7e6 + 4.7;
