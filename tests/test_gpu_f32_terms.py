@@ -187,3 +187,52 @@ def test_many_keys_that_are_not_finite(waves, splits):
     cols = torch.arange(d) != 9
     assert (out[..., cols] - ref[..., cols]).abs().max() <= 1e-5
     assert not torch.isfinite(out[7:, :, 9]).any()
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_and_queries_beyond_the_terms_with_the_rotary_embedding(H, oracle, d, waves):
+    """The fp32 instructions rotate the queries that they take from memory: the same bits as on inputs rotated beforehand."""
+    cfg = I.FoldConfig("f32_rope", 71, 1, 4, 2, d, 100, 0, "f32")
+    q, k, v = I.chunk_qkv(cfg, 0, 0)
+    v[10, 0, 5] = 2.0 ** 70
+    q[60, 1, 3] = 2.0 ** 61
+    k[:, :, [3, 3 + d // 2]] *= 2.0 ** -60  # (a pair of the rotation: logits of ordinary size)
+    cos, sin = I.rope_tables(d, 0, 100)
+    q_rot, k_rot = (torch.from_numpy(oracle.rope(t.numpy(), cos.numpy(), sin.numpy())) for t in (q, k))
+    outs = []
+    for args, rope in (((q, k, v), (cos, sin)), ((q_rot, k_rot, v), None)):
+        fold = H.GpuFold(cfg, capacity=100)
+        fold.cache.set_tuning(1, waves)
+        outs.append(fold.step(0, *args, rope=rope).cpu())
+        fold.close()
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("splits", [0, 2])
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_beyond_the_terms_under_a_window(H, oracle, d, waves, splits):
+    """Key 150 holds a value of 2^65 and a window of 40 keys passes over it: the rows that see it match the oracle (relative to
+    that value), all others keep every bit."""
+    n, window = 300, (2, 40)
+    cfg = I.FoldConfig("f32_window", 72, 1, 4, 2, d, n, 0, "f32")
+    q, k, v = I.chunk_qkv(cfg, 0, 0)
+    big = v.clone()
+    big[150, :, 9] = 2.0 ** 65
+    outs = []
+    for value in (v, big):
+        fold = H.GpuFold(cfg, capacity=n)
+        fold.cache.set_tuning(0, splits)
+        fold.cache.set_tuning(1, waves)
+        outs.append(fold.step(0, q, k, value, window=window).cpu())
+        fold.close()
+    sees = torch.zeros(n, dtype=torch.bool)
+    sees[150:150 + window[1]] = True
+    assert torch.equal(outs[0][~sees], outs[1][~sees])
+    ref = torch.from_numpy(H.oracle_step(H.make_oracle(oracle, cfg, capacity=n), q, k, big, window=window)[0])
+    err = (outs[1].double() - ref).abs()
+    cols = torch.arange(d) != 9
+    assert err[..., cols].max() <= 1e-5
+    assert (err[sees][..., 9] <= 1e-5 * ref[sees][..., 9].abs()).all()
