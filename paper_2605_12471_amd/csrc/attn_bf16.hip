@@ -44,14 +44,18 @@
 //    P is rounded to bf16 by the hardware pack convert; row sums add the unrounded fp32 values.
 //  * Optional split of the key range over workgroups: partial (max, sum, O) go to a workspace
 //    and are merged by the combine kernel.
-//  * Start and end of a workgroup are kept short (they are 4 % of a short-prefix launch): the ring is
-//    filled before the Q rows are fetched, all Q loads are in flight together, the first reference is
-//    set without touching the still-zero O, and the finished O^T is turned in the dead ring space so
-//    that every store instruction writes whole rows.  Code a launch runs once is fetched at about 3 bytes
-//    per ns, so what is outside the main loop is kept small rather than unrolled, and a piece of the
-//    prefix stays in the main loop to its last tile.  Measured inside the kernel, entry to first tile:
-//    two-unit kernel 9.2 -> 7.0 us, one-unit kernel 4.9 -> 3.9 us; the last four tiles of a prefix piece
-//    8.0 -> 5.9 us (two-unit, against the copy of the loop with clamped rows that they took before).
+//  * Start and end of a workgroup are kept short (they are 4 % of a short-prefix launch and half of a
+//    small one): every line of the kernel arguments is fetched in one round trip, the first two tiles are
+//    on their way before the Q rows and the rest of the ring after them (a wait for Q is a wait for all
+//    that was issued before), the first reference is set without touching the still-zero O, and the
+//    finished O^T is turned in the dead ring space so that every store instruction writes whole rows.
+//    Code a launch runs once costs what it is long, about 3 bytes per ns: what is outside the main loop
+//    is kept small rather than unrolled, row addresses take a few 32-bit instructions (a row's place is
+//    formed once per lane and handed round), the copy of the chunk's rows runs behind the results'
+//    stores, and a piece of the prefix stays in the main loop to its last tile.  Measured inside the
+//    kernel (100 tokens on 2000 keys, 7 pieces), from entry to the first tile and from the last tile to
+//    the end: one-unit kernel 3.9 -> 3.1 us and 3.5 -> 2.0 us, two-unit kernel 6.1 -> 5.2 and 6.9 -> 3.5,
+//    against 64-bit row arithmetic written out for every store and the ring filled ahead of Q.
 #include <type_traits>
 
 #include "kvfold_internal.h"
@@ -101,6 +105,7 @@ __device__ __forceinline__ void mfma_settle_a(floatx16& x) {
 // LDS; two for the one-unit kernel so that two workgroups share a CU's 160 KB.  A deeper ring bought
 // nothing in measurements, neither on L2-resident prefixes nor on HBM-bound decode-shaped steps.
 constexpr int kRingTwoUnits = 3, kRingOneUnit = 2;
+constexpr int vote_bytes(int qb) { return qb == 2 ? 16 : 0; }  // (the one-unit kernel has no vote, and two workgroups fill the LDS to its last byte)
 constexpr float kRescaleThreshold = 16.0f;  // log2 units: stale running max tolerated up to 2^16
 constexpr float kSumThreshold = 1048576.0f;             // 2^20: row sum of a half that moves the reference up
 constexpr float kRedoThreshold = 1152921504606846976.0f;  // 2^60: beyond this the workgroup starts over
@@ -176,6 +181,9 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
 
   // rings: K slots [0, NK), V slots [NK, NK + NV)
 
+  // every line of the arguments is fetched now, in one round trip (they are not in the scalar cache yet)
+  asm volatile("" ::"s"(p.q), "s"(p.n_tokens), "s"(p.units_per_head), "s"(p.k_new), "s"(p.by_group.mul), "s"(p.copy_rows));
+
   // ---- which workgroup am I (XCD-aware: a KV head stays on its XCDs, see logical_workgroup())
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
   const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
@@ -201,7 +209,9 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   const float sc = p.scale_log2e;
 
   // ---- my units
-  int tok[QB], head[QB];  // of this lane's row (the chunk's last row where the unit runs past it)
+  const unsigned n_packed = (unsigned)(C * G);
+  int tok[QB];            // of this lane's row (the chunk's last row where the unit runs past it)
+  unsigned q_row[QB];     // its place among the [token][query head] rows
   int unit_of[QB];        // the units themselves, wave-uniform
   bool unit_valid[QB];
   int my_vis[QB];     // keys visible to this lane's query row
@@ -223,10 +233,10 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     const int u = !pair_units ? n * QB + qb : (qb == 0 ? n : p.units_per_head - 1 - n);
     const bool valid = !pair_units ? u < p.units_per_head : (qb == 0 ? 2 * n <= p.units_per_head - 1 : 2 * n < p.units_per_head - 1);
     const int uc = u < 0 ? 0 : (u < p.units_per_head ? u : p.units_per_head - 1);
-    const UnitRows ur(uc, p);
-    const bool inside = ur.tok(m) < C;
-    tok[qb] = inside ? ur.tok(m) : C - 1;
-    head[qb] = g * G + (inside ? ur.head(m) : G - 1);
+    unsigned row = (unsigned)(uc * kRowsPerUnit + m);  // packed row of the KV head
+    row = row < n_packed ? row : n_packed - 1;
+    tok[qb] = (int)quot(row, p.by_group);
+    q_row[qb] = row + (unsigned)tok[qb] * (unsigned)(Hq - G) + (unsigned)(g * G);
     unit_of[qb] = uc;
     unit_valid[qb] = valid;
     {
@@ -235,7 +245,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (win && vis_last - p.window > lb_last) lb_last = vis_last - p.window;
     }
     my_vis[qb] = (int)p.len_prev + tok[qb] + 1;
-    vis_first[qb] = (int)p.len_prev + ur.tok0 + 1;
+    vis_first[qb] = (int)p.len_prev + unit_first_token(uc, p.by_group) + 1;
   }
   const bool idle = !unit_valid[0];  // (then the second unit does not exist either)
   const int vis_min = vis_first[0];  // units ascend with the tokens, so unit 0 has the nearest horizon
@@ -282,41 +292,37 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);  // bytes from one token's row to the next
   const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
   const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
-  // This workgroup's share of the copy: rows [r0, r1) of K and of V, 16 bytes per lane and access, loaded once the
-  // ring refill and the Q loads are on their way and stored while the Q rows are scaled, so that its latency is not
-  // paid on its own.
-  constexpr int kCopyBatch = 4;
-  int copy_r0 = 0, copy_nvec = 0;
+  // This workgroup's share of the copy: rows [r0, r1) of K and of V, 16 bytes per lane and access, loaded before the
+  // results are stored and stored behind them, so that its latency is not paid on its own.
+  constexpr int kCopyRows = 256 / CH;  // rows of a turn: a thread moves 16 bytes of a K row and of the V row
+  constexpr int kCopyTurns = 2;        // turns whose loads are in flight together
+  int copy_r0 = 0, copy_r1 = 0;
   if (fused) {
     copy_r0 = rem * p.copy_rows;
-    const int r1 = copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C;
-    copy_nvec = (r1 > copy_r0 ? r1 - copy_r0 : 0) * CH;  // 16-byte vectors per tensor
+    copy_r1 = copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C;
   }
-  auto copy_src = [&](int idx) __attribute__((always_inline)) -> const uintx4* {
-    const bool is_v = idx >= copy_nvec;
-    const int e = is_v ? idx - copy_nvec : idx, r = copy_r0 + e / CH, c = e % CH;
-    return reinterpret_cast<const uintx4*>((is_v ? vnew : knew) + (int64_t)r * new_stride + c * 16);
-  };
-  auto copy_dst = [&](int idx) __attribute__((always_inline)) -> uintx4* {
-    const bool is_v = idx >= copy_nvec;
-    const int e = is_v ? idx - copy_nvec : idx, r = copy_r0 + e / CH, c = e % CH;
-    return reinterpret_cast<uintx4*>(const_cast<unsigned char*>(is_v ? vbase : kbase) + (p.len_prev + r) * ROWB + c * 16);
-  };
-  uintx4 copy_v[kCopyBatch] = {};
-  auto copy_load = [&](int i0) __attribute__((always_inline)) {
+  uintx4 copy_k[kCopyTurns] = {}, copy_v[kCopyTurns] = {};
+  auto copy_load = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kCopyBatch; ++u)
-      if (i0 + u * 256 < 2 * copy_nvec && tid + i0 + u * 256 < 2 * copy_nvec) copy_v[u] = *copy_src(tid + i0 + u * 256);
+    for (int u = 0; u < kCopyTurns; ++u) {
+      const int r = r0 + u * kCopyRows + tid / CH;
+      if (r0 + u * kCopyRows < copy_r1 && r < copy_r1) {
+        const unsigned off = (unsigned)r * new_stride + (unsigned)(tid % CH) * 16u;
+        copy_k[u] = *reinterpret_cast<const uintx4*>(knew + off);
+        copy_v[u] = *reinterpret_cast<const uintx4*>(vnew + off);
+      }
+    }
   };
-  auto copy_store = [&](int i0) __attribute__((always_inline)) {
+  auto copy_store = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kCopyBatch; ++u)
-      if (i0 + u * 256 < 2 * copy_nvec && tid + i0 + u * 256 < 2 * copy_nvec)
-        __builtin_nontemporal_store(copy_v[u], copy_dst(tid + i0 + u * 256));
-    // the loads end here on every path: one that the compiler took to be pending would be waited for in the main loop,
-    // together with the whole ring
-#pragma unroll
-    for (int u = 0; u < kCopyBatch; ++u) asm volatile("" ::"v"(copy_v[u]));
+    for (int u = 0; u < kCopyTurns; ++u) {
+      const int r = r0 + u * kCopyRows + tid / CH;
+      if (r0 + u * kCopyRows < copy_r1 && r < copy_r1) {
+        const unsigned off = (unsigned)((int)p.len_prev + r) * (unsigned)ROWB + (unsigned)(tid % CH) * 16u;
+        __builtin_nontemporal_store(copy_k[u], reinterpret_cast<uintx4*>(const_cast<unsigned char*>(kbase) + off));
+        __builtin_nontemporal_store(copy_v[u], reinterpret_cast<uintx4*>(const_cast<unsigned char*>(vbase) + off));
+      }
+    }
   };
 
   // ---- DMA addressing: wavefront w moves slabs w, w+4, ...; lane l lands at chunk (l % CH) of row
@@ -371,30 +377,29 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     }
   };
 
-  // ---- the ring is filled first (only addresses are needed), then the Q fragments are fetched: the two
-  // latencies overlap.  Q, pre-multiplied by scale*log2(e), stays in registers for the whole kernel.
-  // Code that a launch runs once is fetched at about 3 bytes per ns (measured: an unrolled fill of 6 KB took 2.3 us of
-  // a workgroup's start), so the fill is a loop.
-  auto prefill = [&]() __attribute__((always_inline)) {
+  // ---- the first two tiles, then the Q fragments, then the rest of the ring: the latencies overlap, and Q does not
+  // queue behind tiles that are wanted later.  Q, pre-multiplied by scale*log2(e), stays in registers for the whole
+  // kernel.  Code that a launch runs once is fetched at about 3 bytes per ns (measured: an unrolled fill of 6 KB took
+  // 2.3 us of a workgroup's start), so the fill is a loop.
+  auto prefill = [&](int j0, int j1) __attribute__((always_inline)) {
     // Steady state at the top of the even step of tile t: K[t], K[t+1], V[t] are in LDS and visible, the
     // groups {K[t+1+j], V[t+j]}, j = 1 .. NV-1, are in flight.  Tile t_begin + j takes ring slot j.
 #pragma unroll 1
-    for (int j = 0; j <= NV; ++j) {
+    for (int j = j0; j <= j1; ++j) {
       issue_tile(false, t_begin + j, j);
       if (j > 0) issue_tile(true, t_begin + j - 1, j - 1);
     }
   };
-  if (t_begin < t_end) prefill();
+  prefill(0, 1);
   bf16x8 qf[QB][KS];
   {
     bf16x8 raw[QB][KS];  // every load in flight before the first is waited for
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + ((int64_t)tok[qb] * Hq + head[qb]) * D;
+      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + (uint64_t)q_row[qb] * D;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) raw[qb][ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16 + hi * 8);
     }
-    copy_load(0);
     if (p.rope_cos) {
       // Rotary embedding at the row's absolute position (Sec. 2), half-split pairs (j, j + D/2), fp32 with
       // the sine product rounded first, result rounded to bf16: bit for bit what a caller that rotates q
@@ -425,11 +430,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       }
   }
 
-  copy_store(0);
-  for (int i0 = kCopyBatch * 256; i0 < 2 * copy_nvec; i0 += kCopyBatch * 256) {
-    copy_load(i0);
-    copy_store(i0);
-  }
+  prefill(2, NV);
 
   // ---- LDS read offsets (per lane) of the tile currently being read, ring slot included; moved
   // from slot to slot once per tile
@@ -889,8 +890,8 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       int t_plain = tlogical((Lm1 + 1) / BN < t_new ? (Lm1 + 1) / BN : t_new);
       t_plain = t_plain >= t_end ? t_end : t_plain - NV - 1;
       if (t_plain > t_fast) t_plain = t_fast;
-      // Prologue.  The first pass finds the ring filled ahead of the Q loads; a second pass fills it again.
-      if (exact) prefill();
+      // Prologue.  The first pass finds the ring's fill under way; a second pass fills it again.
+      if (exact) prefill(0, NV);
       if (t_begin + NV < t_end)  // every group of the fill is whole
         wait_vm<(NV - 1) * LPG>();
       else
@@ -972,25 +973,26 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       }
       wait_vm<0>();  // nothing of ours may still be writing LDS when the workgroup retires or starts over
       wait_lds<0>();
-      if (!SUM_MODE || exact) break;
+      if (!SUM_MODE || exact) {
+        __syncthreads();  // every wavefront of the workgroup is through with the rings
+        break;
+      }
       {
-        // Did a row sum of any wavefront overflow?  The rings are dead now: their first bytes carry the vote.
-        __builtin_amdgcn_s_barrier();
-        if (l == 0) *LDS_PTR(int, lds0 + 4u * (unsigned)w) = overflowed;
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_s_barrier();
+        // Did a row sum of any wavefront overflow?  (The votes have words of their own behind the rings.)
+        if (l == 0) *LDS_PTR(int, lds0 + (unsigned)((NK + NV) * TILEB) + 4u * (unsigned)w) = overflowed;
+        __syncthreads();  // ... which also finds every wavefront through with the rings
         int any_overflow = 0;
 #pragma unroll
-        for (int ww = 0; ww < 4; ++ww) any_overflow |= *LDS_PTR(const int, lds0 + 4u * (unsigned)ww);
+        for (int ww = 0; ww < 4; ++ww) any_overflow |= *LDS_PTR(const int, lds0 + (unsigned)((NK + NV) * TILEB) + 4u * (unsigned)ww);
         any_overflow = __builtin_amdgcn_readfirstlane(any_overflow);
-        __builtin_amdgcn_s_barrier();  // every wavefront has read the vote before the next pass refills the ring
         if (__builtin_expect(any_overflow == 0, 1)) break;
       }
     }
+    mfma_settle_a(o[0][0]);  // (one wait for all; the others are tied behind it)
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-      for (int db = 0; db < DB; ++db) mfma_settle_a(o[qb][db]);
+      for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(o[qb][db]));
   } else {
     reset_state();
   }
@@ -998,21 +1000,44 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   // ---- epilogue.  O^T leaves through LDS (the rings are dead by now): a lane holds four consecutive
   // columns of one row, which stored directly would be 8- or 16-byte pieces scattered over 32 rows per
   // instruction; turned in LDS, every store instruction writes whole rows, 16 bytes per lane.
-  __builtin_amdgcn_s_barrier();  // every wavefront of the workgroup is through with the rings
-  const int64_t n_rows = (int64_t)C * Hq;
   // (the lane's place and its row's token and head are formed anew: nothing is held for them through the main loop)
   const int le = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), hie = le >> 5, me = le & 31;
+  copy_load(copy_r0);  // (in flight while the results leave)
   constexpr int OROWF = D * 4 + 16;  // padded LDS row: fp32 partials
   constexpr int OROWH = D * 2 + 16;  // padded LDS row: bf16 output
   const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROWF);  // this wavefront's staging area, reused by its units
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const float l_tot = pair_sum(l_run[qb]);
-    const UnitRows ur(unit_of[qb], p);
-    const int tok_e = ur.tok(me), head_e = g * G + ur.head(me);
-    const bool store_row = unit_valid[qb] && hie == 0 && tok_e < C;
-    // offset of row r of the unit in [token][query head] rows
-    auto out_row = [&](int r) __attribute__((always_inline)) -> int64_t { return (int64_t)ur.tok(r) * Hq + g * G + ur.head(r); };
+    const unsigned row0 = (unsigned)(unit_of[qb] * kRowsPerUnit);
+    // rows of the unit that exist
+    const int n_live = !unit_valid[qb] ? 0 : (int)(n_packed - row0) < kRowsPerUnit ? (int)(n_packed - row0) : kRowsPerUnit;
+    const bool store_row = hie == 0 && me < n_live;
+    // place of the lane's row among the KV head's rows of [token][query head]
+    const unsigned my_row = row0 + (unsigned)me, my_tok = quot(my_row, p.by_group), my_place = my_row + my_tok * (unsigned)(Hq - G);
+    // `rows` whole rows of `chunks` 16-byte pieces, turned in LDS, to dst (the KV head's first row); few instructions per
+    // store and a loop: written out with 64-bit row arithmetic for each store this took 3 us of a workgroup's end
+    auto store_rows = [&](unsigned char* dst, auto bytes_tag, unsigned lds_row) __attribute__((always_inline)) {
+      constexpr int BYTES = decltype(bytes_tag)::value, CPR = BYTES / 16, RPI = 64 / CPR;
+      const unsigned r_lane = (unsigned)le / CPR, c = (unsigned)le % CPR * 16u;
+      unsigned char* lane_dst = dst + c;
+      unsigned at = obase + r_lane * lds_row + c;
+#pragma unroll 1
+      for (unsigned i = r_lane; i < (unsigned)kRowsPerUnit; i += 4 * RPI) {
+        uintx4 x[4];
+#pragma unroll
+        for (unsigned j = 0; j < 4; ++j) x[j] = *LDS_PTR(const uintx4, at + j * RPI * lds_row);
+#pragma unroll
+        for (unsigned j = 0; j < 4; ++j) asm volatile("" : "+v"(x[j]));
+#pragma unroll
+        for (unsigned j = 0; j < 4; ++j) {
+          const unsigned r = i + j * RPI;
+          const unsigned at_row = (unsigned)__builtin_amdgcn_ds_bpermute((int)(4 * r), (int)my_place);
+          if ((int)r < n_live) __builtin_nontemporal_store(x[j], reinterpret_cast<uintx4*>(lane_dst + (uint64_t)at_row * BYTES));
+        }
+        at += 4 * RPI * lds_row;
+      }
+    };
     if (p.n_splits == 1) {
       const float inv = 1.f / l_tot;
 #pragma unroll
@@ -1025,16 +1050,8 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
           *LDS_PTR(bf16x4, obase + (unsigned)(me * OROWH + (db * 32 + 8 * rg + 4 * hie) * 2)) = v;
         }
       if (p.lse && store_row)
-        p.lse[(int64_t)head_e * C + tok_e] = (m_run[qb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
-      constexpr int CPR = D / 8;        // 16-byte chunks per row
-      constexpr int RPI = 64 / CPR;     // rows per store instruction
-#pragma unroll
-      for (int i = 0; i < kRowsPerUnit / RPI; ++i) {
-        const int r = i * RPI + le / CPR, c = le % CPR;
-        const uintx4 x = *LDS_PTR(const uintx4, obase + (unsigned)(r * OROWH + c * 16));
-        if (unit_valid[qb] && ur.tok(r) < C)
-          __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(reinterpret_cast<__bf16*>(p.out) + out_row(r) * D + c * 8));
-      }
+        p.lse[(int64_t)(g * G + (int)(my_row - my_tok * (unsigned)G)) * C + my_tok] = (m_run[qb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
+      store_rows(reinterpret_cast<unsigned char*>(p.out) + (uint64_t)(g * G) * (D * 2), std::integral_constant<int, D * 2>{}, OROWH);
     } else {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -1045,26 +1062,23 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
           for (int e = 0; e < 4; ++e) v[e] = o[qb][db][rg * 4 + e];
           *LDS_PTR(floatx4, obase + (unsigned)(me * OROWF + (db * 32 + 8 * rg + 4 * hie) * 4)) = v;
         }
-      if (store_row) {
-        float2 ml = make_float2(m_run[qb], l_tot);
-        *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + (int64_t)tok_e * Hq + head_e) * 2) = ml;
-      }
-      constexpr int CPR = D / 4;        // 16-byte chunks per row
-      constexpr int RPI = 64 / CPR;     // rows per store instruction
-#pragma unroll
-      for (int i = 0; i < kRowsPerUnit / RPI; ++i) {
-        const int r = i * RPI + le / CPR, c = le % CPR;
-        const floatx4 x = *LDS_PTR(const floatx4, obase + (unsigned)(r * OROWF + c * 16));
-        if (unit_valid[qb] && ur.tok(r) < C)
-          __builtin_nontemporal_store(x, reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + out_row(r)) * D + c * 4));
-      }
+      const uint64_t first = (uint64_t)split * (uint64_t)(C * Hq) + (uint64_t)(g * G);  // the head's first row of this piece
+      if (store_row)
+        *reinterpret_cast<float2*>(p.part_ml + (first + my_place) * 2) = make_float2(m_run[qb], l_tot);
+      store_rows(reinterpret_cast<unsigned char*>(p.part_o) + first * (D * 4), std::integral_constant<int, D * 4>{}, OROWF);
     }
+  }
+
+  copy_store(copy_r0);
+  for (int r0 = copy_r0 + kCopyTurns * kCopyRows; r0 < copy_r1; r0 += kCopyTurns * kCopyRows) {
+    copy_load(r0);
+    copy_store(r0);
   }
 }
 
 template <int D, int QB, int NV>
 static hipError_t prepare_one() {
-  constexpr int lds_bytes = (2 * NV + 1) * kTileKeys * D * 2;
+  constexpr int lds_bytes = (2 * NV + 1) * kTileKeys * D * 2 + vote_bytes(QB);
   // per device: the attribute belongs to the device's copy of the kernel (idempotent; a benign race at worst
   // sets it twice)
   static bool attr_done[64] = {};
@@ -1081,7 +1095,7 @@ static hipError_t prepare_one() {
 
 template <int D, int QB, int NV>
 static hipError_t launch_one(const AttnParams& p, hipStream_t s) {
-  constexpr int lds_bytes = (2 * NV + 1) * kTileKeys * D * 2;
+  constexpr int lds_bytes = (2 * NV + 1) * kTileKeys * D * 2 + vote_bytes(QB);
   hipError_t e = prepare_one<D, QB, NV>();  // a no-op after kvfold_cache_create
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((attn_bf16_kernel<D, QB, NV>), dim3(padded_grid(p.n_wgs)), dim3(256), lds_bytes, s, p);

@@ -37,7 +37,8 @@ inline FastDiv fast_div(int d) {
   return f;
 }
 KVFOLD_HD unsigned quot(unsigned n, int d) { return n / (unsigned)d; }
-KVFOLD_HD unsigned quot(unsigned n, const FastDiv& d) { return (unsigned)(((unsigned long long)n * d.mul) >> d.shift); }
+// (in two 32-bit steps: the high word of 2 n mul, which is (n mul) >> 31, then the rest of the shift)
+KVFOLD_HD unsigned quot(unsigned n, const FastDiv& d) { return (unsigned)(((unsigned long long)(2 * n) * d.mul) >> 32) >> (d.shift - 31); }
 
 // 32-row units of one KV head: its n_tokens * G packed rows, the last unit filled up.
 KVFOLD_HD int units_of_head(int n_tokens, int G) { return (int)(((long long)n_tokens * G + kRowsPerUnit - 1) / kRowsPerUnit); }
