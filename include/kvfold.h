@@ -245,10 +245,10 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
  *                              round of workgroups), 1 = never, 2 = always.
- *   KVFOLD_TUNE_FUSED_APPEND   bf16 mode: the attention kernel copies the chunk's rows into the cache itself
+ *   KVFOLD_TUNE_FUSED_APPEND   the attention kernel copies the chunk's rows into the cache itself
  *                              (and reads the chunk's own rows from k_new / v_new) whenever neither rotary
- *                              embedding nor a storage round trip is in play and n_tokens * n_kv_heads * head_dim * 2 bytes is
- *                              below 2^32 (the kernel addresses the chunk with 32-bit byte offsets; larger
+ *                              embedding nor a storage round trip is in play and the chunk's K rows (n_tokens * n_kv_heads * head_dim
+ *                              elements) take less than 2^32 bytes (the kernel addresses the chunk with 32-bit byte offsets; larger
  *                              chunks go through the separate append kernel); 0 = automatic, 1 = never.
  *                              Either way k_new / v_new must stay valid until the step's work on the
  *                              stream is done, and the cache ends up with the same bits.
@@ -277,7 +277,8 @@ typedef struct {
   int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32, and bf16 steps of at */
                            /* most 32 rows per KV head, which have a kernel of their own: 1)            */
   int32_t tiles_per_split; /* 64-key tiles per piece                                                    */
-  int32_t fused_append;    /* 1: the attention kernel appends the chunk's rows itself (kvfold_step_ex)  */
+  int32_t fused_append;    /* 1: the bf16 attention kernel appends the chunk's rows itself              */
+                           /* (kvfold_step_ex); 0 for fp32, where workgroups of four wavefronts do so too */
   int32_t pair_units;      /* 1: every wavefront owns an early and a late row block of the chunk        */
   int32_t pair_order;      /* 1: workgroups ordered so that each CU gets a heavy and a light one        */
 } kvfold_plan_t;

@@ -90,6 +90,9 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   constexpr int ITEMS = BN * D / 8;          // vectors of 8 values per tensor and tile
   constexpr int PER = ITEMS >= NT ? ITEMS / NT : 1;
   constexpr float kThresh = 8.0f;
+  // The next tile's values on their way together with its keys, a step ahead of their use, where there are registers for it
+  // (D = 128 has none left); 32 keys of half the width are worked off faster than memory answers.
+  constexpr bool kBothAhead = D == 64;
 
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUFB];
   // keys with a number that the terms cannot hold: by tile, for the two tiles in flight and one being cleared, and the list
@@ -160,29 +163,75 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
   const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
 
+  // ---- fused append (paper Sec. 2: the chunk's K/V rows join the cache): rows from chunk0 on are read as handed in,
+  // [C][Hkv][d], so that no workgroup waits for another's copy; the copy into the cache, for the steps to come, is shared
+  // out over the workgroups of the KV head.  As a kernel of its own it was one launch of the three that a short step took:
+  // a fold of 4 x 128 tokens, 4 heads on 1, D = 64, 63.4 us with it, 56.9 without (three of these from loading the first
+  // tile's values with its keys).  Not with eight wavefronts: their steps are long, and what the second source costs the
+  // main loop in scalar registers is as much as the launch (512 tokens on 16K keys, 28 heads on 4: 645 us with the append
+  // kernel, 647 without).
+  const bool fused = NW == 4 && p.k_new != nullptr;
+  const int chunk0 = fused ? (int)p.len_prev : 0x7fffffff;
+  const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);  // bytes from one token's row to the next
+  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
+  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
+  auto row_at = [&](bool is_v, int row) __attribute__((always_inline)) -> const unsigned char* {
+    const bool nw = row >= chunk0;
+    const unsigned char* base = nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase);
+    return base + (unsigned)(row - (nw ? chunk0 : 0)) * (nw ? new_stride : (unsigned)ROWB);
+  };
+  // ... of a tile whose rows are all in the cache (old), or not
+  auto row_of = [&](bool is_v, int row, auto old_tag) __attribute__((always_inline)) -> const unsigned char* {
+    if constexpr (decltype(old_tag)::value || NW != 4) return (is_v ? vbase : kbase) + (unsigned)row * (unsigned)ROWB;
+    return row_at(is_v, row);
+  };
+  auto is_old = [&](int h) __attribute__((always_inline)) -> bool { return first_key(h) + BN <= chunk0; };
+  // This workgroup's share of the copy: rows [copy_r0, copy_r1) of K and of V, 16 bytes per thread, loaded before the
+  // results are stored and stored behind them.
+  constexpr int CPR = ROWB / 16, kCopyRows = NT / CPR;
+  const int copy_r0 = fused ? rem * p.copy_rows : 0;
+  const int copy_r1 = fused ? (copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C) : 0;
+  uintx4 copy_k = {}, copy_v = {};
+  auto copy_load = [&](int r0) __attribute__((always_inline)) {
+    const int r = r0 + tid / CPR;
+    if (r < copy_r1) {
+      const unsigned off = (unsigned)r * new_stride + (unsigned)(tid % CPR) * 16u;
+      copy_k = *reinterpret_cast<const uintx4*>(knew + off);
+      copy_v = *reinterpret_cast<const uintx4*>(vnew + off);
+    }
+  };
+  auto copy_store = [&](int r0) __attribute__((always_inline)) {
+    const int r = r0 + tid / CPR;
+    if (r < copy_r1) {
+      const unsigned off = (unsigned)(chunk0 + r) * (unsigned)ROWB + (unsigned)(tid % CPR) * 16u;
+      __builtin_nontemporal_store(copy_k, reinterpret_cast<uintx4*>(const_cast<unsigned char*>(kbase) + off));
+      __builtin_nontemporal_store(copy_v, reinterpret_cast<uintx4*>(const_cast<unsigned char*>(vbase) + off));
+    }
+  };
+
   // ---- split of a tile on its way into LDS.  K: thread = (row, 8 columns), read as it lies; the fragment of contraction
   // step ks, lane (m, hi), goes to slot m ^ (2 ks + hi) % 8 of its 32, so that neighbouring threads, which hold neighbouring
   // columns of one row, write different banks.  V: thread = (column, the 8 keys that registers 8 tt .. 8 tt + 7 of S^T stand
   // for in its half-wave).  Rows past the last one are read as the last one (and masked).  With fewer vectors than
   // threads (D = 64, eight wavefronts) the first half of the wavefronts splits K, the second V.
   const bool k_mine = ITEMS >= NT || tid < ITEMS, v_mine = ITEMS >= NT || tid >= NT - ITEMS;
-  float stage[PER][8];
-  auto load_k = [&](int h) __attribute__((always_inline)) {
+  float stage_k[PER][8], stage_v[PER][8];
+  auto load_k = [&](int h, auto old_tag) __attribute__((always_inline)) {
     const int key0 = first_key(h);
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
       const int ci = it * NT + tid;
       int row = key0 + ci / (D / 8);
       if (row > L - 1) row = L - 1;
-      const float4* src = reinterpret_cast<const float4*>(kbase + (unsigned)row * (unsigned)ROWB + (ci % (D / 8)) * 32);
+      const float4* src = reinterpret_cast<const float4*>(row_of(false, row, old_tag) + (ci % (D / 8)) * 32);
       if (k_mine) {
         const float4 a = src[0], b = src[1];
-        stage[it][0] = a.x; stage[it][1] = a.y; stage[it][2] = a.z; stage[it][3] = a.w;
-        stage[it][4] = b.x; stage[it][5] = b.y; stage[it][6] = b.z; stage[it][7] = b.w;
+        stage_k[it][0] = a.x; stage_k[it][1] = a.y; stage_k[it][2] = a.z; stage_k[it][3] = a.w;
+        stage_k[it][4] = b.x; stage_k[it][5] = b.y; stage_k[it][6] = b.z; stage_k[it][7] = b.w;
       }
     }
   };
-  auto load_v = [&](int h) __attribute__((always_inline)) {
+  auto load_v = [&](int h, auto old_tag) __attribute__((always_inline)) {
     const int key0 = first_key(h);
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
@@ -194,12 +243,12 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
         for (int j = 0; j < 8; ++j) {
           int row = key + 8 * (j >> 2) + (j & 3);
           if (row > L - 1) row = L - 1;
-          stage[it][j] = *reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB + (vi % D) * 4);
+          stage_v[it][j] = *reinterpret_cast<const float*>(row_of(true, row, old_tag) + (vi % D) * 4);
         }
       }
     }
   };
-  auto put = [&](int h, bool is_v) __attribute__((always_inline)) {
+  auto put = [&](int h, bool is_v, float (&stage)[PER][8]) __attribute__((always_inline)) {
     unsigned char* buf = smem + (h & 1) * BUFB + (is_v ? kTerms * TERMB : 0);
     if (is_v ? v_mine : k_mine) {
       float probe = 0.f;
@@ -252,7 +301,10 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   bool odd_q = false, odd_row = false;  // some row of the unit, this lane's row
   if (tid < 3) odd_keys[tid] = 0;
   if (tid == 3) odd_tiles = 0;
-  if (h_begin < h_end) load_k(h_begin);
+  if (h_begin < h_end) {
+    load_k(h_begin, std::false_type{});
+    load_v(h_begin, std::false_type{});
+  }
   {
     float raw[KS][8];
     const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)tok * Hq + head) * D + hi * 8;
@@ -309,9 +361,8 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
 
   if (h_begin < h_end) {
     __syncthreads();  // the words above are clear
-    put(h_begin, false);
-    load_v(h_begin);
-    put(h_begin, true);
+    put(h_begin, false, stage_k);
+    put(h_begin, true, stage_v);
   }
   floatx16 s;
   auto logits = [&](int h, auto split_tag) __attribute__((always_inline)) {
@@ -348,7 +399,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       int row = key0 + m2, t2 = ur.tok(m2), h2 = ur.head(m2);
       if (row > L - 1) row = L - 1;
       if (t2 > C - 1) t2 = C - 1, h2 = G - 1;
-      const float* krow = reinterpret_cast<const float*>(kbase + (unsigned)row * (unsigned)ROWB) + hi2 * 8;
+      const float* krow = reinterpret_cast<const float*>(row_at(false, row)) + hi2 * 8;
       const float* qrow = reinterpret_cast<const float*>(p.q) + ((int64_t)t2 * Hq + g * G + h2) * D;
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -458,7 +509,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
         for (int j = 0; j < 4; ++j) {
           int row = key0 + 2 * r0 + j + 4 * (l2 >> 5);
           if (row > L - 1) row = L - 1;
-          const float* vrow = reinterpret_cast<const float*>(vbase + (unsigned)row * (unsigned)ROWB) + (l2 & 31);
+          const float* vrow = reinterpret_cast<const float*>(row_at(true, row)) + (l2 & 31);
 #pragma unroll
           for (int db = 0; db < DB; ++db) v[j][db] = vrow[db * 32];
         }
@@ -475,16 +526,17 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   // (A second wavefront per SIMD that does its O^T one step later, so that the two are never in the softmax together, was
   // 4 % slower; a priority for one of the two changed nothing.)
   unsigned hide = 0;
-  for (int h = h_begin; h < h_end; ++h) {
+  auto step = [&](int h, auto old_tag) __attribute__((always_inline)) {
     __syncthreads();  // tile h is in LDS, and nobody reads tile h - 1 any more
     const int hn = h + 1 < h_end ? h + 1 : h;  // (past the last tile it is fetched again, for nobody)
     const bool work = !idle && first_key(h) < vis_last;  // (else every row is masked)
     const unsigned hide_before = hide;
     hide = __builtin_amdgcn_readfirstlane(odd_keys[(unsigned)h % 3u]);
-    load_k(hn);
+    load_k(hn, old_tag);
+    if (kBothAhead) load_v(hn, old_tag);
     if (work) logits(h, by_terms);
-    put(h + 1, false);
-    load_v(hn);
+    put(h + 1, false, stage_k);
+    if (!kBothAhead) load_v(hn, old_tag);
     if (__builtin_expect((hide | hide_before) != 0, 0)) {
       if (tid == 0) {
         if (hide_before) odd_keys[(unsigned)(h + 2) % 3u] = 0;  // tile h - 1's, next used for tile h + 2
@@ -499,9 +551,16 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       softmax(h, hide);
       add_values(h, by_terms);
     }
-    put(h + 1, true);
-  }
+    put(h + 1, true, stage_v);
+  };
+  // (two loops: with the choice between the two sources inside one, every tile of the prefix pays for it, 2.5 %)
+  int h = h_begin;
+  for (; h < h_end && (NW != 4 || is_old(h + 1 < h_end ? h + 1 : h)); ++h) step(h, std::true_type{});
+  if (NW == 4)
+    for (; h < h_end; ++h) step(h, std::false_type{});
   __syncthreads();
+
+  copy_load(copy_r0);  // (in flight while the results leave)
 
   // ---- keys and rows for the fp32 instructions, and the epilogue: first the rows whose query the terms can hold
   const int n_odd = __builtin_amdgcn_readfirstlane(odd_tiles);
@@ -555,6 +614,12 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       }
     }
     if (!odd_q) break;
+  }
+
+  copy_store(copy_r0);
+  for (int r0 = copy_r0 + kCopyRows; r0 < copy_r1; r0 += kCopyRows) {
+    copy_load(r0);
+    copy_store(r0);
   }
 }
 

@@ -259,9 +259,9 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.rope_sin = opt.rope_sin;
   at.n_sink = opt.n_sink;
   at.window = (int32_t)opt.window;
-  // The bf16 attention kernel appends by itself when nothing has to happen to the rows on their way in and the
+  // The attention kernel appends by itself when nothing has to happen to the rows on their way in and the
   // chunk's rows can be addressed with 32-bit byte offsets.
-  const bool fused_append = fused_append_applies(pc, n_tokens, len_prev, opt.rope_cos != nullptr);
+  const bool fused_append = attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
   finish_attn_params(at);

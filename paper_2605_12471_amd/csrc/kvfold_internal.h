@@ -52,7 +52,7 @@ struct AttnParams {
   // chunk's absolute positions, [C][d/2] fp32 each
   const float* rope_cos;
   const float* rope_sin;
-  // Append fused into the bf16 attention kernel (nullptr: the cache already holds the chunk's rows): the
+  // Append fused into the attention kernel (nullptr: the cache already holds the chunk's rows): the
   // chunk's K / V rows as handed in, [C][Hkv][d].  Tiles of the chunk are then streamed from here, and every
   // workgroup copies its share of the rows into the cache for the steps to come.
   const void* k_new;

@@ -47,8 +47,15 @@ int64_t workspace_rows(const kvfold_config_t* cfg) {
 // the largest is below C * Hkv * row_bytes, which therefore has to stay below 2^32.
 bool fused_append_applies(const PlanCtx& c, int n_tokens, int64_t len_prev, bool rope) {
   const kvfold_config_t& f = c.cfg;
-  if (f.dtype != KVFOLD_BF16 || rope || c.storage_bits || c.tune_fused_append == 1) return false;
+  if (f.dtype != KVFOLD_BF16) return false;
   (void)len_prev;  // any cache length: a tile that straddles the cache's end is filled from both sides
+  return attention_appends(c, Plan{}, n_tokens, rope);
+}
+
+bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope) {
+  const kvfold_config_t& f = c.cfg;
+  if (f.dtype != KVFOLD_BF16 && pl.waves_per_wg != 4) return false;
+  if (rope || c.storage_bits || c.tune_fused_append == 1) return false;
   const int64_t chunk_bytes = (int64_t)n_tokens * f.n_kv_heads * f.head_dim * elem_size(f.dtype);
   return chunk_bytes < ((int64_t)1 << 32);
 }
@@ -127,7 +134,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     const double active = f.dtype == KVFOLD_BF16 ? std::sqrt(std::sqrt(with_rows)) : std::sqrt(with_rows);
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
     const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / (few_rows ? 5.9e6 : 6.5e6);
-    const int launches = f.dtype != KVFOLD_BF16 || c.storage_bits ? 2 : 1;
+    const int launches = c.storage_bits || waves == 8 ? 2 : 1;
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
       // only split counts that whole tiles can realise; the last piece may be shorter than the others, and the

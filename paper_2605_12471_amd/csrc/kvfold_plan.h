@@ -36,7 +36,9 @@ int64_t workspace_rows(const kvfold_config_t* cfg);
 // Launch geometry of one step of n_tokens rows that leaves the cache at len_after rows; window > 0 selects the
 // sink + sliding-window step (n_sink first keys plus the last `window` keys of every row).
 Plan make_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, int64_t window);
-// Whether the bf16 attention kernel does the append itself for this step.
+// Whether the attention kernel of a step with this plan does the append itself, and whether it is a bf16 kernel that does
+// (kvfold_plan_t::fused_append, which has always been about these).
+bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope);
 bool fused_append_applies(const PlanCtx& c, int n_tokens, int64_t len_prev, bool rope);
 
 }  // namespace kvfold
