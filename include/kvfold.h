@@ -247,7 +247,8 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *                              round of workgroups), 1 = never, 2 = always.
  *   KVFOLD_TUNE_FUSED_APPEND   the attention kernel copies the chunk's rows into the cache itself
  *                              (and reads the chunk's own rows from k_new / v_new) whenever neither rotary
- *                              embedding nor a storage round trip is in play and the chunk's K rows (n_tokens * n_kv_heads * head_dim
+ *                              embedding nor a storage round trip is in play (bf16 steps of at most 32
+ *                              (token, query head) rows per KV head: also then) and the chunk's K rows (n_tokens * n_kv_heads * head_dim
  *                              elements) take less than 2^32 bytes (the kernel addresses the chunk with 32-bit byte offsets; larger
  *                              chunks go through the separate append kernel); 0 = automatic, 1 = never.
  *                              Either way k_new / v_new must stay valid until the step's work on the

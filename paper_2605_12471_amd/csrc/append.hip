@@ -4,6 +4,7 @@
 //
 // HBM-bound: 16 bytes per lane, destination addresses of a wavefront are contiguous (one head's
 // rows are adjacent), source addresses are contiguous per row (d * elem_size bytes).
+#include "append_rows.h"
 #include "kvfold_internal.h"
 
 namespace kvfold {
@@ -25,23 +26,10 @@ __global__ void __launch_bounds__(256) append_kernel(AppendParams p, int log2_vp
 // The same carry with work on the rows' way into the cache: one pass, where the rotation and the storage round trip after
 // it used to be kernels of their own that read the new rows again (1024 tokens, 8 KV heads, both: 5.1 + 5.2 us in two
 // launches before, 5.3 us in one now).  A lane owns 16 bytes of a row; launch-latency bound at these sizes.
-//
-// ROPE, K rows only (Sec. 2: the new tokens' positions continue from the absolute position, so their rotations line up with
-// the original sequence).  Element j pairs with element j + d/2 (half-split layout):
-//     k'_j = k_j cos_j - k_{j+d/2} sin_j,   k'_{j+d/2} = k_{j+d/2} cos_j + k_j sin_j,
-// in fp32 -- the product of the other element with the sine rounded first, then one fused
-// multiply-add -- and rounded to the cache's element type (RNE).  The lane reads the 16 bytes half a row away as well.
-//
-// QUANT, K and V rows: the storage perturbation of the carried cache (Sec. 8, Discussion: a per-step quantisation round
-// trip bf16 -> intN -> bf16).  The paper names no quantiser; the reading: one group = the d elements of one (token, KV head)
-// row, symmetric,
-//   scale = max|x| / (2^(N-1) - 1),  code = round-half-even(x / scale) clamped to +-(2^(N-1) - 1),
-//   x' = code * scale,
-// all in fp32, stored as bf16 (RNE); an all-zero row stays zero.  The d / 8 lanes of a row agree on the maximum by butterfly
-// exchanges inside their lane group.
+// The arithmetic is in append_rows.h.
 template <typename T, int E, bool ROPE, bool QUANT>  // element type, elements per 16-byte vector
 __global__ void __launch_bounds__(256) append_work_kernel(AppendParams p, int log2_vpr, float qmax) {
-  typedef __attribute__((ext_vector_type(E))) T vec_t;
+  typedef row_vec<T, E> vec_t;
   const bool is_v = (blockIdx.y & 1) != 0;
   const int64_t g = blockIdx.y >> 1;
   const int vpr = 1 << log2_vpr, half = vpr >> 1;
@@ -58,33 +46,9 @@ __global__ void __launch_bounds__(256) append_work_kernel(AppendParams p, int lo
       const bool lower = c < half;
       const int a = lower ? c : c - half;
       const vec_t other = row[lower ? c + half : a];
-      const float* cs = p.rope_cos + (i * half + a) * E;
-      const float* sn = p.rope_sin + (i * half + a) * E;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const float mine = (float)v[e], theirs = (float)other[e];
-        const float t = theirs * sn[e];
-        v[e] = (T)__builtin_fmaf(mine, cs[e], lower ? -t : t);
-      }
+      rotate_vec<T, E>(v, other, p.rope_cos + (i * half + a) * E, p.rope_sin + (i * half + a) * E, lower);
     }
-    if (QUANT) {
-      float x[E], amax = 0.f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        x[e] = (float)v[e];
-        amax = fmaxf(amax, fabsf(x[e]));
-      }
-      for (int off = 1; off < vpr; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-      const float scale = amax / qmax;
-      if (scale > 0.f) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          float code = rintf(x[e] / scale);
-          code = fminf(fmaxf(code, -qmax), qmax);
-          v[e] = (T)(code * scale);
-        }
-      }
-    }
+    if (QUANT) round_trip_vec<T, E>(v, vpr, qmax);
     dst[idx] = v;
   }
 }

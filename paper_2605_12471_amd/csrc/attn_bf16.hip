@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
 
   // ---- which workgroup am I (XCD-aware: a KV head stays on its XCDs, see logical_workgroup())
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
-  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
+  const int lid = logical_workgroup(blockIdx.x, gridDim.x, p);
   if (lid >= p.n_wgs) return;
   const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int rem = lid - g * wgs_per_kvh;
@@ -282,16 +282,17 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   const int t_begin = kr.t_begin, t_end = kr.t_end;
   const int t_new = kr.t_straddle >= 0 ? kr.t_straddle : kr.t_new;  // first physical tile with rows of the chunk
 
-  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
-  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
+  const unsigned head_bytes = (unsigned)p.capacity * (unsigned)ROWB;  // (below 2^32, as the host checks)
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (uint64_t)(unsigned)g * head_bytes;
+  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (uint64_t)(unsigned)g * head_bytes;
 
   // ---- fused append (paper Sec. 2: the chunk's K/V rows join the cache): tiles from t_new on lie in the
   // chunk and are streamed from the rows as handed in, [C][Hkv][d], so no workgroup waits for another's
   // copy; the copy into the cache, for the steps to come, is shared out over the workgroups of the KV head.
   const bool fused = p.k_new != nullptr;
   const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);  // bytes from one token's row to the next
-  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
-  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
+  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (unsigned)g * (unsigned)ROWB;
+  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (unsigned)g * (unsigned)ROWB;
   // This workgroup's share of the copy: rows [r0, r1) of K and of V, 16 bytes per lane and access, loaded before the
   // results are stored and stored behind them, so that its latency is not paid on its own.
   constexpr int kCopyRows = 256 / CH;  // rows of a turn: a thread moves 16 bytes of a K row and of the V row

@@ -103,7 +103,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   __shared__ struct { int h; unsigned keys; } odd_list[kOddList];
 
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
-  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
+  const int lid = logical_workgroup(blockIdx.x, gridDim.x, p);
   if (lid >= p.n_wgs) return;
   const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int rem = lid - g * wgs_per_kvh;

@@ -15,6 +15,7 @@
 // One token, 32 heads on 8, D = 128, whole step, general kernel -> this one: 1K keys 12.5 -> 11.8 us (unsplit, one launch
 // instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
 // read gets 5.8 to 6.2).  Below about 8K keys a step is bound by the rate at which its launches are queued.
+#include "append_rows.h"
 #include "kvfold_internal.h"
 #include "wave_ops.h"
 
@@ -48,7 +49,10 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   constexpr int VSW = CH / 4;               // V swizzle: chunk ^= (row & 3) * VSW
   constexpr float kStale = 16.0f;           // log2 units
 
-  const int lid = logical_workgroup((int)blockIdx.x, (int)gridDim.x, p);
+  // every line of the arguments is fetched now, in one round trip (they are not in the scalar cache yet)
+  asm volatile("" ::"s"(p.q), "s"(p.n_tokens), "s"(p.len_prev), "s"(p.k_new), "s"(p.work_k), "s"(p.by_group.mul), "s"(p.copy_rows));
+
+  const int lid = logical_workgroup(blockIdx.x, gridDim.x, p);
   if (lid >= p.n_wgs) return;
   const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
   const int split = lid - g * p.n_splits;   // one workgroup per KV head and piece
@@ -64,17 +68,19 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   TileMap tm;
   tm.ns_t = 0;
   tm.skip = 0;
-  tm.ntiles = (int)((p.len_prev + C + kTileKeys - 1) / kTileKeys);
+  const unsigned len_after = (unsigned)p.len_prev + (unsigned)C;
+  tm.ntiles = (int)((len_after + kTileKeys - 1) / kTileKeys);
   const bool fused = p.k_new != nullptr;
   const KeyRange kr = key_range(tm, split, p.tiles_per_split, p.len_prev, C, fused);
-  const int b_all = (int)((p.len_prev + C + 31) / 32);
+  const int b_all = (int)((len_after + 31) / 32);
   const int b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;  // blocks of 32 keys
 
-  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (int64_t)g * p.capacity * ROWB;
-  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (int64_t)g * p.capacity * ROWB;
+  const unsigned head_bytes = (unsigned)p.capacity * (unsigned)ROWB;  // (below 2^32, as the host checks)
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (uint64_t)(unsigned)g * head_bytes;
+  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v_cache) + (uint64_t)(unsigned)g * head_bytes;
   const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);
-  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
-  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
+  const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (unsigned)g * (unsigned)ROWB;
+  const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (unsigned)g * (unsigned)ROWB;
 
   // Blocks of cache rows that all exist are plain; else each row comes from the cache or the chunk, or is redirected to the
   // piece's last row (and masked).
@@ -109,9 +115,18 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   // The wavefront's blocks, every fourth of the piece's, in cyclic order from a place that differs from piece to piece and
   // head to head: pieces and heads lie powers of two apart, and workgroups in step would ask the same few memory channels
   // for their rows.
-  const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + 3) / 4 : 0;
+  const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (int)((unsigned)(b_end - b_first + 3) / 4u) : 0;
   int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
-  if (n_blocks > 0) {
+  // A chunk whose rows need work on their way (append_rows.h): this workgroup appends those it is going to read, ahead of any
+  // block that holds some.
+  int work_r0 = 0, work_r1 = 0;
+  if (__builtin_expect(p.work_k && kr.t_begin < kr.t_end, 0)) {
+    work_r0 = kr.t_begin * kTileKeys - (int)p.len_prev;
+    if (work_r0 < 0) work_r0 = 0;
+    work_r1 = (int)kr.row_lim + 1 - (int)p.len_prev;
+  }
+  const bool block_first = work_r1 <= work_r0 || b * 32 + 32 <= (int)p.len_prev;
+  if (block_first && n_blocks > 0) {
     fetch(false, b);
     fetch(true, b);
   }
@@ -141,6 +156,17 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * p.scale_log2e);
+  }
+
+  if (__builtin_expect(work_r1 > work_r0, 0)) {
+    append_work_rows<D>(reinterpret_cast<const unsigned char*>(p.work_k) + g * ROWB, reinterpret_cast<const unsigned char*>(p.work_v) + g * ROWB, new_stride,
+                        const_cast<unsigned char*>(kbase) + (uint64_t)p.len_prev * ROWB, const_cast<unsigned char*>(vbase) + (uint64_t)p.len_prev * ROWB,
+                        p.rope_cos, p.rope_sin, p.work_qmax, work_r0, work_r1, tid);
+    __syncthreads();
+    if (!block_first && n_blocks > 0) {
+      fetch(false, b);
+      fetch(true, b);
+    }
   }
 
   // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes per thread and turn

@@ -76,6 +76,12 @@ int static_scratch(int device, unsigned char** out) {
   return KVFOLD_OK;
 }
 
+// Whether two ranges of memory have no byte in common.
+bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x + a_bytes <= y || y + b_bytes <= x;
+}
+
 struct DeviceGuard {
   int prev = -1;
   bool switched = false;
@@ -261,9 +267,20 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.window = (int32_t)opt.window;
   // The attention kernel appends by itself when nothing has to happen to the rows on their way in and the
   // chunk's rows can be addressed with 32-bit byte offsets.
-  const bool fused_append = attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
+  // (fp32, and below: not from rows that the step's own stores reach, which an append kernel in front has used up by then)
+  const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
+  bool rows_apart = true;
+  for (const void* rows : {k_new, v_new})
+    rows_apart = rows_apart && apart(rows, new_bytes, out, out_bytes) && apart(rows, new_bytes, c->kv, c->kv_bytes) &&
+                 (!lse || apart(rows, new_bytes, lse, (size_t)n_tokens * f.n_q_heads * sizeof(float)));
+  const bool fused_append = attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr) && (f.dtype == KVFOLD_BF16 || rows_apart);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
+  // A few rows that need work on their way: the workgroups that read them do it.
+  const bool work_rows = rows_apart && attention_works_on_rows(pc, pl, n_tokens, opt.rope_cos != nullptr);
+  at.work_k = work_rows ? k_new : nullptr;
+  at.work_v = work_rows ? v_new : nullptr;
+  at.work_qmax = pc.storage_bits ? (float)((1 << (pc.storage_bits - 1)) - 1) : 0.f;
   finish_attn_params(at);
   if (pl.n_splits > 1 && ((int64_t)pl.n_splits * n_tokens * f.n_q_heads > pc.ws_rows || !part_o))
     return KVFOLD_ERR_HIP;  // planner bug guard
@@ -275,11 +292,11 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     e = hipEventRecord(ev[0], s);
     if (e != hipSuccess) return hip_fail(e);
   }
-  if (!fused_append) {
-    e = launch_append(ap, pc.storage_bits, s);  // (a storage round trip rules the fused append out)
+  const bool own_append = !fused_append && !work_rows;  // the append is a kernel of its own, ahead of the attention kernel
+  if (own_append) {
+    e = launch_append(ap, pc.storage_bits, s);
     if (e != hipSuccess) return hip_fail(e);
   }
-  const bool own_append = !fused_append;  // something ran between ev[0] and the attention kernel
   if (ev && own_append) (void)hipEventRecord(ev[1], s);
   if (f.dtype != KVFOLD_BF16)
     e = launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);

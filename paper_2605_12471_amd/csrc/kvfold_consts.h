@@ -119,15 +119,17 @@ KVFOLD_HD KeyRange key_range(const TileMap& tm, int split, int tiles_per_split, 
   k.t_begin = split * tiles_per_split;
   k.t_end = k.t_begin + tiles_per_split;
   if (k.t_end > tm.ntiles) k.t_end = tm.ntiles;
+  // (32 bits: a cache has at most 2^30 rows, and this is part of what a workgroup does before its first fetch)
   const int last = k.t_end - 1;  // (only used when the piece is not empty)
-  const long long row_end = (long long)(last + (last >= tm.ns_t ? tm.skip : 0)) * kTileKeys + kTileKeys - 1;
-  const long long Lm1 = len_prev + n_tokens - 1;
-  const long long lim = row_end < Lm1 ? row_end : Lm1;
+  const int row_end = (last + (last >= tm.ns_t ? tm.skip : 0)) * kTileKeys + kTileKeys - 1;
+  const int Lm1 = (int)len_prev + n_tokens - 1;
+  const int lim = row_end < Lm1 ? row_end : Lm1;
   k.row_lim = (unsigned)(lim < 0 ? 0 : lim);
-  const bool reaches_chunk = fused && lim >= len_prev;
-  k.chunk_row0 = reaches_chunk ? (unsigned)len_prev : 0xffffffffu;
-  k.t_new = reaches_chunk ? (int)((len_prev + kTileKeys - 1) / kTileKeys) : 0x7fffffff;
-  k.t_straddle = reaches_chunk && len_prev % kTileKeys ? (int)(len_prev / kTileKeys) : -1;
+  const bool reaches_chunk = fused && lim >= (int)len_prev;
+  const unsigned row0 = (unsigned)len_prev;
+  k.chunk_row0 = reaches_chunk ? row0 : 0xffffffffu;
+  k.t_new = reaches_chunk ? (int)((row0 + kTileKeys - 1) / kTileKeys) : 0x7fffffff;
+  k.t_straddle = reaches_chunk && row0 % kTileKeys ? (int)(row0 / kTileKeys) : -1;
   return k;
 }
 

@@ -57,6 +57,12 @@ struct AttnParams {
   // workgroup copies its share of the rows into the cache for the steps to come.
   const void* k_new;
   const void* v_new;
+  // Few-rows kernel, rows that need work on their way into the cache (nullptr: not this step): the chunk's K / V rows as handed
+  // in.  Every workgroup appends the rows that it is going to read (rotated if rope_cos, through the storage round trip if
+  // work_qmax > 0) and then reads them from the cache like all others.
+  const void* work_k;
+  const void* work_v;
+  float work_qmax;
   // Sink + sliding-window step (window > 0; 0: every key up to the row's own position is visible): the row at
   // absolute position p sees keys j < n_sink and p - window < j <= p.  Tiles between the sink tiles and the
   // window are skipped (see tile_map()).
@@ -117,10 +123,11 @@ inline int padded_grid(int n_wgs) { return (n_wgs + kNumXcd - 1) / kNumXcd * kNu
 // A KV head that spans k = 8 / Hkv XCDs has its workgroups dealt to those XCDs in turn, not in k contiguous
 // runs: every XCD then gets the same mix of heavy and light workgroups and of prefix splits (a contiguous
 // run would put all late token blocks, or a whole split, on one XCD and the light rest on its neighbour).
-__device__ __forceinline__ int logical_workgroup(int b, int grid, const AttnParams& p) {
-  const int x = b % kNumXcd, j = b / kNumXcd, lk = p.xcd_share_log2;
-  if (lk >= 0) return (x >> lk) * (p.wgs_per_head * p.n_splits) + (j << lk) + (x & ((1 << lk) - 1));  // grid = Hkv * wgs per head
-  return x * (grid / kNumXcd) + j;
+__device__ __forceinline__ int logical_workgroup(unsigned b, unsigned grid, const AttnParams& p) {
+  const unsigned x = b % kNumXcd, j = b / kNumXcd;
+  const int lk = p.xcd_share_log2;
+  if (lk >= 0) return (int)((x >> lk) * (unsigned)(p.wgs_per_head * p.n_splits) + (j << lk) + (x & ((1u << lk) - 1)));  // grid = Hkv * wgs per head
+  return (int)(x * (grid / kNumXcd) + j);
 }
 
 // Packed rows of one unit (row j of unit u: packed row 32 u + j of the KV head, j < 32): token and head of the group.

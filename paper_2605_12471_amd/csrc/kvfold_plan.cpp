@@ -52,6 +52,17 @@ bool fused_append_applies(const PlanCtx& c, int n_tokens, int64_t len_prev, bool
   return attention_appends(c, Plan{}, n_tokens, rope);
 }
 
+bool attention_works_on_rows(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope) {
+  const kvfold_config_t& f = c.cfg;
+  if (!pl.few_rows || !(rope || c.storage_bits) || c.tune_fused_append == 1) return false;
+  // A launch less (3 us), against the work done once more by each workgroup that reaches the chunk.  Measured on 300, 5000
+  // and 32K keys, append kernel / this, D = 128, 32 heads on 8: rotary embedding, 1 token 10.4 / 8.7, 13.7 / 11.9, 28.8 / 26.8 us,
+  // 8 tokens 11.6 / 10.3, 15.8 / 13.7, 31.2 / 28.9; round trip, 8 tokens 11.9 / 9.9, 16.2 / 13.2, 30.6 / 28.1.  More rows are
+  // for the general kernel, whose ring has to be filled behind the rows: 37 tokens with the rotary embedding on 32K keys 45.9 / 46.8, and
+  // every other step paid 0.5 % for the code.  The round trip, with its divisions, takes 90 ns a row: up to 16 rows.
+  return !c.storage_bits || (int64_t)n_tokens * f.head_dim * elem_size(f.dtype) <= 4096;
+}
+
 bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope) {
   const kvfold_config_t& f = c.cfg;
   if (f.dtype != KVFOLD_BF16 && pl.waves_per_wg != 4) return false;
@@ -134,7 +145,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     const double active = f.dtype == KVFOLD_BF16 ? std::sqrt(std::sqrt(with_rows)) : std::sqrt(with_rows);
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
     const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / (few_rows ? 5.9e6 : 6.5e6);
-    const int launches = c.storage_bits || waves == 8 ? 2 : 1;
+    const int launches = (c.storage_bits && !attention_works_on_rows(c, pl, n_tokens, false)) || waves == 8 ? 2 : 1;
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
       // only split counts that whole tiles can realise; the last piece may be shorter than the others, and the

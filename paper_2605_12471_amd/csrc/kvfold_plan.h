@@ -36,6 +36,9 @@ int64_t workspace_rows(const kvfold_config_t* cfg);
 // Launch geometry of one step of n_tokens rows that leaves the cache at len_after rows; window > 0 selects the
 // sink + sliding-window step (n_sink first keys plus the last `window` keys of every row).
 Plan make_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, int64_t window);
+// Whether the rows of a step with this plan, which need work on their way into the cache, are appended by the workgroups of
+// the few-rows kernel that read them.
+bool attention_works_on_rows(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope);
 // Whether the attention kernel of a step with this plan does the append itself, and whether it is a bf16 kernel that does
 // (kvfold_plan_t::fused_append, which has always been about these).
 bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope);

@@ -1,0 +1,80 @@
+"""Few rows that need work on their way into the cache (rotary embedding, storage round trip): the workgroups of the few-rows
+kernel that read them append them themselves."""
+import pytest
+import torch
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import fold_harness
+    return fold_harness
+
+
+# cache ends before, on and behind block and tile edges; the most rows that take this route and the first that do not; pieces that begin
+# inside the chunk
+@pytest.mark.parametrize("Hq,Hkv,d,chunks,splits,upw", [
+    (32, 8, 128, [130, 1, 1, 8, 9, 3], 0, 0),
+    (28, 4, 64, [63, 1, 4, 3, 5, 1, 52, 2], 0, 0),
+    (4, 4, 128, [96, 16, 17, 32, 33, 1, 31], 0, 0),
+    (4, 4, 64, [60, 32, 31, 20], 3, 0),
+    (8, 2, 128, [64, 8, 8, 1, 15, 2], 2, 1),
+])
+@pytest.mark.parametrize("rope,bits,window", [(True, 0, None), (True, 8, None), (False, 4, None), (False, 8, (4, 50))])
+def test_rows_worked_on_by_their_readers_equal_the_append_kernel(H, Hq, Hkv, d, chunks, splits, upw, rope, bits, window):
+    """Same outputs and same cache, bit for bit, as with the append kernel in front (tuning knob)."""
+    cfg = I.FoldConfig("work", 28, 1, Hq, Hkv, d, max(chunks), 0, "bf16")
+    res = []
+    for knob in (0, 1):
+        gpu = H.GpuFold(cfg, capacity=sum(chunks), chunk_tokens=max(chunks))
+        gpu.cache.set_tuning(kv.TUNE_FUSED_APPEND, knob)
+        gpu.cache.set_tuning(kv.TUNE_SPLITS, splits)
+        gpu.cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, upw)
+        if bits:
+            gpu.cache.set_storage_roundtrip(bits)
+        outs, pos = [], 0
+        for step, C in enumerate(chunks):
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            kw = {}
+            if rope:
+                kw["rope"] = I.rope_tables(d, pos, C)
+            elif window:
+                kw["window"] = window
+            outs.append(gpu.step(0, q, k, v, **kw).clone())
+            pos += C
+        torch.cuda.synchronize()
+        K, V = gpu.cache.view(0)
+        res.append((outs, K[:, :pos].clone(), V[:, :pos].clone()))
+        gpu.close()
+    for a, b in zip(res[0][0], res[1][0]):
+        assert torch.equal(a, b)
+    assert torch.equal(res[0][1], res[1][1]) and torch.equal(res[0][2], res[1][2])
+
+
+@pytest.mark.parametrize("dtype,rope", [("bf16", True), ("f32", False)])
+def test_output_on_top_of_the_new_rows(H, dtype, rope):
+    """The output may take the place of k_new or v_new (as many KV heads as query heads): the rows are used up before it is
+    written."""
+    cfg = I.FoldConfig("inplace", 29, 1, 4, 4, 64, 256, 0, dtype)
+    chunks = [256, 33, 1]
+    got = []
+    for on in (None, "k", "v"):
+        gpu = H.GpuFold(cfg, capacity=sum(chunks), chunk_tokens=256)
+        outs, pos = [], 0
+        for step, C in enumerate(chunks):
+            q, k, v = (t.cuda().contiguous() for t in I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos))
+            out = {None: torch.empty_like(q), "k": k, "v": v}[on]
+            kw = {"rope": tuple(t.cuda() for t in I.rope_tables(64, pos, C))} if rope else {}
+            gpu.cache.step(0, q, k, v, out, **kw)
+            outs.append(out.clone())
+            pos += C
+        torch.cuda.synchronize()
+        K, V = gpu.cache.view(0)
+        got.append(outs + [K[:, :pos].clone(), V[:, :pos].clone()])
+        gpu.close()
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
