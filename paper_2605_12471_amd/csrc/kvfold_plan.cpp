@@ -87,8 +87,8 @@ KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_row
     if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
     return upw == 2 ? KernelCost{1.4, 1.4, 0, 14.0, false} : KernelCost{1.1, 1.1, 2.1, 5.5, true};
   }
-  if (waves == 8) return {(6.9 + 2.0 * with_rows) * d, 12.0 * d, 0, 8.7, false};
-  return {9.0 * d, 9.0 * d, 14.0 * d, 7.1, head_dim == 64};
+  if (waves == 8) return {(6.3 + 2.1 * with_rows) * d, 12.1 * d, 0, 7.7, false};
+  return {7.7 * d, 9.3 * d, 16.0 * d, 5.2, head_dim == 64};
 }
 
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
@@ -133,12 +133,16 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //    wavefronts without rows leave theirs to the others.
     //  * K and V rows come from memory at 6.5 TB/s with two workgroups per CU, a little less with fewer in flight.
     //  * Unsplit, several rounds, heaviest workgroups first: the slots left over in the last round idle for
-    //    the length of the lightest workgroups only (first token block: the prefix and little else).
+    //    the length of the lightest workgroups only (first token block: the prefix and little else); never less than the
+    //    heaviest workgroup's own chain.
     //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.
     //  * A step is not queued faster than its launches: some 9 us with one, 3.5 us more for each further one.
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
     // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
-    // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.
+    // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.  The fp32 kernel's are fitted again,
+    // since workgroups of four wavefronts append and start sooner, to 182 shapes (up to 1500 tokens on 0 to 60K keys): 2.1 %
+    // above the best on average, more than 10 % in 17; with the figures before 4.0 % and 35, and without the heaviest
+    // workgroup's chain 6.5 % (1476 tokens on an empty cache, 28 heads on 4: 236 us unsplit).
     const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
     const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, few_rows, with_rows);
     const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
@@ -169,6 +173,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       double t = rounds * (double)tps * std::max(k.idle, full * active * std::sqrt(fill));
       if (cand == 1 && window <= 0 && rounds >= 2.0)
         t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
+      if (cand == 1 && window <= 0) t = std::max(t, (double)tps * k.idle);
       const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;
       if (few_rows) {
         // 5.9 TB/s from one workgroup per CU on, less where some CUs have one more than others; near that rate both times
