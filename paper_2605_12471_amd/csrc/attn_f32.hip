@@ -528,15 +528,22 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   unsigned hide = 0;
   auto step = [&](int h, auto old_tag) __attribute__((always_inline)) {
     __syncthreads();  // tile h is in LDS, and nobody reads tile h - 1 any more
-    const int hn = h + 1 < h_end ? h + 1 : h;  // (past the last tile it is fetched again, for nobody)
+    // Four wavefronts: nothing is fetched or split past the last tile (a piece of two halves spends a tenth of its time on
+    // that).  Eight: the last tile once more, for nobody, which their long loops do not notice.
+    const bool more = NW != 4 || h + 1 < h_end;
+    const int hn = h + 1 < h_end ? h + 1 : h;
     const bool work = !idle && first_key(h) < vis_last;  // (else every row is masked)
     const unsigned hide_before = hide;
     hide = __builtin_amdgcn_readfirstlane(odd_keys[(unsigned)h % 3u]);
-    load_k(hn, old_tag);
-    if (kBothAhead) load_v(hn, old_tag);
+    if (more) {
+      load_k(hn, old_tag);
+      if (kBothAhead) load_v(hn, old_tag);
+    }
     if (work) logits(h, by_terms);
-    put(h + 1, false, stage_k);
-    if (!kBothAhead) load_v(hn, old_tag);
+    if (more) {
+      put(h + 1, false, stage_k);
+      if (!kBothAhead) load_v(hn, old_tag);
+    }
     if (__builtin_expect((hide | hide_before) != 0, 0)) {
       if (tid == 0) {
         if (hide_before) odd_keys[(unsigned)(h + 2) % 3u] = 0;  // tile h - 1's, next used for tile h + 2
@@ -551,7 +558,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
       softmax(h, hide);
       add_values(h, by_terms);
     }
-    put(h + 1, true, stage_v);
+    if (more) put(h + 1, true, stage_v);
   };
   // (two loops: with the choice between the two sources inside one, every tile of the prefix pays for it, 2.5 %)
   int h = h_begin;
