@@ -81,7 +81,7 @@ struct KernelCost {
 };
 KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_rows, double with_rows) {
   const double d = head_dim / 128.0;
-  if (few_rows) return {0.46, 0.46, 0.46, 4.6, true};
+  if (few_rows) return head_dim == 64 ? KernelCost{0.34, 0.34, 0.34, 3.4, true} : KernelCost{0.46, 0.46, 0.46, 4.6, true};
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
     if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
@@ -136,7 +136,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //    the length of the lightest workgroups only (first token block: the prefix and little else); never less than the
     //    heaviest workgroup's own chain.
     //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.
-    //  * A step is not queued faster than its launches: some 9 us with one, 3.5 us more for each further one.
+    //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
     // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
     // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.  The fp32 kernel's are fitted again,
@@ -171,6 +171,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       const double rounds = std::max(1.0, std::ceil(busy / slots - 1e-9));
       const double fill = busy / (rounds * slots);
       double t = rounds * (double)tps * std::max(k.idle, full * active * std::sqrt(fill));
+      // few rows: the blocks of an odd number of tiles do not go round the four wavefronts (measured, one token on 4187
+      // keys, 2 / 3 / 4 tiles a piece: 12.0 / 11.4 / 10.5 us a step; on 8000: 14.1 / 14.0 / 12.7)
+      if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
       if (cand == 1 && window <= 0 && rounds >= 2.0)
         t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
       if (cand == 1 && window <= 0) t = std::max(t, (double)tps * k.idle);
@@ -187,7 +190,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       }
       t += (k.start_end + (two_per_cu && !few_rows ? 0.5 : 0.0)) * rounds;
       if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 6.7e6 + 4.7;
-      t = std::max(t, 5.2 + 3.5 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
+      t = std::max(t, 4.0 + 2.65 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
       if (t < best * (few_rows ? 1.0 : 0.985)) {
         best = t;
         s = cand;
