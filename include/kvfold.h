@@ -100,6 +100,8 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache);
  *   pos_offset  absolute position of the chunk's first token; must equal the
  *               layer's current length (else KVFOLD_ERR_POSITION)
  *   out    device, [C][Hq][d]   attention output, element type = cfg.dtype
+ *               (may lie on k_new or v_new, which are used up before it is
+ *               written)
  *   stream hipStream_t (NULL = default stream)
  *
  * Asynchronous: work is enqueued on `stream`, nothing is synchronised or

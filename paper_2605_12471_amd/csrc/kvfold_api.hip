@@ -266,14 +266,22 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.n_sink = opt.n_sink;
   at.window = (int32_t)opt.window;
   // The attention kernel appends by itself when nothing has to happen to the rows on their way in and the
-  // chunk's rows can be addressed with 32-bit byte offsets.
-  // (fp32, and below: not from rows that the step's own stores reach, which an append kernel in front has used up by then)
+  // chunk's rows can be addressed with 32-bit byte offsets -- and when none of its own stores reaches the rows before they are
+  // used up: each workgroup copies its share behind its results, and reads rows that others copy.  Else an append kernel in
+  // front uses them up.  The output of a split step is stored behind the whole attention kernel.  A few-rows workgroup has
+  // read all rows of its KV head before it stores, so there the output may also take their very place.  (fp32 and rows that need
+  // work: apart from the cache as well.)
   const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
-  bool rows_apart = true;
-  for (const void* rows : {k_new, v_new})
-    rows_apart = rows_apart && apart(rows, new_bytes, out, out_bytes) && apart(rows, new_bytes, c->kv, c->kv_bytes) &&
-                 (!lse || apart(rows, new_bytes, lse, (size_t)n_tokens * f.n_q_heads * sizeof(float)));
-  const bool fused_append = attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr) && (f.dtype == KVFOLD_BF16 || rows_apart);
+  bool rows_apart = true, results_apart = true;
+  for (const void* rows : {k_new, v_new}) {
+    const bool from_out = apart(rows, new_bytes, out, out_bytes);
+    const bool from_lse = !lse || apart(rows, new_bytes, lse, (size_t)n_tokens * f.n_q_heads * sizeof(float));
+    const bool in_place = pl.few_rows && at.group == 1 && rows == out;
+    results_apart = results_apart && (from_out || in_place) && from_lse;
+    rows_apart = rows_apart && from_out && from_lse && apart(rows, new_bytes, c->kv, c->kv_bytes);
+  }
+  const bool may_append = f.dtype == KVFOLD_BF16 ? results_apart || pl.n_splits > 1 : rows_apart;
+  const bool fused_append = may_append && attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
   // A few rows that need work on their way: the workgroups that read them do it.

@@ -55,20 +55,31 @@ def test_rows_worked_on_by_their_readers_equal_the_append_kernel(H, Hq, Hkv, d, 
     assert torch.equal(res[0][1], res[1][1]) and torch.equal(res[0][2], res[1][2])
 
 
-@pytest.mark.parametrize("dtype,rope", [("bf16", True), ("f32", False)])
-def test_output_on_top_of_the_new_rows(H, dtype, rope):
-    """The output may take the place of k_new or v_new (as many KV heads as query heads): the rows are used up before it is
-    written."""
-    cfg = I.FoldConfig("inplace", 29, 1, 4, 4, 64, 256, 0, dtype)
-    chunks = [256, 33, 1]
+# unsplit steps of one workgroup per head and of several, few rows, split steps (second count); other head counts: the output is longer
+# than the rows and begins on them
+@pytest.mark.parametrize("splits", [0, 2])
+@pytest.mark.parametrize("dtype,rope,Hq,d,window", [
+    ("bf16", True, 4, 64, None), ("bf16", False, 4, 64, None), ("bf16", False, 4, 128, None), ("bf16", False, 4, 128, (4, 200)),
+    ("bf16", False, 8, 128, None), ("f32", False, 4, 64, None), ("f32", False, 4, 128, None),
+])
+def test_output_on_top_of_the_new_rows(H, dtype, rope, Hq, d, window, splits):
+    """The output may take the place of k_new or v_new: the rows are used up before it is written."""
+    cfg = I.FoldConfig("inplace", 29, 1, Hq, 4, d, 256, 0, dtype)
+    chunks = [64, 256, 33, 1, 128, 100, 17]
     got = []
     for on in (None, "k", "v"):
         gpu = H.GpuFold(cfg, capacity=sum(chunks), chunk_tokens=256)
+        gpu.cache.set_tuning(kv.TUNE_SPLITS, splits)
         outs, pos = [], 0
         for step, C in enumerate(chunks):
             q, k, v = (t.cuda().contiguous() for t in I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos))
-            out = {None: torch.empty_like(q), "k": k, "v": v}[on]
-            kw = {"rope": tuple(t.cuda() for t in I.rope_tables(64, pos, C))} if rope else {}
+            out = torch.empty_like(q)
+            rows = {None: None, "k": k, "v": v}[on]
+            if rows is not None:
+                at = out.view(-1)[:rows.numel()].view(rows.shape)
+                at.copy_(rows)
+                k, v = (at, v) if on == "k" else (k, at)
+            kw = {"rope": tuple(t.cuda() for t in I.rope_tables(d, pos, C))} if rope else {"window": window} if window else {}
             gpu.cache.step(0, q, k, v, out, **kw)
             outs.append(out.clone())
             pos += C
