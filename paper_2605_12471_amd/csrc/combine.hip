@@ -56,7 +56,10 @@ __global__ void __launch_bounds__(kCombineThreads) combine_kernel(CombineParams 
     float mn = m;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (ml[u].y == 0.f) ml[u].x = -INFINITY;  // no visible key for the row in this piece
+      if (ml[u].y == 0.f) {  // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
+        ml[u].x = -INFINITY;
+        o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
       mn = fmaxf(mn, ml[u].x);
     }
     const float ref = mn == -INFINITY ? 0.f : mn, a = __builtin_amdgcn_exp2f(m - ref);

@@ -1,0 +1,56 @@
+"""The merge of split steps: a piece in which a row sees no key leaves the row as it is."""
+import math
+
+import pytest
+import torch
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    from tests import fold_harness
+    return fold_harness
+
+
+# Two pieces that meet at key 64, one head per group, 48 keys before the chunk: row i stands at position 48 + i, so that the edge lies inside
+# a unit of 32 rows.  Without a window rows 0 .. 15 see nothing of the second piece, where key 70 lies; with one of 32 keys, rows
+# from 47 on see nothing of the first, where key 20 lies.  More pieces than a thread of the merge has in one LDS group: long prefix.
+@pytest.mark.parametrize("bad", [math.inf, math.nan])
+@pytest.mark.parametrize("dtype,d,prev,n,upw,splits,window,key,clean", [
+    ("f32", 128, 48, 32, 1, 2, None, 70, slice(0, 16)),
+    ("f32", 64, 48, 80, 2, 2, None, 70, slice(0, 16)),
+    ("bf16", 128, 48, 32, 0, 2, None, 70, slice(0, 16)),   # the kernel for few rows
+    ("bf16", 64, 48, 32, 0, 2, None, 70, slice(0, 16)),
+    ("bf16", 128, 48, 64, 1, 2, None, 70, slice(0, 16)),
+    ("bf16", 64, 48, 64, 2, 2, None, 70, slice(0, 16)),
+    ("bf16", 128, 48, 72, 2, 2, None, 70, slice(0, 16)),
+    ("bf16", 128, 48, 64, 1, 2, (0, 32), 20, slice(47, 64)),
+    ("f32", 128, 48, 64, 1, 2, (0, 32), 20, slice(47, 64)),
+    ("bf16", 128, 1200, 64, 1, 20, None, 1223, slice(0, 16)),
+    ("f32", 128, 1200, 64, 1, 20, None, 1223, slice(0, 16)),
+])
+def test_a_value_that_a_row_does_not_see_leaves_it_as_it_is(H, dtype, d, prev, n, upw, splits, window, key, clean, bad):
+    cfg = I.FoldConfig("merge", 31, 1, 2, 2, d, max(prev, n), 0, dtype)
+    res = []
+    for value in (1.0, bad):
+        gpu = H.GpuFold(cfg, capacity=prev + n, chunk_tokens=max(prev, n))
+        gpu.cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, upw)
+        pos = 0
+        for step, C in enumerate((prev, n)):
+            gpu.cache.set_tuning(kv.TUNE_SPLITS, splits if step else 1)
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            if pos <= key < pos + C:
+                v[key - pos, :, 3] = value
+            if step:
+                assert gpu.cache.plan(n, prev + n)[1] == splits
+            out, lse = gpu.step(0, q, k, v, want_lse=True, **({"window": window} if window and step else {}))
+            pos += C
+        res.append((out.clone(), lse.clone()))
+        gpu.close()
+    (plain, plain_lse), (out, lse) = res
+    assert torch.isfinite(plain).all() and not torch.isfinite(out).all()
+    assert torch.equal(out[clean], plain[clean]) and torch.equal(lse[:, clean], plain_lse[:, clean])
