@@ -82,14 +82,15 @@ __global__ void __launch_bounds__(kCombineThreads) combine_kernel(CombineParams 
     __syncthreads();
     if (sg != 0) return;
     for (unsigned g = 1; g < SG; ++g) m = fmaxf(m, red_ml[grp + g].x);
-    const float b0 = __builtin_amdgcn_exp2f(red_ml[grp].x - m);  // (some piece has keys for every row: m is finite)
+    const float ref = m == -INFINITY ? 0.f : m;  // (-inf: every logit of the row is)
+    const float b0 = __builtin_amdgcn_exp2f(red_ml[grp].x - ref);
     l *= b0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] *= b0;
     for (unsigned g = 1; g < SG; ++g) {
       const floatx2 x = red_ml[grp + g];
       const floatx4 o = red_o[tid + (g << LV)];
-      const float b = __builtin_amdgcn_exp2f(x.x - m);
+      const float b = __builtin_amdgcn_exp2f(x.x - ref);
       l = __builtin_fmaf(x.y, b, l);
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(o[e], b, acc[e]);

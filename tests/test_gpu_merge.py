@@ -54,3 +54,34 @@ def test_a_value_that_a_row_does_not_see_leaves_it_as_it_is(H, dtype, d, prev, n
     (plain, plain_lse), (out, lse) = res
     assert torch.isfinite(plain).all() and not torch.isfinite(out).all()
     assert torch.equal(out[clean], plain[clean]) and torch.equal(lse[:, clean], plain_lse[:, clean])
+
+
+@pytest.mark.parametrize("dtype,d,n,upw", [("f32", 128, 40, 1), ("f32", 64, 72, 2), ("bf16", 128, 16, 0), ("bf16", 64, 40, 1), ("bf16", 128, 72, 2)])
+@pytest.mark.parametrize("splits", [1, 2, 20])
+def test_rows_whose_every_key_is_hidden(H, dtype, d, n, upw, splits):
+    """A query with -inf where every key is positive: all its logits are -inf, the log-sum-exp too, and there is no output; the other rows
+    keep their bits."""
+    prev = 1200
+    cfg = I.FoldConfig("hidden", 32, 1, 2, 2, d, prev, 0, dtype)
+    res = []
+    for value in (0.0, -math.inf):
+        gpu = H.GpuFold(cfg, capacity=prev + n, chunk_tokens=prev)
+        gpu.cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, upw)
+        pos = 0
+        for step, C in enumerate((prev, n)):
+            gpu.cache.set_tuning(kv.TUNE_SPLITS, splits if step else 1)
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            k[:, :, 5] = 1.0
+            if step:
+                q[3::7, :, 5] = value
+                assert gpu.cache.plan(n, prev + n)[1] in (splits, 19)  # (16 tokens have 19 tiles of keys)
+            out, lse = gpu.step(0, q, k, v, want_lse=True)
+            pos += C
+        res.append((out.clone(), lse.clone()))
+        gpu.close()
+    (plain, plain_lse), (out, lse) = res
+    hidden = torch.zeros(n, dtype=torch.bool, device="cuda")
+    hidden[3::7] = True
+    assert torch.isfinite(plain).all() and torch.isfinite(plain_lse).all()
+    assert torch.isnan(out[hidden]).all() and (lse[:, hidden] == -math.inf).all()
+    assert torch.equal(out[~hidden], plain[~hidden]) and torch.equal(lse[:, ~hidden], plain_lse[:, ~hidden])
