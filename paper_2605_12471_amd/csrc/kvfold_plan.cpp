@@ -91,6 +91,11 @@ KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_row
   return {7.7 * d, 9.3 * d, 16.0 * d, 5.2, head_dim == 64};
 }
 
+// Whether every XCD gets the same mix of a KV head's workgroups (logical_workgroup(): heads whole, or dealt to their XCDs in turn).
+bool evenly_dealt(int n_kv_heads, int wgs_per_kvh) {
+  return n_kv_heads % kNumXcd == 0 || (n_kv_heads < kNumXcd && kNumXcd % n_kv_heads == 0 && wgs_per_kvh % (kNumXcd / n_kv_heads) == 0);
+}
+
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
 // estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
@@ -135,6 +140,10 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //  * Unsplit, several rounds, heaviest workgroups first: the slots left over in the last round idle for
     //    the length of the lightest workgroups only (first token block: the prefix and little else); never less than the
     //    heaviest workgroup's own chain.
+    //  * A KV head's workgroups lie on its XCDs in runs where they cannot be dealt to them in turn: one XCD then has the heavy
+    //    ones, another the light or empty ones (28 heads on 4, one / two units per wavefront: 3249 tokens, 178 / 89 workgroups a head,
+    //    78 / 115 us; 3273 tokens on 153 keys, 179 / 90 workgroups, 117 / 89; fp32, 8 heads on 2, 295 tokens on 1252 keys, 130
+    //    workgroups a head of which 16 are empty: 53 us, two rounds for the first XCD of each head).
     //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.
     //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
@@ -150,6 +159,10 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
     const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / (few_rows ? 5.9e6 : 6.5e6);
     const int launches = (c.storage_bits && !attention_works_on_rows(c, pl, n_tokens, false)) || waves == 8 ? 2 : 1;
+    // (unsplit, not evenly dealt: mean and least keys of the workgroups on the XCD that gets the latest tokens' part of a KV head)
+    const double heads = f.n_kv_heads / (double)kNumXcd, part = heads - std::floor(heads);
+    const double late_keys = (std::floor(heads) * mean_keys + part * (la - 0.5 * part * n_tokens)) / heads;
+    const double late_least = la - (heads < 1.0 ? part : 1.0) * n_tokens;
     double best = 1e30;
     for (int64_t cand = 1; cand <= s_max; ++cand) {
       // only split counts that whole tiles can realise; the last piece may be shorter than the others, and the
@@ -157,13 +170,14 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       const int64_t tps = (ntiles + cand - 1) / cand;
       if ((ntiles + tps - 1) / tps != cand) continue;
       const int64_t w = base * cand;
+      const bool even = evenly_dealt(f.n_kv_heads, (int)(w / f.n_kv_heads));
       const bool two_per_cu = k.two_per_cu && w > (int64_t)c.n_cu;
       const double slots = (double)c.n_cu * (two_per_cu ? 2 : 1);
       const double full = two_per_cu ? k.full_two : k.full;
       // Workgroups with work: piece j is empty for the tokens before j * tps tiles less the prefix, so of the pieces from
-      // first_cut on only the later tokens' have any.
+      // first_cut on only the later tokens' have any.  (Not evenly dealt, some XCD has none of the empty ones.)
       double busy = (double)w;
-      if (cand > 1 && window <= 0) {
+      if (cand > 1 && window <= 0 && even) {
         const int64_t keys = tps * kTileKeys, prefix = len_after - n_tokens, first_cut = prefix / keys + 1, cut = cand - first_cut;
         if (cut > 0)
           busy = (double)base * ((double)first_cut + (double)cut * (1.0 + ((double)prefix - 0.5 * (double)(keys * (first_cut + cand - 1))) / n_tokens));
@@ -175,7 +189,8 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // keys, 2 / 3 / 4 tiles a piece: 12.0 / 11.4 / 10.5 us a step; on 8000: 14.1 / 14.0 / 12.7)
       if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
       if (cand == 1 && window <= 0 && rounds >= 2.0)
-        t = (double)tps * std::max(k.idle, full) * ((double)w * mean_keys + (rounds * slots - (double)w) * (la - n_tokens + kRowsPerUnit)) / (slots * la);
+        t = (double)tps * std::max(k.idle, full) *
+            ((double)w * (even ? mean_keys : late_keys) + (rounds * slots - (double)w) * ((even ? la - n_tokens : late_least) + kRowsPerUnit)) / (slots * la);
       if (cand == 1 && window <= 0) t = std::max(t, (double)tps * k.idle);
       const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;
       if (few_rows) {

@@ -1,0 +1,35 @@
+"""The launch plan where an estimate that was off made steps slower than they had been.  Times: the kernels of one step on the GPU, the
+plan asked for / the one that was taken."""
+import pytest
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import binding
+
+
+def _plan(dtype, hq, hkv, d, n, prev):
+    cfg = binding.make_config(1, hq, hkv, d, max(n, 256), 131072, dtype)
+    rc, plan = kv.kvfold_plan_for(cfg, 256, n, prev + n)
+    assert rc == 0
+    return plan
+
+
+@pytest.mark.parametrize("hq,hkv,n,prev,units", [
+    (28, 4, 3559, 95, 2),     # 98 / 125 us
+    (28, 4, 3559, 0, 2),      # 95 / 120
+    (28, 4, 3273, 153, 2),    # 89 / 117
+    (28, 4, 2752, 536, 2),    # 93 / 110
+    (28, 4, 3249, 0, 1),      # 78 / 115 (not taken, but the other way round: here two units are the ones not evenly dealt)
+])
+def test_unsplit_steps_whose_workgroups_are_not_evenly_dealt(hq, hkv, n, prev, units):
+    plan = _plan(kv.KVFOLD_BF16, hq, hkv, 128, n, prev)
+    assert plan.n_splits == 1 and plan.units_per_wave == units
+
+
+@pytest.mark.parametrize("hq,hkv,n,prev", [
+    (8, 2, 295, 1252),     # 41 / 53 us with 13 pieces
+    (4, 1, 897, 146),      # 38 / 49 with 9
+])
+def test_pieces_that_are_not_evenly_dealt_fit_one_round(hq, hkv, n, prev):
+    plan = _plan(kv.KVFOLD_F32, hq, hkv, 128, n, prev)
+    per_head = plan.n_workgroups // hkv
+    assert plan.n_workgroups <= 256 or per_head % (8 // hkv) == 0
