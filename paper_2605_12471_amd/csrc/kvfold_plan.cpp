@@ -74,21 +74,25 @@ bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope
 namespace {
 
 // What a workgroup of an attention kernel costs, in us (see plan_with()): per 64-key tile on an otherwise idle chip and on
-// a full one (one workgroup per CU, two per CU), and once.
+// a full one (one workgroup per CU, two per CU), and once.  fp32: on a full one, as the share by which a tile takes longer than
+// on an idle one where all wavefronts have rows.
 struct KernelCost {
   double idle, full, full_two, start_end;
   bool two_per_cu;
 };
 KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_rows, double with_rows) {
-  const double d = head_dim / 128.0;
   if (few_rows) return head_dim == 64 ? KernelCost{0.34, 0.34, 0.34, 3.4, true} : KernelCost{0.46, 0.46, 0.46, 4.6, true};
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
     if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
     return upw == 2 ? KernelCost{1.4, 1.4, 0, 14.0, false} : KernelCost{1.1, 1.1, 2.1, 5.5, true};
   }
-  if (waves == 8) return {(6.3 + 2.1 * with_rows) * d, 12.1 * d, 0, 7.7, false};
-  return {7.7 * d, 9.3 * d, 16.0 * d, 5.2, head_dim == 64};
+  // eight wavefronts: a tile takes half as long again once some SIMD has two of them with rows (measured per tile, 1 to 4 / 5 to 8
+  // units: 5.6 / 8.4 us, 64 wide 3.2 / 4.8; on a full chip 5.8 to 7.3 / 9.7 to 12, 3.7 / 5.9); their start and end has
+  // the append kernel's launch in it.  Four: 6.9 to 7.2, full 7.4 to 8.1; 64 wide 4.1, 4.4, two per CU 5.7 to 7.
+  const bool one_per_simd = with_rows <= 0.5;
+  if (head_dim == 64) return waves == 8 ? KernelCost{one_per_simd ? 3.35 : 4.5, 0.21, 0, 9.0, false} : KernelCost{4.6, 0.09, 0.63, 4.2, true};
+  return waves == 8 ? KernelCost{one_per_simd ? 5.5 : 8.0, 0.28, 0, 9.4, false} : KernelCost{7.8, 0.13, 0, 4.4, false};
 }
 
 // Whether every XCD gets the same mix of a KV head's workgroups (logical_workgroup(): heads whole, or dealt to their XCDs in turn).
@@ -148,14 +152,16 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
     // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
-    // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.  The fp32 kernel's are fitted again,
-    // since workgroups of four wavefronts append and start sooner, to 182 shapes (up to 1500 tokens on 0 to 60K keys): 2.1 %
-    // above the best on average, more than 10 % in 17; with the figures before 4.0 % and 35, and without the heaviest
-    // workgroup's chain 6.5 % (1476 tokens on an empty cache, 28 heads on 4: 236 us unsplit).
+    // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.  The fp32 kernel's are fitted again
+    // to the kernels' own times (captured graphs, no launch in the way) of 1100 shapes (1 to 64 heads, 1 to 2500 tokens on 0 to
+    // 80K keys, windows among them), both wavefront counts: 1.0 % above the best on average, more than 10 % in 40; the figures before,
+    // fitted to 182 of these, 2.4 % and 100, and slower by up to 20 % than those of the kernel that did not append where a few
+    // workgroups read many keys (64 tokens on 60K keys, 8 heads on 2: four wavefronts 124 us, eight 149).
     const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
     const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, few_rows, with_rows);
     const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
-    const double active = f.dtype == KVFOLD_BF16 ? std::sqrt(std::sqrt(with_rows)) : std::sqrt(with_rows);
+    const bool fp32 = f.dtype != KVFOLD_BF16;
+    const double active = std::sqrt(std::sqrt(with_rows));
     const double kv_rows = window > 0 ? std::min(la, (double)ntiles * kTileKeys) : la;
     const double kv_us = 2.0 * f.n_kv_heads * f.head_dim * (double)elem_size(f.dtype) * kv_rows / (few_rows ? 5.9e6 : 6.5e6);
     const int launches = (c.storage_bits && !attention_works_on_rows(c, pl, n_tokens, false)) || waves == 8 ? 2 : 1;
@@ -184,12 +190,14 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       }
       const double rounds = std::max(1.0, std::ceil(busy / slots - 1e-9));
       const double fill = busy / (rounds * slots);
-      double t = rounds * (double)tps * std::max(k.idle, full * active * std::sqrt(fill));
+      const double worst = fp32 ? k.idle * (1.0 + full * with_rows) : std::max(k.idle, full);  // a tile, every slot taken
+      double t = rounds * (double)tps * (fp32 ? k.idle * (1.0 + full * with_rows * std::sqrt(fill) * (two_per_cu ? std::sqrt(std::sqrt(fill)) : fill))
+                                              : std::max(k.idle, full * active * std::sqrt(fill)));
       // few rows: the blocks of an odd number of tiles do not go round the four wavefronts (measured, one token on 4187
       // keys, 2 / 3 / 4 tiles a piece: 12.0 / 11.4 / 10.5 us a step; on 8000: 14.1 / 14.0 / 12.7)
       if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
       if (cand == 1 && window <= 0 && rounds >= 2.0)
-        t = (double)tps * std::max(k.idle, full) *
+        t = (double)tps * worst *
             ((double)w * (even ? mean_keys : late_keys) + (rounds * slots - (double)w) * ((even ? la - n_tokens : late_least) + kRowsPerUnit)) / (slots * la);
       if (cand == 1 && window <= 0) t = std::max(t, (double)tps * k.idle);
       const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;
@@ -204,7 +212,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
         t = std::max(t, kv_piece * (few_in_flight ? std::sqrt(std::sqrt(std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w)))) : 1.0));
       }
       t += (k.start_end + (two_per_cu && !few_rows ? 0.5 : 0.0)) * rounds;
-      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / 6.7e6 + 4.7;
+      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / (fp32 ? 5.7e6 : 6.7e6) + (fp32 ? 3.9 : 4.7);
       t = std::max(t, 4.0 + 2.65 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
       if (t < best * (few_rows ? 1.0 : 0.985)) {
         best = t;

@@ -33,3 +33,16 @@ def test_pieces_that_are_not_evenly_dealt_fit_one_round(hq, hkv, n, prev):
     plan = _plan(kv.KVFOLD_F32, hq, hkv, 128, n, prev)
     per_head = plan.n_workgroups // hkv
     assert plan.n_workgroups <= 256 or per_head % (8 // hkv) == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev,waves", [
+    (8, 2, 128, 64, 60000, 4),      # 124 / 149 us
+    (8, 2, 128, 64, 25645, 4),      # 71 / 81
+    (4, 1, 128, 127, 33421, 4),     # 90 / 109
+    (32, 32, 64, 573, 858, 4),      # 66 / 78
+    (28, 4, 128, 512, 16384, 8),    # 635 / 643 with 4 pieces instead of 9
+])
+def test_fp32_wavefronts_per_workgroup(hq, hkv, d, n, prev, waves):
+    plan = _plan(kv.KVFOLD_F32, hq, hkv, d, n, prev)
+    units = -(-n * (hq // hkv) // 32)
+    assert plan.n_workgroups == plan.n_splits * hkv * -(-units // waves)
