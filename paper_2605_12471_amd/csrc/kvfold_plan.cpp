@@ -148,7 +148,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //    ones, another the light or empty ones (28 heads on 4, one / two units per wavefront: 3249 tokens, 178 / 89 workgroups a head,
     //    78 / 115 us; 3273 tokens on 153 keys, 179 / 90 workgroups, 117 / 89; fp32, 8 heads on 2, 295 tokens on 1252 keys, 130
     //    workgroups a head of which 16 are empty: 53 us, two rounds for the first XCD of each head).
-    //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.
+    //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.  (Few rows: the rest of what a launch
+    //    costs is in the pace at which they are queued; with 4.7 us here 12 tokens on 1091 keys, 32 heads, stayed unsplit, 16.4 us
+    //    for 13.1.)
     //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
     // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
@@ -193,8 +195,10 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       const double worst = fp32 ? k.idle * (1.0 + full * with_rows) : std::max(k.idle, full);  // a tile, every slot taken
       double t = rounds * (double)tps * (fp32 ? k.idle * (1.0 + full * with_rows * std::sqrt(fill) * (two_per_cu ? std::sqrt(std::sqrt(fill)) : fill))
                                               : std::max(k.idle, full * active * std::sqrt(fill)));
-      // few rows: the blocks of an odd number of tiles do not go round the four wavefronts (measured, one token on 4187
-      // keys, 2 / 3 / 4 tiles a piece: 12.0 / 11.4 / 10.5 us a step; on 8000: 14.1 / 14.0 / 12.7)
+      // few rows: the blocks of an odd number of tiles do not go round the four wavefronts.  (Over 560 shapes on as many layers as
+      // keep the caches out of the chip's own, the choice is 0.8 % above the best with this and 1.0 % without the second
+      // term.  A step's two launches follow each other in steps of 0.8 us, which is the scatter: one token on 4187 keys, 2 / 3 / 4 / 5 tiles
+      // a piece 12.4 / 11.7 / 10.8 / 11.5 us, on 4538 12.4 / 11.0 / 11.7 / 11.6.)
       if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
       if (cand == 1 && window <= 0 && rounds >= 2.0)
         t = (double)tps * worst *
@@ -212,7 +216,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
         t = std::max(t, kv_piece * (few_in_flight ? std::sqrt(std::sqrt(std::sqrt(std::sqrt(2.0 * c.n_cu / (double)w)))) : 1.0));
       }
       t += (k.start_end + (two_per_cu && !few_rows ? 0.5 : 0.0)) * rounds;
-      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / (fp32 ? 5.7e6 : 6.7e6) + (fp32 ? 3.9 : 4.7);
+      if (cand > 1) t += (double)cand * rows * (f.head_dim + 2) * 8.0 / (fp32 ? 5.7e6 : 6.7e6) + (few_rows ? 3.4 : fp32 ? 3.9 : 4.7);
       t = std::max(t, 4.0 + 2.65 * (launches + (cand > 1 ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)
       if (t < best * (few_rows ? 1.0 : 0.985)) {
         best = t;

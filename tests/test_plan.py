@@ -46,3 +46,12 @@ def test_fp32_wavefronts_per_workgroup(hq, hkv, d, n, prev, waves):
     plan = _plan(kv.KVFOLD_F32, hq, hkv, d, n, prev)
     units = -(-n * (hq // hkv) // 32)
     assert plan.n_workgroups == plan.n_splits * hkv * -(-units // waves)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev", [
+    (32, 32, 128, 12, 1091),     # 13.1 / 16.4 us, unsplit
+    (32, 32, 64, 21, 1196),      # 9.1 / 10.7
+    (32, 32, 64, 1, 1111),       # 8.3 / 9.3
+])
+def test_few_rows_are_split_where_the_merge_is_worth_it(hq, hkv, d, n, prev):
+    assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).n_splits > 1
