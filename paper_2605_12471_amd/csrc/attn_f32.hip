@@ -78,8 +78,9 @@ __device__ __forceinline__ floatx16 mfma16(const uintx4& a, const uintx4& b, con
 
 // NW wavefronts per workgroup, one workgroup per CU at D = 128 (96 KB of LDS).  Eight (two per SIMD) share the split of a
 // tile among twice the rows and have one wavefront's vector work behind the other's matrix work; four are for chunks that
-// leave half of the eight without rows.  WIN: the sink + sliding-window step.
-template <int D, bool WIN, int NW>
+// leave half of the eight without rows.  WIN: the sink + sliding-window step.  FUSED (four wavefronts): the kernel appends the
+// chunk's rows itself.
+template <int D, bool WIN, int NW, bool FUSED>
 __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p) {
   constexpr int NT = NW * 64;
   constexpr int ROWB = D * 4;       // bytes per row of the cache
@@ -92,7 +93,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   constexpr float kThresh = 8.0f;
   // The next tile's values on their way together with its keys, a step ahead of their use, where there are registers for it
   // (D = 128 has none left); 32 keys of half the width are worked off faster than memory answers.
-  constexpr bool kBothAhead = D == 64;
+  constexpr bool kBothAhead = D == 64 && (FUSED || NW == 8);
 
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUFB];
   // keys with a number that the terms cannot hold: by tile, for the two tiles in flight and one being cleared, and the list
@@ -169,20 +170,22 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   // a fold of 4 x 128 tokens, 4 heads on 1, D = 64, 63.4 us with it, 56.9 without (three of these from loading the first
   // tile's values with its keys).  Not with eight wavefronts: their steps are long, and what the second source costs the
   // main loop in scalar registers is as much as the launch (512 tokens on 16K keys, 28 heads on 4: 645 us with the append
-  // kernel, 647 without).
-  const bool fused = NW == 4 && p.k_new != nullptr;
+  // kernel, 647 without).  Nor for long pieces of four (attention_appends()): the instance without the second source is 1 to 2 % faster
+  // per tile, 3.5 % 64 wide (64 tokens on 14K keys, 8 heads on 2, 40 tiles a piece: 269 us with it, 265 without; 64 wide 158 and 153;
+  // one instance for both, before: 270 and 161 where the rows need the append kernel anyway, for the rotary embedding).
+  const bool fused = FUSED && p.k_new != nullptr;
   const int chunk0 = fused ? (int)p.len_prev : 0x7fffffff;
   const unsigned new_stride = (unsigned)(p.n_kv_heads * ROWB);  // bytes from one token's row to the next
   const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (int64_t)g * ROWB;
   const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (int64_t)g * ROWB;
   auto row_at = [&](bool is_v, int row) __attribute__((always_inline)) -> const unsigned char* {
-    const bool nw = row >= chunk0;
+    const bool nw = FUSED && row >= chunk0;
     const unsigned char* base = nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase);
     return base + (unsigned)(row - (nw ? chunk0 : 0)) * (nw ? new_stride : (unsigned)ROWB);
   };
   // ... of a tile whose rows are all in the cache (old), or not
   auto row_of = [&](bool is_v, int row, auto old_tag) __attribute__((always_inline)) -> const unsigned char* {
-    if constexpr (decltype(old_tag)::value || NW != 4) return (is_v ? vbase : kbase) + (unsigned)row * (unsigned)ROWB;
+    if constexpr (decltype(old_tag)::value || !FUSED) return (is_v ? vbase : kbase) + (unsigned)row * (unsigned)ROWB;
     return row_at(is_v, row);
   };
   auto is_old = [&](int h) __attribute__((always_inline)) -> bool { return first_key(h) + BN <= chunk0; };
@@ -303,7 +306,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   if (tid == 3) odd_tiles = 0;
   if (h_begin < h_end) {
     load_k(h_begin, std::false_type{});
-    load_v(h_begin, std::false_type{});
+    if (FUSED || kBothAhead) load_v(h_begin, std::false_type{});
   }
   {
     float raw[KS][8];
@@ -362,6 +365,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   if (h_begin < h_end) {
     __syncthreads();  // the words above are clear
     put(h_begin, false, stage_k);
+    if (!FUSED && !kBothAhead) load_v(h_begin, std::false_type{});
     put(h_begin, true, stage_v);
   }
   floatx16 s;
@@ -528,9 +532,9 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   unsigned hide = 0;
   auto step = [&](int h, auto old_tag) __attribute__((always_inline)) {
     __syncthreads();  // tile h is in LDS, and nobody reads tile h - 1 any more
-    // Four wavefronts: nothing is fetched or split past the last tile (a piece of two halves spends a tenth of its time on
-    // that).  Eight: the last tile once more, for nobody, which their long loops do not notice.
-    const bool more = NW != 4 || h + 1 < h_end;
+    // Short pieces: nothing is fetched or split past the last tile (a piece of two halves spends a tenth of its time on
+    // that).  Else the last tile once more, for nobody, which long loops do not notice.
+    const bool more = !FUSED || h + 1 < h_end;
     const int hn = h + 1 < h_end ? h + 1 : h;
     const bool work = !idle && first_key(h) < vis_last;  // (else every row is masked)
     const unsigned hide_before = hide;
@@ -562,8 +566,8 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   };
   // (two loops: with the choice between the two sources inside one, every tile of the prefix pays for it, 2.5 %)
   int h = h_begin;
-  for (; h < h_end && (NW != 4 || is_old(h + 1 < h_end ? h + 1 : h)); ++h) step(h, std::true_type{});
-  if (NW == 4)
+  for (; h < h_end && (!FUSED || is_old(h + 1 < h_end ? h + 1 : h)); ++h) step(h, std::true_type{});
+  if (FUSED)
     for (; h < h_end; ++h) step(h, std::false_type{});
   __syncthreads();
 
@@ -630,24 +634,22 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   }
 }
 
-template <int D>
+template <int D, bool WIN>
 static void launch_f32(const AttnParams& p, int waves_per_wg, hipStream_t s) {
   const dim3 grid(padded_grid(p.n_wgs));
-  if (waves_per_wg == 8 && p.window > 0)
-    hipLaunchKernelGGL((attn_f32_kernel<D, true, 8>), grid, dim3(512), 0, s, p);
-  else if (waves_per_wg == 8)
-    hipLaunchKernelGGL((attn_f32_kernel<D, false, 8>), grid, dim3(512), 0, s, p);
-  else if (p.window > 0)
-    hipLaunchKernelGGL((attn_f32_kernel<D, true, 4>), grid, dim3(256), 0, s, p);
+  if (waves_per_wg == 8)
+    hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 8, false>), grid, dim3(512), 0, s, p);
+  else if (p.k_new)
+    hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 4, true>), grid, dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL((attn_f32_kernel<D, false, 4>), grid, dim3(256), 0, s, p);
+    hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 4, false>), grid, dim3(256), 0, s, p);
 }
 
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, int waves_per_wg, hipStream_t s) {
   if (head_dim == 128)
-    launch_f32<128>(p, waves_per_wg, s);
+    p.window > 0 ? launch_f32<128, true>(p, waves_per_wg, s) : launch_f32<128, false>(p, waves_per_wg, s);
   else if (head_dim == 64)
-    launch_f32<64>(p, waves_per_wg, s);
+    p.window > 0 ? launch_f32<64, true>(p, waves_per_wg, s) : launch_f32<64, false>(p, waves_per_wg, s);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -65,7 +65,10 @@ bool attention_works_on_rows(const PlanCtx& c, const Plan& pl, int n_tokens, boo
 
 bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope) {
   const kvfold_config_t& f = c.cfg;
-  if (f.dtype != KVFOLD_BF16 && pl.waves_per_wg != 4) return false;
+  // fp32: short pieces of four wavefronts.  A launch less (2.5 us) against 0.04 us a tile in the loop, 0.12 us 64 wide.  Measured, append
+  // kernel / this, 64 tokens, 8 heads on 2: 9 tiles 77.3 / 76.0 us, 14 110.9 / 110.0, 20 144.2 / 144.5, 28 204.2 / 206.7; 64 wide, 7
+  // tiles 40.6 / 39.5, 9 47.1 / 46.6, 14 66.1 / 66.6, 20 85.3 / 86.7.
+  if (f.dtype != KVFOLD_BF16 && (pl.waves_per_wg != 4 || pl.tiles_per_split >= (f.head_dim == 64 ? 12 : 20))) return false;
   if (rope || c.storage_bits || c.tune_fused_append == 1) return false;
   const int64_t chunk_bytes = (int64_t)n_tokens * f.n_kv_heads * f.head_dim * elem_size(f.dtype);
   return chunk_bytes < ((int64_t)1 << 32);
