@@ -5,13 +5,16 @@
 //     kvfold_consts.h (workgroup_rows, tile_map, key_range, dma_row) and the launch geometry in the planner;
 //     both are used here exactly as the kernels use them.  For many shapes -- chunk length, cache length, group
 //     size, prefix splits, units per wavefront (fp32: wavefronts per workgroup), fused append or not, plain and
-//     sink + sliding-window steps -- every workgroup's pieces are walked as its kernel walks them -- the general bf16
+//     sink + sliding-window steps, few rows that need work on their way (rotary embedding, storage round trip) -- every
+//     workgroup's pieces are walked as its kernel walks them -- the general bf16
 //     kernel's ring with its run-ahead and the last tile fetched again past the end, the few-rows kernel's blocks of
-//     32 keys in cyclic order, the fp32 kernel's half tiles -- and checked:
+//     32 keys in cyclic order, the fp32 kernel's half tiles with their two sources -- and checked:
 //       * every DMA source row lies inside what exists (cache rows below len_prev when the chunk's rows are not
 //         in the cache yet, else below len_prev + C; chunk rows below C), with 32-bit offsets that do not wrap;
 //       * a row that a query of the workgroup can see is fetched unclamped, from the right place;
-//       * the pieces of all splits together cover every visible key of every row of the workgroup exactly once.
+//       * the pieces of all splits together cover every visible key of every row of the workgroup exactly once;
+//       * the chunk's rows are appended exactly once: the workgroups' shares of the copy, or the rows that a few-rows
+//         workgroup works on, which are all that it reads of the chunk, and none of which it fetches ahead of its work.
 //  2. The planner and validate_config over a sweep of configurations (sanitizers watch the arithmetic).
 //  3. The oracle on tiny inputs, plain and windowed (sanitizers watch its indexing).
 #include <cstdint>
@@ -53,12 +56,13 @@ struct Reader {
   int row_bytes;
   bool fused;
   std::vector<int>& seen;
+  int64_t work_row0 = 0, work_row1 = 0;  // chunk rows in the cache that this workgroup has appended itself (readable_cache: all others)
   void read(const DmaRow& d, int64_t key, bool of_piece) {
     if (d.from_chunk) {
       REQUIRE(fused && (int64_t)d.row < n_tokens, "chunk row %u out of %d", d.row, n_tokens);
       REQUIRE((uint64_t)d.row * cfg.n_kv_heads * row_bytes + row_bytes <= (1ull << 32), "32-bit chunk offset wraps");
     } else {
-      REQUIRE((int64_t)d.row < readable_cache, "cache row %u not readable (%lld rows are)", d.row, (long long)readable_cache);
+      REQUIRE((int64_t)d.row < readable_cache || ((int64_t)d.row >= work_row0 && (int64_t)d.row < work_row1), "cache row %u not readable (%lld rows are)", d.row, (long long)readable_cache);
       REQUIRE((uint64_t)d.row * row_bytes + row_bytes <= (1ull << 32), "32-bit cache offset wraps");
     }
     if (of_piece && key <= last_key) {
@@ -93,14 +97,26 @@ static void walk_ring(Reader& rd, const TileMap& tm, const KeyRange& kr, int nv)
     }
 }
 
-// The few-rows kernel: wavefront w takes every fourth block of 32 keys, in cyclic order from a place of its own.
-static void walk_few(Reader& rd, const KeyRange& kr, int split, int g) {
+// The few-rows kernel: wavefront w takes every fourth block of 32 keys, in cyclic order from a place of its own.  work: the
+// workgroup appends the rows of the chunk that its piece holds, after the first block's fetch where that needs none of them.
+static void walk_few(Reader& rd, const KeyRange& kr, int split, int g, bool work, std::vector<int>& appended) {
+  int work_r0 = 0, work_r1 = 0;
+  if (work && kr.t_begin < kr.t_end) {
+    work_r0 = kr.t_begin * kTileKeys - (int)rd.len_prev;
+    if (work_r0 < 0) work_r0 = 0;
+    work_r1 = (int)kr.row_lim + 1 - (int)rd.len_prev;
+  }
+  REQUIRE(work_r1 <= rd.n_tokens, "work on row %d of %d", work_r1 - 1, rd.n_tokens);
+  for (int r = work_r0; r < work_r1; ++r) appended[(size_t)r]++;
   const int b_all = (int)((rd.len_prev + rd.n_tokens + 31) / 32), b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
   for (int w = 0; w < 4; ++w) {
     const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + 3) / 4 : 0;
     int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
     for (int i = 0; i < n_blocks; ++i) {
       REQUIRE(b >= b_first && b < b_end && (b - b_first) % 4 == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_end, w);
+      const bool ahead = i == 0 && (work_r1 <= work_r0 || b * 32 + 32 <= (int)rd.len_prev);  // fetched before the work
+      rd.work_row0 = ahead ? 0 : rd.len_prev + work_r0;
+      rd.work_row1 = ahead ? 0 : rd.len_prev + work_r1;
       const unsigned last = (unsigned)(b * 32 + 31);
       const bool plain = last <= kr.row_lim && last < kr.chunk_row0;
       for (int row = 0; row < 32; ++row)
@@ -110,30 +126,45 @@ static void walk_few(Reader& rd, const KeyRange& kr, int split, int g) {
   }
 }
 
-// The fp32 kernel: half tiles, rows past the last one read as the last one; a last half beyond every row is left out.
+// The fp32 kernel: half tiles, rows past the last one read as the last one; a last half beyond every row is left out.  Fused: the
+// first half and those of the second loop take each row from its own side, those of the first loop, which ends before the
+// first half that is not all cache, are cache rows.
 static void walk_halves(Reader& rd, const TileMap& tm, const KeyRange& kr, int64_t nkeys_wg) {
-  const int64_t len_after = rd.len_prev + rd.n_tokens;
+  const int64_t len_after = rd.len_prev + rd.n_tokens, chunk0 = rd.fused ? rd.len_prev : (int64_t)1 << 40;
   auto first_key = [&](int h) { const int t = h >> 1; return (2 * (int64_t)(t + (t >= tm.ns_t ? tm.skip : 0)) + (h & 1)) * 32; };
+  auto is_old = [&](int h) { return first_key(h) + 32 <= chunk0; };
+  const int h_begin = 2 * kr.t_begin;
   int h_end = 2 * kr.t_end;
-  if (h_end > 2 * kr.t_begin && first_key(h_end - 1) >= nkeys_wg) --h_end;
-  for (int h = 2 * kr.t_begin; h < h_end; ++h)
-    for (int row = 0; row < 32; ++row) {
-      const int64_t key = first_key(h) + row;
-      rd.read(DmaRow{false, (unsigned)(key < len_after ? key : len_after - 1)}, key, true);
+  if (h_end > h_begin && first_key(h_end - 1) >= nkeys_wg) --h_end;
+  auto fetch = [&](int h, bool old) {
+    for (int i = 0; i < 32; ++i) {
+      const int64_t key = first_key(h) + i, row = key < len_after ? key : len_after - 1;
+      const bool from_chunk = !old && row >= chunk0;
+      rd.read(DmaRow{from_chunk, (unsigned)(from_chunk ? row - chunk0 : row)}, key, true);
     }
+  };
+  if (h_begin < h_end) fetch(h_begin, false);
+  int h = h_begin;
+  for (; h < h_end && is_old(h + 1 < h_end ? h + 1 : h); ++h)
+    if (h + 1 < h_end) fetch(h + 1, true);
+  for (; h < h_end; ++h)
+    if (h + 1 < h_end) fetch(h + 1, false);
 }
 
 static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_t len_prev, int n_sink, int64_t window,
-                      int force_splits, int force_upw) {
+                      int force_splits, int force_upw, bool rope = false, int storage_bits = 0) {
   PlanCtx pc{};
   pc.cfg = cfg;
   pc.ws_rows = workspace_rows(&cfg);
   pc.n_cu = n_cu;
   pc.tune_splits = force_splits;
   pc.tune_units_per_wave = force_upw;
+  pc.storage_bits = storage_bits;
   const int64_t len_after = len_prev + n_tokens;
   const Plan pl = make_plan(pc, n_tokens, len_after, n_sink, window);
-  const bool fused = fused_append_applies(pc, n_tokens, len_prev, false);
+  const bool fused = attention_appends(pc, pl, n_tokens, rope), work = attention_works_on_rows(pc, pl, n_tokens, rope);
+  REQUIRE(!(fused && work), "appended twice");
+  REQUIRE(cfg.dtype != KVFOLD_BF16 || fused == fused_append_applies(pc, n_tokens, len_prev, rope), "what kvfold_plan_t reports");
   const int G = cfg.n_q_heads / cfg.n_kv_heads;
   const int upw_wg = pl.waves_per_wg * pl.units_per_wave;
   const int row_bytes = cfg.head_dim * elem_size(cfg.dtype);
@@ -146,6 +177,17 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   REQUIRE((int64_t)pl.wgs_per_head * upw_wg >= pl.units_per_head && (int64_t)pl.units_per_head * kRowsPerUnit >= (int64_t)n_tokens * G,
           "%d workgroups of %d units for %d tokens x %d heads", pl.wgs_per_head, upw_wg, n_tokens, G);
 
+  // the chunk's rows, one KV head: its workgroups' shares of the copy
+  std::vector<int> appended((size_t)n_tokens);
+  if (fused) {
+    const int per_kvh = pl.wgs_per_head * pl.n_splits, copy_rows = (n_tokens + per_kvh - 1) / per_kvh;
+    for (int rem = 0; rem < per_kvh; ++rem)
+      for (int r = rem * copy_rows; r < (rem + 1) * copy_rows && r < n_tokens; ++r) {
+        REQUIRE((uint64_t)r * cfg.n_kv_heads * row_bytes + row_bytes <= (1ull << 32), "32-bit chunk offset wraps");
+        REQUIRE((uint64_t)(len_prev + r) * row_bytes + row_bytes <= (1ull << 32), "32-bit cache offset wraps");
+        appended[(size_t)r]++;
+      }
+  }
   std::vector<int> seen((size_t)len_after);
   for (int ug = 0; ug < pl.wgs_per_head; ++ug) {
     RowRange rr;
@@ -166,13 +208,13 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       const KeyRange kr = key_range(tm, split, pl.tiles_per_split, len_prev, n_tokens, fused);
       if (kr.t_begin >= kr.t_end) continue;  // an empty piece touches nothing
       // (a piece that never reads the chunk as handed in ends below len_prev, so the clamp keeps it there too)
-      const int64_t readable_cache = fused ? len_prev : len_after;
+      const int64_t readable_cache = fused || work ? len_prev : len_after;
       REQUIRE((int64_t)kr.row_lim < len_after, "row_lim");
       Reader rd{cfg, n_tokens, len_prev, readable_cache, len_prev + rr.row_hi, row_bytes, fused, seen};
       if (cfg.dtype != KVFOLD_BF16)
         walk_halves(rd, tm, kr, len_prev + rr.row_hi + 1);
       else if (pl.few_rows)
-        walk_few(rd, kr, split, (split * 5 + ug) % cfg.n_kv_heads);
+        walk_few(rd, kr, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
       else
         walk_ring(rd, tm, kr, pl.units_per_wave == 2 ? 3 : 2);
     }
@@ -186,6 +228,8 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
     }
     for (int64_t j = 0; j < len_after; ++j) REQUIRE(seen[(size_t)j] <= 1, "key %lld fetched twice", (long long)j);
   }
+  if (fused || work)  // (few rows: one workgroup per piece, so that the walk above has been through all)
+    for (int r = 0; r < n_tokens; ++r) REQUIRE(appended[(size_t)r] == 1, "row %d appended %d times", r, appended[(size_t)r]);
 }
 
 static kvfold_config_t make_cfg(int Hq, int Hkv, int d, int C, int64_t cap, int dtype) {
@@ -219,6 +263,13 @@ static void model_sweep() {
                 if (splits > 0 && (int64_t)splits * C * h[0] > workspace_rows(&cfg)) continue;
                 walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw);
                 ++steps;
+                // rows with work on their way: few rows of bf16, and fp32 behind the append kernel
+                const bool few = dtype == KVFOLD_BF16 && units_of_head(C, h[0] / h[1]) == 1;
+                for (int work : {1, 2, 3}) {
+                  if (w[1] > 0 || !(few || (dtype == KVFOLD_F32 && work == 1))) continue;
+                  walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw, (work & 1) != 0, work & 2 ? 8 : 0);
+                  ++steps;
+                }
               }
           }
   // the benchmark's shapes at their real sizes, plain and with the streaming baseline's window
