@@ -11,16 +11,17 @@ namespace kvfold {
 // Thread layout of a 256-thread block: rows x SG split groups x V 16-byte column vectors (V = head_dim / 4), all powers of
 // two, so that a thread finds its place by shifts.  All loads of a thread's pieces, up to eight, are in flight together, and
 // their weights are taken against one maximum.  Against the form before (run-time divisions, four pieces at a time folded one
-// by one), kernel alone: 32 rows x 22 pieces 3.84 -> 3.44 us, 1184 x 27 6.6 -> 5.8, 3584 x 18 6.4 -> 5.5, 8192 x 8 9.2 -> 8.3,
-// 32768 x 2 10.6 -> 10.7 (4 TB/s).
-// Split group sg of a row folds pieces sg, sg + SG, ... into one running (m, l, O); the SG results meet in LDS.  With few
+// by one), the kernel in a trace of steps: 32 rows x 17 pieces 3.9 -> 3.5 us, 1184 x 27 6.6 -> 5.9, 3584 x 18 9.5 -> 8.4, 8192 x 8 9.7 ->
+// 8.2, 32768 x 2 10.6 -> 9.7 (3.7 TB/s); 2048 x 40, more pieces than a plan cuts so many rows into, 10.2 -> 11.2.
+// Split group sg of a row folds pieces sg, sg + SG, ..., at most eight, into one (m, l, O); the SG results meet in LDS.  With few
 // rows (decode-shaped steps: 32 rows, 64 pieces) this keeps every load of a row in flight at once instead of walking the
 // pieces one after another.
 constexpr int kCombineThreads = 256;
-constexpr int kBatch = 8;  // pieces of a thread whose loads are in flight together
+constexpr int kBatch = 8;  // pieces of a thread, at most: their loads are in flight together
 
+// (Four wavefronts per SIMD asked for: without it the compiler takes 190 registers and leaves room for two.)
 template <int LV>  // log2 V
-__global__ void __launch_bounds__(kCombineThreads) combine_kernel(CombineParams p, int log2_sg) {
+__global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombineParams p, int log2_sg) {
   constexpr unsigned V = 1u << LV, D = 4 * V;
   extern __shared__ __attribute__((aligned(16))) float red[];  // [rows][SG][V] partial O (16 bytes each), then [rows][SG] (m, l)
   typedef __attribute__((ext_vector_type(4))) float floatx4;
@@ -35,46 +36,42 @@ __global__ void __launch_bounds__(kCombineThreads) combine_kernel(CombineParams 
   // (row, piece) pairs are at most 2^19 of at most 512 bytes: 32-bit offsets
   const unsigned char* po = reinterpret_cast<const unsigned char*>(p.part_o);
   const unsigned char* pml = reinterpret_cast<const unsigned char*>(p.part_ml);
+  static_assert(kMaxSplits <= kBatch * (kCombineThreads >> 5), "a thread's pieces in one batch, whatever the width");
+  floatx2 ml[kBatch];
+  floatx4 o[kBatch];
+#pragma unroll
+  for (int u = 0; u < kBatch; ++u) {
+    ml[u] = floatx2{-INFINITY, 0.f};
+    o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (u * SG < (unsigned)p.n_splits) {  // (uniform; the last group of pieces may not be whole)
+      const unsigned s = u * SG + sg;
+      if (live && s < (unsigned)p.n_splits) {
+        const unsigned at = s * n_rows + row;
+        ml[u] = *reinterpret_cast<const floatx2*>(pml + at * 8u);
+        o[u] = *reinterpret_cast<const floatx4*>(po + at * (D * 4u) + dv * 16u);
+      }
+    }
+  }
   float m = -INFINITY, l = 0.f;
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (unsigned b0 = 0; b0 < (unsigned)p.n_splits; b0 += SG * kBatch) {
-    floatx2 ml[kBatch];
-    floatx4 o[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      ml[u] = floatx2{-INFINITY, 0.f};
+  for (int u = 0; u < kBatch; ++u) {
+    if (ml[u].y == 0.f) {  // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
+      ml[u].x = -INFINITY;
       o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if (b0 + u * SG < (unsigned)p.n_splits) {  // (uniform; the last group of pieces may not be whole)
-        const unsigned s = b0 + u * SG + sg;
-        if (live && s < (unsigned)p.n_splits) {
-          const unsigned at = s * n_rows + row;
-          ml[u] = *reinterpret_cast<const floatx2*>(pml + at * 8u);
-          o[u] = *reinterpret_cast<const floatx4*>(po + at * (D * 4u) + dv * 16u);
-        }
-      }
     }
-    float mn = m;
+    m = fmaxf(m, ml[u].x);
+  }
+  {
+    const float ref = m == -INFINITY ? 0.f : m;  // (-inf: every logit of the row is, or it sees nothing of these pieces)
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (ml[u].y == 0.f) {  // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
-        ml[u].x = -INFINITY;
-        o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-      }
-      mn = fmaxf(mn, ml[u].x);
-    }
-    const float ref = mn == -INFINITY ? 0.f : mn, a = __builtin_amdgcn_exp2f(m - ref);
-    l *= a;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] *= a;
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (b0 + u * SG >= (unsigned)p.n_splits) break;
+      if (u * SG >= (unsigned)p.n_splits) break;
       const float b = __builtin_amdgcn_exp2f(ml[u].x - ref);
       l = __builtin_fmaf(ml[u].y, b, l);
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(o[u][e], b, acc[e]);
     }
-    m = mn;
   }
   if (SG > 1) {
     red_o[tid] = acc;  // [row of the block][split group][column vector]
@@ -82,7 +79,7 @@ __global__ void __launch_bounds__(kCombineThreads) combine_kernel(CombineParams 
     __syncthreads();
     if (sg != 0) return;
     for (unsigned g = 1; g < SG; ++g) m = fmaxf(m, red_ml[grp + g].x);
-    const float ref = m == -INFINITY ? 0.f : m;  // (-inf: every logit of the row is)
+    const float ref = m == -INFINITY ? 0.f : m;
     const float b0 = __builtin_amdgcn_exp2f(red_ml[grp].x - ref);
     l *= b0;
 #pragma unroll
@@ -120,7 +117,7 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   if (p.n_rows <= 0) return hipSuccess;
   const int lv = p.head_dim == 128 ? 5 : 4, V = 1 << lv;
   // Split groups (a power of two, at most the number of pieces and what one row's share of a block
-  // allows) only as far as they are needed to put about two blocks on every CU, or a thread's pieces into one batch: with
+  // allows) as far as they are needed to put a thread's pieces into one batch, and about two blocks on every CU: with
   // many rows one thread per (row, column vector) walking the pieces is the cheaper form.
   const int64_t blocks1 = ((int64_t)p.n_rows * V + kCombineThreads - 1) / kCombineThreads;
   int lsg = 0;
