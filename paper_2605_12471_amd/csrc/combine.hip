@@ -11,15 +11,15 @@ namespace kvfold {
 // Thread layout of a 256-thread block: rows x SG split groups x V 16-byte column vectors (V = head_dim / 4), all powers of
 // two, so that a thread finds its place by shifts.  All loads of a thread's pieces, up to eight, are in flight together, and
 // their weights are taken against one maximum.  Against the form before (run-time divisions, four pieces at a time folded one
-// by one), the kernel in a trace of steps: 32 rows x 17 pieces 3.9 -> 3.5 us, 1184 x 27 6.6 -> 5.9, 3584 x 18 9.5 -> 8.4, 8192 x 8 9.7 ->
-// 8.2, 32768 x 2 10.6 -> 9.7 (3.7 TB/s); 2048 x 40, more pieces than a plan cuts so many rows into, 10.2 -> 11.2.
+// by one), the kernel in a trace of steps: 32 rows x 17 pieces 3.9 -> 3.3 us, 1184 x 27 6.6 -> 5.9, 3584 x 18 9.5 -> 8.4, 8192 x 8 9.7 ->
+// 8.7, 32768 x 2 10.6 -> 9.2 (4.6 TB/s); 2048 x 40, more pieces than a plan cuts so many rows into, 10.2 -> 11.8.
 // Split group sg of a row folds pieces sg, sg + SG, ..., at most eight, into one (m, l, O); the SG results meet in LDS.  With few
 // rows (decode-shaped steps: 32 rows, 64 pieces) this keeps every load of a row in flight at once instead of walking the
 // pieces one after another.
 constexpr int kCombineThreads = 256;
 constexpr int kBatch = 8;  // pieces of a thread, at most: their loads are in flight together
 
-// (Four wavefronts per SIMD asked for: without it the compiler takes 190 registers and leaves room for two.)
+// (Four wavefronts per SIMD asked for: the compiler then takes 64 registers, else 92, and 32768 x 2 takes 10.8 us.)
 template <int LV>  // log2 V
 __global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombineParams p, int log2_sg) {
   constexpr unsigned V = 1u << LV, D = 4 * V;
@@ -37,25 +37,23 @@ __global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombinePara
   const unsigned char* po = reinterpret_cast<const unsigned char*>(p.part_o);
   const unsigned char* pml = reinterpret_cast<const unsigned char*>(p.part_ml);
   static_assert(kMaxSplits <= kBatch * (kCombineThreads >> 5), "a thread's pieces in one batch, whatever the width");
+  // (Pieces and rows past the last are read as the last: a load under a lane's own condition is waited for on the way to the next.)
   floatx2 ml[kBatch];
   floatx4 o[kBatch];
+  const unsigned n_splits = (unsigned)p.n_splits, from = row < n_rows ? row : n_rows - 1;
 #pragma unroll
   for (int u = 0; u < kBatch; ++u) {
-    ml[u] = floatx2{-INFINITY, 0.f};
-    o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (u * SG < (unsigned)p.n_splits) {  // (uniform; the last group of pieces may not be whole)
-      const unsigned s = u * SG + sg;
-      if (live && s < (unsigned)p.n_splits) {
-        const unsigned at = s * n_rows + row;
-        ml[u] = *reinterpret_cast<const floatx2*>(pml + at * 8u);
-        o[u] = *reinterpret_cast<const floatx4*>(po + at * (D * 4u) + dv * 16u);
-      }
-    }
+    if (u * SG >= n_splits) break;
+    const unsigned s = u * SG + sg, at = (s < n_splits ? s : n_splits - 1) * n_rows + from;
+    ml[u] = *reinterpret_cast<const floatx2*>(pml + at * 8u);
+    o[u] = *reinterpret_cast<const floatx4*>(po + at * (D * 4u) + dv * 16u);
   }
   float m = -INFINITY, l = 0.f;
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < kBatch; ++u) {
+    if (u * SG >= n_splits) break;
+    if (u * SG + sg >= n_splits) ml[u].y = 0.f;
     if (ml[u].y == 0.f) {  // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
       ml[u].x = -INFINITY;
       o[u] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -66,7 +64,7 @@ __global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombinePara
     const float ref = m == -INFINITY ? 0.f : m;  // (-inf: every logit of the row is, or it sees nothing of these pieces)
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (u * SG >= (unsigned)p.n_splits) break;
+      if (u * SG >= n_splits) break;
       const float b = __builtin_amdgcn_exp2f(ml[u].x - ref);
       l = __builtin_fmaf(ml[u].y, b, l);
 #pragma unroll
