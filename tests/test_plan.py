@@ -28,11 +28,12 @@ def test_unsplit_steps_whose_workgroups_are_not_evenly_dealt(hq, hkv, n, prev, u
 @pytest.mark.parametrize("hq,hkv,n,prev", [
     (8, 2, 295, 1252),     # 41 / 53 us with 13 pieces
     (4, 1, 897, 146),      # 38 / 49 with 9
+    (8, 2, 506, 1131),     # 44 / 62 with 9 (dealt evenly, 255 of 288 workgroups with work)
+    (8, 2, 1023, 305),     # 53 / 78 with 11
 ])
-def test_pieces_that_are_not_evenly_dealt_fit_one_round(hq, hkv, n, prev):
-    plan = _plan(kv.KVFOLD_F32, hq, hkv, 128, n, prev)
-    per_head = plan.n_workgroups // hkv
-    assert plan.n_workgroups <= 256 or per_head % (8 // hkv) == 0
+def test_fp32_pieces_fit_one_round(hq, hkv, n, prev):
+    """... without the empty ones of early tokens making room for others."""
+    assert _plan(kv.KVFOLD_F32, hq, hkv, 128, n, prev).n_workgroups <= 256
 
 
 @pytest.mark.parametrize("hq,hkv,d,n,prev,waves", [
