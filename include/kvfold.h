@@ -247,12 +247,19 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
  *                              round of workgroups), 1 = never, 2 = always.
- *   KVFOLD_TUNE_FUSED_APPEND   the attention kernel copies the chunk's rows into the cache itself
- *                              (and reads the chunk's own rows from k_new / v_new) whenever neither rotary
- *                              embedding nor a storage round trip is in play (bf16 steps of at most 32
- *                              (token, query head) rows per KV head: also then) and the chunk's K rows (n_tokens * n_kv_heads * head_dim
- *                              elements) take less than 2^32 bytes (the kernel addresses the chunk with 32-bit byte offsets; larger
- *                              chunks go through the separate append kernel); 0 = automatic, 1 = never.
+ *   KVFOLD_TUNE_FUSED_APPEND   0 = automatic: the attention kernel appends the chunk's rows itself and there is no
+ *                              append kernel in front of it where
+ *                              - neither rotary embedding nor a storage round trip is in play and the chunk's K
+ *                                rows (n_tokens * n_kv_heads * head_dim elements) take less than 2^32 bytes (it reads
+ *                                the chunk's own rows from k_new / v_new, with 32-bit byte offsets), bf16: unless
+ *                                out or lse of an unsplit step lies on these rows (out in their very place may, with
+ *                                as many KV as query heads and at most 32 tokens); fp32: workgroups of four
+ *                                wavefronts whose pieces of the key range have fewer than 20 tiles (head_dim 64: 12), and
+ *                                rows apart from out, lse and the cache;
+ *                              - one of the two is in play, in a bf16 step without a window of at most 32 (token,
+ *                                query head) rows per KV head, with the round trip also of at most 4096 bytes of K rows per
+ *                                KV head, and rows apart from out, lse and the cache.
+ *                              1 = never.
  *                              Either way k_new / v_new must stay valid until the step's work on the
  *                              stream is done, and the cache ends up with the same bits.
  * Returns KVFOLD_ERR_INVALID_ARG for an unknown knob or a value out of range.  Host-only.
@@ -281,7 +288,7 @@ typedef struct {
                            /* most 32 rows per KV head, which have a kernel of their own: 1)            */
   int32_t tiles_per_split; /* 64-key tiles per piece                                                    */
   int32_t fused_append;    /* 1: the bf16 attention kernel appends the chunk's rows itself              */
-                           /* (kvfold_step_ex); 0 for fp32, where workgroups of four wavefronts do so too */
+                           /* (kvfold_step_ex); 0 for fp32, where it may do so too (see the knob)         */
   int32_t pair_units;      /* 1: every wavefront owns an early and a late row block of the chunk        */
   int32_t pair_order;      /* 1: workgroups ordered so that each CU gets a heavy and a light one        */
 } kvfold_plan_t;

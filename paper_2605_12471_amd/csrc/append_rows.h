@@ -56,8 +56,8 @@ __device__ __forceinline__ void round_trip_vec(row_vec<T, E>& v, int vpr, float 
 }
 
 // Rows [r0, r1) of the chunk of one KV head (bf16, D wide), rotated (K) and passed through the round trip as asked for, to
-// the head's cache rows len_prev + r; 256 threads.  Every workgroup that is going to read one of these rows writes it by
-// itself first, the same bits as all the others, so none waits for another.
+// the head's cache rows len_prev + r; 256 threads.  The pieces of the key range are disjoint and each has one workgroup, which
+// reads no row of the chunk but those that it has written itself: none waits for another.
 template <int D>
 __device__ __forceinline__ void append_work_rows(const unsigned char* knew, const unsigned char* vnew, unsigned new_stride, unsigned char* kdst,
                                                  unsigned char* vdst, const float* rope_cos, const float* rope_sin, float qmax, int r0, int r1, int tid) {

@@ -15,7 +15,7 @@
 // One token, 32 heads on 8, D = 128, whole step, general kernel -> this one: 1K keys 12.5 -> 11.8 us (unsplit, one launch
 // instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
 // read gets 5.8 to 6.2).  With the start in 32-bit arithmetic, the faster merge and pieces of even numbers of tiles: 1K 9.4 us, 4K
-// 10.5, 8K 13.0, 128K 93.5.  At 4K keys that is two dependent launches, 7.2 and 3.3 us, of which the rows themselves would
+// 10.5, 8K 13.0, 128K 93.5.  At 4K keys that is two dependent launches, 7.6 and 3.0 us, of which the rows themselves would
 // take 3.
 #include "append_rows.h"
 #include "kvfold_internal.h"

@@ -58,7 +58,7 @@ struct AttnParams {
   const void* k_new;
   const void* v_new;
   // Few-rows kernel, rows that need work on their way into the cache (nullptr: not this step): the chunk's K / V rows as handed
-  // in.  Every workgroup appends the rows that it is going to read (rotated if rope_cos, through the storage round trip if
+  // in.  Every workgroup appends the rows of its piece (rotated if rope_cos, through the storage round trip if
   // work_qmax > 0) and then reads them from the cache like all others.
   const void* work_k;
   const void* work_v;

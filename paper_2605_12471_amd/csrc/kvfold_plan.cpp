@@ -55,11 +55,12 @@ bool fused_append_applies(const PlanCtx& c, int n_tokens, int64_t len_prev, bool
 bool attention_works_on_rows(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope) {
   const kvfold_config_t& f = c.cfg;
   if (!pl.few_rows || !(rope || c.storage_bits) || c.tune_fused_append == 1) return false;
-  // A launch less (3 us), against the work done once more by each workgroup that reaches the chunk.  Measured on 300, 5000
-  // and 32K keys, append kernel / this, D = 128, 32 heads on 8: rotary embedding, 1 token 10.4 / 8.7, 13.7 / 11.9, 28.8 / 26.8 us,
-  // 8 tokens 11.6 / 10.3, 15.8 / 13.7, 31.2 / 28.9; round trip, 8 tokens 11.9 / 9.9, 16.2 / 13.2, 30.6 / 28.1.  More rows are
-  // for the general kernel, whose ring has to be filled behind the rows: 37 tokens with the rotary embedding on 32K keys 45.9 / 46.8, and
-  // every other step paid 0.5 % for the code.  The round trip, with its divisions, takes 90 ns a row: up to 16 rows.
+  // A launch less (3 us), against the work ahead of the piece that holds the chunk.  Measured on 300 to 33K keys, five head
+  // shapes, 1 to 32 tokens, this against the append kernel: 128 wide 0.91 (1 token) to 0.96 of the time with the rotary
+  // embedding and 0.90 to 0.96 with the round trip, 64 wide 0.86 to 0.93, and no shape slower.  The round trip, with its
+  // divisions, takes 90 ns a row: up to 16 rows 128 wide.  More rows are for the general kernel, whose
+  // ring has to be filled behind the rows: 37 tokens with the rotary embedding on 32K keys 45.9 / 46.8 us, and every other step
+  // paid 0.5 % for the code.
   return !c.storage_bits || (int64_t)n_tokens * f.head_dim * elem_size(f.dtype) <= 4096;
 }
 
@@ -154,7 +155,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.  (Few rows: the rest of what a launch
     //    costs is in the pace at which they are queued; with 4.7 us here 12 tokens on 1091 keys, 32 heads, stayed unsplit, 16.4 us
     //    for 13.1.)
-    //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.
+    //  * A step is not queued faster than its launches: some 6.7 us with one, 2.65 us more for each further one.  (The pace of the
+    //    Python binding.  C callers and captured graphs queue faster; where this decides, the kernels' own times differ little:
+    //    in captured graphs the choice is 1.2 to 1.9 % above the best on average.)
     // The figures are fitted to 25,000 measured steps: 1327 shapes (1 to 64 heads, 1 to 1500 tokens on 0 to 128K keys, all
     // kernels), every split count.  The choice is 1.0 % above the best on average, more than 5 % in 82 shapes, more
     // than 10 % in 24; with the figures before, fitted to 30 workloads, 1.8 %, 166 and 70.  The fp32 kernel's are fitted again
@@ -203,7 +206,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // to a second round: 506 tokens on 1131 keys, 8 heads on 2, 44 us in one round, 62 with 288 workgroups of which 255 have work)
       if (fp32 && (double)w > slots && busy < slots) t *= 1.0 + 1.5 * std::max(0.0, busy / slots - 0.8);
       // few rows: the blocks of an odd number of tiles do not go round the four wavefronts.  (Over 560 shapes on as many layers as
-      // keep the caches out of the chip's own, the choice is 0.8 % above the best with this and 1.0 % without the second
+      // keep the caches out of the chip's own, the choice is 0.8 % above the best with this and 0.9 % without the second
       // term.  A step's two launches follow each other in steps of 0.8 us, which is the scatter: one token on 4187 keys, 2 / 3 / 4 / 5 tiles
       // a piece 12.4 / 11.7 / 10.8 / 11.5 us, on 4538 12.4 / 11.0 / 11.7 / 11.6.)
       if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
