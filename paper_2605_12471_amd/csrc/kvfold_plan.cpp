@@ -151,7 +151,8 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     //  * A KV head's workgroups lie on its XCDs in runs where they cannot be dealt to them in turn: one XCD then has the heavy
     //    ones, another the light or empty ones (28 heads on 4, one / two units per wavefront: 3249 tokens, 178 / 89 workgroups a head,
     //    78 / 115 us; 3273 tokens on 153 keys, 179 / 90 workgroups, 117 / 89; fp32, 8 heads on 2, 295 tokens on 1252 keys, 130
-    //    workgroups a head of which 16 are empty: 53 us, two rounds for the first XCD of each head).
+    //    workgroups a head of which 16 are empty: 53 us, two rounds for the first XCD of each head).  What the others do not take of
+    //    the chip's power goes to the first (64 wide, 28 heads on 4, 2867 tokens, 157 / 79 workgroups a head: 54 / 73 us).
     //  * The merge: its launch, and the fp32 partials written and read once at 6.7 TB/s.  (Few rows: the rest of what a launch
     //    costs is in the pace at which they are queued; with 4.7 us here 12 tokens on 1091 keys, 32 heads, stayed unsplit, 16.4 us
     //    for 13.1.)
@@ -211,7 +212,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // a piece 12.4 / 11.7 / 10.8 / 11.5 us, on 4538 12.4 / 11.0 / 11.7 / 11.6.)
       if (few_rows && tps % 2 && tps > 1) t += k.idle + 0.7;
       if (cand == 1 && window <= 0 && rounds >= 2.0)
-        t = (double)tps * worst *
+        t = (double)tps * (even ? worst : std::max(k.idle, worst * std::sqrt(mean_keys / late_keys))) *
             ((double)w * (even ? mean_keys : late_keys) + (rounds * slots - (double)w) * ((even ? la - n_tokens : late_least) + kRowsPerUnit)) / (slots * la);
       if (cand == 1 && window <= 0) t = std::max(t, (double)tps * k.idle);
       const double kv_piece = kv_us * (double)(tps * cand) / (double)ntiles;

@@ -25,6 +25,18 @@ def test_unsplit_steps_whose_workgroups_are_not_evenly_dealt(hq, hkv, n, prev, u
     assert plan.n_splits == 1 and plan.units_per_wave == units
 
 
+@pytest.mark.parametrize("d,n,prev", [
+    (128, 2500, 0),     # 78 / 85 us
+    (128, 2500, 95),    # 81 / 88
+    (64, 2867, 0),      # 54 / 73
+    (64, 3013, 0),      # 57 / 78
+])
+def test_neither_form_evenly_dealt(d, n, prev):
+    """One unit per wavefront: the XCD with the heavy workgroups has the power that the others leave."""
+    plan = _plan(kv.KVFOLD_BF16, 28, 4, d, n, prev)
+    assert plan.n_splits == 1 and plan.units_per_wave == 1
+
+
 @pytest.mark.parametrize("hq,hkv,n,prev", [
     (8, 2, 295, 1252),     # 41 / 53 us with 13 pieces
     (4, 1, 897, 146),      # 38 / 49 with 9
