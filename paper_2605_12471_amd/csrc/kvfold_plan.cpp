@@ -258,13 +258,15 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   Plan p1 = plan_with(c, n_tokens, len_after, 1, n_sink, window);
   // Prefix shorter than the chunk: the causal part makes late token blocks several times as long as early
   // ones.  If the one-unit-per-wavefront grid is resident at once (two workgroups per CU), pair heavy with
-  // light workgroups on a CU (measured faster than pairing units inside the two-unit kernel only here).
+  // light workgroups on a CU (measured faster than pairing units inside the two-unit kernel only here).  That takes workgroups
+  // which are dealt to a head's XCDs in turn.  In runs, heavy ones share their CUs: with four or eight XCDs to a head the
+  // two-unit kernel was faster in all of 25 shapes, by 12 to 48 % (14 heads on 2, 4282 tokens on 65 keys: 111 / 83 us; 8 on
+  // 1, 7507 on none: 198 / 142); with two, 28 shapes from 5 % slower to 10 % faster, the estimates decide.
   const int64_t wgs1 = (int64_t)f.n_kv_heads * p1.wgs_per_head;
-  if (c.tune_splits == 0 && window <= 0 && len_after < 2 * (int64_t)n_tokens && wgs1 <= 2 * (int64_t)c.n_cu &&
-      wgs1 > (int64_t)c.n_cu && p1.n_splits == 1) {
-    p1.pair_order = 1;
-    return p1;
-  }
+  const bool pair = c.tune_splits == 0 && window <= 0 && len_after < 2 * (int64_t)n_tokens && wgs1 <= 2 * (int64_t)c.n_cu &&
+                    wgs1 > (int64_t)c.n_cu && p1.n_splits == 1;
+  p1.pair_order = pair ? 1 : 0;
+  if (pair && evenly_dealt(f.n_kv_heads, p1.wgs_per_head)) return p1;
   // Two units per wavefront is the faster kernel on a full chip (every LDS fragment feeds two MFMAs); one unit starts
   // sooner and fills the chip with fewer rows.  The estimates decide, the two-unit kernel's taken 10 % longer (part of the
   // fit).  Where units straddle tokens and half of a two-unit workgroup is padding (C = 128, G = 7) the choice changes
@@ -277,6 +279,7 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     if (p2.n_splits == 1 && (int64_t)p2.n_wgs * 4 < (int64_t)c.n_cu * 3 && p1.n_wgs > p2.n_wgs) return p1;  // cannot fill the chip
     return p2;
   }
+  if (pair && 4 * f.n_kv_heads <= kNumXcd) return p2;
   return p1.est_us < p2.est_us * 1.1 ? p1 : p2;
 }
 

@@ -68,3 +68,16 @@ def test_fp32_wavefronts_per_workgroup(hq, hkv, d, n, prev, waves):
 ])
 def test_few_rows_are_split_where_the_merge_is_worth_it(hq, hkv, d, n, prev):
     assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).n_splits > 1
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev,units", [
+    (14, 2, 128, 4282, 65, 2),      # 83 / 111 us
+    (14, 2, 64, 4201, 0, 2),        # 57 / 68
+    (8, 1, 128, 7507, 0, 2),        # 142 / 198
+    (8, 2, 128, 7255, 196, 2),      # 127 / 162
+    (16, 4, 128, 2909, 2237, 2),    # 103 / 112
+    (28, 4, 128, 2038, 0, 1),       # (448 workgroups, dealt in turn)
+])
+def test_heavy_and_light_workgroups_share_cus_only_if_dealt_in_turn(hq, hkv, d, n, prev, units):
+    plan = _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev)
+    assert plan.units_per_wave == units and plan.pair_order == (1 if units == 1 else 0)
