@@ -12,7 +12,7 @@ namespace kvfold {
 // two, so that a thread finds its place by shifts.  All loads of a thread's pieces, up to eight, are in flight together, and
 // their weights are taken against one maximum.  Against the form before (run-time divisions, four pieces at a time folded one
 // by one), the kernel in a trace of steps: 32 rows x 17 pieces 3.9 -> 3.3 us, 1184 x 27 6.6 -> 5.9, 3584 x 18 9.5 -> 8.4, 8192 x 8 9.7 ->
-// 8.7, 32768 x 2 10.6 -> 9.2 (4.6 TB/s); 2048 x 40, more pieces than a plan cuts so many rows into, 10.2 -> 11.8.
+// 8.7, 32768 x 2 10.6 -> 9.2 (4.6 TB/s), 1024 x 56 9.1 -> 7.9, 2048 x 40 10.3 -> 10.0.
 // Split group sg of a row folds pieces sg, sg + SG, ..., at most eight, into one (m, l, O); the SG results meet in LDS.  With few
 // rows (decode-shaped steps: 32 rows, 64 pieces) this keeps every load of a row in flight at once instead of walking the
 // pieces one after another.
@@ -21,14 +21,18 @@ constexpr int kBatch = 8;  // pieces of a thread, at most: their loads are in fl
 
 // (Four wavefronts per SIMD asked for: the compiler then takes 64 registers, else 92, and 32768 x 2 takes 10.8 us.)
 template <int LV>  // log2 V
-__global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombineParams p, int log2_sg) {
+__global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombineParams p, int log2_sg, unsigned dealt) {
   constexpr unsigned V = 1u << LV, D = 4 * V;
   extern __shared__ __attribute__((aligned(16))) float red[];  // [rows][SG][V] partial O (16 bytes each), then [rows][SG] (m, l)
   typedef __attribute__((ext_vector_type(4))) float floatx4;
   typedef __attribute__((ext_vector_type(2))) float floatx2;
   const unsigned tid = threadIdx.x, SG = 1u << log2_sg;
   const unsigned dv = tid & (V - 1), grp = tid >> LV, sg = grp & (SG - 1), rl = grp >> log2_sg;
-  const unsigned row = blockIdx.x * (kCombineThreads >> (LV + log2_sg)) + rl, n_rows = (unsigned)p.n_rows;
+  // Split groups leave a block few rows, one or two of the sixteen that share a line of (m, l): neighbours go to one XCD (the
+  // hardware hands block b to XCD b % 8).  1024 rows x 56 pieces 10.6 -> 7.9 us, 2048 x 40 11.9 -> 10.0; without split groups
+  // the blocks stay as they come (8192 x 8 8.9, else 9.8).
+  const unsigned b = blockIdx.x, block = b < dealt ? b % kNumXcd * (dealt / kNumXcd) + b / kNumXcd : b;
+  const unsigned row = block * (kCombineThreads >> (LV + log2_sg)) + rl, n_rows = (unsigned)p.n_rows;
   const bool live = row < n_rows;
   floatx4* red_o = reinterpret_cast<floatx4*>(red);
   floatx2* red_ml = reinterpret_cast<floatx2*>(red + kCombineThreads * 4);
@@ -122,11 +126,12 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   while ((1 << lsg) < p.n_splits && (2 << lsg) * V <= kCombineThreads && ((blocks1 << lsg) < 512 || p.n_splits > kBatch << lsg)) ++lsg;
   const int rows_per_block = kCombineThreads >> (lv + lsg);
   const dim3 grid((unsigned)((p.n_rows + rows_per_block - 1) / rows_per_block)), block(kCombineThreads);
+  const unsigned dealt = lsg ? grid.x / kNumXcd * kNumXcd : 0;  // blocks of which an XCD gets neighbours
   const size_t lds = lsg ? kCombineThreads * 16 + (kCombineThreads >> lv) * 8 : 0;
   if (lv == 5)
-    hipLaunchKernelGGL(combine_kernel<5>, grid, block, lds, s, p, lsg);
+    hipLaunchKernelGGL(combine_kernel<5>, grid, block, lds, s, p, lsg, dealt);
   else
-    hipLaunchKernelGGL(combine_kernel<4>, grid, block, lds, s, p, lsg);
+    hipLaunchKernelGGL(combine_kernel<4>, grid, block, lds, s, p, lsg, dealt);
   return hipGetLastError();
 }
 

@@ -85,3 +85,28 @@ def test_rows_whose_every_key_is_hidden(H, dtype, d, n, upw, splits):
     assert torch.isfinite(plain).all() and torch.isfinite(plain_lse).all()
     assert torch.isnan(out[hidden]).all() and (lse[:, hidden] == -math.inf).all()
     assert torch.equal(out[~hidden], plain[~hidden]) and torch.equal(lse[:, ~hidden], plain_lse[:, ~hidden])
+
+
+# Rows that fill their blocks and leave some over, blocks that are a multiple of the XCDs' number and not, one split group per row up to eight.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 7, 37, 150, 1030])
+@pytest.mark.parametrize("splits", [2, 9, 18])
+def test_every_row_comes_out_in_its_place(H, d, n, splits):
+    """Against the unsplit step.  Both hold the sums in fp32, in another order: at most 1200 + n terms in 64-key tiles of a 16-long
+    chain, |v| < 6, so some 100 roundings of 2^-24 each."""
+    prev = 1200
+    cfg = I.FoldConfig("rows", 33, 1, 2, 1, d, prev, 0, "f32")
+    res = []
+    for s in (1, splits):
+        gpu = H.GpuFold(cfg, capacity=prev + n, chunk_tokens=prev)
+        pos = 0
+        for step, C in enumerate((prev, n)):
+            gpu.cache.set_tuning(kv.TUNE_SPLITS, s if step else 1)
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            out, lse = gpu.step(0, q, k, v, want_lse=True)
+            pos += C
+        assert s / 2 < gpu.cache.plan(n, prev + n)[1] <= s  # (whole tiles)
+        res.append((out.clone(), lse.clone()))
+        gpu.close()
+    assert (res[0][0] - res[1][0]).abs().max() <= 100 * 2.0 ** -24 * 6
+    assert (res[0][1] - res[1][1]).abs().max() <= 100 * 2.0 ** -24 * 16
