@@ -28,9 +28,7 @@ __global__ void __launch_bounds__(kCombineThreads, 4) combine_kernel(CombinePara
   typedef __attribute__((ext_vector_type(2))) float floatx2;
   const unsigned tid = threadIdx.x, SG = 1u << log2_sg;
   const unsigned dv = tid & (V - 1), grp = tid >> LV, sg = grp & (SG - 1), rl = grp >> log2_sg;
-  // Split groups leave a block few rows, one or two of the sixteen that share a line of (m, l): neighbours go to one XCD (the
-  // hardware hands block b to XCD b % 8).  1024 rows x 56 pieces 10.6 -> 7.9 us, 2048 x 40 11.9 -> 10.0; without split groups
-  // the blocks stay as they come (8192 x 8 8.9, else 9.8).
+  // The hardware hands block b to XCD b % 8; the first `dealt` blocks are neighbours on one XCD instead (launch_combine()).
   const unsigned b = blockIdx.x, block = b < dealt ? b % kNumXcd * (dealt / kNumXcd) + b / kNumXcd : b;
   const unsigned row = block * (kCombineThreads >> (LV + log2_sg)) + rl, n_rows = (unsigned)p.n_rows;
   const bool live = row < n_rows;
@@ -126,7 +124,13 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   while ((1 << lsg) < p.n_splits && (2 << lsg) * V <= kCombineThreads && ((blocks1 << lsg) < 512 || p.n_splits > kBatch << lsg)) ++lsg;
   const int rows_per_block = kCombineThreads >> (lv + lsg);
   const dim3 grid((unsigned)((p.n_rows + rows_per_block - 1) / rows_per_block)), block(kCombineThreads);
-  const unsigned dealt = lsg ? grid.x / kNumXcd * kNumXcd : 0;  // blocks of which an XCD gets neighbours
+  // More groups for the pieces' sake leave a block one of the sixteen rows that share a line of (m, l): neighbouring rows go to one
+  // XCD then.  Whole steps, with blocks as they come / dealt: 1024 rows x 56 pieces 28.1 / 26.4 us, 2048 x 40 48.2 / 46.8.  Nowhere
+  // else: blocks of four rows follow the KV heads of groups of four, and find in their L2 what the attention kernel wrote
+  // from there (121 tokens, 32 heads on 8, 8 pieces 23.2 / 25.9, 64 wide, 66 tokens, 12 pieces 14.4 / 15.4); 45 tokens, 8 heads on
+  // 2, 53 pieces 21.0 / 22.7; 3584 x 18 43.6 / 43.9.
+  const bool for_pieces = lsg > 0 && blocks1 << (lsg - 1) >= 512;
+  const unsigned dealt = for_pieces && rows_per_block == 1 ? grid.x / kNumXcd * kNumXcd : 0;
   const size_t lds = lsg ? kCombineThreads * 16 + (kCombineThreads >> lv) * 8 : 0;
   if (lv == 5)
     hipLaunchKernelGGL(combine_kernel<5>, grid, block, lds, s, p, lsg, dealt);
