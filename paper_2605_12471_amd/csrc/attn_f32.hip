@@ -78,8 +78,8 @@ __device__ __forceinline__ floatx16 mfma16(const uintx4& a, const uintx4& b, con
 
 // NW wavefronts per workgroup, one workgroup per CU at D = 128 (96 KB of LDS).  Eight (two per SIMD) share the split of a
 // tile among twice the rows and have one wavefront's vector work behind the other's matrix work; four are for chunks that
-// leave half of the eight without rows.  WIN: the sink + sliding-window step.  FUSED (four wavefronts): the kernel appends the
-// chunk's rows itself.
+// leave half of the eight without rows.  WIN: the sink + sliding-window step.  FUSED (four wavefronts): for short pieces, and the
+// kernel may append the chunk's rows itself.
 template <int D, bool WIN, int NW, bool FUSED>
 __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p) {
   constexpr int NT = NW * 64;
@@ -634,12 +634,15 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_f32_kernel(AttnParams p)
   }
 }
 
+// Rows that the append kernel has appended (rotary embedding) take the instance of short pieces for the shortest only: its first values
+// come with the first keys, its loop is slower.  Measured, that / the other instance, rotary embedding, 4 tokens, 32 heads on 8: 1 tile 15.2 /
+// 15.6 us, 2 21.9 / 22.2, 3 31.5 / 31.7, 6 51.8 / 51.7, 9 73.1 / 72.4; 64 wide, 64 tokens, 8 heads on 2: 1 tile 11.7 / 11.8, 2 15.8 / 15.7.
 template <int D, bool WIN>
 static void launch_f32(const AttnParams& p, int waves_per_wg, hipStream_t s) {
   const dim3 grid(padded_grid(p.n_wgs));
   if (waves_per_wg == 8)
     hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 8, false>), grid, dim3(512), 0, s, p);
-  else if (p.k_new)
+  else if (p.k_new || p.tiles_per_split <= (D == 64 ? 1 : 3))
     hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 4, true>), grid, dim3(256), 0, s, p);
   else
     hipLaunchKernelGGL((attn_f32_kernel<D, WIN, 4, false>), grid, dim3(256), 0, s, p);
