@@ -205,7 +205,9 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // fp32, a grid of more than a round whose empty workgroups are to make room for the rest: they are slots taken for a while, and not
       // where the rest needs them (measured, with work for less than 0.8 of the slots 0 to 5 % longer, for 0.9 15 %, for all 25 %, up
       // to a second round: 506 tokens on 1131 keys, 8 heads on 2, 44 us in one round, 62 with 288 workgroups of which 255 have work)
-      if (fp32 && (double)w > slots && busy < slots) t *= 1.0 + 1.5 * std::max(0.0, busy / slots - 0.8);
+      // -- and bf16's two-unit kernel with 64-wide heads (4045 tokens on 189 keys, 4 heads on 1: 31 us in 320 workgroups, 45 in 448 of
+      // which 256 have work; 128 wide it lets others in sooner, 3835 tokens on 425 keys, 8 on 2, 360 of which 256 have work 57, 63 with one unit)
+      if ((fp32 || (f.head_dim == 64 && upw == 2)) && (double)w > slots && busy < slots) t *= 1.0 + 1.5 * std::max(0.0, busy / slots - 0.8);
       // few rows: the blocks of an odd number of tiles do not go round the four wavefronts.  (Over 560 shapes on as many layers as
       // keep the caches out of the chip's own, the choice is 0.8 % above the best with this and 0.9 % without the second
       // term.  A step's two launches follow each other in steps of 0.8 us, which is the scatter: one token on 4187 keys, 2 / 3 / 4 / 5 tiles

@@ -81,3 +81,10 @@ def test_few_rows_are_split_where_the_merge_is_worth_it(hq, hkv, d, n, prev):
 def test_heavy_and_light_workgroups_share_cus_only_if_dealt_in_turn(hq, hkv, d, n, prev, units):
     plan = _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev)
     assert plan.units_per_wave == units and plan.pair_order == (1 if units == 1 else 0)
+
+
+@pytest.mark.parametrize("n,prev", [(4045, 189), (4045, 300)])
+def test_64_wide_two_unit_grids_do_not_count_on_empty_workgroups_beyond_a_round(n, prev):
+    """31 to 36 us; 45 with seven pieces of two units a wavefront, 448 workgroups of which 256 have work."""
+    plan = _plan(kv.KVFOLD_BF16, 4, 1, 64, n, prev)
+    assert not (plan.units_per_wave == 2 and plan.n_workgroups > 256 * 5 // 4)
