@@ -240,9 +240,9 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_SPLITS         number of prefix splits of the attention kernel; 0 = automatic.
  *                              Clamped to what the split workspace and the key range allow.
  *   KVFOLD_TUNE_UNITS_PER_WAVE 32-row query blocks owned by one wavefront of the bf16 kernel:
- *                              1 or 2; 0 = automatic, which also gives bf16 steps without a window of at most 32
- *                              (token, query head) rows per KV head a kernel of their own: any other value takes the
- *                              general kernel for these too.  fp32 kernel (always one block per wavefront): 1 or 2 for
+ *                              1 or 2; 0 = automatic, which also gives bf16 steps of few rows (without a window at most
+ *                              32 (token, query head) rows per KV head; more, and windows, where that is faster) a kernel
+ *                              of their own: any other value takes the general kernel for these too.  fp32 kernel (always one block per wavefront): 1 or 2 for
  *                              workgroups of four or eight wavefronts.
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
@@ -284,8 +284,8 @@ int kvfold_cache_plan(const kvfold_cache_t* cache, int32_t n_tokens, int64_t len
 typedef struct {
   int32_t n_workgroups;    /* workgroups of the attention kernel (fp32: of four or eight wavefronts)     */
   int32_t n_splits;        /* pieces the key range is cut into (> 1: a merge kernel follows)            */
-  int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32, and bf16 steps of at */
-                           /* most 32 rows per KV head, which have a kernel of their own: 1)            */
+  int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32, and bf16 steps of few */
+                           /* rows, whose kernel has workgroups of one such block: 1)                   */
   int32_t tiles_per_split; /* 64-key tiles per piece                                                    */
   int32_t fused_append;    /* 1: the bf16 attention kernel appends the chunk's rows itself              */
                            /* (kvfold_step_ex); 0 for fp32, where it may do so too (see the knob)         */

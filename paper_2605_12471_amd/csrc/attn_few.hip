@@ -1,22 +1,33 @@
-// Chunk-prefix attention for few rows: steps whose rows of a KV head fit one unit (C G <= 32: decoding, one token or a few
-// at a time), bf16, every key visible up to the row's own position.  The arithmetic and its rounding points are the general
-// bf16 kernel's (attn_bf16.hip): queries scaled by scale * log2(e) and rounded once more, P = 2^(S - m) rounded to bf16 for
-// P V, row sums in fp32 from the unrounded P, the reference m stale by at most 2^16.
+// Chunk-prefix attention of small steps, bf16: a workgroup owns one unit (32 packed rows of a KV head) and deals the keys of its
+// piece to its wavefronts.  The arithmetic and its rounding points are the general bf16 kernel's (attn_bf16.hip): queries scaled by
+// scale * log2(e) and rounded once more, P = 2^(S - m) rounded to bf16 for P V, row sums in fp32 from the unrounded P, the reference
+// m stale by at most 2^16.
 //
-// Such a step reads every key once and computes next to nothing: it is bound by memory when the cache is long and by what a
-// launch does once when it is short.  The general kernel gives the unit to one wavefront of four, behind a software pipeline
-// whose start and code cost more than a short step's work; here
-//  * the keys of a workgroup's piece are dealt to its four wavefronts in blocks of 32, and each runs alone: its K and V block
-//    come into LDS of its own (16 KB at D = 128, two workgroups per CU), so there is no barrier until the four results are
-//    merged through LDS;
+// Two kinds of step are for it.  Few rows (C G <= 32: decoding, one token or a few at a time, every key visible up to the row's own
+// position) read every key once and compute next to nothing: they are bound by memory when the cache is long and by what a launch does
+// once when it is short.  A few units per KV head on not too many keys, or under a window, are bound by the chain of a wavefront: the
+// general kernel walks a piece tile by tile with its four wavefronts side by side on four units, behind a software pipeline whose start
+// and code cost more than a short step's work, and needs a split and its merge to fill the chip.  Here
+//  * the keys of a workgroup's piece are dealt to its four or eight wavefronts in blocks of 32, and each runs alone: its K and V block
+//    come into LDS of its own (16 KB at D = 128; 128 KB a CU with two workgroups of four or one of eight), so there is no barrier
+//    until the results are merged through LDS;
 //  * the next K block is fetched as soon as S^T is formed, the next V block after O^T: eight wavefronts per CU, each with up
 //    to 16 KB in flight, are more than memory can deliver;
 //  * the loop is not unrolled or pipelined: code that runs once is fetched at about 3 bytes per ns.
+// The price: every unit brings its own copy of each K and V block into LDS, 16 KB where a general workgroup shares them among
+// four or eight units.  Eight blocks of 128-wide rows take a CU 1.45 us, what LDS needs for them (1024 cycles of fragment reads for K
+// and V each, 2048 for the copies that come in), so grids of more than two workgroups per CU and long key ranges stay with the
+// general kernel (choose_plan()).
 // One token, 32 heads on 8, D = 128, whole step, general kernel -> this one: 1K keys 12.5 -> 11.8 us (unsplit, one launch
 // instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
 // read gets 5.8 to 6.2).  With the start in 32-bit arithmetic, the faster merge and pieces of even numbers of tiles: 1K 9.4 us, 4K
 // 10.5, 8K 13.0, 128K 93.5.  At 4K keys that is two dependent launches, 7.6 and 3.0 us, of which the rows themselves would
-// take 3.
+// take 3.  Several units, general kernel -> eight wavefronts: 128 tokens on 1000 keys 18.9 -> 12.4 us, 256 on 300 15.9 -> 11.0, 256 on
+// 2000 26.9 -> 19.4; window 4 + 1020, 256 tokens 18.9 -> 12.5; four wavefronts, 16 tokens on 4187 keys 15.9 -> 14.1.  Inside the
+// kernel, the window step, 12.6 us: 1.6 to the first block, 7.8 for the five or six blocks of a wavefront, 1 until the last is
+// through, 2 for the results through LDS.
+// (The last workgroup of a unit to merge its pieces, partial results past the L2 caches by relaxed device-scope accesses of eight
+// bytes: 64 wide, one token on 1000 keys 7.3 -> 6.3 us, but 4187 keys 8.5 -> 8.4, 128 wide 10.5 -> 11.8, and 4 tokens 11.4 -> 15.8.)
 #include "append_rows.h"
 #include "kvfold_internal.h"
 #include "wave_ops.h"
@@ -33,16 +44,17 @@ typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(2))) float floatx2;
 
-template <int D>
+template <int D, int NW>
 constexpr int few_lds_bytes() {
-  const int rings = 4 * 2 * 32 * D * 2, results = 4 * kRowsPerUnit * (D * 4 + 16) + 4 * kRowsPerUnit * 8;
+  const int rings = NW * 2 * 32 * D * 2, results = NW * kRowsPerUnit * (D * 4 + 16) + NW * kRowsPerUnit * 8;
   return rings > results ? rings : results;
 }
 
-template <int D>
-__global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
+template <int D, int NW, bool WIN, bool MULTI>
+__global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned lds0 = (unsigned)(uintptr_t)((unsigned char __attribute__((address_space(3)))*)smem);
+  constexpr int NT = NW * 64;
   constexpr int CH = D / 8, ROWB = D * 2, KS = D / 16, DB = D / 32;
   constexpr int BLOCKB = 32 * ROWB;         // a K or V block
   constexpr int RPS = 64 / CH;              // rows of a 1 KiB copy
@@ -57,25 +69,30 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   const int lid = logical_workgroup(blockIdx.x, gridDim.x, p);
   if (lid >= p.n_wgs) return;
   const int g = (int)quot((unsigned)lid, p.by_wgs_per_kvh);
-  const int split = lid - g * p.n_splits;   // one workgroup per KV head and piece
+  const int rem = lid - g * (MULTI ? p.wgs_per_head * p.n_splits : p.n_splits);  // one workgroup per KV head, piece and unit
+  const int split = MULTI ? (int)quot((unsigned)rem, p.by_wgs_per_head) : rem;
+  const int u = MULTI ? p.wgs_per_head - 1 - (rem - split * p.wgs_per_head) : 0;  // late units, which see more keys, first
 
   const int tid = threadIdx.x, l = tid & 63, hi = l >> 5, m = l & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int C = p.n_tokens, Hq = p.n_q_heads, G = p.group;
-  const int rows = C * G;                   // packed rows: row j is token j / G, head j % G of the group
-  const int row = m < rows ? m : rows - 1;
+  const int n_packed = C * G, row0 = u * kRowsPerUnit;  // the KV head's packed rows: row j is token j / G, head j % G of the group
+  const int rows = !MULTI || n_packed - row0 < kRowsPerUnit ? n_packed - row0 : kRowsPerUnit;
+  const int row = row0 + (m < rows ? m : rows - 1);
   const int tok = (int)quot((unsigned)row, p.by_group), head = g * G + row - tok * G;
   const int my_vis = (int)p.len_prev + tok + 1;
+  RowRange rr = {0, C - 1};
+  if (MULTI) rr = workgroup_rows(u, 1, p.units_per_head, p.by_group, C);
+  const int vis_first = (int)p.len_prev + rr.row_lo + 1, vis_last = (int)p.len_prev + rr.row_hi + 1;
+  const int lb_last = WIN ? vis_last - p.window : 0;  // the largest of the rows' first keys inside the window
 
-  TileMap tm;
-  tm.ns_t = 0;
-  tm.skip = 0;
-  const unsigned len_after = (unsigned)p.len_prev + (unsigned)C;
-  tm.ntiles = (int)((len_after + kTileKeys - 1) / kTileKeys);
+  const TileMap tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, WIN ? p.n_sink : 0, WIN ? p.window : 0);
   const bool fused = p.k_new != nullptr;
   const KeyRange kr = key_range(tm, split, p.tiles_per_split, p.len_prev, C, fused);
-  const int b_all = (int)((len_after + 31) / 32);
-  const int b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;  // blocks of 32 keys
+  // Blocks of 32 keys of the logical tiles, and the first key of one; the last block of the last tile may lie beyond every row.
+  auto first_key = [&](int b) __attribute__((always_inline)) -> int { return b * 32 + (WIN && (b >> 1) >= tm.ns_t ? tm.skip * kTileKeys : 0); };
+  const int b_all = MULTI ? 2 * tm.ntiles - (first_key(2 * tm.ntiles - 1) >= vis_last ? 1 : 0) : (vis_last + 31) / 32;
+  const int b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
 
   const unsigned head_bytes = (unsigned)p.capacity * (unsigned)ROWB;  // (below 2^32, as the host checks)
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k_cache) + (uint64_t)(unsigned)g * head_bytes;
@@ -84,45 +101,50 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   const unsigned char* knew = reinterpret_cast<const unsigned char*>(p.k_new) + (unsigned)g * (unsigned)ROWB;
   const unsigned char* vnew = reinterpret_cast<const unsigned char*>(p.v_new) + (unsigned)g * (unsigned)ROWB;
 
-  // Blocks of cache rows that all exist are plain; else each row comes from the cache or the chunk, or is redirected to the
-  // piece's last row (and masked).
+  // Blocks whose rows all exist and lie on one side of the old cache's end (one unit: before it) are plain; else each row comes from the cache or the
+  // chunk, or is redirected to the piece's last row (and masked).
   auto plain = [&](int b) __attribute__((always_inline)) -> bool {
-    const unsigned last = (unsigned)(b * 32 + 31);
-    return last <= kr.row_lim && last < kr.chunk_row0;
+    const unsigned first = (unsigned)first_key(b), last = first + 31;
+    return last <= kr.row_lim && (last < kr.chunk_row0 || (MULTI && first >= kr.chunk_row0));
   };
   const unsigned my_lds = lds0 + (unsigned)(w * 2 * BLOCKB);
   const int lrow = l / CH;  // + i * RPS for copy i
   auto fetch = [&](bool is_v, int b) __attribute__((always_inline)) {
     const unsigned lds = my_lds + (is_v ? BLOCKB : 0);
-    const unsigned char* base = is_v ? vbase : kbase;
     const unsigned chunk = is_v ? (unsigned)((l % CH) ^ ((lrow & 3) * VSW)) : (unsigned)((l % CH) ^ (lrow % KSW));
+    const int key0 = first_key(b);
     if (__builtin_expect(plain(b), 1)) {
-      const unsigned off = (unsigned)(b * 32 + lrow) * ROWB;
+      const bool nw = MULTI && (unsigned)key0 >= kr.chunk_row0;  // rows of the chunk as handed in (fused append)
+      const unsigned stride = nw ? new_stride : (unsigned)ROWB;
+      const unsigned char* base = (nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase)) + (uint64_t)((unsigned)key0 - (nw ? kr.chunk_row0 : 0u)) * stride;
+      unsigned off = (unsigned)lrow * stride;
 #pragma unroll
-      for (int i = 0; i < SLABS; ++i)
-        dma16(base, off + (unsigned)(i * RPS * ROWB) + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
+      for (int i = 0; i < SLABS; ++i) {
+        dma16(base, off + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
+        off += (unsigned)RPS * stride;
+      }
     } else {
 #pragma unroll 1
       for (int i = 0; i < SLABS; ++i) {
-        const DmaRow src = dma_row(kr, b >> 1, (b & 1) * 32 + lrow + i * RPS);
+        const DmaRow src = dma_row(kr, key0 / kTileKeys, key0 % kTileKeys + lrow + i * RPS);
         const unsigned c16 = (is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16;
         if (src.from_chunk)
           dma16(is_v ? vnew : knew, src.row * new_stride + c16, lds + (unsigned)(i * 1024));
         else
-          dma16(base, src.row * (unsigned)ROWB + c16, lds + (unsigned)(i * 1024));
+          dma16(is_v ? vbase : kbase, src.row * (unsigned)ROWB + c16, lds + (unsigned)(i * 1024));
       }
     }
   };
 
-  // The wavefront's blocks, every fourth of the piece's, in cyclic order from a place that differs from piece to piece and
+  // The wavefront's blocks, every NW-th of the piece's, in cyclic order from a place that differs from piece to piece and
   // head to head: pieces and heads lie powers of two apart, and workgroups in step would ask the same few memory channels
   // for their rows.
-  const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (int)((unsigned)(b_end - b_first + 3) / 4u) : 0;
-  int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
-  // A chunk whose rows need work on their way (append_rows.h): this workgroup appends those it is going to read, ahead of any
-  // block that holds some.
+  const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (int)((unsigned)(b_end - b_first + NW - 1) / (unsigned)NW) : 0;
+  int b = b_first + NW * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
+  // A chunk whose rows need work on their way (append_rows.h): this workgroup, the only one of its piece, appends those it is going
+  // to read, ahead of any block that holds some.
   int work_r0 = 0, work_r1 = 0;
-  if (__builtin_expect(p.work_k && kr.t_begin < kr.t_end, 0)) {
+  if (!MULTI && __builtin_expect(p.work_k && kr.t_begin < kr.t_end, 0)) {
     work_r0 = kr.t_begin * kTileKeys - (int)p.len_prev;
     if (work_r0 < 0) work_r0 = 0;
     work_r1 = (int)kr.row_lim + 1 - (int)p.len_prev;
@@ -160,7 +182,7 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
       for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * p.scale_log2e);
   }
 
-  if (__builtin_expect(work_r1 > work_r0, 0)) {
+  if (!MULTI && __builtin_expect(work_r1 > work_r0, 0)) {
     append_work_rows<D>(reinterpret_cast<const unsigned char*>(p.work_k) + g * ROWB, reinterpret_cast<const unsigned char*>(p.work_v) + g * ROWB, new_stride,
                         const_cast<unsigned char*>(kbase) + (uint64_t)p.len_prev * ROWB, const_cast<unsigned char*>(vbase) + (uint64_t)p.len_prev * ROWB,
                         p.rope_cos, p.rope_sin, p.work_qmax, work_r0, work_r1, tid);
@@ -171,17 +193,37 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     }
   }
 
-  // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes per thread and turn
-  if (fused) {
-    const int r0 = split * p.copy_rows, r1 = r0 + p.copy_rows < C ? r0 + p.copy_rows : C;
-    const int nvec = (r1 > r0 ? r1 - r0 : 0) * CH;
-    for (int i = tid; i < 2 * nvec; i += 256) {
-      const bool is_v = i >= nvec;
-      const int e = is_v ? i - nvec : i, r = r0 + e / CH, c = e % CH;
-      const uintx4 x = *reinterpret_cast<const uintx4*>((is_v ? vnew : knew) + (int64_t)r * new_stride + c * 16);
-      __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(const_cast<unsigned char*>(is_v ? vbase : kbase) + (p.len_prev + r) * ROWB + c * 16));
+  // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes of a K row and of the V row per thread and turn, loaded
+  // here and stored behind the results.  (One unit per KV head: at most 32 rows, all loaded here, so that the output may lie on
+  // them.  Stored here, 16 layers of one token on 4K keys take 170.6 us, not 168.7: the first tiles wait for these rows as well.)
+  constexpr int kCopyRows = NT / CH, kCopyTurns = kCopyRows >= kRowsPerUnit ? 1 : kRowsPerUnit / kCopyRows;
+  const int copy_r0 = fused ? rem * p.copy_rows : 0;
+  const int copy_r1 = fused ? (copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C) : 0;
+  uintx4 copy_k[kCopyTurns] = {}, copy_v[kCopyTurns] = {};
+  auto copy_load = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kCopyTurns; ++i) {
+      const int r = r0 + i * kCopyRows + tid / CH;
+      if (r < copy_r1) {
+        const unsigned off = (unsigned)r * new_stride + (unsigned)(tid % CH) * 16u;
+        copy_k[i] = *reinterpret_cast<const uintx4*>(knew + off);
+        copy_v[i] = *reinterpret_cast<const uintx4*>(vnew + off);
+      }
     }
-  }
+  };
+  auto copy_store = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kCopyTurns; ++i) {
+      const int r = r0 + i * kCopyRows + tid / CH;
+      if (r < copy_r1) {
+        const unsigned off = (unsigned)((int)p.len_prev + r) * (unsigned)ROWB + (unsigned)(tid % CH) * 16u;
+        __builtin_nontemporal_store(copy_k[i], reinterpret_cast<uintx4*>(const_cast<unsigned char*>(kbase) + off));
+        __builtin_nontemporal_store(copy_v[i], reinterpret_cast<uintx4*>(const_cast<unsigned char*>(vbase) + off));
+      }
+    }
+  };
+
+  copy_load(copy_r0);
 
   // ---- LDS read offsets (general kernel's layouts): K fragment ks, row m, chunk 2 ks + hi; V^T by the transpose read, lane i
   // of a 16-lane group supplies row i / 4 of a 4-row group and 4 columns
@@ -204,7 +246,7 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
 
 #pragma unroll 1
   for (int i = 0; i < n_blocks; ++i) {
-    const int nb = b + 4 < b_end ? b + 4 : b_first;
+    const int nb = b + NW < b_end ? b + NW : b_first;
     const bool more = i + 1 < n_blocks;
     // copies complete in order; a block that is not plain may have taken more of them than SLABS
     if (plain(b))
@@ -222,12 +264,16 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     asm volatile("" : "+v"(s)::"memory");  // every read of the K block has returned
     if (more) fetch(false, nb);
 
-    const int key0 = b * 32;
-    if (key0 + 32 > (int)p.len_prev + 1) {  // wave-uniform: some row does not see the whole block
+    const int key0 = first_key(b);
+    const bool left = WIN && key0 < lb_last && key0 + 32 > p.n_sink;  // keys between the sinks and the window
+    if (key0 + 32 > vis_first || left) {  // wave-uniform: some row does not see the whole block
       const int rel = my_vis - key0 - 4 * hi;
+      const int rel_lb = WIN ? rel - p.window : -1, rel_sink = WIN ? p.n_sink - key0 - 4 * hi : 0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (8 * (r >> 2) + (r & 3) >= rel) s[r] = -INFINITY;
+      for (int r = 0; r < 16; ++r) {
+        const int kk = 8 * (r >> 2) + (r & 3);
+        if (kk >= rel || (WIN && kk < rel_lb && kk >= rel_sink)) s[r] = -INFINITY;
+      }
     }
     float mx = s[0];
 #pragma unroll
@@ -278,11 +324,11 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
     b = nb;
   }
 
-  // ---- the four results meet in LDS: [wavefront][row][D] and [wavefront][row] (m, l)
-  wait_vm<0>();
+  // ---- the wavefronts' results meet in LDS: [wavefront][row][D] and [wavefront][row] (m, l)
+  wait_vm<0>();  // (the chunk's rows are used up before the output may take their place)
   __syncthreads();
   constexpr int OROW = D * 4 + 16;
-  const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROW), mlbase = lds0 + (unsigned)(4 * kRowsPerUnit * OROW);
+  const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROW), mlbase = lds0 + (unsigned)(NW * kRowsPerUnit * OROW);
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -300,25 +346,25 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
   const int c = tid % V;
   const int64_t n_rows = (int64_t)C * Hq;
 #pragma unroll 1
-  for (int r = tid / V; r < rows; r += 256 / V) {
-    floatx2 ml[4];
+  for (int r = tid / V; r < rows; r += NT / V) {
+    floatx2 ml[NW];
     float M = -INFINITY;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) {
+    for (int ww = 0; ww < NW; ++ww) {
       ml[ww] = *LDS_PTR(const floatx2, mlbase + (unsigned)((ww * kRowsPerUnit + r) * 8));
       M = fmaxf(M, ml[ww].x);
     }
     float L = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) {
+    for (int ww = 0; ww < NW; ++ww) {
       const floatx4 x = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
       const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);  // (0: it saw no visible key)
       L += f * ml[ww].y;
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] += f * x[e];
     }
-    const int t = (int)quot((unsigned)r, p.by_group), h = g * G + r - t * G;
+    const int t = (int)quot((unsigned)(row0 + r), p.by_group), h = g * G + row0 + r - t * G;
     const int64_t at = (int64_t)t * Hq + h;
     if (p.n_splits == 1) {
       const float inv = 1.f / L;
@@ -332,28 +378,55 @@ __global__ void __launch_bounds__(256, 2) attn_few_kernel(AttnParams p) {
       if (c == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + at) * 2) = make_float2(M, L);
     }
   }
+
+  copy_store(copy_r0);
+  if (MULTI)
+    for (int r0 = copy_r0 + kCopyTurns * kCopyRows; r0 < copy_r1; r0 += kCopyTurns * kCopyRows) {
+      copy_load(r0);
+      copy_store(r0);
+    }
 }
 
-template <int D>
+template <int D, int NW, bool WIN, bool MULTI>
 static hipError_t prepare_few_one() {
   // once per device (idempotent; a benign race at worst sets it twice)
   static bool attr_done[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_done[dev]) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D>());
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D, NW, WIN, MULTI>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D, NW>());
   if (e == hipSuccess) attr_done[dev] = true;
   return e;
 }
-hipError_t prepare_attn_few(int head_dim) { return head_dim == 128 ? prepare_few_one<128>() : prepare_few_one<64>(); }
+template <int D>
+static hipError_t prepare_few() {
+  hipError_t e = prepare_few_one<D, 4, false, false>();
+  if (e == hipSuccess) e = prepare_few_one<D, 4, false, true>();
+  if (e == hipSuccess) e = prepare_few_one<D, 8, false, true>();
+  if (e == hipSuccess) e = prepare_few_one<D, 8, true, true>();
+  return e;
+}
+hipError_t prepare_attn_few(int head_dim) { return head_dim == 128 ? prepare_few<128>() : prepare_few<64>(); }
 
-hipError_t launch_attn_few(const AttnParams& p, int head_dim, hipStream_t s) {
-  const dim3 grid(padded_grid(p.n_wgs)), block(256);
+template <int D>
+static void launch_few(const AttnParams& p, int key_waves, hipStream_t s) {
+  const dim3 grid(padded_grid(p.n_wgs));
+  if (key_waves == 4 && p.units_per_head == 1)
+    hipLaunchKernelGGL((attn_few_kernel<D, 4, false, false>), grid, dim3(256), (few_lds_bytes<D, 4>()), s, p);
+  else if (key_waves == 4)
+    hipLaunchKernelGGL((attn_few_kernel<D, 4, false, true>), grid, dim3(256), (few_lds_bytes<D, 4>()), s, p);
+  else if (p.window > 0)
+    hipLaunchKernelGGL((attn_few_kernel<D, 8, true, true>), grid, dim3(512), (few_lds_bytes<D, 8>()), s, p);
+  else
+    hipLaunchKernelGGL((attn_few_kernel<D, 8, false, true>), grid, dim3(512), (few_lds_bytes<D, 8>()), s, p);
+}
+
+hipError_t launch_attn_few(const AttnParams& p, int head_dim, int key_waves, hipStream_t s) {
   if (head_dim == 128)
-    hipLaunchKernelGGL(attn_few_kernel<128>, grid, block, few_lds_bytes<128>(), s, p);
+    launch_few<128>(p, key_waves, s);
   else if (head_dim == 64)
-    hipLaunchKernelGGL(attn_few_kernel<64>, grid, block, few_lds_bytes<64>(), s, p);
+    launch_few<64>(p, key_waves, s);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

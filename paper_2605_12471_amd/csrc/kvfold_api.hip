@@ -308,8 +308,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   if (ev && own_append) (void)hipEventRecord(ev[1], s);
   if (f.dtype != KVFOLD_BF16)
     e = launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
-  else if (pl.few_rows)
-    e = launch_attn_few(at, f.head_dim, s);
+  else if (pl.key_waves)
+    e = launch_attn_few(at, f.head_dim, pl.key_waves, s);
   else
     e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s);
   if (e != hipSuccess) return hip_fail(e);

@@ -109,8 +109,8 @@ hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int units_per_wav
 // Sets the LDS size attribute of every bf16 attention kernel variant of this head dimension on the current
 // device (once per device; launches then have nothing left that could fail for a valid configuration).
 hipError_t prepare_attn_bf16(int head_dim);
-// The kernel for steps of at most 32 packed rows per KV head, no window; prepare as above.
-hipError_t launch_attn_few(const AttnParams& p, int head_dim, hipStream_t s);
+// The kernel whose workgroups deal the keys of one unit to key_waves wavefronts (4, or 8, which a window asks for); prepare as above.
+hipError_t launch_attn_few(const AttnParams& p, int head_dim, int key_waves, hipStream_t s);
 hipError_t prepare_attn_few(int head_dim);
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, int waves_per_wg, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);

@@ -104,10 +104,52 @@ bool evenly_dealt(int n_kv_heads, int wgs_per_kvh) {
   return n_kv_heads % kNumXcd == 0 || (n_kv_heads < kNumXcd && kNumXcd % n_kv_heads == 0 && wgs_per_kvh % (kNumXcd / n_kv_heads) == 0);
 }
 
+Plan finish_plan(Plan pl, int64_t s, int64_t s_max, int ntiles, int64_t base) {
+  if (s > s_max) s = s_max;
+  pl.tiles_per_split = (int)((ntiles + s - 1) / s);
+  if (pl.tiles_per_split < 1) pl.tiles_per_split = 1;
+  pl.n_splits = (ntiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
+  if (pl.n_splits < 1) pl.n_splits = 1;
+  pl.n_wgs = (int)(base * pl.n_splits);
+  return pl;
+}
+
+// The split count of the kernel that deals the keys of one unit to its wavefronts, for more than one unit per KV head or a window, and what
+// the step takes, in us: a wavefront's chain of 32-key blocks, every block of a CU through its LDS, the rows from memory, further rounds
+// of workgroups (which overlap with the one before but for their start), and the merge.  Fitted to 7951 measured steps (captured
+// graphs): 568 shapes (1 to 64 heads, 1 to 1500 tokens on 16 to 127K keys, windows among them), both wavefront counts, every split count;
+// the choice is 1.7 % above the best of these on average and more than 10 % above it in 16.
+void plan_key_waves(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64_t s_max, int waves, double kv_rows,
+                    double seen, int64_t& s, double& est_us) {
+  struct Cost {
+    double start_end, block, cu_block, bytes_per_us, round, merge, merge_bytes_per_us;
+  };
+  const bool wide = c.cfg.head_dim == 128;
+  const Cost k = wide ? (waves == 4 ? Cost{6.12, 0.348, 0.141, 10.7e6, 1.68, 1.42, 2.71e6} : Cost{6.29, 0.363, 0.144, 9.3e6, 3.95, 2.17, 2.85e6})
+                      : (waves == 4 ? Cost{4.42, 0.443, 0.064, 11.4e6, 1.09, 2.06, 2.62e6} : Cost{4.89, 0.186, 0.080, 9.0e6, 2.04, 2.48, 2.63e6});
+  const double slots = (double)c.n_cu * (8 / waves) * (wide ? 1 : 2);  // workgroups that LDS has room for
+  const double kv_us = 4.0 * c.cfg.n_kv_heads * c.cfg.head_dim * kv_rows / k.bytes_per_us;
+  est_us = 1e30;
+  for (int64_t cand = 1; cand <= s_max; ++cand) {
+    const int64_t tps = (ntiles + cand - 1) / cand;
+    if ((ntiles + tps - 1) / tps != cand) continue;
+    const double w = (double)(base * cand);
+    double t = k.start_end + (double)((2 * tps + waves - 1) / waves) * k.block + std::max(1.0, std::ceil(w / c.n_cu) * seen) * 2.0 * (double)tps * k.cu_block + kv_us +
+               (std::ceil(w / slots) - 1.0) * k.round;
+    if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
+    t = std::max(t, 4.0 + 2.65 * (cand > 1 ? 2 : 1)) + 0.1 * t;  // (as in plan_with())
+    if (t < est_us) {
+      est_us = t;
+      s = cand;
+    }
+    if (w > 2.0 * slots) break;
+  }
+}
+
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
 // estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
-               int waves = kUnitsPerWg, bool few_rows = false) {
+               int waves = kUnitsPerWg, int key_waves = 0) {
   const kvfold_config_t& f = c.cfg;
   const int G = f.n_q_heads / f.n_kv_heads;
   Plan pl;
@@ -116,16 +158,19 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.units_per_head = units_of_head(n_tokens, G);
   pl.units_per_wave = upw;
   pl.waves_per_wg = waves;
+  pl.key_waves = key_waves;
+  const bool few_rows = key_waves == 4 && pl.units_per_head == 1 && window <= 0;
   pl.few_rows = few_rows;
-  const int per_wg = waves * upw;
+  const int per_wg = key_waves > 0 ? 1 : waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
   // tiles of the longest key range of any workgroup (the kernels cut exactly this many into pieces)
   int ntiles = (int)((len_after + kTileKeys - 1) / kTileKeys);
   if (window > 0) {
     ntiles = 1;
-    for (int ug = 0; ug < pl.wgs_per_head; ++ug) {
-      const RowRange rr = workgroup_rows(ug, per_wg, pl.units_per_head, G, n_tokens);
+    const int step = key_waves > 0 ? kUnitsPerWg : per_wg;  // (workgroups of one unit: a bound from four units at a time, a quarter of the host work)
+    for (int ug = 0; ug * step < pl.units_per_head; ++ug) {
+      const RowRange rr = workgroup_rows(ug, step, pl.units_per_head, G, n_tokens);
       ntiles = std::max(ntiles, tile_map(len_after - n_tokens, rr.row_lo, rr.row_hi, n_sink, window).ntiles);
     }
   }
@@ -166,6 +211,11 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     // 80K keys, windows among them), both wavefront counts: 1.0 % above the best on average, more than 10 % in 40; the figures before,
     // fitted to 182 of these, 2.4 % and 100, and slower by up to 20 % than those of the kernel that did not append where a few
     // workgroups read many keys (64 tokens on 60K keys, 8 heads on 2: four wavefronts 124 us, eight 149).
+    if (key_waves > 0 && !few_rows) {
+      plan_key_waves(c, rows, base, ntiles, s_max, key_waves, window > 0 ? std::min((double)len_after, (double)ntiles * kTileKeys) : (double)len_after,
+                     window > 0 ? 1.0 : ((double)len_after - 0.5 * n_tokens) / (double)len_after, s, pl.est_us);
+      return finish_plan(pl, s, s_max, ntiles, base);
+    }
     const double with_rows = (double)pl.units_per_head / (double)((int64_t)pl.wgs_per_head * per_wg);  // share of the units
     const KernelCost k = kernel_cost(f.dtype, f.head_dim, upw, waves, few_rows, with_rows);
     const double la = (double)len_after, mean_keys = la - 0.5 * n_tokens;
@@ -238,13 +288,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     }
     pl.est_us = best;
   }
-  if (s > s_max) s = s_max;
-  pl.tiles_per_split = (int)((ntiles + s - 1) / s);
-  if (pl.tiles_per_split < 1) pl.tiles_per_split = 1;
-  pl.n_splits = (ntiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
-  if (pl.n_splits < 1) pl.n_splits = 1;
-  pl.n_wgs = (int)(base * pl.n_splits);
-  return pl;
+  return finish_plan(pl, s, s_max, ntiles, base);
 }
 
 Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, int64_t window) {
@@ -256,7 +300,7 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
   if (window <= 0 && units_of_head(n_tokens, f.n_q_heads / f.n_kv_heads) == 1)
-    return plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, true);
+    return plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, 4);
   Plan p1 = plan_with(c, n_tokens, len_after, 1, n_sink, window);
   // Prefix shorter than the chunk: the causal part makes late token blocks several times as long as early
   // ones.  If the one-unit-per-wavefront grid is resident at once (two workgroups per CU), pair heavy with
@@ -282,7 +326,20 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return p2;
   }
   if (pair && 4 * f.n_kv_heads <= kNumXcd) return p2;
-  return p1.est_us < p2.est_us * 1.1 ? p1 : p2;
+  Plan best = p1.est_us < p2.est_us * 1.1 ? p1 : p2;
+  // Few units on not too many keys: the chain of one wavefront through the general kernels' tiles is longer than the whole step where the
+  // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
+  // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all
+  // its keys for itself, so that full grids are not for it: up to two workgroups per CU.  Over 480 shapes with more than one unit or a
+  // window the steps take 0.88 of the time (0.84 on up to 30K keys), and 5 are 3 % or more slower (16 heads on 2, 64 wide, 15 tokens on 114K
+  // keys 1.24, on 66K 1.15).
+  if (c.tune_pair_units == 0 && (int64_t)p1.units_per_head * f.n_kv_heads <= 2 * (int64_t)c.n_cu)
+    for (int waves : {8, 4}) {
+      if (waves == 4 && window > 0) continue;
+      const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, waves);
+      if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : 0.95)) best = pk;
+    }
+  return best;
 }
 
 }  // namespace

@@ -97,9 +97,9 @@ static void walk_ring(Reader& rd, const TileMap& tm, const KeyRange& kr, int nv)
     }
 }
 
-// The few-rows kernel: wavefront w takes every fourth block of 32 keys, in cyclic order from a place of its own.  work: the
-// workgroup appends the rows of the chunk that its piece holds, after the first block's fetch where that needs none of them.
-static void walk_few(Reader& rd, const KeyRange& kr, int split, int g, bool work, std::vector<int>& appended) {
+// The few-rows kernel: each of its 4 or 8 wavefronts takes every 4th or 8th block of 32 keys, in cyclic order from a place of its own.
+// work: the workgroup appends the rows of the chunk that its piece holds, after the first block's fetch where that needs none of them.
+static void walk_few(Reader& rd, const TileMap& tm, const KeyRange& kr, int nw, int64_t nkeys, int split, int g, bool work, std::vector<int>& appended) {
   int work_r0 = 0, work_r1 = 0;
   if (work && kr.t_begin < kr.t_end) {
     work_r0 = kr.t_begin * kTileKeys - (int)rd.len_prev;
@@ -108,20 +108,22 @@ static void walk_few(Reader& rd, const KeyRange& kr, int split, int g, bool work
   }
   REQUIRE(work_r1 <= rd.n_tokens, "work on row %d of %d", work_r1 - 1, rd.n_tokens);
   for (int r = work_r0; r < work_r1; ++r) appended[(size_t)r]++;
-  const int b_all = (int)((rd.len_prev + rd.n_tokens + 31) / 32), b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
-  for (int w = 0; w < 4; ++w) {
-    const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + 3) / 4 : 0;
-    int b = b_first + 4 * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
+  auto first_key = [&](int b) { return b * 32 + ((b >> 1) >= tm.ns_t ? tm.skip * kTileKeys : 0); };
+  const int b_all = 2 * tm.ntiles - (first_key(2 * tm.ntiles - 1) >= nkeys ? 1 : 0), b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
+  for (int w = 0; w < nw; ++w) {
+    const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + nw - 1) / nw : 0;
+    int b = b_first + nw * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
     for (int i = 0; i < n_blocks; ++i) {
-      REQUIRE(b >= b_first && b < b_end && (b - b_first) % 4 == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_end, w);
+      REQUIRE(b >= b_first && b < b_end && (b - b_first) % nw == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_end, w);
       const bool ahead = i == 0 && (work_r1 <= work_r0 || b * 32 + 32 <= (int)rd.len_prev);  // fetched before the work
       rd.work_row0 = ahead ? 0 : rd.len_prev + work_r0;
       rd.work_row1 = ahead ? 0 : rd.len_prev + work_r1;
-      const unsigned last = (unsigned)(b * 32 + 31);
-      const bool plain = last <= kr.row_lim && last < kr.chunk_row0;
-      for (int row = 0; row < 32; ++row)
-        rd.read(plain ? DmaRow{false, (unsigned)(b * 32 + row)} : dma_row(kr, b >> 1, (b & 1) * 32 + row), (int64_t)b * 32 + row, true);
-      b = b + 4 < b_end ? b + 4 : b_first;
+      const unsigned first = (unsigned)first_key(b), last = first + 31;
+      const bool plain = last <= kr.row_lim && (last < kr.chunk_row0 || first >= kr.chunk_row0), nw_rows = first >= kr.chunk_row0;
+      for (unsigned row = 0; row < 32; ++row)
+        rd.read(plain ? DmaRow{nw_rows, first + row - (nw_rows ? kr.chunk_row0 : 0u)} : dma_row(kr, (int)first / kTileKeys, (int)first % kTileKeys + (int)row),
+                (int64_t)first + row, true);
+      b = b + nw < b_end ? b + nw : b_first;
     }
   }
 }
@@ -166,7 +168,7 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   REQUIRE(!(fused && work), "appended twice");
   REQUIRE(cfg.dtype != KVFOLD_BF16 || fused == fused_append_applies(pc, n_tokens, len_prev, rope), "what kvfold_plan_t reports");
   const int G = cfg.n_q_heads / cfg.n_kv_heads;
-  const int upw_wg = pl.waves_per_wg * pl.units_per_wave;
+  const int upw_wg = pl.key_waves ? 1 : pl.waves_per_wg * pl.units_per_wave;
   const int row_bytes = cfg.head_dim * elem_size(cfg.dtype);
   REQUIRE(pl.n_splits >= 1 && pl.n_splits <= kMaxSplits && pl.tiles_per_split >= 1, "plan");
   REQUIRE(pl.n_splits == 1 || (int64_t)pl.n_splits * n_tokens * cfg.n_q_heads <= pc.ws_rows, "workspace");
@@ -174,6 +176,9 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   if (window > 0) REQUIRE(!pl.pair_units && !pl.pair_order, "pairing under a window");
   REQUIRE(pl.waves_per_wg == kUnitsPerWg || (pl.waves_per_wg == 8 && cfg.dtype == KVFOLD_F32 && pl.units_per_wave == 1), "wavefronts");
   REQUIRE(!pl.few_rows || (cfg.dtype == KVFOLD_BF16 && window <= 0 && pl.units_per_head == 1 && pl.wgs_per_head == 1), "few rows");
+  REQUIRE(pl.key_waves == 0 || pl.key_waves == 8 || (pl.key_waves == 4 && window <= 0), "wavefronts that share a unit's keys");
+  REQUIRE(pl.key_waves == 0 || (cfg.dtype == KVFOLD_BF16 && pl.wgs_per_head == pl.units_per_head && !pl.pair_units && !pl.pair_order), "one unit a workgroup");
+  REQUIRE(!work || (pl.key_waves == 4 && pl.units_per_head == 1), "rows are worked on by the one workgroup of a piece");
   REQUIRE((int64_t)pl.wgs_per_head * upw_wg >= pl.units_per_head && (int64_t)pl.units_per_head * kRowsPerUnit >= (int64_t)n_tokens * G,
           "%d workgroups of %d units for %d tokens x %d heads", pl.wgs_per_head, upw_wg, n_tokens, G);
 
@@ -213,8 +218,8 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       Reader rd{cfg, n_tokens, len_prev, readable_cache, len_prev + rr.row_hi, row_bytes, fused, seen};
       if (cfg.dtype != KVFOLD_BF16)
         walk_halves(rd, tm, kr, len_prev + rr.row_hi + 1);
-      else if (pl.few_rows)
-        walk_few(rd, kr, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
+      else if (pl.key_waves)
+        walk_few(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
       else
         walk_ring(rd, tm, kr, pl.units_per_wave == 2 ? 3 : 2);
     }

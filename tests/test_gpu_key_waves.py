@@ -1,0 +1,59 @@
+"""bf16 steps whose workgroups deal the keys of one 32-row unit to their wavefronts, with more than one unit per KV head or under a
+window: every row against the oracle, with the launch plan's own choice, which is checked to be this kernel's."""
+import pytest
+
+import paper_2605_12471_amd as kv
+from paper_2605_12471_amd import binding
+from paper_2605_12471_amd import inputs as I
+from test_gpu_parity_small import H, _run_case  # noqa: F401  (H: the fixture)
+from test_gpu_window import _run_window_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _one_unit_workgroups(Hq, Hkv, d, chunks, window=None):
+    """Which of the steps have one workgroup per unit and piece (the general kernels' have four units or eight)."""
+    cfg = binding.make_config(1, Hq, Hkv, d, max(chunks), sum(chunks), kv.KVFOLD_BF16)
+    pos, got = 0, []
+    for n in chunks:
+        rc, pl = kv.kvfold_plan_for(cfg, 256, n, pos + n, *(window or (0, 0)))
+        assert rc == 0
+        units = -(-n * (Hq // Hkv) // 32)
+        got.append(pl.n_workgroups == Hkv * units * pl.n_splits and units > 1)
+        pos += n
+    return got
+
+
+# The old cache's end before, on and behind every edge of a 32-key block and a 64-key tile; units that fill and straddle tokens; the last
+# unit with one row to 32; pieces that end before the chunk, inside it and behind it; more chunk rows than a workgroup copies in a turn.
+@pytest.mark.parametrize("Hq,Hkv,d,chunks", [
+    (8, 2, 128, [33, 31, 32, 9, 23, 64, 65, 127, 40]),
+    (8, 2, 64, [33, 31, 32, 9, 23, 64, 65, 127, 40]),
+    (7, 1, 128, [37, 5, 64, 300, 41, 100]),
+    (28, 4, 128, [500, 37, 128, 30]),
+    (3, 3, 64, [65, 33, 97, 1000, 34]),
+    (40, 1, 128, [1, 2, 61, 3, 200]),
+    (32, 8, 128, [1100, 37, 100]),
+    (4, 1, 64, [1, 700, 257]),
+])
+def test_edges_of_blocks_units_and_the_chunk(H, oracle, Hq, Hkv, d, chunks):
+    cfg = I.FoldConfig("key_waves", 70, 1, Hq, Hkv, d, max(chunks), 0, "bf16")
+    assert sum(_one_unit_workgroups(Hq, Hkv, d, chunks)) >= len(chunks) // 2
+    _run_case(H, oracle, cfg, chunks)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_sink,window", [(4, 100), (0, 64), (4, 1), (70, 50), (0, 1), (33, 31), (4, 5000)])
+def test_windows(H, oracle, d, n_sink, window):
+    """Windows shorter than a block and longer than the cache, sinks across two tiles, one row to several units."""
+    chunks = [300, 1, 7, 40, 65, 96, 33]
+    cfg = I.FoldConfig("key_waves_win", 71, 1, 8, 2, d, max(chunks), 0, "bf16")
+    assert sum(_one_unit_workgroups(8, 2, d, chunks, (n_sink, window))) >= 3
+    _run_window_case(H, oracle, cfg, chunks, n_sink, window)
+
+
+@pytest.mark.parametrize("profile", sorted(I.LOGIT_PROFILES))
+def test_logit_jumps(H, oracle, profile):
+    chunks = [400, 40, 9, 70]
+    cfg = I.FoldConfig("key_waves_jump", 72, 1, 4, 1, 128, 400, 0, "bf16")
+    _run_case(H, oracle, cfg, chunks, profile=profile, check_lse=False)
