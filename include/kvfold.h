@@ -242,8 +242,9 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *   KVFOLD_TUNE_UNITS_PER_WAVE 32-row query blocks owned by one wavefront of the bf16 kernel:
  *                              1 or 2; 0 = automatic, which also gives bf16 steps of few rows (without a window at most
  *                              32 (token, query head) rows per KV head; more, and windows, where that is faster) a kernel
- *                              of their own: any other value takes the general kernel for these too.  fp32 kernel (always one block per wavefront): 1 or 2 for
- *                              workgroups of four or eight wavefronts.
+ *                              of their own: any other value takes the general kernel for these too.  fp32 (always one block per wavefront): 1 or 2 for
+ *                              the general kernel with workgroups of four or eight wavefronts; 0 = automatic, which also gives
+ *                              steps of few blocks a kernel of their own.
  *   KVFOLD_TUNE_PAIR_UNITS     two-unit kernel: each wavefront owns an early and a late row
  *                              block of the chunk (evens out the causal part); 0 = automatic (single
  *                              round of workgroups), 1 = never, 2 = always.
@@ -253,8 +254,8 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *                                rows (n_tokens * n_kv_heads * head_dim elements) take less than 2^32 bytes (it reads
  *                                the chunk's own rows from k_new / v_new, with 32-bit byte offsets), bf16: unless
  *                                out or lse of an unsplit step lies on these rows (out in their very place may, with
- *                                as many KV as query heads and at most 32 tokens); fp32: workgroups of four
- *                                wavefronts whose pieces of the key range have fewer than 20 tiles (head_dim 64: 12), and
+ *                                as many KV as query heads and at most 32 tokens); fp32: the kernel for
+ *                                few blocks, and workgroups of four wavefronts whose pieces of the key range have fewer than 20 tiles (head_dim 64: 12), and
  *                                rows apart from out, lse and the cache;
  *                              - one of the two is in play, in a bf16 step without a window of at most 32 (token,
  *                                query head) rows per KV head, with the round trip also of at most 4096 bytes of K rows per

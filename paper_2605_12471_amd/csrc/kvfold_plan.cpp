@@ -69,7 +69,7 @@ bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope
   // fp32: short pieces of four wavefronts.  A launch less (2.5 us) against 0.04 us a tile in the loop, 0.12 us 64 wide.  Measured, append
   // kernel / this, 64 tokens, 8 heads on 2: 9 tiles 77.3 / 76.0 us, 14 110.9 / 110.0, 20 144.2 / 144.5, 28 204.2 / 206.7; 64 wide, 7
   // tiles 40.6 / 39.5, 9 47.1 / 46.6, 14 66.1 / 66.6, 20 85.3 / 86.7.
-  if (f.dtype != KVFOLD_BF16 && (pl.waves_per_wg != 4 || pl.tiles_per_split >= (f.head_dim == 64 ? 12 : 20))) return false;
+  if (f.dtype != KVFOLD_BF16 && !pl.key_waves && (pl.waves_per_wg != 4 || pl.tiles_per_split >= (f.head_dim == 64 ? 12 : 20))) return false;
   if (rope || c.storage_bits || c.tune_fused_append == 1) return false;
   const int64_t chunk_bytes = (int64_t)n_tokens * f.n_kv_heads * f.head_dim * elem_size(f.dtype);
   return chunk_bytes < ((int64_t)1 << 32);
@@ -146,6 +146,34 @@ void plan_key_waves(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, in
   }
 }
 
+// The same for the fp32 kernel of that kind.  One workgroup per CU; what a wavefront's chain of blocks takes is for the most part what
+// a CU gets from memory, some 37 GB/s on its own.  Fitted to 2500 measured steps (captured graphs): 416 shapes (1 to 64 heads, 1 to 600
+// tokens on 0 to 65K keys, windows among them), every split count; the choice is 0.4 % above the best of these on average (64 wide
+// 0.7 %), more than 10 % above it in one.
+void plan_key_waves_f32(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64_t s_max, int waves, double kv_rows,
+                        double seen, int64_t& s, double& est_us) {
+  struct Cost {
+    double start_end, block, cu_block, full, bytes_per_us, round, merge, merge_bytes_per_us;
+  };
+  const Cost k = c.cfg.head_dim == 128 ? Cost{7.72, 3.19, 0.112, 0.04, 4.87e6, 3.73, 1.90, 2.46e6} : Cost{6.64, 0.463, 0.359, 0.12, 5.96e6, 3.57, 2.20, 3.34e6};
+  const double kv_us = 8.0 * c.cfg.n_kv_heads * c.cfg.head_dim * kv_rows / k.bytes_per_us;
+  est_us = 1e30;
+  for (int64_t cand = 1; cand <= s_max; ++cand) {
+    const int64_t tps = (ntiles + cand - 1) / cand;
+    if ((ntiles + tps - 1) / tps != cand) continue;
+    if (cand > 1 && base * cand > c.n_cu) break;
+    const double w = (double)(base * cand), rounds = std::max(1.0, std::ceil(w / c.n_cu)), passes = std::max(1.0, rounds * seen);
+    const double chain = passes * ((double)((2 * tps + waves - 1) / waves) * k.block + 2.0 * (double)tps * k.cu_block) * (1.0 + k.full * w / (rounds * c.n_cu));
+    double t = k.start_end + std::sqrt(std::sqrt(chain * chain * chain * chain + kv_us * kv_us * kv_us * kv_us)) + (rounds - 1.0) * k.round;
+    if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
+    t = std::max(t, 4.0 + 2.65 * (cand > 1 ? 2 : 1)) + 0.1 * t;  // (as in plan_with())
+    if (t < est_us) {
+      est_us = t;
+      s = cand;
+    }
+  }
+}
+
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
 // estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
@@ -159,7 +187,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.units_per_wave = upw;
   pl.waves_per_wg = waves;
   pl.key_waves = key_waves;
-  const bool few_rows = key_waves == 4 && pl.units_per_head == 1 && window <= 0;
+  const bool few_rows = f.dtype == KVFOLD_BF16 && key_waves == 4 && pl.units_per_head == 1 && window <= 0;
   pl.few_rows = few_rows;
   const int per_wg = key_waves > 0 ? 1 : waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
@@ -211,6 +239,11 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     // 80K keys, windows among them), both wavefront counts: 1.0 % above the best on average, more than 10 % in 40; the figures before,
     // fitted to 182 of these, 2.4 % and 100, and slower by up to 20 % than those of the kernel that did not append where a few
     // workgroups read many keys (64 tokens on 60K keys, 8 heads on 2: four wavefronts 124 us, eight 149).
+    if (key_waves > 0 && f.dtype != KVFOLD_BF16) {
+      plan_key_waves_f32(c, rows, base, ntiles, s_max, key_waves, window > 0 ? std::min((double)len_after, (double)ntiles * kTileKeys) : (double)len_after,
+                         window > 0 ? 1.0 : ((double)len_after - 0.5 * n_tokens) / (double)len_after, s, pl.est_us);
+      return finish_plan(pl, s, s_max, ntiles, base);
+    }
     if (key_waves > 0 && !few_rows) {
       plan_key_waves(c, rows, base, ntiles, s_max, key_waves, window > 0 ? std::min((double)len_after, (double)ntiles * kTileKeys) : (double)len_after,
                      window > 0 ? 1.0 : ((double)len_after - 0.5 * n_tokens) / (double)len_after, s, pl.est_us);
@@ -296,7 +329,17 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   if (f.dtype != KVFOLD_BF16) {
     const Plan w4 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 4), w8 = plan_with(c, n_tokens, len_after, 1, n_sink, window, 8);
     if (c.tune_units_per_wave) return c.tune_units_per_wave == 2 ? w8 : w4;
-    return c.tune_splits > 0 ? (w4.units_per_head <= 4 ? w4 : w8) : (w4.est_us <= w8.est_us ? w4 : w8);
+    if (c.tune_splits > 0) return w4.units_per_head <= 4 ? w4 : w8;
+    const Plan best = w4.est_us <= w8.est_us ? w4 : w8;
+    // Few units on not too many keys: the kernel that deals a unit's keys to its wavefronts is done in 0.81 of the time (64 wide 0.83) over
+    // the 416 shapes, and 5 % slower in one of them (32 heads on 8, 64 wide, 311 tokens, window 4 + 544: 32.6 / 34.3 us).  One token, 32
+    // heads on 8: 300 keys 15.5 -> 12.5 us, 4187 28 -> 19.9, 30K 92 -> 58; 128 tokens, 4 heads on 1, 64 wide, no keys 12.0 -> 7.5.  Every
+    // unit splits the keys into terms anew, so that the gain is gone where several units read long ranges (128 wide, 8 heads on 2, 37 tokens =
+    // five units on 30K keys 70 / 73 us) and needs a margin where there are many of them.
+    const int64_t units = w4.units_per_head;
+    if (units * f.n_kv_heads > 2 * (int64_t)c.n_cu || (f.head_dim == 128 && units > 4 && units * len_after > 144 * 1024)) return best;
+    const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, f.head_dim == 64 ? 8 : 4);
+    return pk.est_us < best.est_us * (units > 16 ? 0.9 : 0.95) ? pk : best;
   }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
   if (window <= 0 && units_of_head(n_tokens, f.n_q_heads / f.n_kv_heads) == 1)

@@ -153,6 +153,29 @@ static void walk_halves(Reader& rd, const TileMap& tm, const KeyRange& kr, int64
     if (h + 1 < h_end) fetch(h + 1, false);
 }
 
+// The fp32 kernel of that kind: blocks in the same order, rows past the last one read as the last one; a block whose rows all exist and lie
+// on one side of the old cache's end is read from one base.  (After its last block a wavefront fetches that one once more.)
+static void walk_few_f32(Reader& rd, const TileMap& tm, const KeyRange& kr, int nw, int64_t nkeys, int split, int g) {
+  const int64_t len_after = rd.len_prev + rd.n_tokens, chunk0 = rd.fused ? rd.len_prev : (int64_t)1 << 40;
+  auto first_key = [&](int b) { return (int64_t)b * 32 + ((b >> 1) >= tm.ns_t ? tm.skip * kTileKeys : 0); };
+  const int b_all = 2 * tm.ntiles - (first_key(2 * tm.ntiles - 1) >= nkeys ? 1 : 0), b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
+  for (int w = 0; w < nw; ++w) {
+    const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + nw - 1) / nw : 0;
+    int b = b_first + nw * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_blocks) >> 16);
+    for (int i = 0; i < n_blocks; ++i) {
+      REQUIRE(b >= b_first && b < b_end && (b - b_first) % nw == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_end, w);
+      const int64_t first = first_key(b), last = first + 31;
+      const bool plain = last < len_after && (last < chunk0 || first >= chunk0), nw_rows = first >= chunk0;
+      for (int j = 0; j < 32; ++j) {
+        const int64_t key = first + j, row = key < len_after ? key : len_after - 1;
+        const bool from_chunk = plain ? nw_rows : row >= chunk0;
+        rd.read(DmaRow{from_chunk, (unsigned)((plain ? key : row) - (from_chunk ? chunk0 : 0))}, key, true);
+      }
+      b = b + nw < b_end ? b + nw : b_first;
+    }
+  }
+}
+
 static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_t len_prev, int n_sink, int64_t window,
                       int force_splits, int force_upw, bool rope = false, int storage_bits = 0) {
   PlanCtx pc{};
@@ -176,8 +199,9 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   if (window > 0) REQUIRE(!pl.pair_units && !pl.pair_order, "pairing under a window");
   REQUIRE(pl.waves_per_wg == kUnitsPerWg || (pl.waves_per_wg == 8 && cfg.dtype == KVFOLD_F32 && pl.units_per_wave == 1), "wavefronts");
   REQUIRE(!pl.few_rows || (cfg.dtype == KVFOLD_BF16 && window <= 0 && pl.units_per_head == 1 && pl.wgs_per_head == 1), "few rows");
-  REQUIRE(pl.key_waves == 0 || pl.key_waves == 8 || (pl.key_waves == 4 && window <= 0), "wavefronts that share a unit's keys");
-  REQUIRE(pl.key_waves == 0 || (cfg.dtype == KVFOLD_BF16 && pl.wgs_per_head == pl.units_per_head && !pl.pair_units && !pl.pair_order), "one unit a workgroup");
+  REQUIRE(pl.key_waves == 0 || pl.key_waves == 8 || (pl.key_waves == 4 && (window <= 0 || cfg.dtype == KVFOLD_F32)), "wavefronts that share a unit's keys");
+  REQUIRE(pl.key_waves == 0 || cfg.dtype == KVFOLD_BF16 || pl.key_waves == (cfg.head_dim == 64 ? 8 : 4), "fp32 wavefronts");
+  REQUIRE(pl.key_waves == 0 || (pl.wgs_per_head == pl.units_per_head && !pl.pair_units && !pl.pair_order), "one unit a workgroup");
   REQUIRE(!work || (pl.key_waves == 4 && pl.units_per_head == 1), "rows are worked on by the one workgroup of a piece");
   REQUIRE((int64_t)pl.wgs_per_head * upw_wg >= pl.units_per_head && (int64_t)pl.units_per_head * kRowsPerUnit >= (int64_t)n_tokens * G,
           "%d workgroups of %d units for %d tokens x %d heads", pl.wgs_per_head, upw_wg, n_tokens, G);
@@ -216,7 +240,9 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       const int64_t readable_cache = fused || work ? len_prev : len_after;
       REQUIRE((int64_t)kr.row_lim < len_after, "row_lim");
       Reader rd{cfg, n_tokens, len_prev, readable_cache, len_prev + rr.row_hi, row_bytes, fused, seen};
-      if (cfg.dtype != KVFOLD_BF16)
+      if (cfg.dtype != KVFOLD_BF16 && pl.key_waves)
+        walk_few_f32(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads);
+      else if (cfg.dtype != KVFOLD_BF16)
         walk_halves(rd, tm, kr, len_prev + rr.row_hi + 1);
       else if (pl.key_waves)
         walk_few(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
