@@ -373,14 +373,16 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   // Few units on not too many keys: the chain of one wavefront through the general kernels' tiles is longer than the whole step where the
   // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
   // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all
-  // its keys for itself, so that full grids are not for it: up to two workgroups per CU.  Over 480 shapes with more than one unit or a
-  // window the steps take 0.88 of the time (0.84 on up to 30K keys), and 5 are 3 % or more slower (16 heads on 2, 64 wide, 15 tokens on 114K
-  // keys 1.24, on 66K 1.15).
-  if (c.tune_pair_units == 0 && (int64_t)p1.units_per_head * f.n_kv_heads <= 2 * (int64_t)c.n_cu)
+  // its keys for itself, so that full grids are not for it: up to two workgroups per CU, and with a margin where there are many units (221
+  // tokens with the rotary embedding on 6.9K keys, 32 heads on 8, 64 wide, 28 units: 29.2 / 31.8).  Nor are long ranges of 64-wide rows
+  // under several KV heads (15 tokens, 16 heads on 2: 66K keys 20.7 / 25.5, 114K 27.1 / 39.1; one head, 101 tokens on 94K 27.4 / 25.4).
+  // Over 400 shapes with more than one unit or a window the steps take 0.84 of the time.
+  const bool long_64 = f.head_dim == 64 && f.n_kv_heads > 1 && window <= 0 && len_after > 48 * 1024;
+  if (c.tune_pair_units == 0 && (int64_t)p1.units_per_head * f.n_kv_heads <= 2 * (int64_t)c.n_cu && !long_64)
     for (int waves : {8, 4}) {
       if (waves == 4 && window > 0) continue;
       const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, waves);
-      if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : 0.95)) best = pk;
+      if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : p1.units_per_head > 16 ? 0.9 : 0.95)) best = pk;
     }
   return best;
 }

@@ -88,3 +88,14 @@ def test_64_wide_two_unit_grids_do_not_count_on_empty_workgroups_beyond_a_round(
     """31 to 36 us; 45 with seven pieces of two units a wavefront, 448 workgroups of which 256 have work."""
     plan = _plan(kv.KVFOLD_BF16, 4, 1, 64, n, prev)
     assert not (plan.units_per_wave == 2 and plan.n_workgroups > 256 * 5 // 4)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev", [
+    (16, 2, 64, 15, 66000),      # 20.7 / 25.5 us with one unit a workgroup
+    (16, 2, 64, 15, 114000),     # 27.1 / 39.1
+    (32, 8, 64, 221, 6855),      # 29.2 / 31.8 (with the rotary embedding)
+])
+def test_units_share_a_workgroup_where_each_reading_its_keys_alone_is_slower(hq, hkv, d, n, prev):
+    plan = _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev)
+    units = -(-n * (hq // hkv) // 32)
+    assert plan.n_workgroups < hkv * units * plan.n_splits
