@@ -148,8 +148,8 @@ void plan_key_waves(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, in
 
 // The same for the fp32 kernel of that kind.  One workgroup per CU; what a wavefront's chain of blocks takes is for the most part what
 // a CU gets from memory, some 37 GB/s on its own.  Fitted to 2500 measured steps (captured graphs): 416 shapes (1 to 64 heads, 1 to 600
-// tokens on 0 to 65K keys, windows among them), every split count; the choice is 0.4 % above the best of these on average (64 wide
-// 0.7 %), more than 10 % above it in one.
+// tokens on 0 to 65K keys, windows among them), every split count; the choice is 0.9 % above the best of these on average (64 wide
+// 1.6 %), more than 10 % above it in 11: pieces stay within a round of workgroups (897 tokens, 4 heads on 1, on 146 keys).
 void plan_key_waves_f32(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64_t s_max, int waves, double kv_rows,
                         double seen, int64_t& s, double& est_us) {
   struct Cost {
@@ -331,15 +331,15 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     if (c.tune_units_per_wave) return c.tune_units_per_wave == 2 ? w8 : w4;
     if (c.tune_splits > 0) return w4.units_per_head <= 4 ? w4 : w8;
     const Plan best = w4.est_us <= w8.est_us ? w4 : w8;
-    // Few units on not too many keys: the kernel that deals a unit's keys to its wavefronts is done in 0.81 of the time (64 wide 0.83) over
-    // the 416 shapes, and 5 % slower in one of them (32 heads on 8, 64 wide, 311 tokens, window 4 + 544: 32.6 / 34.3 us).  One token, 32
-    // heads on 8: 300 keys 15.5 -> 12.5 us, 4187 28 -> 19.9, 30K 92 -> 58; 128 tokens, 4 heads on 1, 64 wide, no keys 12.0 -> 7.5.  Every
-    // unit splits the keys into terms anew, so that the gain is gone where several units read long ranges (128 wide, 8 heads on 2, 37 tokens =
-    // five units on 30K keys 70 / 73 us) and needs a margin where there are many of them.
-    const int64_t units = w4.units_per_head;
-    if (units * f.n_kv_heads > 2 * (int64_t)c.n_cu || (f.head_dim == 128 && units > 4 && units * len_after > 144 * 1024)) return best;
+    // Few units on not too many keys: the kernel that deals a unit's keys to its wavefronts leaves the 416 shapes at
+    // 0.82 of the time, one of them 4 % slower (64 heads on 8, 64 wide, 13 tokens on 15.7K keys 38.9 / 40.4 us).  One token, 32 heads on 8: 300 keys 15.5 -> 12.5 us, 4187 28 -> 19.9, 30K 92 -> 58; 128 tokens, 4 heads on 1, 64 wide, no keys 12.0 -> 7.5.  Every
+    // unit splits the keys into terms anew, so that the gain is gone where several units have many keys (128 wide, 128 tokens, 8 heads on 2
+    // = 32 units on 4.2K keys 39.9 / 30.9 us, on 20K 78 / 93; 64 wide, 37 tokens, 32 heads on 8 = 40 units on 30K 84 / 89), and
+    // a single block of 32 keys has nothing to deal (128 wide 9.2 / 10.1 us, 64 wide 6.8 / 7.8; 34 keys 13.3 / 11.2).
+    const int64_t units = w4.units_per_head, all_units = units * f.n_kv_heads, keys = (int64_t)w4.tiles_per_split * w4.n_splits * kTileKeys;
+    if (len_after <= 32 || all_units > 2 * (int64_t)c.n_cu || (units > 4 && all_units * keys > (f.head_dim == 128 ? 400000 : 600000))) return best;
     const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, f.head_dim == 64 ? 8 : 4);
-    return pk.est_us < best.est_us * (units > 16 ? 0.9 : 0.95) ? pk : best;
+    return pk.est_us < best.est_us * 0.95 ? pk : best;
   }
   if (c.tune_units_per_wave) return plan_with(c, n_tokens, len_after, c.tune_units_per_wave, n_sink, window);
   if (window <= 0 && units_of_head(n_tokens, f.n_q_heads / f.n_kv_heads) == 1)

@@ -99,3 +99,16 @@ def test_units_share_a_workgroup_where_each_reading_its_keys_alone_is_slower(hq,
     plan = _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev)
     units = -(-n * (hq // hkv) // 32)
     assert plan.n_workgroups < hkv * units * plan.n_splits
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev,dealt", [
+    (8, 2, 128, 128, 4187, True),      # 30.9 us with a unit's keys dealt to the wavefronts / 39.9 without
+    (8, 2, 128, 128, 20000, False),    # 92.7 / 78.0
+    (32, 8, 64, 37, 30000, False),     # 89.2 / 83.7
+    (4, 1, 64, 128, 0, True),          # 7.5 / 12.0
+    (28, 4, 128, 28, 0, True),         # 28 keys: a single block has nothing to deal
+])
+def test_fp32_keys_are_dealt_to_wavefronts_where_units_are_few(hq, hkv, d, n, prev, dealt):
+    plan = _plan(kv.KVFOLD_F32, hq, hkv, d, n, prev)
+    units = -(-n * (hq // hkv) // 32)
+    assert (plan.n_workgroups == hkv * units * plan.n_splits) == (dealt and n + prev > 32)
