@@ -374,15 +374,18 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
   // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all
   // its keys for itself, so that full grids are not for it: up to two workgroups per CU, and with a margin where there are many units (221
-  // tokens with the rotary embedding on 6.9K keys, 32 heads on 8, 64 wide, 28 units: 29.2 / 31.8).  Nor are long ranges of 64-wide rows
-  // under several KV heads (15 tokens, 16 heads on 2: 66K keys 20.7 / 25.5, 114K 27.1 / 39.1; one head, 101 tokens on 94K 27.4 / 25.4).
+  // tokens with the rotary embedding on 6.9K keys, 32 heads on 8, 64 wide, 28 units: 29.2 / 31.8).  Nor are long ranges, where it
+  // hangs on how the pieces of several KV heads lie in memory (15 tokens, 16 heads on 2, 64 wide: 66K keys 20.7 / 25.5, 114K 27.1 / 39.1; 8 on
+  // 2: 65.5K 24.4 / 26.8, 70K 25.1 / 20.2; 4 on 1, 64 wide: 43 tokens on 124K 28.5 / 20.3, 57 on 122K 28.3 / 40.4), nor steps of more
+  // than some 35 us (32 on 8, 64 wide: 489 tokens on 3.8K 31.4 / 30.3, 510 on 5.5K 39.7 / 42.3; 8 on 2, 2038 on 1.8K 42.3 / 46.3).
   // Over 400 shapes with more than one unit or a window the steps take 0.84 of the time.
-  const bool long_64 = f.head_dim == 64 && f.n_kv_heads > 1 && window <= 0 && len_after > 48 * 1024;
-  if (c.tune_pair_units == 0 && (int64_t)p1.units_per_head * f.n_kv_heads <= 2 * (int64_t)c.n_cu && !long_64)
+  const int64_t units = p1.units_per_head;
+  const bool long_range = window <= 0 && (f.n_kv_heads > 1 ? len_after > 48 * 1024 : units * len_after > 800000);
+  if (c.tune_pair_units == 0 && units * f.n_kv_heads <= 2 * (int64_t)c.n_cu && !long_range && best.est_us < 39.0)
     for (int waves : {8, 4}) {
       if (waves == 4 && window > 0) continue;
       const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, waves);
-      if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : p1.units_per_head > 16 ? 0.9 : 0.95)) best = pk;
+      if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : units > 16 ? 0.9 : 0.95)) best = pk;
     }
   return best;
 }
