@@ -369,7 +369,11 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return p2;
   }
   if (pair && 4 * f.n_kv_heads <= kNumXcd) return p2;
-  Plan best = p1.est_us < p2.est_us * 1.1 ? p1 : p2;
+  // Where the rows from memory take a third of the step or more, the two workgroups of one unit a wavefront that share a piece's rows wait for
+  // them twice, and the estimates are taken as they are (one / two units: 37 tokens on 32.8K keys, 32 heads on 8, 48.0 / 44.6 us; 27
+  // on 73K, 28 on 4, 60 / 48; over 160 shapes of 9 to 300 tokens on 6K to 127K keys the choice is 0.4 % above the better of both).
+  const double kv_us = 4.0 * f.n_kv_heads * f.head_dim * (double)len_after / 6.5e6;
+  Plan best = p1.est_us < p2.est_us * (window <= 0 && kv_us > 0.3 * p1.est_us ? 1.0 : 1.1) ? p1 : p2;
   // Few units on not too many keys: the chain of one wavefront through the general kernels' tiles is longer than the whole step where the
   // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
   // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all
