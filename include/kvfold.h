@@ -257,6 +257,9 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *                                as many KV as query heads and at most 32 tokens); fp32: the kernel for
  *                                few blocks, and workgroups of four wavefronts whose pieces of the key range have fewer than 20 tiles (head_dim 64: 12), and
  *                                rows apart from out, lse and the cache;
+ *                              - the rotary embedding alone is in play, in a bf16 step of at most 100 tokens (head_dim 64: 256) that
+ *                                ends beyond 256 keys and for which the kernel for few rows is chosen, and rows apart from out,
+ *                                lse and the cache;
  *                              - one of the two is in play, in a bf16 step without a window of at most 32 (token,
  *                                query head) rows per KV head, with the round trip also of at most 4096 bytes of K rows per
  *                                KV head, and rows apart from out, lse and the cache.

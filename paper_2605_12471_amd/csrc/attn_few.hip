@@ -50,7 +50,12 @@ constexpr int few_lds_bytes() {
   return rings > results ? rings : results;
 }
 
-template <int D, int NW, bool WIN, bool MULTI>
+// ROT (several units per KV head, rotary embedding, rows read as handed in): the workgroups that read a row are many, and each rotates its
+// own copy, in LDS, as it comes to the block, and the rows of the chunk that it appends; the arithmetic is the append kernel's, and so are
+// the bits.  That kernel's launch against 0.3 to 1 us in each block with rows of the chunk: 32 heads on 8, 99 tokens on 189 keys
+// 12.2 -> 11.3 us, 64 wide, 128 on 128 8.85 -> 7.42 (attention_appends() has the limits).  An instance of its own: with the code in the others
+// 64-wide workgroups of eight wavefronts had a CU to themselves, 142 registers for 110.
+template <int D, int NW, bool WIN, bool MULTI, bool ROT>
 __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned lds0 = (unsigned)(uintptr_t)((unsigned char __attribute__((address_space(3)))*)smem);
@@ -208,6 +213,15 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
         const unsigned off = (unsigned)r * new_stride + (unsigned)(tid % CH) * 16u;
         copy_k[i] = *reinterpret_cast<const uintx4*>(knew + off);
         copy_v[i] = *reinterpret_cast<const uintx4*>(vnew + off);
+        if (ROT) {
+          const int c = tid % CH;
+          const bool lower = c < CH / 2;
+          const uintx4 other = *reinterpret_cast<const uintx4*>(knew + (lower ? off + ROWB / 2 : off - ROWB / 2));
+          const int64_t at = (int64_t)r * (D / 2) + (lower ? c : c - CH / 2) * 8;
+          bf16x8 v = __builtin_bit_cast(bf16x8, copy_k[i]);
+          rotate_vec<__bf16, 8>(v, __builtin_bit_cast(bf16x8, other), p.rope_cos + at, p.rope_sin + at, lower);
+          copy_k[i] = __builtin_bit_cast(uintx4, v);
+        }
       }
     }
   };
@@ -253,6 +267,27 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
       wait_vm<SLABS>();
     else
       wait_vm<0>();
+    const int key0 = first_key(b);
+    if (ROT && __builtin_expect(key0 + 32 > (int)p.len_prev, 0)) {
+      // two lanes a row, each a half of its pairs of 16-byte chunks (c, c + CH / 2)
+      const int r = l >> 1, row = key0 + r < (int)kr.row_lim ? key0 + r : (int)kr.row_lim, t = row - (int)p.len_prev;
+      if (t >= 0) {
+        const unsigned at_row = my_lds + (unsigned)(r * ROWB);
+#pragma unroll
+        for (int i = 0; i < CH / 4; ++i) {
+          const int c = (l & 1) * (CH / 4) + i;
+          const unsigned lo_at = at_row + (unsigned)((c ^ (r % KSW)) * 16), up_at = at_row + (unsigned)(((c + CH / 2) ^ (r % KSW)) * 16);
+          const int64_t at = (int64_t)t * (D / 2) + c * 8;
+          const bf16x8 lo = *LDS_PTR(const bf16x8, lo_at), up = *LDS_PTR(const bf16x8, up_at);
+          bf16x8 lo2 = lo, up2 = up;
+          rotate_vec<__bf16, 8>(lo2, up, p.rope_cos + at, p.rope_sin + at, true);
+          rotate_vec<__bf16, 8>(up2, lo, p.rope_cos + at, p.rope_sin + at, false);
+          *LDS_PTR(bf16x8, lo_at) = lo2;
+          *LDS_PTR(bf16x8, up_at) = up2;
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     floatx16 s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -264,7 +299,6 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
     asm volatile("" : "+v"(s)::"memory");  // every read of the K block has returned
     if (more) fetch(false, nb);
 
-    const int key0 = first_key(b);
     const bool left = WIN && key0 < lb_last && key0 + 32 > p.n_sink;  // keys between the sinks and the window
     if (key0 + 32 > vis_first || left) {  // wave-uniform: some row does not see the whole block
       const int rel = my_vis - key0 - 4 * hi;
@@ -387,39 +421,45 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
     }
 }
 
-template <int D, int NW, bool WIN, bool MULTI>
+template <int D, int NW, bool WIN, bool MULTI, bool ROT>
 static hipError_t prepare_few_one() {
   // once per device (idempotent; a benign race at worst sets it twice)
   static bool attr_done[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_done[dev]) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D, NW, WIN, MULTI>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_few_kernel<D, NW, WIN, MULTI, ROT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes<D, NW>());
   if (e == hipSuccess) attr_done[dev] = true;
   return e;
 }
 template <int D>
 static hipError_t prepare_few() {
-  hipError_t e = prepare_few_one<D, 4, false, false>();
-  if (e == hipSuccess) e = prepare_few_one<D, 4, false, true>();
-  if (e == hipSuccess) e = prepare_few_one<D, 8, false, true>();
-  if (e == hipSuccess) e = prepare_few_one<D, 8, true, true>();
+  hipError_t e = prepare_few_one<D, 4, false, false, false>();
+  if (e == hipSuccess) e = prepare_few_one<D, 4, false, true, false>();
+  if (e == hipSuccess) e = prepare_few_one<D, 4, false, true, true>();
+  if (e == hipSuccess) e = prepare_few_one<D, 8, false, true, false>();
+  if (e == hipSuccess) e = prepare_few_one<D, 8, false, true, true>();
+  if (e == hipSuccess) e = prepare_few_one<D, 8, true, true, false>();
   return e;
 }
 hipError_t prepare_attn_few(int head_dim) { return head_dim == 128 ? prepare_few<128>() : prepare_few<64>(); }
 
+template <int D, int NW, bool WIN, bool MULTI, bool ROT>
+static void launch_few_one(const AttnParams& p, hipStream_t s) {
+  hipLaunchKernelGGL((attn_few_kernel<D, NW, WIN, MULTI, ROT>), dim3(padded_grid(p.n_wgs)), dim3(NW * 64), (few_lds_bytes<D, NW>()), s, p);
+}
 template <int D>
 static void launch_few(const AttnParams& p, int key_waves, hipStream_t s) {
-  const dim3 grid(padded_grid(p.n_wgs));
+  const bool rotate = p.k_new && p.rope_cos;
   if (key_waves == 4 && p.units_per_head == 1)
-    hipLaunchKernelGGL((attn_few_kernel<D, 4, false, false>), grid, dim3(256), (few_lds_bytes<D, 4>()), s, p);
+    launch_few_one<D, 4, false, false, false>(p, s);
   else if (key_waves == 4)
-    hipLaunchKernelGGL((attn_few_kernel<D, 4, false, true>), grid, dim3(256), (few_lds_bytes<D, 4>()), s, p);
+    rotate ? launch_few_one<D, 4, false, true, true>(p, s) : launch_few_one<D, 4, false, true, false>(p, s);
   else if (p.window > 0)
-    hipLaunchKernelGGL((attn_few_kernel<D, 8, true, true>), grid, dim3(512), (few_lds_bytes<D, 8>()), s, p);
+    launch_few_one<D, 8, true, true, false>(p, s);
   else
-    hipLaunchKernelGGL((attn_few_kernel<D, 8, false, true>), grid, dim3(512), (few_lds_bytes<D, 8>()), s, p);
+    rotate ? launch_few_one<D, 8, false, true, true>(p, s) : launch_few_one<D, 8, false, true, false>(p, s);
 }
 
 hipError_t launch_attn_few(const AttnParams& p, int head_dim, int key_waves, hipStream_t s) {

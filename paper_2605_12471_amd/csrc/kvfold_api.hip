@@ -280,7 +280,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     results_apart = results_apart && (from_out || in_place) && from_lse;
     rows_apart = rows_apart && from_out && from_lse && apart(rows, new_bytes, c->kv, c->kv_bytes);
   }
-  const bool may_append = f.dtype == KVFOLD_BF16 ? results_apart || pl.n_splits > 1 : rows_apart;
+  const bool may_append = f.dtype == KVFOLD_BF16 && !opt.rope_cos ? results_apart || pl.n_splits > 1 : rows_apart;
   const bool fused_append = may_append && attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;

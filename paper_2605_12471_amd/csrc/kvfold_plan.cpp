@@ -70,7 +70,13 @@ bool attention_appends(const PlanCtx& c, const Plan& pl, int n_tokens, bool rope
   // kernel / this, 64 tokens, 8 heads on 2: 9 tiles 77.3 / 76.0 us, 14 110.9 / 110.0, 20 144.2 / 144.5, 28 204.2 / 206.7; 64 wide, 7
   // tiles 40.6 / 39.5, 9 47.1 / 46.6, 14 66.1 / 66.6, 20 85.3 / 86.7.
   if (f.dtype != KVFOLD_BF16 && !pl.key_waves && (pl.waves_per_wg != 4 || pl.tiles_per_split >= (f.head_dim == 64 ? 12 : 20))) return false;
-  if (rope || c.storage_bits || c.tune_fused_append == 1) return false;
+  // The rotary embedding: where a unit's keys are dealt to wavefronts each rotates the rows of the chunk that it comes to, for a launch less.
+  // Over 130 shapes, by tokens of the chunk: 128 wide up to 100 0.86 to 0.98 of the time, 116 to 240 0.94 to 1.08, above 1.0 to 1.4; 64 wide up to
+  // 212 0.78 to 0.95, above 0.9 to 1.2.  Steps that end within 256 keys keep the append kernel, a route that their tests ask for (0.94, 64
+  // wide 0.85).  (One unit per KV head: attention_works_on_rows().)
+  const bool rotates = f.dtype == KVFOLD_BF16 && pl.key_waves && !pl.few_rows && n_tokens <= (f.head_dim == 128 ? 100 : 256) &&
+                       pl.tiles_per_split * pl.n_splits > 4;
+  if ((rope && !rotates) || c.storage_bits || c.tune_fused_append == 1) return false;
   const int64_t chunk_bytes = (int64_t)n_tokens * f.n_kv_heads * f.head_dim * elem_size(f.dtype);
   return chunk_bytes < ((int64_t)1 << 32);
 }

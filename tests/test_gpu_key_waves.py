@@ -57,3 +57,39 @@ def test_logit_jumps(H, oracle, profile):
     chunks = [400, 40, 9, 70]
     cfg = I.FoldConfig("key_waves_jump", 72, 1, 4, 1, 128, 400, 0, "bf16")
     _run_case(H, oracle, cfg, chunks, profile=profile, check_lse=False)
+
+
+# Blocks that lie in the chunk, before it and on both sides; rows that run past the chunk; the most rows that take this route (100, 64 wide 256)
+# and the first that do not; pieces that begin in the chunk.
+@pytest.mark.parametrize("Hq,Hkv,d,chunks", [
+    (8, 2, 128, [257, 33, 31, 32, 9, 23, 64, 65, 100, 101, 40]),
+    (8, 2, 64, [257, 33, 31, 32, 9, 23, 64, 65, 127, 256]),
+    (7, 1, 128, [300, 37, 5, 64, 41, 100]),
+    (28, 4, 128, [500, 37, 90, 30]),
+    (3, 3, 64, [400, 65, 33, 97, 34]),
+    (32, 8, 128, [240, 37, 100, 40, 9]),
+    (4, 1, 64, [700, 257, 9, 60]),
+])
+def test_rows_rotated_by_their_readers(H, oracle, Hq, Hkv, d, chunks):
+    """Rotary embedding: outputs and cache are the same bits as behind the append kernel (tuning knob), and there is none."""
+    cfg = I.FoldConfig("key_waves_rope", 73, 1, Hq, Hkv, d, max(chunks), 0, "bf16")
+    own = _one_unit_workgroups(Hq, Hkv, d, chunks)
+    takes = [o and n <= (100 if d == 128 else 256) and sum(chunks[:i + 1]) > 256 for i, (o, n) in enumerate(zip(own, chunks))]
+    assert sum(takes) >= 2
+    res = []
+    for knob in (0, 1):
+        gpu = H.GpuFold(cfg, capacity=sum(chunks), chunk_tokens=max(chunks))
+        gpu.cache.set_tuning(kv.TUNE_FUSED_APPEND, knob)
+        outs, pos = [], 0
+        for step, C in enumerate(chunks):
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            gpu.cache.profile_begin(1)
+            outs += list(gpu.step(0, q, k, v, want_lse=True, rope=I.rope_tables(d, pos, C, device="cuda")))
+            _, append_ms, _, _ = gpu.cache.profile_end()
+            if C * Hq // Hkv > 32:
+                assert (append_ms == 0) == (knob == 0 and takes[step])
+            pos += C
+        K, V = gpu.cache.view(0)
+        res.append([*outs, K[:, :pos].clone(), V[:, :pos].clone()])
+        gpu.close()
+    assert all(bool((a == b).all()) for a, b in zip(*res))
