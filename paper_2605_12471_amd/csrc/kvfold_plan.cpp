@@ -375,11 +375,14 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return p2;
   }
   if (pair && 4 * f.n_kv_heads <= kNumXcd) return p2;
-  // Where the rows from memory take a third of the step or more, the two workgroups of one unit a wavefront that share a piece's rows wait for
-  // them twice, and the estimates are taken as they are (one / two units: 37 tokens on 32.8K keys, 32 heads on 8, 48.0 / 44.6 us; 27
-  // on 73K, 28 on 4, 60 / 48; over 160 shapes of 9 to 300 tokens on 6K to 127K keys the choice is 0.4 % above the better of both).
+  // Where a piece's two workgroups of one unit a wavefront are dealt to different XCDs (logical_workgroup()), each brings its rows from beyond an L2 of its own; one
+  // workgroup of two units brings them once.  Where the rows take a third of the step or more the estimates are taken as they are: 39
+  // shapes of 28 heads on 4 and 12 on 4 0.74 to 0.95 of the time (27 tokens on 73K keys, 28 on 4: 60 / 48 us; 20 on 104K 73.6 / 54.1).  Not where both share an L2:
+  // over 289 shapes with 8 and 16 KV heads 0.99, but single ones 0.90 to 1.15 (213 tokens on 25.6K keys, 16 on 16: 60.9 / 69.9).
   const double kv_us = 4.0 * f.n_kv_heads * f.head_dim * (double)len_after / 6.5e6;
-  Plan best = p1.est_us < p2.est_us * (window <= 0 && kv_us > 0.3 * p1.est_us ? 1.0 : 1.1) ? p1 : p2;
+  const bool read_twice = window <= 0 && kv_us > 0.3 * p1.est_us && p1.wgs_per_head == 2 && f.n_kv_heads < kNumXcd &&
+                          evenly_dealt(f.n_kv_heads, p1.n_wgs / f.n_kv_heads);
+  Plan best = p1.est_us < p2.est_us * (read_twice ? 1.0 : 1.1) ? p1 : p2;
   // Few units on not too many keys: the chain of one wavefront through the general kernels' tiles is longer than the whole step where the
   // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
   // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all

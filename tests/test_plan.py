@@ -112,3 +112,13 @@ def test_fp32_keys_are_dealt_to_wavefronts_where_units_are_few(hq, hkv, d, n, pr
     plan = _plan(kv.KVFOLD_F32, hq, hkv, d, n, prev)
     units = -(-n * (hq // hkv) // 32)
     assert (plan.n_workgroups == hkv * units * plan.n_splits) == (dealt and n + prev > 32)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev,units", [
+    (32, 8, 128, 37, 32768, 1),     # one unit a wavefront as fast, and what these steps have always taken
+    (16, 16, 128, 213, 25614, 1),   # 60.9 / 69.9 us
+    (32, 8, 128, 52, 32711, 1),     # 44.8 / 50.4
+    (28, 4, 128, 20, 104146, 2),    # 54.1 / 73.6: the two workgroups of a piece do not share an L2
+])
+def test_two_units_a_wavefront_where_a_piece_would_be_read_twice(hq, hkv, d, n, prev, units):
+    assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).units_per_wave == units
