@@ -382,21 +382,31 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
 #pragma unroll 1
   for (int r = tid / V; r < rows; r += NT / V) {
     floatx2 ml[NW];
+    floatx4 x[NW];
     float M = -INFINITY;
+    bool some = false;
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) {
       ml[ww] = *LDS_PTR(const floatx2, mlbase + (unsigned)((ww * kRowsPerUnit + r) * 8));
+      x[ww] = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
       M = fmaxf(M, ml[ww].x);
+      some = some || ml[ww].y == 0.f;
+    }
+    // A wavefront of whose keys the row saw none is left out: its O may be NaN, 0 times a value that is not finite.
+    if (__any(some)) {
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[ww][e] = ml[ww].y == 0.f ? 0.f : x[ww][e];
     }
     float L = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) {
-      const floatx4 x = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
-      const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);  // (0: it saw no visible key)
+      const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);
       L += f * ml[ww].y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += f * x[e];
+      for (int e = 0; e < 4; ++e) acc[e] += f * x[ww][e];
     }
     const int t = (int)quot((unsigned)(row0 + r), p.by_group), h = g * G + row0 + r - t * G;
     const int64_t at = (int64_t)t * Hq + h;

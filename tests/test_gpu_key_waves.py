@@ -93,3 +93,31 @@ def test_rows_rotated_by_their_readers(H, oracle, Hq, Hkv, d, chunks):
         res.append([*outs, K[:, :pos].clone(), V[:, :pos].clone()])
         gpu.close()
     assert all(bool((a == b).all()) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,window,key,blind", [
+    (32, None, 47, slice(0, 16)),          # one unit: wavefront 1 has block 1, of which the first 16 rows see nothing
+    (64, None, 47, slice(0, 16)),          # several units
+    (64, (0, 8), 10, slice(23, None)),     # block 0 lies behind the window of the rows from token 23 on
+])
+def test_rows_do_not_notice_wavefronts_whose_keys_they_do_not_see(H, d, n, window, key, blind):
+    """An infinite value leaves NaN in a wavefront's sums for rows that see none of its keys (0 times infinity); these rows keep every bit."""
+    cfg = I.FoldConfig("key_waves_inf", 74, 1, 4, 4, d, 64, 0, "bf16")
+    assert n <= 32 or _one_unit_workgroups(4, 4, d, [16, n], window)[1]
+    outs = []
+    for value in (None, float("inf")):
+        gpu = H.GpuFold(cfg, capacity=80, chunk_tokens=64)
+        pos = 0
+        for step, C in enumerate((16, n)):
+            q, k, v = I.chunk_qkv(cfg, 0, step, n_tokens=C, token_base=pos)
+            if value is not None and pos <= key < pos + C:
+                v[key - pos, :, 5] = value
+            out = gpu.step(0, q, k, v, window=window).cpu()
+            pos += C
+        outs.append(out)
+        gpu.close()
+    sees = 1 if window else key - 16  # a row of the last step that sees the key
+    assert not outs[1][sees, :, 5].isfinite().any()
+    differ = int((outs[0][blind] != outs[1][blind]).sum())
+    assert bool(outs[0].isfinite().all()) and differ == 0
