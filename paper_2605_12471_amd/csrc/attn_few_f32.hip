@@ -264,7 +264,9 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) attn_few_f32_kernel(AttnParam
 #pragma unroll 1
   for (int i = 0; i < n_blocks; ++i) {
     const int nb = i + 1 < n_blocks ? (b + NW < b_end ? b + NW : b_first) : b;  // (after the last one: it once more, for nobody)
-    wait_vm<16>();  // (the block's keys: behind them its values are on their way)
+    // The block's keys have arrived: vector memory loads return in order, and the first of its values, whose register is asked for here, was
+    // loaded behind them.  (How many loads the compiler makes of the values is its own affair: nothing counts them.)
+    asm volatile("" : "+v"(vr[0])::"memory");
     const int slot = SLOTS == 2 ? i & 1 : 0;
     if (SLOTS == 2 && i + 1 < n_blocks) fetch_k(nb, slot ^ 1);
     floatx4 kr[2];
