@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   // every line of the arguments is fetched now, in one round trip (they are not in the scalar cache yet)
   asm volatile("" ::"s"(p.q), "s"(p.n_tokens), "s"(p.units_per_head), "s"(p.k_new), "s"(p.by_group.mul), "s"(p.copy_rows));
 
-  // ---- which workgroup am I (XCD-aware: a KV head stays on its XCDs, see logical_workgroup())
+  // ---- which workgroup am I (XCD-aware: a KV head stays on its XCDs, see logical_id())
   const int wgs_per_kvh = p.wgs_per_head * p.n_splits;
   const int lid = logical_workgroup(blockIdx.x, gridDim.x, p);
   if (lid >= p.n_wgs) return;

@@ -289,7 +289,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.work_k = work_rows ? k_new : nullptr;
   at.work_v = work_rows ? v_new : nullptr;
   at.work_qmax = pc.storage_bits ? (float)((1 << (pc.storage_bits - 1)) - 1) : 0.f;
-  finish_attn_params(at);
+  finish_attn_params(at, pl.key_waves > 0);
   if (pl.n_splits > 1 && ((int64_t)pl.n_splits * n_tokens * f.n_q_heads > pc.ws_rows || !part_o))
     return KVFOLD_ERR_HIP;  // planner bug guard
 

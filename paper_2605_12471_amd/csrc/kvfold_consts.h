@@ -21,6 +21,29 @@ constexpr int kNumXcd = 8;
 #define KVFOLD_HD inline
 #endif
 
+// Which workgroup the hardware's block b of `grid` is: logical ids run KV head major, then split, then workgroup of the head, heaviest
+// first; per_kvh of them belong to a KV head.  Dealt out in 8 contiguous runs, one per XCD, they keep the workgroups of a KV head, and of
+// a piece of its keys, on one XCD's L2 (share_log2 < 0).  A KV head that spans k = 8 / Hkv = 2^share_log2 XCDs may have its
+// workgroups dealt to those XCDs in turn instead: every XCD then gets the same mix of heavy and light workgroups and of prefix splits (a
+// contiguous run would put all late token blocks, or a whole split, on one XCD and the light rest on its neighbour).
+KVFOLD_HD int logical_id(unsigned b, unsigned grid, unsigned per_kvh, int share_log2) {
+  const unsigned x = b % kNumXcd, j = b / kNumXcd;
+  if (share_log2 >= 0) return (int)((x >> share_log2) * per_kvh + (j << share_log2) + (x & ((1u << share_log2) - 1)));  // grid = Hkv * per_kvh
+  return (int)(x * (grid / kNumXcd) + j);
+}
+inline int padded_grid(int n_wgs) { return (n_wgs + kNumXcd - 1) / kNumXcd * kNumXcd; }
+// share_log2 of a launch.  one_unit_wgs: workgroups of one unit, whose keys are dealt to their wavefronts.  Each of these streams all the keys of
+// its piece, so that the units of a piece belong on one XCD, where the first to ask brings a row into the L2 for all: dealt in turn, every
+// row came from beyond an L2 as many times as the piece has units on different XCDs.  57 tokens on 36K keys, 4 heads on 1, 28.5 us where the general
+// kernel takes 20.5; 19 on 43K, 8 heads on 2, 26.4 dealt, 18 in runs (a split count that does not deal evenly).
+inline int xcd_share_log2(int n_kv_heads, int wgs_per_head, int n_splits, bool one_unit_wgs) {
+  if (one_unit_wgs && wgs_per_head > 1 && n_splits > 1) return -1;
+  if (n_kv_heads >= kNumXcd || kNumXcd % n_kv_heads || wgs_per_head * n_splits % (kNumXcd / n_kv_heads)) return -1;
+  int lk = 0;
+  while ((n_kv_heads << lk) < kNumXcd) ++lk;
+  return lk;
+}
+
 // Quotients by a divisor that the host knows: n / d = (n * mul) >> shift for every n < 2^31.  With l = ceil(log2 d),
 // mul = ceil(2^(31+l) / d) < 2^32 overshoots by e = mul * d - 2^(31+l) < 2^l, and n * e < 2^(31+l).  Integer division
 // has no instruction on the GPU; the half dozen that a workgroup needs to find its place took 1 us of its start.

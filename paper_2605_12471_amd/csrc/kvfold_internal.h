@@ -72,22 +72,18 @@ struct AttnParams {
   FastDiv by_group, by_wgs_per_head, by_wgs_per_kvh;
   int32_t group_inv16;      // floor(2^16 / G) + 1
   int32_t copy_rows;        // fused append: chunk rows that one workgroup copies, ceil(C / (wgs_per_head * S))
-  int32_t xcd_share_log2;   // log2 of the XCDs that share one KV head, -1: contiguous runs (see logical_workgroup())
+  int32_t xcd_share_log2;   // log2 of the XCDs that a KV head's workgroups are dealt to, -1: contiguous runs (see logical_id())
 };
 
-// Fills in what follows from the launch geometry.
-inline void finish_attn_params(AttnParams& p) {
+// Fills in what follows from the launch geometry (one_unit_wgs: see xcd_share_log2()).
+inline void finish_attn_params(AttnParams& p, bool one_unit_wgs) {
   const int per_kvh = p.wgs_per_head * p.n_splits;
   p.by_group = fast_div(p.group);
   p.by_wgs_per_head = fast_div(p.wgs_per_head);
   p.by_wgs_per_kvh = fast_div(per_kvh);
   p.group_inv16 = 65536 / p.group + 1;
   p.copy_rows = (p.n_tokens + per_kvh - 1) / per_kvh;
-  p.xcd_share_log2 = -1;
-  if (p.n_kv_heads < kNumXcd && kNumXcd % p.n_kv_heads == 0 && per_kvh % (kNumXcd / p.n_kv_heads) == 0) {
-    p.xcd_share_log2 = 0;
-    while ((p.n_kv_heads << p.xcd_share_log2) < kNumXcd) ++p.xcd_share_log2;
-  }
+  p.xcd_share_log2 = xcd_share_log2(p.n_kv_heads, p.wgs_per_head, p.n_splits, one_unit_wgs);
 }
 
 struct CombineParams {
@@ -117,19 +113,8 @@ hipError_t launch_attn_few_f32(const AttnParams& p, int head_dim, hipStream_t s)
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, int waves_per_wg, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 
-// Padded grid size and the XCD-aware remap used by the attention kernels: the hardware hands
-// workgroup b to XCD b % 8, so logical ids are dealt out in 8 contiguous ranges, one per XCD,
-// which keeps the workgroups of one KV head on one XCD's L2.
-inline int padded_grid(int n_wgs) { return (n_wgs + kNumXcd - 1) / kNumXcd * kNumXcd; }
-// Logical id (KV head major, then split, then workgroup of the head, heaviest first) of hardware block b.
-// A KV head that spans k = 8 / Hkv XCDs has its workgroups dealt to those XCDs in turn, not in k contiguous
-// runs: every XCD then gets the same mix of heavy and light workgroups and of prefix splits (a contiguous
-// run would put all late token blocks, or a whole split, on one XCD and the light rest on its neighbour).
 __device__ __forceinline__ int logical_workgroup(unsigned b, unsigned grid, const AttnParams& p) {
-  const unsigned x = b % kNumXcd, j = b / kNumXcd;
-  const int lk = p.xcd_share_log2;
-  if (lk >= 0) return (int)((x >> lk) * (unsigned)(p.wgs_per_head * p.n_splits) + (j << lk) + (x & ((1u << lk) - 1)));  // grid = Hkv * wgs per head
-  return (int)(x * (grid / kNumXcd) + j);
+  return logical_id(b, grid, (unsigned)(p.wgs_per_head * p.n_splits), p.xcd_share_log2);
 }
 
 // Packed rows of one unit (row j of unit u: packed row 32 u + j of the KV head, j < 32): token and head of the group.

@@ -105,7 +105,7 @@ KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_row
   return waves == 8 ? KernelCost{one_per_simd ? 5.5 : 8.0, 0.28, 0, 9.4, false} : KernelCost{7.8, 0.13, 0, 4.4, false};
 }
 
-// Whether every XCD gets the same mix of a KV head's workgroups (logical_workgroup(): heads whole, or dealt to their XCDs in turn).
+// Whether every XCD gets the same mix of a KV head's workgroups (logical_id(): heads whole, or dealt to their XCDs in turn).
 bool evenly_dealt(int n_kv_heads, int wgs_per_kvh) {
   return n_kv_heads % kNumXcd == 0 || (n_kv_heads < kNumXcd && kNumXcd % n_kv_heads == 0 && wgs_per_kvh % (kNumXcd / n_kv_heads) == 0);
 }
@@ -375,7 +375,7 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     return p2;
   }
   if (pair && 4 * f.n_kv_heads <= kNumXcd) return p2;
-  // Where a piece's two workgroups of one unit a wavefront are dealt to different XCDs (logical_workgroup()), each brings its rows from beyond an L2 of its own; one
+  // Where a piece's two workgroups of one unit a wavefront are dealt to different XCDs (logical_id()), each brings its rows from beyond an L2 of its own; one
   // workgroup of two units brings them once.  Where the rows take a third of the step or more the estimates are taken as they are: 39
   // shapes of 28 heads on 4 and 12 on 4 0.74 to 0.95 of the time (27 tokens on 73K keys, 28 on 4: 60 / 48 us; 20 on 104K 73.6 / 54.1).  Not where both share an L2:
   // over 289 shapes with 8 and 16 KV heads 0.99, but single ones 0.90 to 1.15 (213 tokens on 25.6K keys, 16 on 16: 60.9 / 69.9).
@@ -387,9 +387,9 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   // keys of a unit are dealt to all wavefronts of a workgroup, and often no merge is left (32 heads on 8, 128 tokens on 1000 keys: 18.9 us,
   // 12.4 with eight wavefronts; 256 on 4187: 32.7 / 33.0; window 4 + 1020, 256 tokens 18.9 / 14).  Each unit streams all
   // its keys for itself, so that full grids are not for it: up to two workgroups per CU, and with a margin where there are many units (221
-  // tokens with the rotary embedding on 6.9K keys, 32 heads on 8, 64 wide, 28 units: 29.2 / 31.8).  Nor are long ranges, where it
-  // hangs on how the pieces of several KV heads lie in memory (15 tokens, 16 heads on 2, 64 wide: 66K keys 20.7 / 25.5, 114K 27.1 / 39.1; 8 on
-  // 2: 65.5K 24.4 / 26.8, 70K 25.1 / 20.2; 4 on 1, 64 wide: 43 tokens on 124K 28.5 / 20.3, 57 on 122K 28.3 / 40.4), nor steps of more
+  // tokens with the rotary embedding on 6.9K keys, 32 heads on 8, 64 wide, 28 units: 29.2 / 31.8).  Long ranges stay out as they did while the units of a
+  // piece lay on different XCDs and each row came from memory for every one of them (xcd_share_log2(): 15 tokens, 16 heads on 2, 64 wide, 66K
+  // keys 20.7 / 25.5, 114K 27.1 / 39.1); they have not been measured since.  So do steps of more
   // than some 35 us (32 on 8, 64 wide: 489 tokens on 3.8K 31.4 / 30.3, 510 on 5.5K 39.7 / 42.3; 8 on 2, 2038 on 1.8K 42.3 / 46.3).
   // Over 400 shapes with more than one unit or a window the steps take 0.84 of the time.
   const int64_t units = p1.units_per_head;

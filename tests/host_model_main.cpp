@@ -14,13 +14,16 @@
 //       * a row that a query of the workgroup can see is fetched unclamped, from the right place;
 //       * the pieces of all splits together cover every visible key of every row of the workgroup exactly once;
 //       * the chunk's rows are appended exactly once: the workgroups' shares of the copy, or the rows that a few-rows
-//         workgroup works on, which are all that it reads of the chunk, and none of which it fetches ahead of its work.
+//         workgroup works on, which are all that it reads of the chunk, and none of which it fetches ahead of its work;
+//       * the blocks of the grid are the workgroups, each once, and the units of a piece lie on one XCD where each streams its keys for itself.
 //  2. The planner and validate_config over a sweep of configurations (sanitizers watch the arithmetic).
 //  3. The oracle on tiny inputs, plain and windowed (sanitizers watch its indexing).
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <set>
+#include <utility>
 #include <vector>
 
 #include "../paper_2605_12471_amd/csrc/kvfold_plan.h"
@@ -205,6 +208,25 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   REQUIRE(!work || (pl.key_waves == 4 && pl.units_per_head == 1), "rows are worked on by the one workgroup of a piece");
   REQUIRE((int64_t)pl.wgs_per_head * upw_wg >= pl.units_per_head && (int64_t)pl.units_per_head * kRowsPerUnit >= (int64_t)n_tokens * G,
           "%d workgroups of %d units for %d tokens x %d heads", pl.wgs_per_head, upw_wg, n_tokens, G);
+
+  // the grid: every workgroup is one block's, and where the keys of one unit are dealt to wavefronts the units of a piece share an XCD (but for
+  // a piece that the end of an XCD's run cuts)
+  {
+    const int per_kvh = pl.wgs_per_head * pl.n_splits, grid = padded_grid(pl.n_wgs);
+    const int lk = xcd_share_log2(cfg.n_kv_heads, pl.wgs_per_head, pl.n_splits, pl.key_waves > 0);
+    std::vector<int> blocks((size_t)pl.n_wgs);
+    std::set<std::pair<int, int>> piece_on_xcd;
+    for (int b = 0; b < grid; ++b) {
+      const int lid = logical_id((unsigned)b, (unsigned)grid, (unsigned)per_kvh, lk);
+      REQUIRE(lid >= 0, "workgroup of block %d", b);
+      if (lid >= pl.n_wgs) continue;
+      blocks[(size_t)lid]++;
+      piece_on_xcd.insert({lid / pl.wgs_per_head, b % kNumXcd});
+    }
+    for (int i = 0; i < pl.n_wgs; ++i) REQUIRE(blocks[(size_t)i] == 1, "workgroup %d has %d blocks", i, blocks[(size_t)i]);
+    if (pl.key_waves && pl.n_splits > 1)
+      REQUIRE((int)piece_on_xcd.size() <= cfg.n_kv_heads * pl.n_splits + kNumXcd - 1, "%d pieces on %d XCDs together", cfg.n_kv_heads * pl.n_splits, (int)piece_on_xcd.size());
+  }
 
   // the chunk's rows, one KV head: its workgroups' shares of the copy
   std::vector<int> appended((size_t)n_tokens);
