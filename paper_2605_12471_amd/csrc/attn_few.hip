@@ -53,10 +53,12 @@ constexpr int few_lds_bytes() {
 // ROT (several units per KV head, rotary embedding, rows read as handed in): the workgroups that read a row are many, and each rotates its
 // own copy, in LDS, as it comes to the block, and the rows of the chunk that it appends; the arithmetic is the append kernel's, and so are
 // the bits.  That kernel's launch against 0.3 to 1 us in each block with rows of the chunk: 32 heads on 8, 99 tokens on 189 keys
-// 12.2 -> 11.3 us, 64 wide, 128 on 128 8.85 -> 7.42 (attention_appends() has the limits).  An instance of its own: with the code in the others
-// 64-wide workgroups of eight wavefronts had a CU to themselves, 142 registers for 110.
+// 12.2 -> 11.3 us, 64 wide, 128 on 128 8.85 -> 7.42 (attention_appends() has the limits).  An instance of its own, for the registers that it takes.
+// 64 wide: at most 128 registers, so that a CU has room for two workgroups of eight wavefronts, on which the plan counts; a row's chunks are
+// rotated one after the other for that.  With 142 registers steps of more than 256 workgroups took two rounds: 430 shapes, those 78 of
+// them 1.11 of the general kernel's time, now 0.96 (89 tokens on 7K keys, 32 heads on 8: 24.4 -> 20.4 us), the others 0.74 as before.
 template <int D, int NW, bool WIN, bool MULTI, bool ROT>
-__global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
+__global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned lds0 = (unsigned)(uintptr_t)((unsigned char __attribute__((address_space(3)))*)smem);
   constexpr int NT = NW * 64;
@@ -273,7 +275,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_few_kernel(AttnParams p) {
       const int r = l >> 1, row = key0 + r < (int)kr.row_lim ? key0 + r : (int)kr.row_lim, t = row - (int)p.len_prev;
       if (t >= 0) {
         const unsigned at_row = my_lds + (unsigned)(r * ROWB);
-#pragma unroll
+#pragma unroll D == 64 ? 1 : CH / 4
         for (int i = 0; i < CH / 4; ++i) {
           const int c = (l & 1) * (CH / 4) + i;
           const unsigned lo_at = at_row + (unsigned)((c ^ (r % KSW)) * 16), up_at = at_row + (unsigned)(((c + CH / 2) ^ (r % KSW)) * 16);

@@ -263,6 +263,16 @@ def test_kernels_use_no_scratch_memory():
             assert int(re.search(r"AGPRs: (\d+)", b).group(1)) >= 192
 
 
+def test_two_workgroups_of_64_wide_rows_fit_a_cu():
+    """The launch plan counts on two workgroups of eight wavefronts (four of four) a CU where rows are 64 wide: four wavefronts on a SIMD."""
+    if not os.path.exists(build.RESOURCE_REPORT):
+        build.build_library()
+    blocks = [b for b in open(build.RESOURCE_REPORT).read().split("Function Name: ")[1:] if "attn_few_kernelILi64" in b.splitlines()[0]]
+    assert blocks
+    for b in blocks:
+        assert int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", b).group(1)) >= 4, b.splitlines()[0]
+
+
 def test_header_is_plain_c_and_the_c_client_builds(tmp_path):
     """include/kvfold.h compiles as strict C99 on its own (no C++ or HIP in the interface), and the plain-C caller of the
     library compiles with gcc and links against the built library."""
