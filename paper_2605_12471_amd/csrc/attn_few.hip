@@ -362,6 +362,14 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
 
   // ---- the wavefronts' results meet in LDS: [wavefront][row][D] and [wavefront][row] (m, l)
   wait_vm<0>();  // (the chunk's rows are used up before the output may take their place)
+  const float l_tot = pair_sum(l_run);
+  if (__builtin_expect(n_blocks > 0 && __any(l_tot == 0.f), 0)) {
+    // rows that saw none of the wavefront's keys: O may be NaN, 0 times a value that is not finite
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] = l_tot == 0.f ? 0.f : o[db][r];
+  }
   __syncthreads();
   constexpr int OROW = D * 4 + 16;
   const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROW), mlbase = lds0 + (unsigned)(NW * kRowsPerUnit * OROW);
@@ -374,7 +382,6 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
       for (int e = 0; e < 4; ++e) v[e] = o[db][rg * 4 + e];
       *LDS_PTR(floatx4, obase + (unsigned)(m * OROW + (db * 32 + 8 * rg + 4 * hi) * 4)) = v;
     }
-  const float l_tot = pair_sum(l_run);
   if (hi == 0) *LDS_PTR(floatx2, mlbase + (unsigned)((w * kRowsPerUnit + m) * 8)) = floatx2{m_run, l_tot};
   __syncthreads();
 
@@ -384,31 +391,21 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
 #pragma unroll 1
   for (int r = tid / V; r < rows; r += NT / V) {
     floatx2 ml[NW];
-    floatx4 x[NW];
     float M = -INFINITY;
-    bool some = false;
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) {
       ml[ww] = *LDS_PTR(const floatx2, mlbase + (unsigned)((ww * kRowsPerUnit + r) * 8));
-      x[ww] = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
       M = fmaxf(M, ml[ww].x);
-      some = some || ml[ww].y == 0.f;
-    }
-    // A wavefront of whose keys the row saw none is left out: its O may be NaN, 0 times a value that is not finite.
-    if (__any(some)) {
-#pragma unroll
-      for (int ww = 0; ww < NW; ++ww)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[ww][e] = ml[ww].y == 0.f ? 0.f : x[ww][e];
     }
     float L = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) {
-      const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);
+      const floatx4 x = *LDS_PTR(const floatx4, lds0 + (unsigned)((ww * kRowsPerUnit + r) * OROW + c * 16));
+      const float f = ml[ww].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[ww].x - M);  // (0: it saw no visible key)
       L += f * ml[ww].y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += f * x[ww][e];
+      for (int e = 0; e < 4; ++e) acc[e] += f * x[e];
     }
     const int t = (int)quot((unsigned)(row0 + r), p.by_group), h = g * G + row0 + r - t * G;
     const int64_t at = (int64_t)t * Hq + h;
