@@ -93,12 +93,13 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
   const int vis_first = (int)p.len_prev + rr.row_lo + 1, vis_last = (int)p.len_prev + rr.row_hi + 1;
   const int lb_last = WIN ? vis_last - p.window : 0;  // the largest of the rows' first keys inside the window
 
-  const TileMap tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, WIN ? p.n_sink : 0, WIN ? p.window : 0);
+  TileMap tm = {0, 0, (int)(((unsigned)vis_last + kTileKeys - 1) / kTileKeys)};
+  if (MULTI) tm = tile_map(p.len_prev, rr.row_lo, rr.row_hi, WIN ? p.n_sink : 0, WIN ? p.window : 0);
   const bool fused = p.k_new != nullptr;
   const KeyRange kr = key_range(tm, split, p.tiles_per_split, p.len_prev, C, fused);
   // Blocks of 32 keys of the logical tiles, and the first key of one; the last block of the last tile may lie beyond every row.
   auto first_key = [&](int b) __attribute__((always_inline)) -> int { return b * 32 + (WIN && (b >> 1) >= tm.ns_t ? tm.skip * kTileKeys : 0); };
-  const int b_all = MULTI ? 2 * tm.ntiles - (first_key(2 * tm.ntiles - 1) >= vis_last ? 1 : 0) : (vis_last + 31) / 32;
+  const int b_all = MULTI ? 2 * tm.ntiles - (first_key(2 * tm.ntiles - 1) >= vis_last ? 1 : 0) : (int)(((unsigned)vis_last + 31) / 32);
   const int b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
 
   const unsigned head_bytes = (unsigned)p.capacity * (unsigned)ROWB;  // (below 2^32, as the host checks)
@@ -123,8 +124,12 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
     if (__builtin_expect(plain(b), 1)) {
       const bool nw = MULTI && (unsigned)key0 >= kr.chunk_row0;  // rows of the chunk as handed in (fused append)
       const unsigned stride = nw ? new_stride : (unsigned)ROWB;
-      const unsigned char* base = (nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase)) + (uint64_t)((unsigned)key0 - (nw ? kr.chunk_row0 : 0u)) * stride;
+      const unsigned char* base = nw ? (is_v ? vnew : knew) : (is_v ? vbase : kbase);
       unsigned off = (unsigned)lrow * stride;
+      if (MULTI)
+        base += (uint64_t)((unsigned)key0 - (nw ? kr.chunk_row0 : 0u)) * stride;
+      else
+        off += (unsigned)key0 * ROWB;
 #pragma unroll
       for (int i = 0; i < SLABS; ++i) {
         dma16(base, off + ((is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16), lds + (unsigned)(i * 1024));
@@ -133,7 +138,7 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
     } else {
 #pragma unroll 1
       for (int i = 0; i < SLABS; ++i) {
-        const DmaRow src = dma_row(kr, key0 / kTileKeys, key0 % kTileKeys + lrow + i * RPS);
+        const DmaRow src = dma_row(kr, (int)((unsigned)key0 / kTileKeys), (int)((unsigned)key0 % kTileKeys) + lrow + i * RPS);
         const unsigned c16 = (is_v ? chunk : chunk ^ (unsigned)((i * RPS) % KSW)) * 16;
         if (src.from_chunk)
           dma16(is_v ? vnew : knew, src.row * new_stride + c16, lds + (unsigned)(i * 1024));
@@ -200,12 +205,22 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
     }
   }
 
-  // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes of a K row and of the V row per thread and turn, loaded
-  // here and stored behind the results.  (One unit per KV head: at most 32 rows, all loaded here, so that the output may lie on
-  // them.  Stored here, 16 layers of one token on 4K keys take 170.6 us, not 168.7: the first tiles wait for these rows as well.)
+  // ---- fused append: this workgroup's share of the chunk's rows, 16 bytes per thread and turn.  One unit per KV head: here, ahead of the
+  // output, which may lie on them.  Several: loaded here, a K and a V row at a time, and stored behind the results.  (The one unit's
+  // behind its results as well: one token on 17 to 12K keys 1.005 of the time, with the rotary embedding 1.011.)
+  if (!MULTI && fused) {
+    const int r0 = split * p.copy_rows, r1 = r0 + p.copy_rows < C ? r0 + p.copy_rows : C;
+    const int nvec = (r1 > r0 ? r1 - r0 : 0) * CH;
+    for (int i = tid; i < 2 * nvec; i += NT) {
+      const bool is_v = i >= nvec;
+      const int e = is_v ? i - nvec : i, r = r0 + e / CH, c = e % CH;
+      const uintx4 x = *reinterpret_cast<const uintx4*>((is_v ? vnew : knew) + (int64_t)r * new_stride + c * 16);
+      __builtin_nontemporal_store(x, reinterpret_cast<uintx4*>(const_cast<unsigned char*>(is_v ? vbase : kbase) + (p.len_prev + r) * ROWB + c * 16));
+    }
+  }
   constexpr int kCopyRows = NT / CH, kCopyTurns = kCopyRows >= kRowsPerUnit ? 1 : kRowsPerUnit / kCopyRows;
-  const int copy_r0 = fused ? rem * p.copy_rows : 0;
-  const int copy_r1 = fused ? (copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C) : 0;
+  const int copy_r0 = MULTI && fused ? rem * p.copy_rows : 0;
+  const int copy_r1 = MULTI && fused ? (copy_r0 + p.copy_rows < C ? copy_r0 + p.copy_rows : C) : 0;
   uintx4 copy_k[kCopyTurns] = {}, copy_v[kCopyTurns] = {};
   auto copy_load = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
@@ -239,7 +254,7 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
     }
   };
 
-  copy_load(copy_r0);
+  if (MULTI) copy_load(copy_r0);
 
   // ---- LDS read offsets (general kernel's layouts): K fragment ks, row m, chunk 2 ks + hi; V^T by the transpose read, lane i
   // of a 16-lane group supplies row i / 4 of a 4-row group and 4 columns
@@ -422,12 +437,13 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : 2) attn_few_kernel(Attn
     }
   }
 
-  copy_store(copy_r0);
-  if (MULTI)
+  if (MULTI) {
+    copy_store(copy_r0);
     for (int r0 = copy_r0 + kCopyTurns * kCopyRows; r0 < copy_r1; r0 += kCopyTurns * kCopyRows) {
       copy_load(r0);
       copy_store(r0);
     }
+  }
 }
 
 template <int D, int NW, bool WIN, bool MULTI, bool ROT>
