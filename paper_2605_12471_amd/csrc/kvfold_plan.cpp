@@ -392,12 +392,18 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
   // keys 20.7 / 25.5, 114K 27.1 / 39.1); they have not been measured since.  So do steps of more
   // than some 35 us (32 on 8, 64 wide: 489 tokens on 3.8K 31.4 / 30.3, 510 on 5.5K 39.7 / 42.3; 8 on 2, 2038 on 1.8K 42.3 / 46.3).
   // Over 400 shapes with more than one unit or a window the steps take 0.84 of the time.
+  // (With one query head per KV head a unit's rows are 32 tokens, and with the rotary embedding each of eight wavefronts loads the angles of all of them:
+  // 8 heads on 8, 38 tokens on 152 keys 13.0 us general, 14.7 with eight, 13.1 with four.  The plan does not ask for the embedding, so that a
+  // rotated step has the bits of the step on rotated rows; eight wavefronts have to be 0.4 us better there.  Over 800 shapes steps with
+  // the embedding take 0.834 of the general kernels' time, 0.853 without this, 3 of them more than 3 % longer than there instead of 17; plain ones 0.770,
+  // 0.763 without.)
   const int64_t units = p1.units_per_head;
   const bool long_range = window <= 0 && (f.n_kv_heads > 1 ? len_after > 48 * 1024 : units * len_after > 800000);
   if (c.tune_pair_units == 0 && units * f.n_kv_heads <= 2 * (int64_t)c.n_cu && !long_range && best.est_us < 39.0)
     for (int waves : {8, 4}) {
       if (waves == 4 && window > 0) continue;
-      const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, waves);
+      Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, waves);
+      if (waves == 8 && f.n_q_heads == f.n_kv_heads && window <= 0) pk.est_us += 0.4 * f.head_dim / 128;
       if (pk.est_us < best.est_us * (best.key_waves ? 1.0 : units > 16 ? 0.9 : 0.95)) best = pk;
     }
   return best;

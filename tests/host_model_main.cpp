@@ -366,6 +366,18 @@ static void planner_sweep() {
   std::printf("planner: %ld plans\n", n);
 }
 
+// One query head per KV head: each of eight wavefronts would load the rotary angles of 32 tokens (13.0 us before, 14.7 with eight, and the like).
+static void plans_of_single_heads() {
+  struct { int heads, n; int64_t len_prev; } slow[] = {{8, 38, 152}, {8, 36, 102}, {8, 40, 391}};
+  for (auto& t : slow) {
+    PlanCtx pc{};
+    pc.cfg = make_cfg(t.heads, t.heads, 128, 256, 131072, KVFOLD_BF16);
+    pc.ws_rows = workspace_rows(&pc.cfg);
+    pc.n_cu = 256;
+    REQUIRE(make_plan(pc, t.n, t.len_prev + t.n, 0, 0).key_waves != 8, "%d tokens on %lld keys", t.n, (long long)t.len_prev);
+  }
+}
+
 static void oracle_tiny() {
   const int64_t Hq = 4, Hkv = 2, d = 8, cap = 40, C = 9, len_prev = 31;
   std::vector<double> K((size_t)Hkv * cap * d), V(K.size()), q((size_t)C * Hq * d);
@@ -404,6 +416,7 @@ static void oracle_tiny() {
 int main() {
   model_sweep();
   planner_sweep();
+  plans_of_single_heads();
   oracle_tiny();
   std::printf("ok: %ld checks\n", g_checks);
   return 0;
