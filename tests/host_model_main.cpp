@@ -5,8 +5,8 @@
 //     kvfold_consts.h (workgroup_rows, tile_map, key_range, dma_row) and the launch geometry in the planner;
 //     both are used here exactly as the kernels use them.  For many shapes -- chunk length, cache length, group
 //     size, prefix splits, units per wavefront (fp32: wavefronts per workgroup), fused append or not, plain and
-//     sink + sliding-window steps, few rows that need work on their way (rotary embedding, storage round trip) -- every
-//     workgroup's pieces are walked as its kernel walks them -- the general bf16
+//     sink + sliding-window steps, few rows that need work on their way (rotary embedding, storage round trip), several units that rotate
+//     the chunk's rows themselves -- every workgroup's pieces are walked as its kernel walks them -- the general bf16
 //     kernel's ring with its run-ahead and the last tile fetched again past the end, the few-rows kernel's blocks of
 //     32 keys in cyclic order, the fp32 kernel's half tiles with their two sources -- and checked:
 //       * every DMA source row lies inside what exists (cache rows below len_prev when the chunk's rows are not
@@ -39,7 +39,7 @@ int kvfold_oracle_append_bytes(unsigned char*, int64_t, int64_t, int64_t, int64_
 
 using namespace kvfold;
 
-static long g_checks = 0;
+static long g_checks = 0, g_rotated = 0;  // g_rotated: steps whose readers rotate the chunk's rows
 #define REQUIRE(cond, ...)                                   \
   do {                                                       \
     ++g_checks;                                              \
@@ -192,7 +192,10 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   const Plan pl = make_plan(pc, n_tokens, len_after, n_sink, window);
   const bool fused = attention_appends(pc, pl, n_tokens, rope), work = attention_works_on_rows(pc, pl, n_tokens, rope);
   REQUIRE(!(fused && work), "appended twice");
-  REQUIRE(cfg.dtype != KVFOLD_BF16 || fused == fused_append_applies(pc, n_tokens, len_prev, rope), "what kvfold_plan_t reports");
+  const bool rotates = rope && fused;  // several units read the chunk's rows as handed in, and rotate what they read and append
+  REQUIRE(cfg.dtype != KVFOLD_BF16 || rotates || fused == fused_append_applies(pc, n_tokens, len_prev, rope), "what kvfold_plan_t reports");
+  REQUIRE(!rotates || (cfg.dtype == KVFOLD_BF16 && pl.key_waves && pl.units_per_head > 1 && window <= 0 && storage_bits == 0), "rows rotated by their readers");
+  if (rotates) ++g_rotated;
   const int G = cfg.n_q_heads / cfg.n_kv_heads;
   const int upw_wg = pl.key_waves ? 1 : pl.waves_per_wg * pl.units_per_wave;
   const int row_bytes = cfg.head_dim * elem_size(cfg.dtype);
@@ -304,27 +307,30 @@ static void model_sweep() {
   const int64_t prefixes[] = {0, 63, 64, 500, 1024, 5000};
   const int64_t windows[][2] = {{0, 0}, {4, 1020}, {0, 1}, {4, 1}, {1, 33}, {70, 50}, {130, 129}, {0, 1 << 20}};
   long steps = 0;
-  for (auto& h : heads)
-    for (int C : chunks)
-      for (int64_t Lp : prefixes)
-        for (auto& w : windows)
-          for (int dtype : {(int)KVFOLD_BF16, (int)KVFOLD_F32}) {
-            kvfold_config_t cfg = make_cfg(h[0], h[1], 128, C, Lp + C, dtype);
-            REQUIRE(validate_config(&cfg) == KVFOLD_OK, "config");
-            for (int splits : {0, 2, 5})
-              for (int upw : {0, 1, 2}) {
-                if (splits > 0 && (int64_t)splits * C * h[0] > workspace_rows(&cfg)) continue;
-                walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw);
-                ++steps;
-                // rows with work on their way: few rows of bf16, and fp32 behind the append kernel
-                const bool few = dtype == KVFOLD_BF16 && units_of_head(C, h[0] / h[1]) == 1;
-                for (int work : {1, 2, 3}) {
-                  if (w[1] > 0 || !(few || (dtype == KVFOLD_F32 && work == 1))) continue;
-                  walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw, (work & 1) != 0, work & 2 ? 8 : 0);
+  for (int d : {128, 64})
+    for (auto& h : heads)
+      for (int C : chunks)
+        for (int64_t Lp : prefixes)
+          for (auto& w : windows)
+            for (int dtype : {(int)KVFOLD_BF16, (int)KVFOLD_F32}) {
+              kvfold_config_t cfg = make_cfg(h[0], h[1], d, C, Lp + C, dtype);
+              REQUIRE(validate_config(&cfg) == KVFOLD_OK, "config");
+              for (int splits : {0, 2, 5})
+                for (int upw : {0, 1, 2}) {
+                  if (splits > 0 && (int64_t)splits * C * h[0] > workspace_rows(&cfg)) continue;
+                  if (d == 64 && (splits > 0 || upw > 0)) continue;  // (the widths differ in the plan's own choice)
+                  walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw);
                   ++steps;
+                  // rows with work on their way: few rows of bf16, several units with the rotary embedding alone, and fp32 behind the append kernel
+                  const bool few = dtype == KVFOLD_BF16 && units_of_head(C, h[0] / h[1]) == 1;
+                  for (int work : {1, 2, 3}) {
+                    if (w[1] > 0 || !(few || work == 1)) continue;
+                    walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw, (work & 1) != 0, work & 2 ? 8 : 0);
+                    ++steps;
+                  }
                 }
-              }
-          }
+            }
+  REQUIRE(g_rotated >= 50, "%ld steps rotate the chunk's rows where they are read", g_rotated);
   // the benchmark's shapes at their real sizes, plain and with the streaming baseline's window
   struct { int Hq, Hkv, C; int64_t Lp; } big[] = {{32, 8, 2048, 14336}, {32, 8, 256, 130816}, {32, 8, 4096, 126976},
                                                  {28, 4, 128, 65408}, {28, 4, 8192, 57344}, {32, 8, 16, 131056}, {32, 8, 1, 131071}};

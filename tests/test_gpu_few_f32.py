@@ -1,6 +1,7 @@
 """fp32 steps whose workgroups deal the keys of one 32-row unit to their wavefronts: every row against the oracle, with the launch plan's
 own choice, which is checked to be this kernel's."""
 import pytest
+import torch
 
 import paper_2605_12471_amd as kv
 from paper_2605_12471_amd import binding
@@ -69,27 +70,41 @@ def test_numbers_that_the_terms_can_and_cannot_hold(d, n, hq, hkv, check):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_rows_beyond_the_terms_with_the_rotary_embedding_and_under_a_window(H, oracle, d):
+    """The same for the fp32 instructions' own rotation of the queries, for a window that passes over such a value, and for rows that do not see
+    a key that is not finite."""
+    assert _one_unit_workgroups(4, 2, d, [100]) == [True]
+    terms.test_values_and_queries_beyond_the_terms_with_the_rotary_embedding(H, oracle, d, 0)
+    assert _one_unit_workgroups(4, 2, d, [300], (2, 40)) == [True]
+    terms.test_values_beyond_the_terms_under_a_window(H, oracle, d, 0, 0)
+    assert _one_unit_workgroups(4, 2, d, [200]) == [True]
+    terms.test_rows_do_not_notice_what_they_do_not_see(d, 0, 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_more_blocks_with_odd_keys_than_a_wavefront_lists(H, d):
     """A value beyond the terms' range in every block of 32 keys: the whole piece goes through the fp32 instructions.  Column 5 of the output is
-    that value's, 2^100 times the mean weight of one key in 32; the other columns keep their tolerance."""
+    2^100 times the weight of these keys together, against 64 bits; the other columns keep their tolerance."""
     h, n, prev = 256, 1, 36 * 32 * (8 if d == 64 else 4)  # one workgroup a head: 36 blocks a wavefront
     rc, pl = kv.kvfold_plan_for(binding.make_config(1, h, h, d, 64, prev + n, kv.KVFOLD_F32), 256, n, prev + n)
     assert rc == 0 and pl.n_splits == 1 and pl.n_workgroups == h
     cfg = I.FoldConfig("few_f32_odd", 82, 1, h, h, d, n, 0, "f32")
     outs = []
+    q, k, v = I.chunk_qkv(cfg, 0, 0, n_tokens=n, token_base=0)
     for odd in (False, True):
         gpu = H.GpuFold(cfg, capacity=prev + n, chunk_tokens=64)
         K, V = gpu.cache.view(0)
-        q, k, v = I.chunk_qkv(cfg, 0, 0, n_tokens=n, token_base=0)
         for t, part in ((K, 1), (V, 2)):
             t[:, :prev].copy_(terms._random(prev, h, d, part).transpose(0, 1))
         if odd:
             V[:, 0:prev:32, 5] = 2.0 ** 100
         gpu.cache.set_length(-1, prev)
         outs.append(gpu.step(0, q, k, v).cpu().double())
+        logits = torch.cat([(K[:, :prev].double() @ q[0].cuda().double()[..., None])[..., 0].cpu(), (q[0].double() * k[0].double()).sum(-1, keepdim=True)], 1)
         gpu.close()
     plain, with_odd = outs
     rest = [c for c in range(d) if c != 5]
     assert (with_odd - plain)[..., rest].abs().max() <= 1e-5
-    share = with_odd[..., 5] / 2.0 ** 100
-    assert (share > 1 / 64).all() and (share < 1 / 16).all()
+    weights = torch.softmax(logits / d ** 0.5, 1)
+    share = with_odd[0, :, 5] / 2.0 ** 100  # (the other keys' values are 2^-100 of it)
+    assert (share / weights[:, 0:prev:32].sum(1) - 1.0).abs().max() <= 1e-5  # (the mode's tolerance)
