@@ -15,9 +15,9 @@
 //    to 16 KB in flight, are more than memory can deliver;
 //  * the loop is not unrolled or pipelined: code that runs once is fetched at about 3 bytes per ns.
 // The price: every unit brings its own copy of each K and V block into LDS, 16 KB where a general workgroup shares them among
-// four or eight units.  Eight blocks of 128-wide rows take a CU 1.45 us, what LDS needs for them (1024 cycles of fragment reads for K
-// and V each, 2048 for the copies that come in), so grids of more than two workgroups per CU and long key ranges stay with the
-// general kernel (choose_plan()).
+// four or eight units.  Eight blocks of 128-wide rows take a full CU 1.45 us (1.15 in the fit to whole steps, plan_key_waves()), so grids of
+// more than two workgroups per CU stay with the general kernel (choose_plan()), and the units of a piece belong on one XCD, whose L2 has the
+// rows for all of them (xcd_share_log2()).
 // One token, 32 heads on 8, D = 128, whole step, general kernel -> this one: 1K keys 12.5 -> 11.8 us (unsplit, one launch
 // instead of two), 4K 15.6 -> 13.5, 16K 23.0 -> 18.8, 32K 33.5 -> 29.8, 128K 102.5 -> 95 us (5.9 TB/s; a plain streaming
 // read gets 5.8 to 6.2).  With the start in 32-bit arithmetic, the faster merge and pieces of even numbers of tiles: 1K 9.4 us, 4K

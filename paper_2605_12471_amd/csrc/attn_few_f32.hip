@@ -7,12 +7,14 @@
 // piece with one wavefront's chain: split, products, softmax and split again, 8 us per 64 keys.  Here every wavefront has keys of its own
 // and nothing to wait for until the results meet in LDS:
 //  * K blocks of 32 keys come into LDS of the wavefront's own by direct copies; V comes into registers, whole rows per half-wave (the
-//    columns of a matrix instruction's 32 are every fourth or every second one of the head); both while the block before is worked off;
+//    columns of a matrix instruction's 32 are every fourth or every second one of the head); both a block ahead;
 //  * the queries' terms are formed once per workgroup, a share in each wavefront, and read from LDS as they are used;
 //  * the split of the next operands stands behind the matrix instructions of these, in an order that the compiler keeps: one
 //    wavefront alone issues a vector instruction every 5.2 cycles and hides six of them under a matrix instruction's 32.
-// What bounds it: one CU gets some 37 GB/s from beyond its XCD's L2, 32 keys of 128-wide rows for four wavefronts in 3.6 us, so that
-// a step wants its keys on many CUs; 30K keys and more are bound by memory.  Four wavefronts where rows are 128 wide (eight have 256
+// What bounds it: 32 keys of 128-wide rows for each of four wavefronts take a CU 3.6 us, some 37 GB/s from beyond its XCD's L2, so that
+// a step wants its keys on many CUs; 30K keys and more are bound by memory.  (That is this loop's rate, not the chip's: 128 wide, the wait for
+// a block's values waits for the copies of the next keys as well, which were asked for behind them, and nothing is on its way through
+// softmax and P V.  attn_few.hip's blocks come at 46 GB/s a CU.)  Four wavefronts where rows are 128 wide (eight have 256
 // registers each and spill: one token on 30K keys 76 us, four 58), eight where they are 64 wide, one workgroup per CU.
 // Captured steps, the better form of the general kernel -> this one: 32 heads on 8, one token on 300 / 4187 / 30K keys 15.5 -> 12.5,
 // 28.1 -> 19.9, 91.8 -> 58.2 us (4.2 TB/s); 37 tokens on 300 20.0 -> 14.9; 8 heads on 2, one token on 30K 54.4 -> 27.9; 64 wide, 4 on
