@@ -37,13 +37,13 @@ PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA (256 CU x 4096 FLOP/clk x 2
 PEAK_F32_MODE_TFLOPS = PEAK_BF16_TFLOPS / 7   # an fp32 product is eight (Q K^T) or six (P V) bf16 products of terms
 PEAK_HBM_GBS = 8000.0
 
-KERNEL_SOURCES = ("attn_bf16.hip", "wave_ops.h", "kvfold_internal.h", "kvfold_consts.h")
+KERNEL_SOURCES = ("attn_bf16.hip", "attn_few.hip", "append_rows.h", "wave_ops.h", "kvfold_internal.h", "kvfold_consts.h", "kvfold_plan.cpp", "kvfold_plan.h")
 
 
 def kernel_source_hash():
-    """Short hash of the attention kernel's code -- its sources with comments and white space taken out: a measured
-    HBM-traffic figure is only reported for the kernel it was measured on, and rewording a comment does not make
-    it another kernel."""
+    """Short hash of the code of the bf16 attention kernels and of the plan that chooses between them -- the sources with comments and
+    white space taken out: a measured HBM-traffic figure is only reported for the kernels and launches it was measured on, and
+    rewording a comment does not make it others."""
     h = hashlib.sha256()
     for name in KERNEL_SOURCES:
         with open(os.path.join(ROOT, "paper_2605_12471_amd", "csrc", name), "r") as f:
