@@ -340,12 +340,12 @@ Plan choose_plan(const PlanCtx& c, int n_tokens, int64_t len_after, int n_sink, 
     // Few units on not too many keys: the kernel that deals a unit's keys to its wavefronts leaves the 416 shapes at
     // 0.82 of the time, one of them 4 % slower (64 heads on 8, 64 wide, 13 tokens on 15.7K keys 38.9 / 40.4 us).  One token, 32 heads on 8: 300 keys 15.5 -> 12.5 us, 4187 28 -> 19.9, 30K 92 -> 58; 128 tokens, 4 heads on 1, 64 wide, no keys 12.0 -> 7.5.  Every
     // unit splits the keys into terms anew, so that the gain is gone where many units have many keys (128 wide, 128 tokens, 8 heads on 2
-    // = 32 units on 4.2K keys 39.9 / 30.9 us, on 20K 78 / 93; 64 wide, 37 tokens, 32 heads on 8 = 40 units on 30K 84 / 89), and
-    // a single block of 32 keys has nothing to deal (128 wide 9.2 / 10.1 us, 64 wide 6.8 / 7.8; 34 keys 13.3 / 11.2).  The line between is
-    // drawn by the product of units and keys, with the units of a piece on different XCDs (xcd_share_log2()) and for 32 units and more; 5 to 16 units in
-    // all on longer caches stay with the general kernel without having been measured there.
+    // = 32 units on 4.2K keys 39.9 / 30.9 us, on 20K 78 / 93; 64 wide, 37 tokens, 32 heads on 8 = 40 units on 30K 84 / 89; three and four units a
+    // head beyond the line 0.97 to 1.10 of the time, 10 tokens on 65K, 28 heads on 4, 113.6 / 124.5; two of them 0.78 to 0.89), and
+    // a single block of 32 keys has nothing to deal (128 wide 9.2 / 10.1 us, 64 wide 6.8 / 7.8; 34 keys 13.3 / 11.2).  The line is
+    // drawn by the product of units and keys; 5 to 16 units in all on longer caches stay with the general kernel without having been measured there.
     const int64_t units = w4.units_per_head, all_units = units * f.n_kv_heads, keys = (int64_t)w4.tiles_per_split * w4.n_splits * kTileKeys;
-    if (len_after <= 32 || all_units > 2 * (int64_t)c.n_cu || (units > 4 && all_units * keys > (f.head_dim == 128 ? 400000 : 600000))) return best;
+    if (len_after <= 32 || all_units > 2 * (int64_t)c.n_cu || (units > 2 && all_units * keys > (f.head_dim == 128 ? 400000 : 600000))) return best;
     const Plan pk = plan_with(c, n_tokens, len_after, 1, n_sink, window, kUnitsPerWg, f.head_dim == 64 ? 8 : 4);
     return pk.est_us < best.est_us * 0.95 ? pk : best;
   }

@@ -122,3 +122,16 @@ def test_fp32_keys_are_dealt_to_wavefronts_where_units_are_few(hq, hkv, d, n, pr
 ])
 def test_two_units_a_wavefront_where_a_piece_would_be_read_twice(hq, hkv, d, n, prev, units):
     assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).units_per_wave == units
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev,dealt", [
+    (28, 4, 128, 10, 65536, False),    # 113.6 us / 124.5 with a unit's keys dealt to the wavefronts
+    (16, 16, 64, 124, 15584, False),   # 71.7 / 77.5
+    (12, 4, 64, 39, 55847, False),     # 63.1 / 68.0
+    (8, 2, 128, 22, 62438, True),      # 105.2 without / 63.4: few units in all
+    (32, 8, 128, 11, 26579, True),     # 87.1 / 77.0: two units a head
+])
+def test_fp32_keys_of_three_and_four_units_a_head_on_long_caches(hq, hkv, d, n, prev, dealt):
+    plan = _plan(kv.KVFOLD_F32, hq, hkv, d, n, prev)
+    units = -(-n * (hq // hkv) // 32)
+    assert (plan.n_workgroups == hkv * units * plan.n_splits) == dealt
