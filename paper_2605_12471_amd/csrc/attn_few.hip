@@ -3,8 +3,8 @@
 // scale * log2(e) and rounded once more, P = 2^(S - m) rounded to bf16 for P V, row sums in fp32 from the unrounded P, the reference
 // m stale by at most 2^16.
 //
-// Two kinds of step are for it.  Few rows (C G <= 32: decoding, one token or a few at a time, every key visible up to the row's own
-// position) read every key once and compute next to nothing: they are bound by memory when the cache is long and by what a launch does
+// Two kinds of step are for it.  Few rows (C G <= 32, a few tokens at a time, every key visible up to the row's own position; at most 16 rows,
+// and all of them 64 wide, have a kernel of their own by now, attn_decode.hip; the figures of one token below are from before) read every key once and compute next to nothing: they are bound by memory when the cache is long and by what a launch does
 // once when it is short.  A few units per KV head on not too many keys, or under a window, are bound by the chain of a wavefront: the
 // general kernel walks a piece tile by tile with its four wavefronts side by side on four units, behind a software pipeline whose start
 // and code cost more than a short step's work, and needs a split and its merge to fill the chip.  Here
@@ -462,8 +462,8 @@ static hipError_t prepare_few_one() {
 }
 template <int D>
 static hipError_t prepare_few() {
-  hipError_t e = prepare_few_one<D, 4, false, false, false>();
-  if (e == hipSuccess) e = prepare_few_one<D, 4, false, true, false>();
+  hipError_t e = prepare_few_one<D, 4, false, true, false>();
+  if (D == 128 && e == hipSuccess) e = prepare_few_one<128, 4, false, false, false>();
   if (e == hipSuccess) e = prepare_few_one<D, 4, false, true, true>();
   if (e == hipSuccess) e = prepare_few_one<D, 8, false, true, false>();
   if (e == hipSuccess) e = prepare_few_one<D, 8, false, true, true>();
@@ -479,8 +479,8 @@ static void launch_few_one(const AttnParams& p, hipStream_t s) {
 template <int D>
 static void launch_few(const AttnParams& p, int key_waves, hipStream_t s) {
   const bool rotate = p.k_new && p.rope_cos;
-  if (key_waves == 4 && p.units_per_head == 1)
-    launch_few_one<D, 4, false, false, false>(p, s);
+  if (D == 128 && key_waves == 4 && p.units_per_head == 1)  // (64 wide: attn_decode.hip)
+    launch_few_one<128, 4, false, false, false>(p, s);
   else if (key_waves == 4)
     rotate ? launch_few_one<D, 4, false, true, true>(p, s) : launch_few_one<D, 4, false, true, false>(p, s);
   else if (p.window > 0)

@@ -310,6 +310,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     e = launch_attn_few_f32(at, f.head_dim, s);
   else if (f.dtype != KVFOLD_BF16)
     e = launch_attn_f32(at, f.head_dim, pl.waves_per_wg, s);
+  else if (pl.direct)
+    e = launch_attn_decode(at, f.head_dim, s);
   else if (pl.key_waves)
     e = launch_attn_few(at, f.head_dim, pl.key_waves, s);
   else

@@ -108,7 +108,9 @@ hipError_t prepare_attn_bf16(int head_dim);
 // The kernel whose workgroups deal the keys of one unit to key_waves wavefronts (4, or 8, which a window asks for); prepare as above.
 hipError_t launch_attn_few(const AttnParams& p, int head_dim, int key_waves, hipStream_t s);
 hipError_t prepare_attn_few(int head_dim);
-// The same in fp32: four wavefronts, eight where heads are 64 wide.
+// One unit per KV head, no window: at most 16 packed rows, 32 where heads are 64 wide (Plan::direct).
+hipError_t launch_attn_decode(const AttnParams& p, int head_dim, hipStream_t s);
+// The same as launch_attn_few in fp32: four wavefronts, eight where heads are 64 wide.
 hipError_t launch_attn_few_f32(const AttnParams& p, int head_dim, hipStream_t s);
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, int waves_per_wg, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);

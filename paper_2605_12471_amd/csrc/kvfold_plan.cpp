@@ -91,7 +91,7 @@ struct KernelCost {
   bool two_per_cu;
 };
 KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_rows, double with_rows) {
-  if (few_rows) return head_dim == 64 ? KernelCost{0.34, 0.34, 0.34, 3.4, true} : KernelCost{0.46, 0.46, 0.46, 4.6, true};
+  if (few_rows) return KernelCost{0.46, 0.46, 0.46, 4.6, true};  // (128 wide; 64 wide: plan_direct())
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
     if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
@@ -180,6 +180,35 @@ void plan_key_waves_f32(const PlanCtx& c, int64_t rows, int64_t base, int ntiles
   }
 }
 
+// The same for the kernel whose keys come straight into registers (attn_decode.hip).  A piece's chain and the rows' way from memory overlap
+// in part; per tile a CU's workgroups share its way to the L2, and neither odd numbers of tiles nor, below them, the blocks of a
+// wavefront make a difference.  Fitted to 2200 measured steps (captured graphs, caches from memory): 142 shapes (1 to 64
+// heads, 1 to 16 tokens on 64 to 131K keys), every split count; the choice is 0.6 % above the best of these on average (64 wide 0.2
+// %), 5 % at most; with the few-rows kernel's figures 1.0 % and 8 % (one token on 4187 keys, 32 heads on 8, 17 pieces 9.91 us, 22 9.30).
+void plan_direct(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64_t s_max, double len_after, int64_t& s, double& est_us) {
+  struct Cost {
+    double start_end, tile, bytes_per_us, uneven, round, merge, merge_bytes_per_us;
+  };
+  const Cost k = c.cfg.head_dim == 128 ? Cost{2.73, 0.595, 7.45e6, 0.29, 1.62, 3.33, 1.60e6} : Cost{2.74, 0.353, 8.0e6, 0.28, 2.25, 3.12, 1.40e6};
+  // (long caches, where 26 to 64 pieces of 8 heads are within 2 % of one another, have two workgroups per CU in flight)
+  const double kAlone = 1.02;
+  const double kv_us = 4.0 * c.cfg.n_kv_heads * c.cfg.head_dim * len_after / k.bytes_per_us;
+  est_us = 1e30;
+  for (int64_t cand = 1; cand <= s_max; ++cand) {
+    const int64_t tps = (ntiles + cand - 1) / cand;
+    if ((ntiles + tps - 1) / tps != cand) continue;
+    const double w = (double)(base * cand), per_cu = std::ceil(w / c.n_cu);
+    const double chain = per_cu * (double)tps * k.tile;
+    const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : kAlone);
+    double t = k.start_end + std::sqrt(chain * chain + mem * mem) + (per_cu > 2.0 ? k.round : 0.0);
+    if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
+    if (t < est_us) {
+      est_us = t;
+      s = cand;
+    }
+  }
+}
+
 // Launch geometry for `upw` units per wavefront and `waves` wavefronts per workgroup: the split count with the smallest
 // estimated time (a forced split count overrides that).
 Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n_sink, int64_t window,
@@ -195,6 +224,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.key_waves = key_waves;
   const bool few_rows = f.dtype == KVFOLD_BF16 && key_waves == 4 && pl.units_per_head == 1 && window <= 0;
   pl.few_rows = few_rows;
+  pl.direct = few_rows && (f.head_dim == 64 || n_tokens * G <= 16);
   const int per_wg = key_waves > 0 ? 1 : waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
@@ -248,6 +278,10 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
     if (key_waves > 0 && f.dtype != KVFOLD_BF16) {
       plan_key_waves_f32(c, rows, base, ntiles, s_max, key_waves, window > 0 ? std::min((double)len_after, (double)ntiles * kTileKeys) : (double)len_after,
                          window > 0 ? 1.0 : ((double)len_after - 0.5 * n_tokens) / (double)len_after, s, pl.est_us);
+      return finish_plan(pl, s, s_max, ntiles, base);
+    }
+    if (pl.direct) {
+      plan_direct(c, rows, base, ntiles, s_max, (double)len_after, s, pl.est_us);
       return finish_plan(pl, s, s_max, ntiles, base);
     }
     if (key_waves > 0 && !few_rows) {

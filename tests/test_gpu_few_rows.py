@@ -22,6 +22,14 @@ def test_edges_of_blocks_tiles_and_rows(H, oracle, d, G, Hkv, splits):
     _run_case(H, oracle, cfg, [1, n, 31, 1, n, 61 - n, 1, 1, 200, n, 1, max(1, n - 1), 1], splits=splits)
 
 
+@pytest.mark.parametrize("G,d", [(16, 128), (17, 128), (16, 64), (17, 64)])
+def test_sixteen_rows_and_more(H, oracle, G, d):
+    """16 rows of 128 columns and 32 of 64 have their keys straight from memory; a wavefront's blocks from none to a handful, odd and
+    even numbers, the last one with rows of the chunk, beyond it, or neither."""
+    cfg = I.FoldConfig("few16", 67, 1, G, 1, d, 160, 0, "bf16")
+    _run_case(H, oracle, cfg, [1, 1, 30, 1, 95, 1, 1, 127, 1, 160, 1, 94, 1, 1], splits=1)
+
+
 @pytest.mark.parametrize("profile", sorted(I.LOGIT_PROFILES))
 def test_logit_jumps(H, oracle, profile):
     cfg = I.FoldConfig("few_jump", 66, 1, 4, 1, 128, 400, 0, "bf16")
