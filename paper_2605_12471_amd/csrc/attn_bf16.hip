@@ -101,10 +101,13 @@ __device__ __forceinline__ void mfma_settle_a(floatx16& x) {
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+a"(x));
 }
 
-// V ring slots (the K ring has one more): three for the two-unit kernel, one workgroup per CU, 112 KB of
-// LDS; two for the one-unit kernel so that two workgroups share a CU's 160 KB.  A deeper ring bought
-// nothing in measurements, neither on L2-resident prefixes nor on HBM-bound decode-shaped steps.
-constexpr int kRingTwoUnits = 3, kRingOneUnit = 2;
+// V ring slots (the K ring has one more): three where one workgroup has a CU to itself, 112 KB of LDS (the two-unit kernel, and the
+// one-unit kernel in grids that leave no CU two of them); two for the one-unit kernel else, so that two workgroups share a CU's 160 KB
+// (64 wide three or four).  With two slots a tile is asked for one tile's time ahead of its use, which a workgroup alone on its CU spends
+// waiting: 37 tokens, 32 heads on 8, on 32K keys, 16 pieces 49.8 -> 41.1 us, 64 tokens 53.6 -> 48.0, 64 workgroups with 128 tiles each
+// 130 -> 105; 64 wide 64 tokens 34.8 -> 32.5.  Four slots 41.6, 48.6 and 106: the longer fill is not won back.  (Where two share a CU a deeper
+// ring bought nothing, and 64 wide took the third workgroup's room.)
+constexpr int kRingAlone = 3, kRingShared = 2;
 constexpr int vote_bytes(int qb) { return qb == 2 ? 16 : 0; }  // (the one-unit kernel has no vote, and two workgroups fill the LDS to its last byte)
 constexpr float kRescaleThreshold = 16.0f;  // log2 units: stale running max tolerated up to 2^16
 constexpr float kSumThreshold = 1048576.0f;             // 2^20: row sum of a half that moves the reference up
@@ -1103,22 +1106,26 @@ static hipError_t launch_one(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t prepare_attn_bf16(int head_dim) {
-  hipError_t e = hipErrorInvalidValue;
-  if (head_dim == 128) {
-    e = prepare_one<128, 2, kRingTwoUnits>();
-    if (e == hipSuccess) e = prepare_one<128, 1, kRingOneUnit>();
-  } else if (head_dim == 64) {
-    e = prepare_one<64, 2, kRingTwoUnits>();
-    if (e == hipSuccess) e = prepare_one<64, 1, kRingOneUnit>();
-  }
+template <int D>
+static hipError_t prepare_all() {
+  hipError_t e = prepare_one<D, 2, kRingAlone>();
+  if (e == hipSuccess) e = prepare_one<D, 1, kRingAlone>();
+  if (e == hipSuccess) e = prepare_one<D, 1, kRingShared>();
   return e;
 }
 
-hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int qb, hipStream_t s) {
-  if (head_dim == 128) return qb == 2 ? launch_one<128, 2, kRingTwoUnits>(p, s) : launch_one<128, 1, kRingOneUnit>(p, s);
-  if (head_dim == 64) return qb == 2 ? launch_one<64, 2, kRingTwoUnits>(p, s) : launch_one<64, 1, kRingOneUnit>(p, s);
-  return hipErrorInvalidValue;
+hipError_t prepare_attn_bf16(int head_dim) {
+  return head_dim == 128 ? prepare_all<128>() : head_dim == 64 ? prepare_all<64>() : hipErrorInvalidValue;
+}
+
+template <int D>
+static hipError_t launch_any(const AttnParams& p, int qb, int n_cu, hipStream_t s) {
+  if (qb == 2) return launch_one<D, 2, kRingAlone>(p, s);
+  return p.n_wgs <= n_cu ? launch_one<D, 1, kRingAlone>(p, s) : launch_one<D, 1, kRingShared>(p, s);
+}
+
+hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int qb, int n_cu, hipStream_t s) {
+  return head_dim == 128 ? launch_any<128>(p, qb, n_cu, s) : head_dim == 64 ? launch_any<64>(p, qb, n_cu, s) : hipErrorInvalidValue;
 }
 
 }  // namespace kvfold

@@ -315,7 +315,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   else if (pl.key_waves)
     e = launch_attn_few(at, f.head_dim, pl.key_waves, s);
   else
-    e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, s);
+    e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, pc.n_cu, s);
   if (e != hipSuccess) return hip_fail(e);
   if (ev) (void)hipEventRecord(ev[2], s);
   if (pl.n_splits > 1) {

@@ -101,7 +101,7 @@ struct CombineParams {
 
 // storage_bits 4 or 8 (bf16 only): the rows take the storage round trip bf16 -> intN -> bf16 on their way; 0: they do not.
 hipError_t launch_append(const AppendParams& p, int storage_bits, hipStream_t s);
-hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int units_per_wave, hipStream_t s);
+hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int units_per_wave, int n_cu, hipStream_t s);
 // Sets the LDS size attribute of every bf16 attention kernel variant of this head dimension on the current
 // device (once per device; launches then have nothing left that could fail for a valid configuration).
 hipError_t prepare_attn_bf16(int head_dim);

@@ -359,6 +359,16 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
         s = cand;
       }
     }
+    // One unit per wavefront, two workgroups a head of whose wavefronts more than a third have no rows (five units): two such workgroups on a CU
+    // have little to fill each other's waits with, and one alone, with the deeper ring it then has (attn_bf16.hip), is faster if all CUs get
+    // one.  32 heads on 8, 37 tokens on 32K keys 44.1 us with 27 pieces, 41.4 with 16; 40 on 16K 30.3 / 27.3, 34 on 65K 74 / 69.5, 37 on 100K
+    // 110 / 106.  (With six to eight units 66 tokens on 98K 149.5 / 159; 64 wide 37 on 32K 29.0 / 30.4.)
+    const int64_t alone = c.n_cu / base;
+    if (!fp32 && key_waves == 0 && upw == 1 && f.head_dim == 128 && window <= 0 && pl.wgs_per_head == 2 && with_rows < 0.65 && base * s > c.n_cu &&
+        alone <= s_max && base * alone * 10 >= (int64_t)c.n_cu * 9) {
+      s = alone;
+      best *= 0.95;
+    }
     pl.est_us = best;
   }
   return finish_plan(pl, s, s_max, ntiles, base);

@@ -33,3 +33,14 @@ def test_long_prefix_pieces(H, oracle, upw, pair):
     cfg = I.FoldConfig("units_long", 62, 1, 4, 1, 128, 700, 0, "bf16")
     _run_case(H, oracle, cfg, [700, 580, 131, 389, 20], splits=2, upw=upw, pair=pair)
     _run_case(H, oracle, cfg, [700, 580, 131, 389, 20], splits=1, upw=upw, pair=pair)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_grids_of_one_and_of_two_workgroups_a_cu(H, oracle, d, splits):
+    """The one-unit kernel's ring has a slot more where no CU gets a second workgroup: 130 heads, as many workgroups and three times as
+    many, one unit a workgroup and four; pieces of one tile to the ring's length and over, on and off the tile grid."""
+    cfg = I.FoldConfig("units_rings", 63, 1, 130, 130, d, 128, 0, "bf16")
+    _run_case(H, oracle, cfg, [128, 33, 64, 95, 1 + 32], splits=splits, upw=1)
+    cfg = I.FoldConfig("units_ring_alone", 64, 1, 5, 5, d, 300, 0, "bf16")
+    _run_case(H, oracle, cfg, [300, 33, 300, 60, 40], splits=splits, upw=1)

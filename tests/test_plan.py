@@ -70,6 +70,16 @@ def test_few_rows_are_split_where_the_merge_is_worth_it(hq, hkv, d, n, prev):
     assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).n_splits > 1
 
 
+@pytest.mark.parametrize("n,prev", [
+    (37, 32768),     # 41.4 / 44.1 us, 27 pieces
+    (40, 16384),     # 27.3 / 30.3
+])
+def test_five_units_a_head_have_their_cus_to_themselves(n, prev):
+    """Two workgroups a head of whose eight wavefronts three have no rows."""
+    plan = _plan(kv.KVFOLD_BF16, 32, 8, 128, n, prev)
+    assert plan.units_per_wave == 1 and plan.n_workgroups == 256
+
+
 @pytest.mark.parametrize("hq,hkv,d,n,prev,units", [
     (14, 2, 128, 4282, 65, 2),      # 83 / 111 us
     (14, 2, 64, 4201, 0, 2),        # 57 / 68
