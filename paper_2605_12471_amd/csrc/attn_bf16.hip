@@ -381,10 +381,12 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
     }
   };
 
-  // ---- the first two tiles, then the Q fragments, then the rest of the ring: the latencies overlap, and Q does not
-  // queue behind tiles that are wanted later.  Q, pre-multiplied by scale*log2(e), stays in registers for the whole
-  // kernel.  Code that a launch runs once is fetched at about 3 bytes per ns (measured: an unrolled fill of 6 KB took
-  // 2.3 us of a workgroup's start), so the fill is a loop.
+  // ---- the Q rows, the first two tiles, then the rest of the ring.  The Q rows come through LDS as well, into the part of the ring that the
+  // first two tiles leave free: copies complete in order, so that Q is waited for alone and while the tiles are on their way; loads into
+  // registers would be waited for by the compiler, which counts no copies, together with all that was issued around them (then Q was
+  // there 4.5 us after a workgroup's start, two tiles of every workgroup later, and the rest of the ring was asked for only then).  Q,
+  // pre-multiplied by scale*log2(e), stays in registers for the whole kernel.  Code that a launch runs once is fetched at about 3 bytes
+  // per ns (measured: an unrolled fill of 6 KB took 2.3 us of a workgroup's start), so the fill is a loop.
   auto prefill = [&](int j0, int j1) __attribute__((always_inline)) {
     // Steady state at the top of the even step of tile t: K[t], K[t+1], V[t] are in LDS and visible, the
     // groups {K[t+1+j], V[t+j]}, j = 1 .. NV-1, are in flight.  Tile t_begin + j takes ring slot j.
@@ -394,16 +396,33 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (j > 0) issue_tile(true, t_begin + j - 1, j - 1);
     }
   };
+  // This wavefront's 32 QB rows: the K slots from the third on, then the V slots from the second on.  A row's chunks lie as a K row's do.
+  constexpr int QAREA = QB * HALFB;
+  static_assert(4 * QAREA <= (NK - 2 + NV - 1) * TILEB && (NK - 2) * TILEB % QAREA == 0, "Q does not fit the free slots");
+  const unsigned q_lds = lds0 + (unsigned)(2 * TILEB + w * QAREA) + (w * QAREA >= (NK - 2) * TILEB ? (unsigned)TILEB : 0u);
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    unsigned place[32 / RPS];  // of the rows that the lane fetches from: held by the lanes whose rows they are
+#pragma unroll
+    for (int i = 0; i < 32 / RPS; ++i) place[i] = (unsigned)__builtin_amdgcn_ds_bpermute(4 * (i * RPS + l / CH), (int)q_row[qb]);
+#pragma unroll
+    for (int i = 0; i < 32 / RPS; ++i) {
+      const unsigned char* qrow = reinterpret_cast<const unsigned char*>(p.q) + (uint64_t)place[i] * ROWB + (unsigned)(((l % CH) ^ ((i * RPS + l / CH) % KSW)) * 16);
+      dma16_at(qrow, q_lds + (unsigned)(qb * HALFB + i * 1024));
+    }
+  }
   prefill(0, 1);
   bf16x8 qf[QB][KS];
   {
-    bf16x8 raw[QB][KS];  // every load in flight before the first is waited for
+    bf16x8 raw[QB][KS];
+    if (t_begin + 1 < t_end)
+      wait_vm<3 * SLABS>();  // (K, K and V; more where a tile is filled from both sides)
+    else
+      wait_vm<0>();
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + (uint64_t)q_row[qb] * D;
+    for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) raw[qb][ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16 + hi * 8);
-    }
+      for (int ks = 0; ks < KS; ++ks) raw[qb][ks] = *LDS_PTR(const bf16x8, q_lds + (unsigned)(qb * HALFB + m * ROWB + (((ks * 2 + hi) ^ (m % KSW)) * 16)));
     if (p.rope_cos) {
       // Rotary embedding at the row's absolute position (Sec. 2), half-split pairs (j, j + D/2), fp32 with
       // the sine product rounded first, result rounded to bf16: bit for bit what a caller that rotates q
@@ -434,6 +453,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       }
   }
 
+  __builtin_amdgcn_s_barrier();  // every wavefront has its Q out of the slots that are filled now
   prefill(2, NV);
 
   // ---- LDS read offsets (per lane) of the tile currently being read, ring slot included; moved
@@ -950,6 +970,9 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
           step(sA, sB, 2 * t, even, masked, mixed, both);
           step(sB, sA, 2 * t + 1, odd, masked, mixed, both, t + 1 == t_dead && t_dead < t_end);
         }
+        // The main loop's first instructions within the first half of a 32-byte piece of code: a loop whose head lies at the end of one costs
+        // every tile a fetch.  4096 tokens on 127K keys, 32 heads on 8, head at byte 4, 8 and 16 of a piece 6392 to 6400 us, 20 6443, 28 6470.
+        asm volatile(".p2align 5\n\ts_nop 0");
         for (; t < t_plain; ++t) {
           step(sA, sB, 2 * t, even, unmasked, plain, both);
           step(sB, sA, 2 * t + 1, odd, unmasked, plain, both);

@@ -26,6 +26,11 @@ __device__ __forceinline__ void dma16(const unsigned char* base_uniform, unsigne
                : "memory", "m0");
 }
 
+// The same from an address of each lane's own.
+__device__ __forceinline__ void dma16_at(const unsigned char* from, unsigned lds_base_uniform) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(from), "s"(lds_base_uniform) : "memory", "m0");
+}
+
 // Wait until at most N of the wavefront's vector memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vm() {
