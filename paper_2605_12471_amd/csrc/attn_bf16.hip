@@ -69,6 +69,7 @@ typedef __attribute__((ext_vector_type(4))) short short4_;
 typedef __attribute__((ext_vector_type(8))) short short8_;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
+typedef __attribute__((ext_vector_type(2))) unsigned uintx2;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 
 // Wait until at most N LDS reads are outstanding (compiler-visible, so that it adds none of its own
@@ -1033,9 +1034,79 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
   constexpr int OROWF = D * 4 + 16;  // padded LDS row: fp32 partials
   constexpr int OROWH = D * 2 + 16;  // padded LDS row: bf16 output
   const unsigned obase = lds0 + (unsigned)(w * kRowsPerUnit * OROWF);  // this wavefront's staging area, reused by its units
+  float l_all[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) l_all[qb] = pair_sum(l_run[qb]);
+
+  // ---- two pieces: the later of a row's two wavefronts has them both in the end.  Each leaves its partial results, lane by lane as they lie
+  // in its registers, and then counts itself; who finds the count odd is the second, fetches the other's and goes on as if there were one
+  // piece.  Nobody waits for anybody.  The counts are even between steps, whatever ran in between.  Partial results by accesses of device
+  // scope (past the L2, which the other piece need not share).  The arithmetic is the combine kernel's, in the order of the pieces, so that
+  // the bits do not depend on who came second.  Against that kernel: its launch, the turn through LDS, and the second's way through memory.
+  bool whole = p.n_splits == 1;
+  if (p.merge_count && !idle) {
+    constexpr int kDeviceScope = 16, kRawBuffer = 0x00020000;  // sc1; word 3 of a descriptor: untyped
+    const unsigned n_waves = (unsigned)(p.n_kv_heads * p.wgs_per_head * kUnitsPerWg), wave = (unsigned)((g * p.wgs_per_head + ug) * kUnitsPerWg + w);
+    const unsigned mine = (unsigned)split * n_waves + wave, theirs = (unsigned)(1 - split) * n_waves + wave;
+    const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(p.part_o, 0, 2 * n_waves * (unsigned)(QB * DB * 4096), kRawBuffer);
+    const __amdgpu_buffer_rsrc_t pml = __builtin_amdgcn_make_buffer_rsrc(p.part_ml, 0, 2 * n_waves * (unsigned)(QB * 512), kRawBuffer);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      uintx2 ml;
+      ml[0] = __float_as_uint(m_run[qb]);
+      ml[1] = __float_as_uint(l_all[qb]);
+      __builtin_amdgcn_raw_buffer_store_b64(ml, pml, (unsigned)le * 8u, (mine * QB + (unsigned)qb) * 512u, kDeviceScope);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          uintx4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(o[qb][db][rg * 4 + e]);
+          __builtin_amdgcn_raw_buffer_store_b128(v, po, (unsigned)le * 16u, (mine * QB * DB + (unsigned)(qb * DB + db)) * 4096u + (unsigned)rg * 1024u, kDeviceScope);
+        }
+    }
+    wait_vm<0>();
+    unsigned count = 0;
+    if (le == 0) count = __hip_atomic_fetch_add(p.merge_count + wave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    whole = __builtin_amdgcn_readfirstlane((int)count) & 1;
+    if (whole) {
+      asm volatile("" ::: "memory");
+      uintx2 ml[QB];
+      uintx4 x[QB][DB][4];
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        ml[qb] = __builtin_amdgcn_raw_buffer_load_b64(pml, (unsigned)le * 8u, (theirs * QB + (unsigned)qb) * 512u, kDeviceScope);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int rg = 0; rg < 4; ++rg)
+            x[qb][db][rg] = __builtin_amdgcn_raw_buffer_load_b128(po, (unsigned)le * 16u, (theirs * QB * DB + (unsigned)(qb * DB + db)) * 4096u + (unsigned)rg * 1024u, kDeviceScope);
+      }
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        float m_b = __uint_as_float(ml[qb][0]), l_b = __uint_as_float(ml[qb][1]), m_a = m_run[qb], l_a = l_all[qb];
+        // no visible key for the row in a piece, whose O may be NaN then: 0 times a value that is not finite
+        const bool none_a = l_a == 0.f, none_b = l_b == 0.f;
+        if (none_a) m_a = -INFINITY;
+        if (none_b) m_b = -INFINITY;
+        const float m2 = fmaxf(m_a, m_b), ref = m2 == -INFINITY ? 0.f : m2;
+        const float f_a = __builtin_amdgcn_exp2f(m_a - ref), f_b = __builtin_amdgcn_exp2f(m_b - ref);
+        m_run[qb] = m2;
+        l_all[qb] = split == 0 ? __builtin_fmaf(l_b, f_b, l_a * f_a) : __builtin_fmaf(l_a, f_a, l_b * f_b);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float a = none_a ? 0.f : o[qb][db][r], b = none_b ? 0.f : __uint_as_float(x[qb][db][r >> 2][r & 3]);
+            o[qb][db][r] = split == 0 ? __builtin_fmaf(b, f_b, a * f_a) : __builtin_fmaf(a, f_a, b * f_b);
+          }
+      }
+    }
+  }
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    const float l_tot = pair_sum(l_run[qb]);
+    const float l_tot = l_all[qb];
     const unsigned row0 = (unsigned)(unit_of[qb] * kRowsPerUnit);
     // rows of the unit that exist
     const int n_live = !unit_valid[qb] ? 0 : (int)(n_packed - row0) < kRowsPerUnit ? (int)(n_packed - row0) : kRowsPerUnit;
@@ -1065,7 +1136,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
         at += 4 * RPI * lds_row;
       }
     };
-    if (p.n_splits == 1) {
+    if (whole) {
       const float inv = 1.f / l_tot;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -1079,7 +1150,7 @@ __global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnP
       if (p.lse && store_row)
         p.lse[(int64_t)(g * G + (int)(my_row - my_tok * (unsigned)G)) * C + my_tok] = (m_run[qb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
       store_rows(reinterpret_cast<unsigned char*>(p.out) + (uint64_t)(g * G) * (D * 2), std::integral_constant<int, D * 2>{}, OROWH);
-    } else {
+    } else if (!p.merge_count) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll

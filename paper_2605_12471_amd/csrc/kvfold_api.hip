@@ -29,6 +29,7 @@ struct kvfold_cache {
   size_t kv_bytes;
   float* ws_o;   // split workspace: unnormalised partial outputs
   float* ws_ml;  // split workspace: (max, sum) pairs
+  uint32_t* merge_count;  // kMergeCounters zeros (see AttnParams::merge_count), nullptr where there is no workspace
   std::vector<int64_t> len;
   // optional per-kernel timing: 4 events per step (before append, after append, after attention, after merge)
   std::vector<hipEvent_t> prof_events;
@@ -128,6 +129,7 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
   c->kv_bytes = need;
   c->ws_o = nullptr;
   c->ws_ml = nullptr;
+  c->merge_count = nullptr;
   c->len.assign((size_t)cfg->n_layers, 0);
 
   hipDeviceProp_t prop;
@@ -159,10 +161,17 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
 
   const int64_t ws_rows = workspace_rows(cfg);
   if (ws_rows > 0) {
-    void *po = nullptr, *pm = nullptr;
+    void *po = nullptr, *pm = nullptr, *pc = nullptr;
     e = hipMalloc(&po, (size_t)ws_rows * cfg->head_dim * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&pm, (size_t)ws_rows * 2 * sizeof(float));
+    if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) {
+      e = hipMalloc(&pc, kMergeCounters * sizeof(uint32_t));
+      if (e == hipSuccess) e = hipMemset(pc, 0, kMergeCounters * sizeof(uint32_t));
+      if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // steps may run on streams that do not wait for this one
+    }
     if (e != hipSuccess) {
+      if (pc) (void)hipFree(pc);
+      if (pm) (void)hipFree(pm);
       if (po) (void)hipFree(po);
       if (c->owns_kv) (void)hipFree(c->kv);
       delete c;
@@ -170,7 +179,9 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
     }
     c->ws_o = static_cast<float*>(po);
     c->ws_ml = static_cast<float*>(pm);
+    c->merge_count = static_cast<uint32_t*>(pc);
     c->pc.ws_rows = ws_rows;
+    c->pc.two_meet = pc != nullptr;
   }
   *out_cache = c;
   return KVFOLD_OK;
@@ -216,6 +227,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     const int64_t rows = (int64_t)n_tokens * f.n_q_heads;
     if (2 * rows > kStaticScratchRows) return KVFOLD_ERR_SCRATCH;  // not even two pieces of this step fit
     pc.ws_rows = kStaticScratchRows;
+    pc.two_meet = false;  // (a step of another cache whose work overlaps this one's races on the array, as ever, but on no counters)
     part_ml = reinterpret_cast<float*>(sp);
     part_o = reinterpret_cast<float*>(sp + (size_t)kStaticScratchRows * 2 * sizeof(float));
   }
@@ -260,6 +272,11 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.n_wgs = pl.n_wgs;
   at.pair_order = pl.pair_order;
   at.pair_units = pl.pair_units;
+  const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
+  const size_t lse_bytes = (size_t)n_tokens * f.n_q_heads * sizeof(float);
+  // (Then the results are stored while others still read their queries: rows that lie on other rows' queries are left to the merge kernel.)
+  const bool merge_inside = two_pieces_meet(pc, pl, pl.n_splits) && (out == q || apart(q, out_bytes, out, out_bytes)) && (!lse || apart(q, out_bytes, lse, lse_bytes));
+  at.merge_count = merge_inside ? c->merge_count : nullptr;
   at.scale_log2e = c->scale * 1.4426950408889634f;
   at.rope_cos = opt.rope_cos;
   at.rope_sin = opt.rope_sin;
@@ -268,19 +285,18 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   // The attention kernel appends by itself when nothing has to happen to the rows on their way in and the
   // chunk's rows can be addressed with 32-bit byte offsets -- and when none of its own stores reaches the rows before they are
   // used up: each workgroup copies its share behind its results, and reads rows that others copy.  Else an append kernel in
-  // front uses them up.  The output of a split step is stored behind the whole attention kernel.  A few-rows workgroup has
+  // front uses them up.  The output of a step with a merge kernel is stored behind the whole attention kernel.  A few-rows workgroup has
   // read all rows of its KV head before it stores, so there the output may also take their very place.  (fp32 and rows that need
   // work: apart from the cache as well.)
-  const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
   bool rows_apart = true, results_apart = true;
   for (const void* rows : {k_new, v_new}) {
     const bool from_out = apart(rows, new_bytes, out, out_bytes);
-    const bool from_lse = !lse || apart(rows, new_bytes, lse, (size_t)n_tokens * f.n_q_heads * sizeof(float));
+    const bool from_lse = !lse || apart(rows, new_bytes, lse, lse_bytes);
     const bool in_place = pl.few_rows && at.group == 1 && rows == out;
     results_apart = results_apart && (from_out || in_place) && from_lse;
     rows_apart = rows_apart && from_out && from_lse && apart(rows, new_bytes, c->kv, c->kv_bytes);
   }
-  const bool may_append = f.dtype == KVFOLD_BF16 && !opt.rope_cos ? results_apart || pl.n_splits > 1 : rows_apart;
+  const bool may_append = f.dtype == KVFOLD_BF16 && !opt.rope_cos ? results_apart || (pl.n_splits > 1 && !merge_inside) : rows_apart;
   const bool fused_append = may_append && attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;
@@ -318,7 +334,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, pc.n_cu, s);
   if (e != hipSuccess) return hip_fail(e);
   if (ev) (void)hipEventRecord(ev[2], s);
-  if (pl.n_splits > 1) {
+  const bool merge = pl.n_splits > 1 && !merge_inside;  // by a kernel of its own
+  if (merge) {
     CombineParams cp;
     cp.part_o = part_o;
     cp.part_ml = part_ml;
@@ -334,8 +351,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     if (e != hipSuccess) return hip_fail(e);
   }
   if (ev) {
-    if (pl.n_splits > 1) (void)hipEventRecord(ev[3], s);
-    c->prof_has_merge[(size_t)c->prof_steps] = (char)((pl.n_splits > 1 ? 1 : 0) | (own_append ? 2 : 0));
+    if (merge) (void)hipEventRecord(ev[3], s);
+    c->prof_has_merge[(size_t)c->prof_steps] = (char)((merge ? 1 : 0) | (own_append ? 2 : 0));
     c->prof_steps++;
   }
   c->len[(size_t)layer] = len_prev + n_tokens;
@@ -398,6 +415,7 @@ int kvfold_cache_destroy(kvfold_cache_t* c) {
     if (c->owns_kv && c->kv) (void)hipFree(c->kv);
     if (c->ws_o) (void)hipFree(c->ws_o);
     if (c->ws_ml) (void)hipFree(c->ws_ml);
+    if (c->merge_count) (void)hipFree(c->merge_count);
   }
   delete c;
   return rc;

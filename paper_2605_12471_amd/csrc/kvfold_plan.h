@@ -19,6 +19,7 @@ struct PlanCtx {
   int n_cu;
   int tune_splits, tune_units_per_wave, tune_pair_units, tune_fused_append;
   int storage_bits;
+  bool two_meet;  // a step's two pieces may meet in the attention kernel (bf16, the cache's own workspace)
 };
 
 struct Plan {
@@ -29,6 +30,14 @@ struct Plan {
   int units_per_wave, units_per_head, wgs_per_head, n_splits, tiles_per_split, n_wgs, pair_order, pair_units;
   double est_us;  // the planner's time estimate of the step (0 when the split count was forced)
 };
+
+// Counters of a cache (AttnParams::merge_count), and whether the two pieces of a step with this plan meet in the attention kernel, through
+// them and the workspace, which holds whole units then, a lane's own (m, l) for each of the two lanes of a row.
+constexpr int kMergeCounters = 8192;
+inline bool two_pieces_meet(const PlanCtx& c, const Plan& pl, int n_splits) {
+  const int64_t waves = (int64_t)c.cfg.n_kv_heads * pl.wgs_per_head * kUnitsPerWg;
+  return c.two_meet && n_splits == 2 && !pl.key_waves && waves <= kMergeCounters && 2 * waves * pl.units_per_wave * 64 <= c.ws_rows;
+}
 
 int elem_size(int dtype);
 int validate_config(const kvfold_config_t* c);

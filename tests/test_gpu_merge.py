@@ -110,3 +110,37 @@ def test_every_row_comes_out_in_its_place(H, d, n, splits):
         gpu.close()
     assert (res[0][0] - res[1][0]).abs().max() <= 100 * 2.0 ** -24 * 6
     assert (res[0][1] - res[1][1]).abs().max() <= 100 * 2.0 ** -24 * 16
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("upw", [1, 2])
+@pytest.mark.parametrize("n", [9, 33, 64, 300])
+def test_two_pieces_meet_in_the_attention_kernel(H, d, upw, n):
+    """The bits are the merge kernel's, step after step with whatever counts lie between (static scratch has that kernel merge): partly
+    filled units, wavefronts without rows, a later piece with little in it; and with the output in the place of the queries or, which sends
+    the step to the merge kernel, on other rows' queries."""
+    Hq, Hkv, prev = 8, 2, 700
+    g = torch.Generator("cuda").manual_seed(n + d)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    cache = kv.KvFoldCache(1, Hq, Hkv, d, 300, prev + n, "bf16")
+    for rows in cache.view(0):
+        rows[:, :prev].normal_(generator=g)
+    cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, upw)
+    cache.set_tuning(kv.TUNE_SPLITS, 2)
+
+    def step(q, out, **kw):
+        lse = torch.empty(Hq, n, device="cuda")
+        cache.set_length(0, prev)
+        cache.step(0, q, k, v, out, pos_offset=prev, lse=lse, **kw)
+        torch.cuda.synchronize()
+        return out.clone(), lse
+    want = step(q, torch.empty_like(q), noalloc=True)
+    for _ in range(3):
+        assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.full_like(q, 7.0))))
+    both = torch.empty(q.numel() + Hq * d, device="cuda", dtype=torch.bfloat16)
+    for first in (0, Hq * d):   # the queries' own place; one token further on
+        at = both[:q.numel()].view(q.shape)
+        at.copy_(q)
+        assert all(torch.equal(a, b) for a, b in zip(want, step(at, both[first:first + q.numel()].view(q.shape))))
+    assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.empty_like(q))))
+    cache.close()
