@@ -247,6 +247,27 @@ def _current_stream() -> int:
         return torch.cuda.current_stream().cuda_stream
 
 
+_native = False  # module of csrc/py_step.cpp; None: not there, or built for another torch; False: not looked for yet
+
+
+def _native_step():
+    global _native
+    if _native is False:
+        import importlib.util
+
+        import torch
+        _native = None
+        spec = importlib.util.spec_from_file_location("kvfold_py_step", os.path.join(_HERE, "_lib", "kvfold_py_step.so"))
+        try:
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            if module.torch_version == torch.__version__.split("+")[0]:
+                _native = module
+        except ImportError:  # (also: no such file)
+            pass
+    return _native
+
+
 class KvFoldCache:
     """Owns one library cache handle; ``step`` takes torch tensors on the cache's device."""
 
@@ -261,8 +282,20 @@ class KvFoldCache:
         # what every step needs, as plain Python values: fields of a ctypes structure are slow to read
         self._device, self._hq, self._hkv, self._d = device, n_q_heads, n_kv_heads, head_dim
         self._lib = load_library()
+        self._bound = False  # what the native step knows of this cache; None: there is none
+
+    def _bind(self):
+        native, lib = _native_step(), self._lib
+        if native is None or self.handle is None:
+            self._bound = None
+        else:
+            address = [ctypes.cast(f, ctypes.c_void_p).value
+                       for f in (lib.kvfold_step_ex, lib.kvfold_step_noalloc, lib.kvfold_step_rope, lib.kvfold_step_window)]
+            self._bound = native.bind(*address, self.handle.value, self._device, self._hq, self._hkv, self._d, self.dtype_name != "f32")
+        return self._bound
 
     def close(self):
+        self._bound = None
         if getattr(self, "handle", None) is not None:
             rc = kvfold_cache_destroy(self.handle)
             self.handle = None
@@ -304,9 +337,19 @@ class KvFoldCache:
         """Enqueue one fold step; q/k_new/v_new/out (and lse) are contiguous device tensors.  rope = (cos, sin),
         fp32 device tensors [n][head_dim/2]: q and k_new are unrotated and the step rotates them.  window =
         (n_sink, window): the sink + sliding-window step.  noalloc: through kvfold_step_noalloc."""
+        pos = self.length(layer) if pos_offset is None else pos_offset
+        bound = self._bound
+        if bound is False:
+            bound = self._bind()
+        if bound is not None:
+            rc = _native.step(bound, layer, q, k_new, v_new, out, pos, lse, stream, rope, window, noalloc)
+            if rc == 0:
+                return out
+            if rc is not None:
+                raise KvFoldError(rc, "kvfold_step_window" if window is not None else "kvfold_step_rope" if rope is not None
+                                  else "kvfold_step_noalloc" if noalloc else "kvfold_step_ex")
         shape = q.shape
         n = shape[0] if len(shape) == 3 else -1
-        pos = self.length(layer) if pos_offset is None else pos_offset
         wide, narrow = (n, self._hq, self._d), (n, self._hkv, self._d)
         self._check("q", q, wide)
         self._check("out", out, wide)

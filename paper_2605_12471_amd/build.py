@@ -22,6 +22,7 @@ HIPCC_FLAGS = [
     "-Rpass-analysis=kernel-resource-usage",
 ]
 RESOURCE_REPORT = os.path.join(LIB_DIR, "kernel_resources.txt")
+PY_STEP_PATH = os.path.join(LIB_DIR, "kvfold_py_step.so")
 C_CLIENT_PATH = os.path.join(LIB_DIR, "kvfold_c_client")
 INCLUDE_DIR = os.path.join(os.path.dirname(_HERE), "include")
 
@@ -55,6 +56,22 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+def build_py_step() -> str:
+    """Compile the Python binding's native step (g++) against this interpreter and its torch."""
+    import sysconfig
+
+    import torch
+    home = os.path.dirname(os.path.abspath(torch.__file__))
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", os.path.join(home, "include"),
+           "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "py_step.cpp"), "-o", PY_STEP_PATH,
+           "-L" + os.path.join(home, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    subprocess.run(cmd, check=True)
+    return PY_STEP_PATH
+
+
 def build_c_client() -> str:
     """Compile the plain-C caller of the library (gcc, C11, no HIP compiler): it sees only include/kvfold.h, the HIP
     runtime API and the shared library."""
@@ -69,4 +86,5 @@ def build_c_client() -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_py_step())
     print(build_c_client())
