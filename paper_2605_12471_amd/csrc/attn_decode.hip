@@ -22,6 +22,7 @@
 // token on 88K keys, 32 heads on 2, 128 workgroups, 24.7 -> 25.7.)
 #include "append_rows.h"
 #include "kvfold_internal.h"
+#include "meet.h"
 #include "wave_ops.h"
 
 namespace kvfold {
@@ -38,16 +39,6 @@ typedef __attribute__((ext_vector_type(2))) float floatx2;
 
 constexpr int kDecodeWaves = 4;
 
-// Lanes l and l ^ 16 exchange x; both end with the maximum / the sum.
-__device__ __forceinline__ float row16_max(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float row16_sum(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // NC: groups of 16 rows (1: at most 16 packed rows).
 template <int D, int NC>
 __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnParams p) {
@@ -59,6 +50,7 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
   constexpr int ROWS = NC * 16, OROW = D * 4 + 16;
   __shared__ __attribute__((aligned(16))) unsigned char red_o[NW * ROWS * OROW];
   __shared__ floatx2 red_ml[NW * ROWS];
+  __shared__ int last;
 
   // every line of the arguments is fetched now, in one round trip (they are not in the scalar cache yet)
   asm volatile("" ::"s"(p.q), "s"(p.n_tokens), "s"(p.len_prev), "s"(p.k_new), "s"(p.work_k), "s"(p.by_group.mul), "s"(p.copy_rows));
@@ -159,7 +151,6 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
   struct VBlock {
     vvec d[8];
   };
-  constexpr int kRawBuffer = 0x00020000;  // word 3 of the descriptor: untyped
   const unsigned k_lane = (unsigned)c16 * ROWB + (unsigned)kg * 16, v_lane = (unsigned)(4 * kg) * ROWB + (unsigned)c16 * (VW * 4);
   auto load_k = [&](KBlock& x, int blk, bool there) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(kbase), 0, there ? head_bytes : 0u, kRawBuffer);
@@ -413,6 +404,7 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
   constexpr int V = D / 4;  // 16-byte column vectors of a row
   const int c = tid % V;
   const int64_t n_rows = (int64_t)C * Hq;
+  const Partials<D> parts(p);
 #pragma unroll 1
   for (int r = tid / V; r < rows; r += NT / V) {
     floatx2 ml[NW];
@@ -442,9 +434,32 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
       *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at * D + c * 4) = v;
       if (p.lse && c == 0) p.lse[(int64_t)h * C + t] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
     } else {
-      *reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + at) * D + c * 4) = acc;
-      if (c == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + at) * 2) = make_float2(M, L);
+      if (p.meet_count) {
+        parts.store(split, (unsigned)at, c, acc, M, L);
+      } else {
+        *reinterpret_cast<floatx4*>(p.part_o + ((int64_t)split * n_rows + at) * D + c * 4) = acc;
+        if (c == 0) *reinterpret_cast<float2*>(p.part_ml + ((int64_t)split * n_rows + at) * 2) = make_float2(M, L);
+      }
     }
+  }
+  if (!p.meet_count || !last_to_meet(p, g, &last)) return;
+#pragma unroll 1
+  for (int r = w; r < rows; r += NW) {
+    const int t = (int)quot((unsigned)r, p.by_group), h = g * G + r - t * G;
+    const int64_t at = (int64_t)t * Hq + h;
+    const int cv = l % V, part = l / V;
+    floatx4 acc;
+    float M, L;
+    if (p.n_splits <= 6 * 64 / V)
+      parts.template merge<6>((unsigned)at, part, cv, acc, M, L);
+    else
+      parts.template merge<12>((unsigned)at, part, cv, acc, M, L);
+    const float inv = 1.f / L;
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[e] * inv);
+    if (part == 0) *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at * D + cv * 4) = v;
+    if (p.lse && l == 0) p.lse[(int64_t)h * C + t] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
   }
 }
 

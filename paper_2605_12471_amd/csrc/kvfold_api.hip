@@ -20,6 +20,8 @@
 
 using namespace kvfold;
 
+constexpr size_t kCounterBytes = (kMergeCounters + (size_t)kMeetSplits * kMeetUnits) * sizeof(uint32_t);
+
 struct kvfold_cache {
   PlanCtx pc;  // configuration, workspace size, CU count, tuning knobs, storage round trip: what the planner reads
   int elem_bytes;
@@ -29,7 +31,7 @@ struct kvfold_cache {
   size_t kv_bytes;
   float* ws_o;   // split workspace: unnormalised partial outputs
   float* ws_ml;  // split workspace: (max, sum) pairs
-  uint32_t* merge_count;  // kMergeCounters zeros (see AttnParams::merge_count), nullptr where there is no workspace
+  uint32_t* merge_count;  // kMergeCounters zeros, and those of meet_count behind them (see AttnParams), nullptr where there is no workspace
   std::vector<int64_t> len;
   // optional per-kernel timing: 4 events per step (before append, after append, after attention, after merge)
   std::vector<hipEvent_t> prof_events;
@@ -165,8 +167,8 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
     e = hipMalloc(&po, (size_t)ws_rows * cfg->head_dim * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&pm, (size_t)ws_rows * 2 * sizeof(float));
     if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) {
-      e = hipMalloc(&pc, kMergeCounters * sizeof(uint32_t));
-      if (e == hipSuccess) e = hipMemset(pc, 0, kMergeCounters * sizeof(uint32_t));
+      e = hipMalloc(&pc, kCounterBytes);
+      if (e == hipSuccess) e = hipMemset(pc, 0, kCounterBytes);
       if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // steps may run on streams that do not wait for this one
     }
     if (e != hipSuccess) {
@@ -277,6 +279,8 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   // (Then the results are stored while others still read their queries: rows that lie on other rows' queries are left to the merge kernel.)
   const bool merge_inside = two_pieces_meet(pc, pl, pl.n_splits) && (out == q || apart(q, out_bytes, out, out_bytes)) && (!lse || apart(q, out_bytes, lse, lse_bytes));
   at.merge_count = merge_inside ? c->merge_count : nullptr;
+  const bool meet = pieces_meet(pc, pl, n_tokens, pl.n_splits);
+  at.meet_count = meet ? c->merge_count + kMergeCounters : nullptr;
   at.scale_log2e = c->scale * 1.4426950408889634f;
   at.rope_cos = opt.rope_cos;
   at.rope_sin = opt.rope_sin;
@@ -334,7 +338,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     e = launch_attn_bf16(at, f.head_dim, pl.units_per_wave, pc.n_cu, s);
   if (e != hipSuccess) return hip_fail(e);
   if (ev) (void)hipEventRecord(ev[2], s);
-  const bool merge = pl.n_splits > 1 && !merge_inside;  // by a kernel of its own
+  const bool merge = pl.n_splits > 1 && !merge_inside && !meet;  // by a kernel of its own
   if (merge) {
     CombineParams cp;
     cp.part_o = part_o;

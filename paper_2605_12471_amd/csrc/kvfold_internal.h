@@ -49,6 +49,7 @@ struct AttnParams {
   int32_t pair_units;      // two-unit bf16 kernel: a wavefront owns an early and a late unit of the chunk (see the kernel)
   uint32_t* merge_count;   // bf16 general kernel, two pieces: one counter per KV head and wavefront of its rows, even between steps (nullptr: the
                            // partial results are for the combine kernel)
+  uint32_t* meet_count;    // the last of a KV head's pieces merges them, by these counters (see meet.h; nullptr: the combine kernel)
   float scale_log2e;       // softmax scale * log2(e)
   // Rotary embedding of the queries as they are loaded (nullptr: q is used as handed in): angles of the
   // chunk's absolute positions, [C][d/2] fp32 each

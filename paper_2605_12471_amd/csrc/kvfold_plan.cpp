@@ -185,7 +185,7 @@ void plan_key_waves_f32(const PlanCtx& c, int64_t rows, int64_t base, int ntiles
 // wavefront make a difference.  Fitted to 2200 measured steps (captured graphs, caches from memory): 142 shapes (1 to 64
 // heads, 1 to 16 tokens on 64 to 131K keys), every split count; the choice is 0.6 % above the best of these on average (64 wide 0.2
 // %), 5 % at most; with the few-rows kernel's figures 1.0 % and 8 % (one token on 4187 keys, 32 heads on 8, 17 pieces 9.91 us, 22 9.30).
-void plan_direct(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64_t s_max, double len_after, int64_t& s, double& est_us) {
+void plan_direct(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t rows, int64_t base, int ntiles, int64_t s_max, double len_after, int64_t& s, double& est_us) {
   struct Cost {
     double start_end, tile, bytes_per_us, uneven, round, merge, merge_bytes_per_us;
   };
@@ -202,6 +202,8 @@ void plan_direct(const PlanCtx& c, int64_t rows, int64_t base, int ntiles, int64
     const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : kAlone);
     double t = k.start_end + std::sqrt(chain * chain + mem * mem) + (per_cu > 2.0 ? k.round : 0.0);
     if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
+    // pieces that meet in the last one's workgroup (meet.h): a launch less, but the workgroups of a head count themselves one by one
+    if (pieces_meet(c, pl, n_tokens, cand)) t += 0.09 * std::max(0.0, (double)cand - 8.0) - 1.2;
     if (t < est_us) {
       est_us = t;
       s = cand;
@@ -281,7 +283,7 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       return finish_plan(pl, s, s_max, ntiles, base);
     }
     if (pl.direct) {
-      plan_direct(c, rows, base, ntiles, s_max, (double)len_after, s, pl.est_us);
+      plan_direct(c, pl, n_tokens, rows, base, ntiles, s_max, (double)len_after, s, pl.est_us);
       return finish_plan(pl, s, s_max, ntiles, base);
     }
     if (key_waves > 0 && !few_rows) {

@@ -39,6 +39,14 @@ inline bool two_pieces_meet(const PlanCtx& c, const Plan& pl, int n_splits) {
   return c.two_meet && n_splits == 2 && !pl.key_waves && waves <= kMergeCounters && 2 * waves * pl.units_per_wave * 64 <= c.ws_rows;
 }
 
+// Counters of the kernel whose pieces may meet in the last one's workgroup (meet.h), one for every KV head and number of pieces; and whether
+// they do: at most four rows.
+constexpr int kMeetUnits = 1024, kMeetSplits = 20;
+inline bool pieces_meet(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t n_splits) {
+  const int rows = n_tokens * (c.cfg.n_q_heads / c.cfg.n_kv_heads);
+  return c.two_meet && pl.direct && n_splits > 1 && n_splits <= kMeetSplits && rows <= 4 && c.cfg.n_kv_heads <= kMeetUnits;
+}
+
 int elem_size(int dtype);
 int validate_config(const kvfold_config_t* c);
 size_t bytes_required(const kvfold_config_t* c);

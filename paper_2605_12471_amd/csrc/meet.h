@@ -1,0 +1,93 @@
+// The pieces of a step meet in the attention kernel: the last workgroup of a unit to have stored its partial results merges them all.  For kernels
+// of one unit a workgroup, where that is little to read.  Against the combine kernel (captured graphs, one token, 32 heads on 8): 500 keys 6.74 -> 5.84 us,
+// 1000 7.03 -> 6.53, 2000 8.0 -> 7.6, 64 wide 1000 6.66 -> 5.8, 4187 8.18 -> 7.6.  A head's workgroups count themselves one after the other, 0.1 us each, so
+// that 22 pieces are where it is even (4187 keys, 9.47 / 9.66); a wavefront has a row, and more rows than wavefronts are a
+// second way through memory (28 heads on 4, 2331 keys 7.9 / 9.3 us, 16 rows 10.4 / 11.8).
+#pragma once
+#include "kvfold_internal.h"
+#include "wave_ops.h"
+
+namespace kvfold {
+
+constexpr int kDeviceScope = 16;        // sc1 of a buffer access: past the L2, which another piece's workgroup need not share
+constexpr int kRawBuffer = 0x00020000;  // word 3 of a buffer descriptor: untyped
+
+// The partial results of row `at` of [token][query head], column vector c (four floats): O and, from one thread, (m, l).
+template <int D>
+struct Partials {
+  typedef __attribute__((ext_vector_type(4))) unsigned uintx4;
+  typedef __attribute__((ext_vector_type(2))) unsigned uintx2;
+  typedef __attribute__((ext_vector_type(4))) float floatx4;
+  __amdgpu_buffer_rsrc_t o, ml;
+  unsigned n_rows;
+  __device__ __forceinline__ Partials(const AttnParams& p) : n_rows((unsigned)(p.n_tokens * p.n_q_heads)) {
+    o = __builtin_amdgcn_make_buffer_rsrc(p.part_o, 0, (unsigned)p.n_splits * n_rows * (D * 4u), kRawBuffer);
+    ml = __builtin_amdgcn_make_buffer_rsrc(p.part_ml, 0, (unsigned)p.n_splits * n_rows * 8u, kRawBuffer);
+  }
+  __device__ __forceinline__ void store(int piece, unsigned at, int c, const floatx4& x, float m, float l) const {
+    const unsigned row = (unsigned)piece * n_rows + at;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, x), o, row * (D * 4u) + (unsigned)c * 16u, 0, kDeviceScope);
+    if (c == 0) {
+      uintx2 y;
+      y[0] = __float_as_uint(m);
+      y[1] = __float_as_uint(l);
+      __builtin_amdgcn_raw_buffer_store_b64(y, ml, row * 8u, 0, kDeviceScope);
+    }
+  }
+  // The row's pieces, at most N * 64 / V (V = D / 4 column vectors), by one wavefront: lane (part, c) takes every 64 / V-th of them from the
+  // part-th on, then the parts meet; every lane has O, m and l in the end.  Every load is in flight before the first is waited for;
+  // those past the last piece lie outside the buffer, cost no traffic and bring zeros: no keys.
+  template <int N>
+  __device__ __forceinline__ void merge(unsigned at, int part, int c, floatx4& acc, float& m, float& l) const {
+    constexpr unsigned PARTS = 64 / (D / 4);
+    uintx4 x[N];
+    uintx2 y[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const unsigned row = ((unsigned)i * PARTS + (unsigned)part) * n_rows + at;
+      y[i] = __builtin_amdgcn_raw_buffer_load_b64(ml, row * 8u, 0, kDeviceScope);
+      x[i] = __builtin_amdgcn_raw_buffer_load_b128(o, row * (D * 4u) + (unsigned)c * 16u, 0, kDeviceScope);
+    }
+    m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
+      if (y[i][1] == 0u) {
+        y[i][0] = __float_as_uint(-INFINITY);
+        x[i] = uintx4{0u, 0u, 0u, 0u};
+      }
+      m = fmaxf(m, __uint_as_float(y[i][0]));
+    }
+    m = pair_max(m);
+    if (PARTS == 4) m = row16_max(m);
+    const float ref = m == -INFINITY ? 0.f : m;
+    acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    l = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float b = __builtin_amdgcn_exp2f(__uint_as_float(y[i][0]) - ref);
+      l = __builtin_fmaf(__uint_as_float(y[i][1]), b, l);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(__uint_as_float(x[i][e]), b, acc[e]);
+    }
+    l = pair_sum(l);
+    if (PARTS == 4) l = row16_sum(l);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[e] = pair_sum(acc[e]);
+      if (PARTS == 4) acc[e] = row16_sum(acc[e]);
+    }
+  }
+};
+
+// Whether this workgroup is the last of its unit's n_splits; for all its threads, behind their stores.  The counter is back at zero then, and
+// there is one for every number of pieces, so that it is between steps, whatever ran in between.
+__device__ __forceinline__ bool last_to_meet(const AttnParams& p, int unit, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = atomicInc(p.meet_count + (p.n_splits - 1) * kMeetUnits + unit, (unsigned)p.n_splits - 1u) == (unsigned)p.n_splits - 1u;
+  __syncthreads();
+  return *flag != 0;
+}
+
+}  // namespace kvfold

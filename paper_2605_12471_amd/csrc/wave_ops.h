@@ -17,6 +17,16 @@ __device__ __forceinline__ float pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Lanes l and l ^ 16 exchange x; both end with the maximum / the sum.
+__device__ __forceinline__ float row16_max(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float row16_sum(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // One wavefront-wide 1 KiB copy global -> LDS: lane l's 16 bytes, read from base + off, land at
 // lds_base + 16*l.  The compiler is not told about the LDS write; ordering is done by hand with
 // wait_vm<> + barrier.  The hardware needs one wait state between a write of m0 and a copy to LDS, and the compiler

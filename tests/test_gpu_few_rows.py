@@ -114,3 +114,26 @@ def test_graph_replays():
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(_step(cache, L, args), want)
     cache.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1)])
+@pytest.mark.parametrize("splits", [2, 6, 7, 12, 13, 20, 21])
+def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits):
+    """Up to four rows and twenty pieces: a lane's six, and twelve, and the merge kernel beyond (and in static scratch), with piece counts that change
+    from step to step; within the rounding of the output, and the same bits every time."""
+    L = 64 * 21 + 17
+    cache, args = _filled(Hq, Hkv, d, n, L)
+    cache.set_tuning(kv.TUNE_SPLITS, splits)
+    want = _step(cache, L, args, noalloc=True).float()
+    lse = [torch.empty(Hq, n, device="cuda") for _ in range(2)]
+    one = _step(cache, L, args, lse=lse[0])
+    assert ((one.float() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-6).all()   # one more or less of a bf16's last places at most
+    for other in (3, 20, splits, 11):
+        cache.set_tuning(kv.TUNE_SPLITS, other)
+        again = _step(cache, L, args, lse=lse[1])
+        if other == splits:
+            assert torch.equal(one, again) and torch.equal(*lse)
+    cache.set_tuning(kv.TUNE_SPLITS, 1)
+    _step(cache, L, args, lse=lse[1])
+    assert (lse[0] - lse[1]).abs().max() <= 1e-4
+    cache.close()
