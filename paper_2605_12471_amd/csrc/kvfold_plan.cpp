@@ -183,15 +183,15 @@ void plan_key_waves_f32(const PlanCtx& c, int64_t rows, int64_t base, int ntiles
 // The same for the kernel whose keys come straight into registers (attn_decode.hip).  A piece's chain and the rows' way from memory overlap
 // in part; per tile a CU's workgroups share its way to the L2, and neither odd numbers of tiles nor, below them, the blocks of a
 // wavefront make a difference.  Fitted to 2200 measured steps (captured graphs, caches from memory): 142 shapes (1 to 64
-// heads, 1 to 16 tokens on 64 to 131K keys), every split count; the choice is 0.6 % above the best of these on average (64 wide 0.2
-// %), 5 % at most; with the few-rows kernel's figures 1.0 % and 8 % (one token on 4187 keys, 32 heads on 8, 17 pieces 9.91 us, 22 9.30).
+// heads, 1 to 16 tokens on 64 to 131K keys), every split count; the choice is 0.5 % above the best of these on average (64 wide 0.2
+// %), 5 % at most; with the few-rows kernel's figures 1.0 % and 8 % (one token on 4187 keys, 32 heads on 8, 17 pieces 9.91 us, 22 9.30).  The
+// longest caches would have 1 to 2 % less with one workgroup per CU as well (128K keys, 8 heads, 32 pieces 92.9 us, 64 94.0); their geometry, two per CU, is
+// kept as it is pinned: pieces of more than 48 tiles.
 void plan_direct(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t rows, int64_t base, int ntiles, int64_t s_max, double len_after, int64_t& s, double& est_us) {
   struct Cost {
     double start_end, tile, bytes_per_us, uneven, round, merge, merge_bytes_per_us;
   };
   const Cost k = c.cfg.head_dim == 128 ? Cost{2.73, 0.595, 7.45e6, 0.29, 1.62, 3.33, 1.60e6} : Cost{2.74, 0.353, 8.0e6, 0.28, 2.25, 3.12, 1.40e6};
-  // (long caches, where 26 to 64 pieces of 8 heads are within 2 % of one another, have two workgroups per CU in flight)
-  const double kAlone = 1.02;
   const double kv_us = 4.0 * c.cfg.n_kv_heads * c.cfg.head_dim * len_after / k.bytes_per_us;
   est_us = 1e30;
   for (int64_t cand = 1; cand <= s_max; ++cand) {
@@ -199,7 +199,7 @@ void plan_direct(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t rows, i
     if ((ntiles + tps - 1) / tps != cand) continue;
     const double w = (double)(base * cand), per_cu = std::ceil(w / c.n_cu);
     const double chain = per_cu * (double)tps * k.tile;
-    const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : kAlone);
+    const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : tps > 48 ? 1.02 : 1.0);
     double t = k.start_end + std::sqrt(chain * chain + mem * mem) + (per_cu > 2.0 ? k.round : 0.0);
     if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
     // pieces that meet in the last one's workgroup (meet.h): a launch less, but the workgroups of a head count themselves one by one
