@@ -276,10 +276,12 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.pair_units = pl.pair_units;
   const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
   const size_t lse_bytes = (size_t)n_tokens * f.n_q_heads * sizeof(float);
-  // (Then the results are stored while others still read their queries: rows that lie on other rows' queries are left to the merge kernel.)
-  const bool merge_inside = two_pieces_meet(pc, pl, pl.n_splits) && (out == q || apart(q, out_bytes, out, out_bytes)) && (!lse || apart(q, out_bytes, lse, lse_bytes));
+  // Pieces that meet in the attention kernel: then the results are stored while others still read their queries, and rows that lie on other
+  // rows' queries are left to the merge kernel.
+  const bool off_queries = (out == q || apart(q, out_bytes, out, out_bytes)) && (!lse || apart(q, out_bytes, lse, lse_bytes));
+  const bool merge_inside = off_queries && two_pieces_meet(pc, pl, pl.n_splits);
   at.merge_count = merge_inside ? c->merge_count : nullptr;
-  const bool meet = pieces_meet(pc, pl, n_tokens, pl.n_splits);
+  const bool meet = off_queries && pieces_meet(pc, pl, n_tokens, pl.n_splits);
   at.meet_count = meet ? c->merge_count + kMergeCounters : nullptr;
   at.scale_log2e = c->scale * 1.4426950408889634f;
   at.rope_cos = opt.rope_cos;
@@ -300,7 +302,7 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     results_apart = results_apart && (from_out || in_place) && from_lse;
     rows_apart = rows_apart && from_out && from_lse && apart(rows, new_bytes, c->kv, c->kv_bytes);
   }
-  const bool may_append = f.dtype == KVFOLD_BF16 && !opt.rope_cos ? results_apart || (pl.n_splits > 1 && !merge_inside) : rows_apart;
+  const bool may_append = f.dtype == KVFOLD_BF16 && !opt.rope_cos ? results_apart || (pl.n_splits > 1 && !merge_inside && !meet) : rows_apart;
   const bool fused_append = may_append && attention_appends(pc, pl, n_tokens, opt.rope_cos != nullptr);
   at.k_new = fused_append ? k_new : nullptr;
   at.v_new = fused_append ? v_new : nullptr;

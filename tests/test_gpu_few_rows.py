@@ -137,3 +137,29 @@ def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits):
     _step(cache, L, args, lse=lse[1])
     assert (lse[0] - lse[1]).abs().max() <= 1e-4
     cache.close()
+
+
+@pytest.mark.parametrize("on", ["k", "v", "q", "next"])
+def test_pieces_that_meet_under_an_output_on_the_inputs(on):
+    """The output on rows that other heads' workgroups still read -- new rows, or other rows' queries -- has the same bits."""
+    Hq, Hkv, d, n, L = 64, 32, 128, 2, 900
+    cache, (q, k, v) = _filled(Hq, Hkv, d, n, L)
+    cache.set_tuning(kv.TUNE_SPLITS, 3)
+    want = _step(cache, L, (q, k, v))
+    rows = [t[:, L:L + n].clone() for t in cache.view(0)]
+    for _ in range(5):
+        both = torch.zeros(2 * q.numel(), device="cuda", dtype=torch.bfloat16)
+        at = {"next": d}.get(on, 0)
+        src = {"k": k, "v": v}.get(on, q)
+        put = both[:src.numel()].view(src.shape)
+        put.copy_(src)
+        args = {"k": (q, put, v), "v": (q, k, put)}.get(on, (put, k, v))
+        out = both[at:at + q.numel()].view(q.shape)
+        for t in cache.view(0):
+            t[:, L:L + n] = 0
+        cache.set_length(0, L)
+        cache.step(0, *args, out, pos_offset=L)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert all(torch.equal(t[:, L:L + n], r) for t, r in zip(cache.view(0), rows))
+    cache.close()
