@@ -453,7 +453,7 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
     if (p.n_splits <= 6 * 64 / V)
       parts.template merge<6>((unsigned)at, part, cv, acc, M, L);
     else
-      parts.template merge<12>((unsigned)at, part, cv, acc, M, L);
+      parts.template merge<kMeetSplits * V / 64>((unsigned)at, part, cv, acc, M, L);
     const float inv = 1.f / L;
     bf16x4 v;
 #pragma unroll

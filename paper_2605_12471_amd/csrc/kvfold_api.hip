@@ -20,7 +20,7 @@
 
 using namespace kvfold;
 
-constexpr size_t kCounterBytes = (kMergeCounters + (size_t)kMeetSplits * kMeetUnits) * sizeof(uint32_t);
+constexpr size_t kCounterBytes = (kMergeCounters + (size_t)kMeetUnits * kMeetStride) * sizeof(uint32_t);
 
 struct kvfold_cache {
   PlanCtx pc;  // configuration, workspace size, CU count, tuning knobs, storage round trip: what the planner reads

@@ -199,11 +199,10 @@ void plan_direct(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t rows, i
     if ((ntiles + tps - 1) / tps != cand) continue;
     const double w = (double)(base * cand), per_cu = std::ceil(w / c.n_cu);
     const double chain = per_cu * (double)tps * k.tile;
-    const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : tps > 48 ? 1.02 : 1.0);
+    const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : tps > 48 ? 1.05 : 1.0);
     double t = k.start_end + std::sqrt(chain * chain + mem * mem) + (per_cu > 2.0 ? k.round : 0.0);
     if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
-    // pieces that meet in the last one's workgroup (meet.h): a launch less, but the workgroups of a head count themselves one by one
-    if (pieces_meet(c, pl, n_tokens, cand)) t += 0.09 * std::max(0.0, (double)cand - 8.0) - 1.2;
+    if (pieces_meet(c, pl, n_tokens, cand)) t -= 1.1;  // (meet.h)
     if (t < est_us) {
       est_us = t;
       s = cand;

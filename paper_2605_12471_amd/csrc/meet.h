@@ -1,8 +1,8 @@
 // The pieces of a step meet in the attention kernel: the last workgroup of a unit to have stored its partial results merges them all.  For kernels
-// of one unit a workgroup, where that is little to read.  Against the combine kernel (captured graphs, one token, 32 heads on 8): 500 keys 6.74 -> 5.84 us,
-// 1000 7.03 -> 6.53, 2000 8.0 -> 7.6, 64 wide 1000 6.66 -> 5.8, 4187 8.18 -> 7.6.  A head's workgroups count themselves one after the other, 0.1 us each, so
-// that 22 pieces are where it is even (4187 keys, 9.47 / 9.66); a wavefront has a row, and more rows than wavefronts are a
-// second way through memory (28 heads on 4, 2331 keys 7.9 / 9.3 us, 16 rows 10.4 / 11.8).
+// of one unit a workgroup, where that is little to read.  Against the combine kernel (captured graphs, one token, 32 heads on 8): 500 keys 6.74 -> 5.75 us,
+// 1000 7.03 -> 6.44, 4187 9.48 -> 8.68, 9000 12.4 -> 11.7, 64 wide 1000 6.66 -> 5.36, 4187 8.18 -> 6.60.  The counters of two KV heads lie 256 bytes apart: next
+// to one another the atomics of all heads waited for each other, 0.1 us for every piece (17 pieces of 8 heads 9.56 us, apart 8.90).  A
+// wavefront has a row, and more rows than wavefronts are a second way through memory (28 heads on 4, 2331 keys 7.9 / 8.8 us, 16 rows 10.4 / 11.3).
 #pragma once
 #include "kvfold_internal.h"
 #include "wave_ops.h"
@@ -85,7 +85,7 @@ struct Partials {
 __device__ __forceinline__ bool last_to_meet(const AttnParams& p, int unit, int* flag) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) *flag = atomicInc(p.meet_count + (p.n_splits - 1) * kMeetUnits + unit, (unsigned)p.n_splits - 1u) == (unsigned)p.n_splits - 1u;
+  if (threadIdx.x == 0) *flag = atomicInc(p.meet_count + unit * kMeetStride + p.n_splits, (unsigned)p.n_splits - 1u) == (unsigned)p.n_splits - 1u;
   __syncthreads();
   return *flag != 0;
 }
