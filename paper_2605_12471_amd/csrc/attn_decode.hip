@@ -20,6 +20,8 @@
 // its plan.  17 to 32 rows of 128 columns stay there: here they take 392 registers, one wavefront per SIMD, and gained nothing (14 shapes 0.99,
 // 8 tokens on 4187 keys, 32 heads on 8, 13.0 / 12.9; 2 on 115K, 32 on 2, 29.9 / 32.4).  (A few workgroups on long caches are a little slower, one
 // token on 88K keys, 32 heads on 2, 128 workgroups, 24.7 -> 25.7.)
+#include <type_traits>
+
 #include "append_rows.h"
 #include "kvfold_internal.h"
 #include "meet.h"
@@ -443,24 +445,43 @@ __global__ void __launch_bounds__(kDecodeWaves * 64, 2) attn_decode_kernel(AttnP
     }
   }
   if (!p.meet_count || !last_to_meet(p, g, &last)) return;
-#pragma unroll 1
-  for (int r = w; r < rows; r += NW) {
-    const int t = (int)quot((unsigned)r, p.by_group), h = g * G + r - t * G;
-    const int64_t at = (int64_t)t * Hq + h;
-    const int cv = l % V, part = l / V;
-    floatx4 acc;
-    float M, L;
-    if (p.n_splits <= 6 * 64 / V)
-      parts.template merge<6>((unsigned)at, part, cv, acc, M, L);
-    else
-      parts.template merge<kMeetSplits * V / 64>((unsigned)at, part, cv, acc, M, L);
-    const float inv = 1.f / L;
-    bf16x4 v;
+  // a row or two per wavefront
+  const int cv = l % V, part = l / V;
+  auto finish = [&](auto pieces, auto per_wave) __attribute__((always_inline)) {
+    constexpr int B = decltype(per_wave)::value;
+    unsigned at[B];
+    int at_lse[B];
+    floatx4 acc[B];
+    float M[B], L[B];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[e] * inv);
-    if (part == 0) *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at * D + cv * 4) = v;
-    if (p.lse && l == 0) p.lse[(int64_t)h * C + t] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
-  }
+    for (int j = 0; j < B; ++j) {
+      const int r = w + j * NW < rows ? w + j * NW : rows - 1, t = (int)quot((unsigned)r, p.by_group), h = g * G + r - t * G;
+      at[j] = (unsigned)(t * Hq + h);
+      at_lse[j] = h * C + t;
+    }
+    parts.template merge<decltype(pieces)::value, B>(at, part, cv, acc, M, L);
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      if (w + j * NW >= rows || part != 0) continue;
+      const float inv = 1.f / L[j];
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[j][e] * inv);
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + (int64_t)at[j] * D + cv * 4) = v;
+      if (p.lse && cv == 0) p.lse[at_lse[j]] = (M[j] + __builtin_amdgcn_logf(L[j])) * 0.6931471805599453f;
+    }
+  };
+  constexpr std::integral_constant<int, kMeetSplitsFew * V / 64 * (D == 64 ? 2 : 1)> few{};
+  constexpr std::integral_constant<int, kMeetSplits * V / 64> many{};
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 2> two{};
+  const bool little = p.n_splits <= decltype(few)::value * 64 / V;
+  if (rows <= NW)
+    little ? finish(few, one) : finish(many, one);
+  else if (D == 128 || little)
+    finish(few, two);
+  else
+    finish(many, two);
 }
 
 template <int D, int NC>

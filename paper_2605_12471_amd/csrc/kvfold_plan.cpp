@@ -202,7 +202,7 @@ void plan_direct(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t rows, i
     const double mem = kv_us * (double)(tps * cand) / (double)ntiles * (per_cu > 1.0 ? 1.0 + k.uneven * (per_cu * c.n_cu / w - 1.0) : tps > 48 ? 1.05 : 1.0);
     double t = k.start_end + std::sqrt(chain * chain + mem * mem) + (per_cu > 2.0 ? k.round : 0.0);
     if (cand > 1) t += k.merge + (double)cand * (double)rows * (c.cfg.head_dim + 2) * 8.0 / k.merge_bytes_per_us;
-    if (pieces_meet(c, pl, n_tokens, cand)) t -= 1.1;  // (meet.h)
+    if (pieces_meet(c, pl, n_tokens, cand)) t -= c.cfg.head_dim == 64 || rows <= 4 * c.cfg.n_kv_heads ? 1.1 : 0.6;  // (meet.h)
     if (t < est_us) {
       est_us = t;
       s = cand;

@@ -39,12 +39,14 @@ inline bool two_pieces_meet(const PlanCtx& c, const Plan& pl, int n_splits) {
   return c.two_meet && n_splits == 2 && !pl.key_waves && waves <= kMergeCounters && 2 * waves * pl.units_per_wave * 64 <= c.ws_rows;
 }
 
-// The kernel whose pieces may meet in the last one's workgroup (meet.h), and whether they do: at most four rows.
-constexpr int kMeetUnits = 1024, kMeetSplits = 32;
+// The kernel whose pieces may meet in the last one's workgroup (meet.h), and whether they do: at most four rows, one a wavefront, or eight, then
+// 128 wide at most twelve pieces.
+constexpr int kMeetUnits = 1024, kMeetSplits = 32, kMeetSplitsFew = 12;
 constexpr int kMeetStride = 64;  // words of a KV head, its counter for every number of pieces among them
 inline bool pieces_meet(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t n_splits) {
   const int rows = n_tokens * (c.cfg.n_q_heads / c.cfg.n_kv_heads);
-  return c.two_meet && pl.direct && n_splits > 1 && n_splits <= kMeetSplits && rows <= 4 && c.cfg.n_kv_heads <= kMeetUnits;
+  return c.two_meet && pl.direct && n_splits > 1 && n_splits <= (rows <= 4 || c.cfg.head_dim == 64 ? kMeetSplits : kMeetSplitsFew) && rows <= 8 &&
+         c.cfg.n_kv_heads <= kMeetUnits;
 }
 
 int elem_size(int dtype);

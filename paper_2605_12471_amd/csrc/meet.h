@@ -2,7 +2,8 @@
 // of one unit a workgroup, where that is little to read.  Against the combine kernel (captured graphs, one token, 32 heads on 8): 500 keys 6.74 -> 5.75 us,
 // 1000 7.03 -> 6.44, 4187 9.48 -> 8.68, 9000 12.4 -> 11.7, 64 wide 1000 6.66 -> 5.36, 4187 8.18 -> 6.60.  The counters of two KV heads lie 256 bytes apart: next
 // to one another the atomics of all heads waited for each other, 0.1 us for every piece (17 pieces of 8 heads 9.56 us, apart 8.90).  A
-// wavefront has a row, and more rows than wavefronts are a second way through memory (28 heads on 4, 2331 keys 7.9 / 8.8 us, 16 rows 10.4 / 11.3).
+// wavefront has a row, or two (64 heads on 8, 600 keys 6.97 -> 6.17, 64 wide 28 on 4, 1300 6.89 -> 5.95, 6000 8.0 -> 7.2); two of 128 columns with many pieces
+// are more than it has registers in flight for (28 on 4, 2331 keys 7.9 / 8.7 us with 19), and 16 rows a second way through memory (10.4 / 11.3).
 #pragma once
 #include "kvfold_internal.h"
 #include "wave_ops.h"
@@ -34,48 +35,53 @@ struct Partials {
       __builtin_amdgcn_raw_buffer_store_b64(y, ml, row * 8u, 0, kDeviceScope);
     }
   }
-  // The row's pieces, at most N * 64 / V (V = D / 4 column vectors), by one wavefront: lane (part, c) takes every 64 / V-th of them from the
-  // part-th on, then the parts meet; every lane has O, m and l in the end.  Every load is in flight before the first is waited for;
-  // those past the last piece lie outside the buffer, cost no traffic and bring zeros: no keys.
-  template <int N>
-  __device__ __forceinline__ void merge(unsigned at, int part, int c, floatx4& acc, float& m, float& l) const {
+  // The pieces of B rows, at most N * 64 / V of each (V = D / 4 column vectors), by one wavefront: lane (part, c) takes every 64 / V-th of them
+  // from the part-th on, then the parts meet; every lane has O, m and l in the end.  Every load is in flight before the first is waited
+  // for; those past the last piece lie outside the buffer, cost no traffic and bring zeros: no keys.
+  template <int N, int B>
+  __device__ __forceinline__ void merge(const unsigned (&at)[B], int part, int c, floatx4 (&acc)[B], float (&m)[B], float (&l)[B]) const {
     constexpr unsigned PARTS = 64 / (D / 4);
-    uintx4 x[N];
-    uintx2 y[N];
+    uintx4 x[B][N];
+    uintx2 y[B][N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const unsigned row = ((unsigned)i * PARTS + (unsigned)part) * n_rows + at;
-      y[i] = __builtin_amdgcn_raw_buffer_load_b64(ml, row * 8u, 0, kDeviceScope);
-      x[i] = __builtin_amdgcn_raw_buffer_load_b128(o, row * (D * 4u) + (unsigned)c * 16u, 0, kDeviceScope);
-    }
-    m = -INFINITY;
+    for (int j = 0; j < B; ++j)
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
-      if (y[i][1] == 0u) {
-        y[i][0] = __float_as_uint(-INFINITY);
-        x[i] = uintx4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < N; ++i) {
+        const unsigned row = ((unsigned)i * PARTS + (unsigned)part) * n_rows + at[j];
+        y[j][i] = __builtin_amdgcn_raw_buffer_load_b64(ml, row * 8u, 0, kDeviceScope);
+        x[j][i] = __builtin_amdgcn_raw_buffer_load_b128(o, row * (D * 4u) + (unsigned)c * 16u, 0, kDeviceScope);
       }
-      m = fmaxf(m, __uint_as_float(y[i][0]));
-    }
-    m = pair_max(m);
-    if (PARTS == 4) m = row16_max(m);
-    const float ref = m == -INFINITY ? 0.f : m;
-    acc = floatx4{0.f, 0.f, 0.f, 0.f};
-    l = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float b = __builtin_amdgcn_exp2f(__uint_as_float(y[i][0]) - ref);
-      l = __builtin_fmaf(__uint_as_float(y[i][1]), b, l);
+    for (int j = 0; j < B; ++j) {
+      m[j] = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(__uint_as_float(x[i][e]), b, acc[e]);
-    }
-    l = pair_sum(l);
-    if (PARTS == 4) l = row16_sum(l);
+      for (int i = 0; i < N; ++i) {
+        // no visible key for the row in this piece, whose O may be NaN: 0 times a value that is not finite
+        if (y[j][i][1] == 0u) {
+          y[j][i][0] = __float_as_uint(-INFINITY);
+          x[j][i] = uintx4{0u, 0u, 0u, 0u};
+        }
+        m[j] = fmaxf(m[j], __uint_as_float(y[j][i][0]));
+      }
+      m[j] = pair_max(m[j]);
+      if (PARTS == 4) m[j] = row16_max(m[j]);
+      const float ref = m[j] == -INFINITY ? 0.f : m[j];
+      acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      l[j] = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[e] = pair_sum(acc[e]);
-      if (PARTS == 4) acc[e] = row16_sum(acc[e]);
+      for (int i = 0; i < N; ++i) {
+        const float b = __builtin_amdgcn_exp2f(__uint_as_float(y[j][i][0]) - ref);
+        l[j] = __builtin_fmaf(__uint_as_float(y[j][i][1]), b, l[j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] = __builtin_fmaf(__uint_as_float(x[j][i][e]), b, acc[j][e]);
+      }
+      l[j] = pair_sum(l[j]);
+      if (PARTS == 4) l[j] = row16_sum(l[j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[j][e] = pair_sum(acc[j][e]);
+        if (PARTS == 4) acc[j][e] = row16_sum(acc[j][e]);
+      }
     }
   }
 };

@@ -116,10 +116,10 @@ def test_graph_replays():
     cache.close()
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1)])
+@pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1), (8, 1, 64, 1), (7, 1, 128, 1), (9, 1, 64, 1)])
 @pytest.mark.parametrize("splits,tiles", [(2, 22), (6, 22), (7, 21), (12, 24), (13, 26), (24, 24), (25, 25), (32, 32), (33, 33)])
 def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits, tiles):
-    """Up to four rows and 32 pieces: a lane's six, and more, and the merge kernel beyond (and in static scratch), with piece counts that change
+    """Up to eight rows and 32 pieces: a lane's six, and more, a row of a wavefront or two, and the merge kernel beyond (and in static scratch), with piece counts that change
     from step to step; within the rounding of the output, and the same bits every time."""
     L = 64 * (tiles - 1) + 17
     cache, args = _filled(Hq, Hkv, d, n, L)
