@@ -22,6 +22,19 @@ using namespace kvfold;
 
 constexpr size_t kCounterBytes = (kMergeCounters + (size_t)kMeetUnits * kMeetStride) * sizeof(uint32_t);
 
+// Clears device memory and waits for it, on a stream that waits for no other and that none waits for: a cache may be created beside other streams'
+// work, or while one of them is being captured.  (A small cache is created in 14 us without counters, in 60 with them, by the legacy stream, which would wait
+// for what others have queued, in 26.)
+static hipError_t clear(void* p, size_t bytes) {
+  hipStream_t s;
+  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e != hipSuccess) return e;
+  e = hipMemsetAsync(p, 0, bytes, s);
+  const hipError_t done = hipStreamSynchronize(s);
+  (void)hipStreamDestroy(s);
+  return e != hipSuccess ? e : done;
+}
+
 struct kvfold_cache {
   PlanCtx pc;  // configuration, workspace size, CU count, tuning knobs, storage round trip: what the planner reads
   int elem_bytes;
@@ -31,7 +44,7 @@ struct kvfold_cache {
   size_t kv_bytes;
   float* ws_o;   // split workspace: unnormalised partial outputs
   float* ws_ml;  // split workspace: (max, sum) pairs
-  uint32_t* merge_count;  // kMergeCounters zeros, and those of meet_count behind them (see AttnParams), nullptr where there is no workspace
+  uint32_t* merge_count;  // in ws_ml's allocation: kMergeCounters zeros, and those of meet_count behind them (see AttnParams); nullptr in fp32 and without a workspace
   std::vector<int64_t> len;
   // optional per-kernel timing: 4 events per step (before append, after append, after attention, after merge)
   std::vector<hipEvent_t> prof_events;
@@ -163,16 +176,13 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
 
   const int64_t ws_rows = workspace_rows(cfg);
   if (ws_rows > 0) {
-    void *po = nullptr, *pm = nullptr, *pc = nullptr;
+    // (bf16: the counters lie behind the pairs, from a multiple of 256 bytes on)
+    const size_t ml_bytes = ((size_t)ws_rows * 2 * sizeof(float) + 255) / 256 * 256, counter_bytes = cfg->dtype == KVFOLD_BF16 ? kCounterBytes : 0;
+    void *po = nullptr, *pm = nullptr;
     e = hipMalloc(&po, (size_t)ws_rows * cfg->head_dim * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&pm, (size_t)ws_rows * 2 * sizeof(float));
-    if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) {
-      e = hipMalloc(&pc, kCounterBytes);
-      if (e == hipSuccess) e = hipMemset(pc, 0, kCounterBytes);
-      if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // steps may run on streams that do not wait for this one
-    }
+    if (e == hipSuccess) e = hipMalloc(&pm, ml_bytes + counter_bytes);
+    if (e == hipSuccess && counter_bytes) e = clear(static_cast<char*>(pm) + ml_bytes, counter_bytes);
     if (e != hipSuccess) {
-      if (pc) (void)hipFree(pc);
       if (pm) (void)hipFree(pm);
       if (po) (void)hipFree(po);
       if (c->owns_kv) (void)hipFree(c->kv);
@@ -181,9 +191,9 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
     }
     c->ws_o = static_cast<float*>(po);
     c->ws_ml = static_cast<float*>(pm);
-    c->merge_count = static_cast<uint32_t*>(pc);
+    if (counter_bytes) c->merge_count = reinterpret_cast<uint32_t*>(static_cast<char*>(pm) + ml_bytes);
     c->pc.ws_rows = ws_rows;
-    c->pc.two_meet = pc != nullptr;
+    c->pc.two_meet = counter_bytes != 0;
   }
   *out_cache = c;
   return KVFOLD_OK;
@@ -421,7 +431,6 @@ int kvfold_cache_destroy(kvfold_cache_t* c) {
     if (c->owns_kv && c->kv) (void)hipFree(c->kv);
     if (c->ws_o) (void)hipFree(c->ws_o);
     if (c->ws_ml) (void)hipFree(c->ws_ml);
-    if (c->merge_count) (void)hipFree(c->merge_count);
   }
   delete c;
   return rc;

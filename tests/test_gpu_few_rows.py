@@ -116,6 +116,30 @@ def test_graph_replays():
     cache.close()
 
 
+def test_cache_created_while_a_stream_is_captured():
+    """Creating a cache touches no other stream: not the legacy one, which a capture in relaxed mode would not survive."""
+    L = 1000
+    cache, args = _filled(8, 2, 128, 1, L)
+    want = _step(cache, L, args)
+    out = torch.zeros_like(want)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    cache.set_length(0, L)
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            other = kv.KvFoldCache(1, 8, 2, 128, 1, L + 1, "bf16")
+            cache.step(0, *args, out, pos_offset=L)
+    torch.cuda.synchronize()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    for rows, filled in zip(other.view(0), cache.view(0)):
+        rows.copy_(filled)
+    other.set_length(0, L)
+    assert torch.equal(_step(other, L, args), want)
+    other.close()
+    cache.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1), (8, 1, 64, 1), (7, 1, 128, 1), (9, 1, 64, 1)])
 @pytest.mark.parametrize("splits,tiles", [(2, 22), (6, 22), (7, 21), (12, 24), (13, 26), (24, 24), (25, 25), (32, 32), (33, 33)])
 def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits, tiles):
