@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -23,8 +24,7 @@ using namespace kvfold;
 constexpr size_t kCounterBytes = (kMergeCounters + (size_t)kMeetUnits * kMeetStride) * sizeof(uint32_t);
 
 // Clears device memory and waits for it, on a stream that waits for no other and that none waits for: a cache may be created beside other streams'
-// work, or while one of them is being captured.  (A small cache is created in 14 us without counters, in 60 with them, by the legacy stream, which would wait
-// for what others have queued, in 26.)
+// work, or while one of them is being captured.  (46 us, and 350 in a process that has no other stream yet.)
 static hipError_t clear(void* p, size_t bytes) {
   hipStream_t s;
   hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
@@ -44,7 +44,8 @@ struct kvfold_cache {
   size_t kv_bytes;
   float* ws_o;   // split workspace: unnormalised partial outputs
   float* ws_ml;  // split workspace: (max, sum) pairs
-  uint32_t* merge_count;  // in ws_ml's allocation: kMergeCounters zeros, and those of meet_count behind them (see AttnParams); nullptr in fp32 and without a workspace
+  uint32_t* merge_count;  // a slot of the static counters, or memory of the cache's own: kMergeCounters zeros, and those of meet_count behind them (see AttnParams); nullptr in fp32 and without a workspace
+  int counter_slot;       // -1: none
   std::vector<int64_t> len;
   // optional per-kernel timing: 4 events per step (before append, after append, after attention, after merge)
   std::vector<hipEvent_t> prof_events;
@@ -90,6 +91,33 @@ int static_scratch(int device, unsigned char** out) {
   }
   *out = g_scratch_ptr[device];
   return KVFOLD_OK;
+}
+
+// ---- counters of the caches: zero when the code object is loaded, and as good as zero between steps (AttnParams), so that a cache takes a slot of
+// them, and gives it back, without work on the device (a small cache is created in 10 us; with memory cleared for it 60).  Beyond kCounterSlots caches
+// a GPU, memory of the cache's own.
+constexpr int kCounterSlots = 64;
+static __device__ __align__(256) uint32_t counters[kCounterSlots][kCounterBytes / sizeof(uint32_t)];  // 18 MiB
+std::mutex g_counters_mutex;
+uint64_t g_counters_taken[kMaxDevices] = {};
+
+// A free slot and its address (the device must be current); -1: none.
+int take_counters(int device, uint32_t** out) {
+  void* ptr = nullptr;
+  if (device < 0 || device >= kMaxDevices || hipGetSymbolAddress(&ptr, HIP_SYMBOL(counters)) != hipSuccess || !ptr) return -1;
+  std::lock_guard<std::mutex> lock(g_counters_mutex);
+  for (int i = 0; i < kCounterSlots; ++i)
+    if (!(g_counters_taken[device] >> i & 1)) {
+      g_counters_taken[device] |= uint64_t{1} << i;
+      *out = static_cast<uint32_t*>(ptr) + (size_t)i * (kCounterBytes / sizeof(uint32_t));
+      return i;
+    }
+  return -1;
+}
+
+void give_counters(int device, int slot) {
+  std::lock_guard<std::mutex> lock(g_counters_mutex);
+  g_counters_taken[device] &= ~(uint64_t{1} << slot);
 }
 
 // Whether two ranges of memory have no byte in common.
@@ -145,6 +173,7 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
   c->ws_o = nullptr;
   c->ws_ml = nullptr;
   c->merge_count = nullptr;
+  c->counter_slot = -1;
   c->len.assign((size_t)cfg->n_layers, 0);
 
   hipDeviceProp_t prop;
@@ -176,13 +205,19 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
 
   const int64_t ws_rows = workspace_rows(cfg);
   if (ws_rows > 0) {
-    // (bf16: the counters lie behind the pairs, from a multiple of 256 bytes on)
-    const size_t ml_bytes = ((size_t)ws_rows * 2 * sizeof(float) + 255) / 256 * 256, counter_bytes = cfg->dtype == KVFOLD_BF16 ? kCounterBytes : 0;
-    void *po = nullptr, *pm = nullptr;
+    void *po = nullptr, *pm = nullptr, *pc = nullptr;
     e = hipMalloc(&po, (size_t)ws_rows * cfg->head_dim * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&pm, ml_bytes + counter_bytes);
-    if (e == hipSuccess && counter_bytes) e = clear(static_cast<char*>(pm) + ml_bytes, counter_bytes);
+    if (e == hipSuccess) e = hipMalloc(&pm, (size_t)ws_rows * 2 * sizeof(float));
+    if (e == hipSuccess && cfg->dtype == KVFOLD_BF16) {
+      c->counter_slot = take_counters(cfg->device, &c->merge_count);
+      if (c->counter_slot < 0) {
+        e = hipMalloc(&pc, kCounterBytes);
+        if (e == hipSuccess) e = clear(pc, kCounterBytes);
+        c->merge_count = static_cast<uint32_t*>(pc);
+      }
+    }
     if (e != hipSuccess) {
+      if (pc) (void)hipFree(pc);
       if (pm) (void)hipFree(pm);
       if (po) (void)hipFree(po);
       if (c->owns_kv) (void)hipFree(c->kv);
@@ -191,9 +226,8 @@ int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache) 
     }
     c->ws_o = static_cast<float*>(po);
     c->ws_ml = static_cast<float*>(pm);
-    if (counter_bytes) c->merge_count = reinterpret_cast<uint32_t*>(static_cast<char*>(pm) + ml_bytes);
     c->pc.ws_rows = ws_rows;
-    c->pc.two_meet = counter_bytes != 0;
+    c->pc.two_meet = c->merge_count != nullptr;
   }
   *out_cache = c;
   return KVFOLD_OK;
@@ -431,6 +465,8 @@ int kvfold_cache_destroy(kvfold_cache_t* c) {
     if (c->owns_kv && c->kv) (void)hipFree(c->kv);
     if (c->ws_o) (void)hipFree(c->ws_o);
     if (c->ws_ml) (void)hipFree(c->ws_ml);
+    if (c->merge_count && c->counter_slot < 0) (void)hipFree(c->merge_count);
+    if (c->counter_slot >= 0 && rc == KVFOLD_OK) give_counters(c->pc.cfg.device, c->counter_slot);  // (all steps have ended)
   }
   delete c;
   return rc;

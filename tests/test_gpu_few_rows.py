@@ -140,6 +140,21 @@ def test_cache_created_while_a_stream_is_captured():
     cache.close()
 
 
+def test_counters_of_many_caches():
+    """More caches than there are static counters, in turn and given back in between: the same bits from each, the last one's counters its own."""
+    L = 1000
+    first, args = _filled(8, 2, 128, 1, L)
+    want = _step(first, L, args)
+    caches = [_filled(8, 2, 128, 1, L)[0] for _ in range(70)]
+    assert all(torch.equal(_step(c, L, args), want) for c in caches for _ in range(2))
+    for c in caches[10:30] + [first]:
+        c.close()
+    again = [_filled(8, 2, 128, 1, L)[0] for _ in range(3)]
+    for c in caches[:10] + again + caches[30:]:
+        assert torch.equal(_step(c, L, args), want)
+        c.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1), (8, 1, 64, 1), (7, 1, 128, 1), (9, 1, 64, 1)])
 @pytest.mark.parametrize("splits,tiles", [(2, 22), (6, 22), (7, 21), (12, 24), (13, 26), (24, 24), (25, 25), (32, 32), (33, 33)])
 def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits, tiles):
