@@ -320,12 +320,21 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
   at.pair_units = pl.pair_units;
   const size_t new_bytes = (size_t)n_tokens * f.n_kv_heads * f.head_dim * c->elem_bytes, out_bytes = (size_t)n_tokens * f.n_q_heads * f.head_dim * c->elem_bytes;
   const size_t lse_bytes = (size_t)n_tokens * f.n_q_heads * sizeof(float);
-  // Pieces that meet in the attention kernel: then the results are stored while others still read their queries, and rows that lie on other
-  // rows' queries are left to the merge kernel.
-  const bool off_queries = (out == q || apart(q, out_bytes, out, out_bytes)) && (!lse || apart(q, out_bytes, lse, lse_bytes));
-  const bool merge_inside = off_queries && two_pieces_meet(pc, pl, pl.n_splits);
+  // Pieces that meet in the attention kernel: then the results are stored while others still read their queries, the keys and the rotary
+  // embedding's angles, and results that lie on any of these (but for the rows' own queries) are left to the merge kernel.
+  bool off_inputs = out == q || apart(q, out_bytes, out, out_bytes);
+  if (lse) off_inputs = off_inputs && apart(q, out_bytes, lse, lse_bytes);
+  const size_t angle_bytes = (size_t)n_tokens * (f.head_dim / 2) * sizeof(float);
+  auto keep_off = [&](const void* in, size_t bytes) { off_inputs = off_inputs && apart(in, bytes, out, out_bytes) && (!lse || apart(in, bytes, lse, lse_bytes)); };
+  keep_off(k_layer, layer_block);
+  keep_off(v_layer, layer_block);
+  if (opt.rope_cos) {
+    keep_off(opt.rope_cos, angle_bytes);
+    keep_off(opt.rope_sin, angle_bytes);
+  }
+  const bool merge_inside = off_inputs && two_pieces_meet(pc, pl, pl.n_splits);
   at.merge_count = merge_inside ? c->merge_count : nullptr;
-  const bool meet = off_queries && pieces_meet(pc, pl, n_tokens, pl.n_splits);
+  const bool meet = off_inputs && pieces_meet(pc, pl, n_tokens, pl.n_splits);
   at.meet_count = meet ? c->merge_count + kMergeCounters : nullptr;
   at.scale_log2e = c->scale * 1.4426950408889634f;
   at.rope_cos = opt.rope_cos;

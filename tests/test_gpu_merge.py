@@ -144,3 +144,46 @@ def test_two_pieces_meet_in_the_attention_kernel(H, d, upw, n):
         assert all(torch.equal(a, b) for a, b in zip(want, step(at, both[first:first + q.numel()].view(q.shape))))
     assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.empty_like(q))))
     cache.close()
+
+
+@pytest.mark.parametrize("n,splits", [(1, 4), (2, 3), (64, 2)])
+@pytest.mark.parametrize("on", ["cos", "sin", "keys", "values", "lse on keys", "lse on cos"])
+def test_results_on_what_other_workgroups_still_read(n, splits, on):
+    """Pieces that meet in the attention kernel store results while other workgroups read the angles and the cached rows: results that lie on
+    these go through the merge kernel, with the bits they have elsewhere."""
+    Hq, Hkv, d, prev = 64, 32, 128, 900
+    g = torch.Generator("cuda").manual_seed(n)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    tables = I.rope_tables(d, prev, n, device="cuda")
+    cache = kv.KvFoldCache(1, Hq, Hkv, d, 256, 1024, "bf16")
+    if n > 8:
+        cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, 1)
+    cache.set_tuning(kv.TUNE_SPLITS, splits)
+    filled = [torch.randn(Hkv, prev, d, generator=g, device="cuda").bfloat16() for _ in range(2)]
+
+    def step(out, lse, rope):
+        for rows, values in zip(cache.view(0), filled):
+            rows[:, :prev] = values
+        cache.set_length(0, prev)
+        torch.cuda.synchronize()
+        cache.profile_begin(1)
+        cache.step(0, q, k, v, out, pos_offset=prev, lse=lse, rope=rope)
+        merge_ms = cache.profile_end()[3]
+        return out.clone(), lse.clone(), merge_ms > 0
+    want = step(torch.empty_like(q), torch.empty(Hq, n, device="cuda"), tables)
+    assert not want[2]
+    for _ in range(3):
+        room = torch.zeros(max(q.numel() // 2, n * d), device="cuda")  # floats
+        rope, out, lse = tables, torch.empty_like(q), torch.empty(Hq, n, device="cuda")
+        if "keys" in on or "values" in on:
+            at = cache.view(0)[0 if "keys" in on else 1].reshape(-1)
+        else:
+            rope = tuple(t if i != on.endswith("sin") else room[:t.numel()].view(t.shape).copy_(t) for i, t in enumerate(tables))
+            at = room.view(torch.bfloat16)
+        if "lse" in on:
+            lse = at[:2 * lse.numel()].view(torch.float32).view(lse.shape)
+        else:
+            out = at[:q.numel()].view(q.shape)
+        got = step(out, lse, rope)
+        assert got[2] and torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    cache.close()
