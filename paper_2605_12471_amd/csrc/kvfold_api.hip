@@ -273,7 +273,6 @@ int step_impl(kvfold_cache_t* c, int layer, const void* q, const void* k_new, co
     const int64_t rows = (int64_t)n_tokens * f.n_q_heads;
     if (2 * rows > kStaticScratchRows) return KVFOLD_ERR_SCRATCH;  // not even two pieces of this step fit
     pc.ws_rows = kStaticScratchRows;
-    pc.two_meet = false;  // (a step of another cache whose work overlaps this one's races on the array, as ever, but on no counters)
     part_ml = reinterpret_cast<float*>(sp);
     part_o = reinterpret_cast<float*>(sp + (size_t)kStaticScratchRows * 2 * sizeof(float));
   }

@@ -19,7 +19,7 @@ struct PlanCtx {
   int n_cu;
   int tune_splits, tune_units_per_wave, tune_pair_units, tune_fused_append;
   int storage_bits;
-  bool two_meet;  // a step's two pieces may meet in the attention kernel (bf16, the cache's own workspace)
+  bool two_meet;  // a step's pieces may meet in the attention kernel (bf16, a cache with counters, whichever array holds the partial results)
 };
 
 struct Plan {

@@ -155,18 +155,34 @@ def test_counters_of_many_caches():
         c.close()
 
 
+def _by_merge_kernel(cache, L, args):
+    """The step with its pieces merged by the merge kernel: the output's first row lies on the last row's last query."""
+    q = args[0]
+    both = torch.zeros(2 * q.numel(), device="cuda", dtype=q.dtype)
+    out = both[q.numel() - 8:2 * q.numel() - 8].view(q.shape)
+    cache.set_length(0, L)
+    cache.profile_begin(1)
+    cache.step(0, both[:q.numel()].view(q.shape).copy_(q), *args[1:], out, pos_offset=L)
+    assert cache.profile_end()[3] > 0
+    return out.clone()
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1), (8, 1, 64, 1), (7, 1, 128, 1), (9, 1, 64, 1)])
 @pytest.mark.parametrize("splits,tiles", [(2, 22), (6, 22), (7, 21), (12, 24), (13, 26), (24, 24), (25, 25), (32, 32), (33, 33)])
 def test_pieces_that_meet_in_the_last_workgroup(Hq, Hkv, d, n, splits, tiles):
-    """Up to eight rows and 32 pieces: a lane's six, and more, a row of a wavefront or two, and the merge kernel beyond (and in static scratch), with piece counts that change
-    from step to step; within the rounding of the output, and the same bits every time."""
+    """Up to eight rows and 32 pieces (128 wide, more than four rows: twelve): a lane's six, and more, a row of a wavefront or two, and the merge kernel beyond, with piece counts that change
+    from step to step; within the rounding of the output, and the same bits every time, wherever the partial results lie."""
     L = 64 * (tiles - 1) + 17
     cache, args = _filled(Hq, Hkv, d, n, L)
     cache.set_tuning(kv.TUNE_SPLITS, splits)
-    want = _step(cache, L, args, noalloc=True).float()
+    want = _by_merge_kernel(cache, L, args).float()
     lse = [torch.empty(Hq, n, device="cuda") for _ in range(2)]
     assert cache.plan(n, L + n)[1] == splits
+    cache.profile_begin(1)
     one = _step(cache, L, args, lse=lse[0])
+    rows = n * Hq // Hkv
+    assert (cache.profile_end()[3] > 0) == (rows > 8 or splits > (32 if d == 64 or rows <= 4 else 12))
+    assert torch.equal(one, _step(cache, L, args, noalloc=True))
     # the sums differ in fp32's last places, so that the outputs are equal or neighbours, and those are at most 2^-7 of the value apart
     assert ((one.float() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-6).all()
     for other in (3, tiles, splits, 11):

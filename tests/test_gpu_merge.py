@@ -116,9 +116,9 @@ def test_every_row_comes_out_in_its_place(H, d, n, splits):
 @pytest.mark.parametrize("upw", [1, 2])
 @pytest.mark.parametrize("n", [9, 33, 64, 300])
 def test_two_pieces_meet_in_the_attention_kernel(H, d, upw, n):
-    """The bits are the merge kernel's, step after step with whatever counts lie between (static scratch has that kernel merge): partly
-    filled units, wavefronts without rows, a later piece with little in it; and with the output in the place of the queries or, which sends
-    the step to the merge kernel, on other rows' queries."""
+    """The bits are the merge kernel's (an output on other rows' queries sends the step there), step after step with whatever counts lie
+    between: partly filled units, wavefronts without rows, a later piece with little in it; with the output in the place of the queries, and
+    with the partial results in static scratch."""
     Hq, Hkv, prev = 8, 2, 700
     g = torch.Generator("cuda").manual_seed(n + d)
     q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
@@ -128,20 +128,21 @@ def test_two_pieces_meet_in_the_attention_kernel(H, d, upw, n):
     cache.set_tuning(kv.TUNE_UNITS_PER_WAVE, upw)
     cache.set_tuning(kv.TUNE_SPLITS, 2)
 
-    def step(q, out, **kw):
+    def step(q, out, merge=False, **kw):
         lse = torch.empty(Hq, n, device="cuda")
         cache.set_length(0, prev)
+        cache.profile_begin(1)
         cache.step(0, q, k, v, out, pos_offset=prev, lse=lse, **kw)
-        torch.cuda.synchronize()
+        assert (cache.profile_end()[3] > 0) == merge
         return out.clone(), lse
-    want = step(q, torch.empty_like(q), noalloc=True)
+    both = torch.empty(q.numel() + Hq * d, device="cuda", dtype=torch.bfloat16)
+    at = both[:q.numel()].view(q.shape)
+    want = step(at.copy_(q), both[Hq * d:].view(q.shape), merge=True)  # the output one token further on
     for _ in range(3):
         assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.full_like(q, 7.0))))
-    both = torch.empty(q.numel() + Hq * d, device="cuda", dtype=torch.bfloat16)
-    for first in (0, Hq * d):   # the queries' own place; one token further on
-        at = both[:q.numel()].view(q.shape)
-        at.copy_(q)
-        assert all(torch.equal(a, b) for a, b in zip(want, step(at, both[first:first + q.numel()].view(q.shape))))
+    assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.full_like(q, 7.0), noalloc=True)))
+    assert all(torch.equal(a, b) for a, b in zip(want, step(at.copy_(q), at)))
+    assert all(torch.equal(a, b) for a, b in zip(want, step(at.copy_(q), both[Hq * d:].view(q.shape), merge=True)))
     assert all(torch.equal(a, b) for a, b in zip(want, step(q, torch.empty_like(q))))
     cache.close()
 
@@ -150,7 +151,7 @@ def test_two_pieces_meet_in_the_attention_kernel(H, d, upw, n):
 @pytest.mark.parametrize("on", ["cos", "sin", "keys", "values", "lse on keys", "lse on cos"])
 def test_results_on_what_other_workgroups_still_read(n, splits, on):
     """Pieces that meet in the attention kernel store results while other workgroups read the angles and the cached rows: results that lie on
-    these go through the merge kernel, with the bits they have elsewhere."""
+    these go through the merge kernel, with the bits of one on other rows' queries, which has always done so."""
     Hq, Hkv, d, prev = 64, 32, 128, 900
     g = torch.Generator("cuda").manual_seed(n)
     q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
@@ -161,7 +162,7 @@ def test_results_on_what_other_workgroups_still_read(n, splits, on):
     cache.set_tuning(kv.TUNE_SPLITS, splits)
     filled = [torch.randn(Hkv, prev, d, generator=g, device="cuda").bfloat16() for _ in range(2)]
 
-    def step(out, lse, rope):
+    def step(out, lse, rope, q=q):
         for rows, values in zip(cache.view(0), filled):
             rows[:, :prev] = values
         cache.set_length(0, prev)
@@ -170,8 +171,10 @@ def test_results_on_what_other_workgroups_still_read(n, splits, on):
         cache.step(0, q, k, v, out, pos_offset=prev, lse=lse, rope=rope)
         merge_ms = cache.profile_end()[3]
         return out.clone(), lse.clone(), merge_ms > 0
-    want = step(torch.empty_like(q), torch.empty(Hq, n, device="cuda"), tables)
-    assert not want[2]
+    assert not step(torch.empty_like(q), torch.empty(Hq, n, device="cuda"), tables)[2]
+    both = torch.zeros(2 * q.numel(), device="cuda", dtype=q.dtype)
+    want = step(both[q.numel() - 8:-8].view(q.shape), torch.empty(Hq, n, device="cuda"), tables, both[:q.numel()].view(q.shape).copy_(q))
+    assert want[2]
     for _ in range(3):
         room = torch.zeros(max(q.numel() // 2, n * d), device="cuda")  # floats
         rope, out, lse = tables, torch.empty_like(q), torch.empty(Hq, n, device="cuda")

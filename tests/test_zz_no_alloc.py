@@ -80,6 +80,28 @@ def test_noalloc_interleaved_on_one_cache_and_unsplit():
         b.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,n,prev", [
+    (32, 8, 128, 1, 4187), (8, 2, 64, 1, 2331), (16, 4, 128, 2, 1300),   # pieces that meet in the last workgroup
+    (32, 8, 64, 1000, 8232),                                             # two pieces that meet, and fill the static array
+    (28, 4, 128, 1, 9000), (32, 8, 128, 200, 8192),                      # more pieces: the merge kernel
+])
+def test_noalloc_steps_have_the_bits_of_step_ex(Hq, Hkv, d, n, prev):
+    """Steps whose pieces fit both arrays are planned and merged alike, wherever the partial results lie."""
+    cfg = I.FoldConfig("noalloc_bits", 64, 1, Hq, Hkv, d, 1000, 0, "bf16")
+    cache = _filled_cache(cfg, 1000, prev, prev + n, n + d)
+    assert cache.plan(n, prev + n)[1] > 1
+    q, k, v = (t.to(DEV) for t in I.chunk_qkv(cfg, 0, 1, n_tokens=n, token_base=prev))
+    got = []
+    for noalloc in (False, True, True, False):
+        out, lse = torch.empty_like(q), torch.empty((Hq, n), dtype=torch.float32, device=DEV)
+        cache.set_length(0, prev)
+        cache.step(0, q, k, v, out, lse=lse, noalloc=noalloc)
+        torch.cuda.synchronize()
+        got.append((out, lse))
+    cache.close()
+    assert all(torch.equal(a, b) for other in got[1:] for a, b in zip(got[0], other))
+
+
 def test_noalloc_rejects_steps_beyond_the_scratch_array():
     """n_tokens * n_q_heads above 65536 rows cannot place two pieces in the array: KVFOLD_ERR_SCRATCH, nothing
     enqueued, the cache untouched."""
