@@ -161,8 +161,11 @@ struct Sched {
   }
 };
 
+// 64 wide, a CU's LDS and registers have room for three workgroups of the one-unit kernel, and have to keep it: with the code that merges two pieces
+// the compiler takes 180 registers where it is asked for two, and 3570 tokens on 30 keys, 32 heads on 8, took 80 us for 71, 2525 on 67 under a
+// window of 267, 32 on 2, 24.8 for 20.2.  Asked for three it takes 156, without a spill, as before that code.
 template <int D, int QB, int NV>
-__global__ void __launch_bounds__(256, (QB == 1 ? 2 : 1)) attn_bf16_kernel(AttnParams p) {
+__global__ void __launch_bounds__(256, (QB == 2 ? 1 : D == 64 && NV == kRingShared ? 3 : 2)) attn_bf16_kernel(AttnParams p) {
   // Sum-driven reference updates (no row max below the causal horizon) for the two-unit kernel, whose
   // single wavefront per SIMD cannot hide the row-max work; the one-unit kernel has a second
   // wavefront to hide it and fewer registers, and takes the exact row max of every half.

@@ -273,6 +273,14 @@ def test_two_workgroups_of_64_wide_rows_fit_a_cu():
         assert int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", b).group(1)) >= 4, b.splitlines()[0]
 
 
+def test_three_workgroups_of_the_64_wide_one_unit_kernel_fit_a_cu():
+    """Full grids of one unit a wavefront and 64-wide rows have three workgroups a CU: three wavefronts on a SIMD."""
+    if not os.path.exists(build.RESOURCE_REPORT):
+        build.build_library()
+    blocks = [b for b in open(build.RESOURCE_REPORT).read().split("Function Name: ")[1:] if "attn_bf16_kernelILi64ELi1ELi2" in b.splitlines()[0]]
+    assert len(blocks) == 1 and int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", blocks[0]).group(1)) >= 3
+
+
 def test_header_is_plain_c_and_the_c_client_builds(tmp_path):
     """include/kvfold.h compiles as strict C99 on its own (no C++ or HIP in the interface), and the plain-C caller of the
     library compiles with gcc and links against the built library."""
