@@ -102,13 +102,6 @@ __device__ __forceinline__ void mfma_settle_a(floatx16& x) {
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+a"(x));
 }
 
-// V ring slots (the K ring has one more): three where one workgroup has a CU to itself, 112 KB of LDS (the two-unit kernel, and the
-// one-unit kernel in grids that leave no CU two of them); two for the one-unit kernel else, so that two workgroups share a CU's 160 KB
-// (64 wide three or four).  With two slots a tile is asked for one tile's time ahead of its use, which a workgroup alone on its CU spends
-// waiting: 37 tokens, 32 heads on 8, on 32K keys, 16 pieces 49.8 -> 41.1 us, 64 tokens 53.6 -> 48.0, 64 workgroups with 128 tiles each
-// 130 -> 105; 64 wide 64 tokens 34.8 -> 32.5.  Four slots 41.6, 48.6 and 106: the longer fill is not won back.  (Where two share a CU a deeper
-// ring bought nothing, and 64 wide took the third workgroup's room.)
-constexpr int kRingAlone = 3, kRingShared = 2;
 constexpr int vote_bytes(int qb) { return qb == 2 ? 16 : 0; }  // (the one-unit kernel has no vote, and two workgroups fill the LDS to its last byte)
 constexpr float kRescaleThreshold = 16.0f;  // log2 units: stale running max tolerated up to 2^16
 constexpr float kSumThreshold = 1048576.0f;             // 2^20: row sum of a half that moves the reference up
@@ -1206,7 +1199,7 @@ static hipError_t launch_one(const AttnParams& p, hipStream_t s) {
 template <int D>
 static hipError_t prepare_all() {
   hipError_t e = prepare_one<D, 2, kRingAlone>();
-  if (e == hipSuccess) e = prepare_one<D, 1, kRingAlone>();
+  if (D == 128 && e == hipSuccess) e = prepare_one<128, 1, kRingAlone>();
   if (e == hipSuccess) e = prepare_one<D, 1, kRingShared>();
   return e;
 }
@@ -1218,7 +1211,7 @@ hipError_t prepare_attn_bf16(int head_dim) {
 template <int D>
 static hipError_t launch_any(const AttnParams& p, int qb, int n_cu, hipStream_t s) {
   if (qb == 2) return launch_one<D, 2, kRingAlone>(p, s);
-  return p.n_wgs <= n_cu ? launch_one<D, 1, kRingAlone>(p, s) : launch_one<D, 1, kRingShared>(p, s);
+  return D == 128 && ring_slots(D, qb, p.n_wgs, n_cu) == kRingAlone ? launch_one<128, 1, kRingAlone>(p, s) : launch_one<D, 1, kRingShared>(p, s);
 }
 
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, int qb, int n_cu, hipStream_t s) {

@@ -44,6 +44,18 @@ inline int xcd_share_log2(int n_kv_heads, int wgs_per_head, int n_splits, bool o
   return lk;
 }
 
+// V ring slots of the general bf16 kernels (the K ring has one more): three for the two-unit kernel, and 128 wide for the one-unit kernel in grids
+// that leave no CU two workgroups, where one has 112 KB of the CU's LDS to itself; two for the one-unit kernel else, so that two workgroups share the
+// 160 KB (64 wide three).  With two slots a tile is asked for one tile's time ahead of its use, which a workgroup alone on its CU spends waiting: 37
+// tokens, 32 heads on 8, on 32K keys, 16 pieces 49.8 -> 41.1 us, 64 tokens 53.6 -> 48.0, 64 workgroups with 128 tiles each 130 -> 105.  Four
+// slots 41.6, 48.6 and 106: the longer fill is not won back.  Where two share a CU a deeper ring bought nothing.  64 wide a tile is half the rows, and
+// 45 steps alone on their CUs take 0.962 of the time with two slots where they do not split the keys and 0.992 where they do (551 tokens on 66 keys, 32
+// heads on 8, 15.5 -> 14.7 us; 379 on 3639, 28 on 4, 26.9 -> 26.0).
+constexpr int kRingAlone = 3, kRingShared = 2;
+inline int ring_slots(int head_dim, int units_per_wave, int n_wgs, int n_cu) {
+  return units_per_wave == 2 || (head_dim == 128 && n_wgs <= n_cu) ? kRingAlone : kRingShared;
+}
+
 // Quotients by a divisor that the host knows: n / d = (n * mul) >> shift for every n < 2^31.  With l = ceil(log2 d),
 // mul = ceil(2^(31+l) / d) < 2^32 overshoots by e = mul * d - 2^(31+l) < 2^l, and n * e < 2^(31+l).  Integer division
 // has no instruction on the GPU; the half dozen that a workgroup needs to find its place took 1 us of its start.

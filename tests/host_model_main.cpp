@@ -272,7 +272,7 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
       else if (pl.key_waves)
         walk_few(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
       else
-        walk_ring(rd, tm, kr, pl.units_per_wave == 2 ? 3 : 2);
+        walk_ring(rd, tm, kr, ring_slots(cfg.head_dim, pl.units_per_wave, pl.n_wgs, n_cu));
     }
     // every key some row of the workgroup can see was fetched exactly once
     for (int r = rr.row_lo; r <= rr.row_hi; ++r) {
@@ -384,6 +384,22 @@ static void plans_of_single_heads() {
   }
 }
 
+// 64 wide the one-unit kernel keeps two ring slots where it is alone on its CUs (14.7 us, 15.5 with three, and the like); the model walks with the
+// launcher's depth.
+static void ring_depths() {
+  struct { int Hq, Hkv, d, n; int64_t len_prev; int slots; } steps[] = {
+    {32, 8, 64, 551, 66, 2}, {28, 4, 64, 379, 3639, 2}, {32, 8, 64, 3570, 30, 2}, {32, 8, 128, 37, 32768, 3}, {28, 4, 128, 128, 32768, 3}, {32, 8, 128, 2048, 0, 2}};
+  for (auto& t : steps) {
+    PlanCtx pc{};
+    pc.cfg = make_cfg(t.Hq, t.Hkv, t.d, 4096, 131072, KVFOLD_BF16);
+    pc.ws_rows = workspace_rows(&pc.cfg);
+    pc.n_cu = 256;
+    pc.two_meet = true;
+    const Plan pl = make_plan(pc, t.n, t.len_prev + t.n, 0, 0);
+    REQUIRE(!pl.key_waves && pl.units_per_wave == 1 && ring_slots(t.d, 1, pl.n_wgs, 256) == t.slots, "%d tokens on %lld keys", t.n, (long long)t.len_prev);
+  }
+}
+
 static void oracle_tiny() {
   const int64_t Hq = 4, Hkv = 2, d = 8, cap = 40, C = 9, len_prev = 31;
   std::vector<double> K((size_t)Hkv * cap * d), V(K.size()), q((size_t)C * Hq * d);
@@ -423,6 +439,7 @@ int main() {
   model_sweep();
   planner_sweep();
   plans_of_single_heads();
+  ring_depths();
   oracle_tiny();
   std::printf("ok: %ld checks\n", g_checks);
   return 0;
