@@ -37,6 +37,33 @@ def test_neither_form_evenly_dealt(d, n, prev):
     assert plan.n_splits == 1 and plan.units_per_wave == 1
 
 
+@pytest.mark.parametrize("hq,hkv,d,n,prev,splits", [
+    (32, 8, 128, 286, 319, 1),    # 13.05 / 15.4 us with two pieces
+    (32, 32, 128, 264, 409, 1),   # 15.4 / 18.0
+    (32, 32, 128, 260, 597, 1),   # 16.7 / 19.9
+    (32, 8, 128, 284, 699, 1),    # 16.7 / 18.7
+    (28, 4, 128, 374, 497, 1),    # 15.6 / 17.7
+    (64, 8, 128, 147, 718, 1),    # 16.4 / 17.8
+    (8, 1, 64, 1202, 1710, 3),    # 22.4 / 27.5
+    (16, 2, 64, 821, 5170, 4),    # 38.2 / 39.6
+    (28, 4, 64, 565, 6793, 4),    # 45 / 49
+])
+def test_pieces_that_meet_are_not_free(hq, hkv, d, n, prev, splits):
+    """Two pieces need no merge kernel, but the later one waits for memory at its end."""
+    assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).n_splits == splits
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,prev", [
+    (32, 8, 64, 596, 1222),     # 20.0 us / 26.7 whole
+    (28, 4, 64, 2485, 8164),    # 195 / 240 with seven
+    (32, 8, 64, 950, 3361),     # 43 / 54.6 whole
+    (28, 4, 128, 670, 461),     # 19.5 / 24.5 whole
+    (28, 4, 128, 632, 797),     # 21.6 / 29.3 whole
+])
+def test_two_pieces_that_meet(hq, hkv, d, n, prev):
+    assert _plan(kv.KVFOLD_BF16, hq, hkv, d, n, prev).n_splits == 2
+
+
 @pytest.mark.parametrize("hq,hkv,n,prev", [
     (8, 2, 295, 1252),     # 41 / 53 us with 13 pieces
     (4, 1, 897, 146),      # 38 / 49 with 9
