@@ -225,7 +225,6 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
   pl.key_waves = key_waves;
   const bool few_rows = f.dtype == KVFOLD_BF16 && key_waves == 4 && pl.units_per_head == 1 && window <= 0;
   pl.few_rows = few_rows;
-  pl.direct = few_rows && (f.head_dim == 64 || n_tokens * G <= 16);
   const int per_wg = key_waves > 0 ? 1 : waves * upw;
   pl.wgs_per_head = (pl.units_per_head + per_wg - 1) / per_wg;
   const int64_t base = (int64_t)f.n_kv_heads * pl.wgs_per_head;
@@ -239,6 +238,14 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       ntiles = std::max(ntiles, tile_map(len_after - n_tokens, rr.row_lo, rr.row_hi, n_sink, window).ntiles);
     }
   }
+  // At most 16 packed rows, 32 where heads are 64 wide: keys straight into registers (attn_decode.hip).  Not 128 wide on long ranges of one or two KV heads, whose
+  // pieces leave half the CUs without a workgroup: the few-rows kernel fetches more per CU there, if its blocks go round the four wavefronts, an even
+  // number of tiles a piece.  Measured, few rows / registers, one token: 16 heads on 2, 32.6K keys (8 tiles) 14.7 / 15.3 us, 2 on 2, 71.7K (18)
+  // 22.4 / 24.9, 16 on 1, 103K (26) 25.2 / 27.1; 8 on 2, 20K (5) 13.0 / 12.2, 33.7K (9) 15.5 / 14.8, 1 on 1, 32.6K (8) 13.4 / 12.9.  From three KV heads
+  // on registers are faster up to 127K keys (3 on 3, 64K 24.8 / 24.2), and 64 wide everywhere.
+  const int tps_min = (ntiles + kMaxSplits - 1) / kMaxSplits;
+  const bool half_idle = 2 * f.n_kv_heads * kMaxSplits <= c.n_cu && f.n_kv_heads * tps_min >= (tps_min % 2 ? 25 : 16);
+  pl.direct = few_rows && (f.head_dim == 64 || (n_tokens * G <= 16 && !half_idle));
   int64_t s_max = ntiles;
   const int64_t rows = (int64_t)n_tokens * f.n_q_heads;
   if (c.ws_rows / rows < s_max) s_max = c.ws_rows / rows;

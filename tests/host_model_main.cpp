@@ -384,6 +384,31 @@ static void plans_of_single_heads() {
   }
 }
 
+// Few rows 128 wide: long ranges of one or two KV heads belong to the kernel that fetches through LDS (us, it / keys straight into registers).
+static void plans_of_few_rows() {
+  struct { int Hq, Hkv, d, n; int64_t len_prev; bool direct; } steps[] = {
+    {16, 2, 128, 1, 32625, false},   // 14.7 / 15.3
+    {8, 2, 128, 1, 47946, false},    // 17.7 / 19.1
+    {2, 2, 128, 1, 71723, false},    // 22.4 / 24.9
+    {2, 2, 128, 16, 109066, false},  // 31.4 / 33.7
+    {16, 1, 128, 1, 103038, false},  // 25.2 / 27.1
+    {4, 1, 128, 1, 118893, false},   // 27.4 / 29.6
+    {16, 2, 128, 1, 28572, true},    // 14.65 / 13.1
+    {8, 2, 128, 1, 20021, true},     // 13.0 / 12.2
+    {1, 1, 128, 1, 32576, true},     // 13.35 / 12.9
+    {3, 3, 128, 1, 64336, true},     // 24.8 / 24.2
+    {32, 8, 128, 1, 130941, true}, {2, 2, 64, 1, 109066, true}, {4, 1, 64, 8, 118893, true}, {17, 1, 128, 1, 1000, false}};
+  for (auto& t : steps) {
+    PlanCtx pc{};
+    pc.cfg = make_cfg(t.Hq, t.Hkv, t.d, 256, 131072, KVFOLD_BF16);
+    pc.ws_rows = workspace_rows(&pc.cfg);
+    pc.n_cu = 256;
+    pc.two_meet = true;
+    const Plan pl = make_plan(pc, t.n, t.len_prev + t.n, 0, 0);
+    REQUIRE(pl.few_rows && pl.direct == t.direct, "%d tokens on %lld keys, %d heads on %d", t.n, (long long)t.len_prev, t.Hq, t.Hkv);
+  }
+}
+
 // 64 wide the one-unit kernel keeps two ring slots where it is alone on its CUs (14.7 us, 15.5 with three, and the like); the model walks with the
 // launcher's depth.
 static void ring_depths() {
@@ -439,6 +464,7 @@ int main() {
   model_sweep();
   planner_sweep();
   plans_of_single_heads();
+  plans_of_few_rows();
   ring_depths();
   oracle_tiny();
   std::printf("ok: %ld checks\n", g_checks);
