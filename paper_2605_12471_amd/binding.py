@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from typing import Optional
 
 KVFOLD_F32 = 0
@@ -248,24 +249,29 @@ def _current_stream() -> int:
 
 
 _native = False  # module of csrc/py_step.cpp; None: not there, or built for another torch; False: not looked for yet
+_native_lock = threading.Lock()
 
 
 def _native_step():
     global _native
     if _native is False:
-        import importlib.util
-
-        import torch
-        _native = None
-        spec = importlib.util.spec_from_file_location("kvfold_py_step", os.path.join(_HERE, "_lib", "kvfold_py_step.so"))
-        try:
-            module = importlib.util.module_from_spec(spec)
-            spec.loader.exec_module(module)
-            if module.torch_version == torch.__version__.split("+")[0]:
-                _native = module
-        except ImportError:  # (also: no such file)
-            pass
+        with _native_lock:  # (a thread that finds another one looking waits for what it finds)
+            if _native is False:
+                _native = _load_native()
     return _native
+
+
+def _load_native():
+    import importlib.util
+
+    import torch
+    spec = importlib.util.spec_from_file_location("kvfold_py_step", os.path.join(_HERE, "_lib", "kvfold_py_step.so"))
+    try:
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError:  # (also: no such file)
+        return None
+    return module if module.torch_version == torch.__version__.split("+")[0] else None
 
 
 class KvFoldCache:

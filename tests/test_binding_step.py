@@ -1,4 +1,7 @@
 """KvFoldCache.step: its native form takes what the plain Python one takes, with the same results, and leaves the rest to it."""
+import importlib.util
+import threading
+
 import pytest
 import torch
 
@@ -11,6 +14,27 @@ N, HQ, HKV, D = 24, 8, 2, 64
 
 def test_the_native_step_is_built_for_this_torch():
     assert binding._native_step() is not None
+
+
+def test_two_threads_whose_first_steps_meet_both_have_it(monkeypatch):
+    """A thread that looks for the native step while another one is loading it does not take it for missing."""
+    monkeypatch.setattr(binding, "_native", False)
+    loading, go_on, real, got = threading.Event(), threading.Event(), importlib.util.module_from_spec, {}
+
+    def slow(spec):
+        loading.set()
+        assert go_on.wait(10)
+        return real(spec)
+    monkeypatch.setattr(importlib.util, "module_from_spec", slow)
+    first, second = (threading.Thread(target=lambda i=i: got.__setitem__(i, binding._native_step())) for i in (0, 1))
+    first.start()
+    assert loading.wait(10)
+    second.start()
+    second.join(0.2)   # (looked already, or waits)
+    go_on.set()
+    first.join(10)
+    second.join(10)
+    assert got[0] is not None and got[1] is got[0]
 
 
 @pytest.fixture()
