@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
+from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
@@ -56,8 +58,9 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
-def build_py_step() -> str:
-    """Compile the Python binding's native step (g++) against this interpreter and its torch."""
+def build_py_step() -> Optional[str]:
+    """Compile the Python binding's native step (g++) against this interpreter and its torch.  Where it does not compile the binding's plain
+    Python step serves: None, the compiler's words on stderr, and no library of an earlier build in its place."""
     import sysconfig
 
     import torch
@@ -68,7 +71,13 @@ def build_py_step() -> str:
            "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
            "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "py_step.cpp"), "-o", PY_STEP_PATH,
            "-L" + os.path.join(home, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
-    subprocess.run(cmd, check=True)
+    if os.path.exists(PY_STEP_PATH):
+        os.remove(PY_STEP_PATH)
+    try:
+        subprocess.run(cmd, check=True)
+    except (OSError, subprocess.CalledProcessError) as e:
+        print("the native step of the Python binding was not built, the plain one serves: %s" % e, file=sys.stderr)
+        return None
     return PY_STEP_PATH
 
 
@@ -86,5 +95,5 @@ def build_c_client() -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
-    print(build_py_step())
+    print(build_py_step() or "(no native step)")
     print(build_c_client())

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import paper_2605_12471_amd as kv
-from paper_2605_12471_amd import binding
+from paper_2605_12471_amd import binding, build
 from paper_2605_12471_amd import inputs as I
 
 N, HQ, HKV, D = 24, 8, 2, 64
@@ -14,6 +14,20 @@ N, HQ, HKV, D = 24, 8, 2, 64
 
 def test_the_native_step_is_built_for_this_torch():
     assert binding._native_step() is not None
+
+
+@pytest.mark.parametrize("fails", ["no source", "no compiler"])
+def test_a_build_without_it_goes_on(monkeypatch, tmp_path, capfd, fails):
+    """Where the native step does not compile the build leaves none, also not an older one, and the plain Python step serves."""
+    path = tmp_path / "kvfold_py_step.so"
+    path.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(build, "PY_STEP_PATH", str(path))
+    if fails == "no compiler":
+        monkeypatch.setenv("PATH", str(tmp_path))
+    else:
+        monkeypatch.setattr(build, "CSRC", str(tmp_path))   # (there is no py_step.cpp)
+    assert build.build_py_step() is None and not path.exists()
+    assert "native step" in capfd.readouterr().err
 
 
 def test_two_threads_whose_first_steps_meet_both_have_it(monkeypatch):
