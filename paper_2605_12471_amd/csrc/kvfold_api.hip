@@ -73,7 +73,6 @@ namespace {
 // pairs of kStaticScratchRows (row, split) pairs first, then their unnormalised partial outputs (head_dim
 // floats each, 128 at most).  Host code never uses the symbol itself as an address: the per-device pointer
 // comes from hipGetSymbolAddress, once per device.
-constexpr int64_t kStaticScratchRows = 1 << 17;                                    // (row, split) pairs
 constexpr size_t kStaticScratchBytes = (size_t)kStaticScratchRows * (128 + 2) * sizeof(float);  // 65 MiB
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;

@@ -10,6 +10,7 @@
 namespace kvfold {
 
 constexpr int64_t kMaxSplitRows = 1 << 19;  // cap on S * C * Hq rows held in a cache's split workspace
+constexpr int64_t kStaticScratchRows = 1 << 17;  // (row, split) pairs of the static array of steps that allocate nothing
 constexpr int kMaxSplits = 64;
 
 // What the planner needs to know of a cache (all host values).

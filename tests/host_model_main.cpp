@@ -5,16 +5,17 @@
 //     kvfold_consts.h (workgroup_rows, tile_map, key_range, dma_row) and the launch geometry in the planner;
 //     both are used here exactly as the kernels use them.  For many shapes -- chunk length, cache length, group
 //     size, prefix splits, units per wavefront (fp32: wavefronts per workgroup), fused append or not, plain and
-//     sink + sliding-window steps, few rows that need work on their way (rotary embedding, storage round trip), several units that rotate
+//     sink + sliding-window steps, pieces that meet in the attention kernel and pieces that do not, few rows that need work on their way (rotary embedding, storage round trip), several units that rotate
 //     the chunk's rows themselves -- every workgroup's pieces are walked as its kernel walks them -- the general bf16
 //     kernel's ring with its run-ahead and the last tile fetched again past the end, the few-rows kernel's blocks of
-//     32 keys in cyclic order, the fp32 kernel's half tiles with their two sources -- and checked:
+//     32 keys in cyclic order, the decoding kernel's last block and its plain ones, the fp32 kernel's half tiles with their two sources -- and checked:
 //       * every DMA source row lies inside what exists (cache rows below len_prev when the chunk's rows are not
 //         in the cache yet, else below len_prev + C; chunk rows below C), with 32-bit offsets that do not wrap;
 //       * a row that a query of the workgroup can see is fetched unclamped, from the right place;
 //       * the pieces of all splits together cover every visible key of every row of the workgroup exactly once;
 //       * the chunk's rows are appended exactly once: the workgroups' shares of the copy, or the rows that a few-rows
 //         workgroup works on, which are all that it reads of the chunk, and none of which it fetches ahead of its work;
+//       * what pieces leave for one another, and the counters they meet by, lie inside what there is;
 //       * the blocks of the grid are the workgroups, each once, and the units of a piece lie on one XCD where each streams its keys for itself.
 //  2. The planner and validate_config over a sweep of configurations (sanitizers watch the arithmetic).
 //  3. The oracle on tiny inputs, plain and windowed (sanitizers watch its indexing).
@@ -40,6 +41,7 @@ int kvfold_oracle_append_bytes(unsigned char*, int64_t, int64_t, int64_t, int64_
 using namespace kvfold;
 
 static long g_checks = 0, g_rotated = 0;  // g_rotated: steps whose readers rotate the chunk's rows
+static long g_met = 0, g_two_met = 0;     // steps whose pieces meet, by the last workgroup and two by two
 #define REQUIRE(cond, ...)                                   \
   do {                                                       \
     ++g_checks;                                              \
@@ -131,6 +133,42 @@ static void walk_few(Reader& rd, const TileMap& tm, const KeyRange& kr, int nw, 
   }
 }
 
+// The kernel whose keys come straight into registers: each of four wavefronts takes every 4th block of 32 keys.  Its last block, if it has rows past the piece's last
+// or of the chunk, comes first, each row from its own place; all others are asked for as they lie in the cache, in cyclic order from a place of its
+// own.  work: the workgroup appends the chunk's rows of its piece ahead of every fetch.
+static void walk_decode(Reader& rd, const TileMap& tm, const KeyRange& kr, int split, int g, bool work, std::vector<int>& appended) {
+  constexpr int nw = 4;
+  const int vis_last = (int)rd.len_prev + rd.n_tokens;
+  REQUIRE(tm.ns_t == 0 && tm.skip == 0 && tm.ntiles == (vis_last + kTileKeys - 1) / kTileKeys && (int64_t)vis_last == rd.last_key + 1, "keys of the unit");
+  int work_r0 = 0, work_r1 = 0;
+  if (work && kr.t_begin < kr.t_end) {
+    work_r0 = kr.t_begin * kTileKeys - (int)rd.len_prev;
+    if (work_r0 < 0) work_r0 = 0;
+    work_r1 = (int)kr.row_lim + 1 - (int)rd.len_prev;
+  }
+  REQUIRE(work_r1 <= rd.n_tokens, "work on row %d of %d", work_r1 - 1, rd.n_tokens);
+  for (int r = work_r0; r < work_r1; ++r) appended[(size_t)r]++;
+  rd.work_row0 = rd.len_prev + work_r0;
+  rd.work_row1 = rd.len_prev + work_r1;
+  const int b_all = (vis_last + 31) / 32, b_end = 2 * kr.t_end < b_all ? 2 * kr.t_end : b_all;
+  for (int w = 0; w < nw; ++w) {
+    const int b_first = 2 * kr.t_begin + w, n_blocks = b_first < b_end ? (b_end - b_first + nw - 1) / nw : 0;
+    if (n_blocks == 0) continue;
+    const int b_last = b_first + nw * (n_blocks - 1);
+    const bool special = (unsigned)b_last * 32u + 31u > kr.row_lim || (unsigned)b_last * 32u + 31u >= kr.chunk_row0;
+    const int n_plain = n_blocks - (special ? 1 : 0), b_plain = b_first + nw * n_plain;
+    int b = b_first + nw * (int)(((((unsigned)(split * 8 + g) * 40503u) & 0xffffu) * (unsigned)n_plain) >> 16);
+    if (special)
+      for (int row = 0; row < 32; ++row) rd.read(dma_row(kr, 0, b_last * 32 + row), (int64_t)b_last * 32 + row, true);
+    for (int i = 0; i < n_plain; ++i) {
+      REQUIRE(b >= b_first && b < b_plain && (b - b_first) % nw == 0, "block %d of [%d, %d), wavefront %d", b, b_first, b_plain, w);
+      REQUIRE((unsigned)b * 32u + 31u <= kr.row_lim && (unsigned)b * 32u + 31u < kr.chunk_row0, "block %d is not plain", b);
+      for (unsigned row = 0; row < 32; ++row) rd.read(DmaRow{false, (unsigned)b * 32u + row}, (int64_t)b * 32 + row, true);
+      b = b + nw < b_plain ? b + nw : b_first;
+    }
+  }
+}
+
 // The fp32 kernel: half tiles, rows past the last one read as the last one; a last half beyond every row is left out.  Fused: the
 // first half and those of the second loop take each row from its own side, those of the first loop, which ends before the
 // first half that is not all cache, are cache rows.
@@ -179,6 +217,36 @@ static void walk_few_f32(Reader& rd, const TileMap& tm, const KeyRange& kr, int 
   }
 }
 
+// Where the pieces of a step leave their results and how they meet: all of it inside what a cache (or the static array) has.
+static void check_pieces(const PlanCtx& pc, const Plan& pl, int n_tokens) {
+  const kvfold_config_t& cfg = pc.cfg;
+  const bool two = two_pieces_meet(pc, pl, pl.n_splits), meet = pieces_meet(pc, pl, n_tokens, pl.n_splits);
+  if (pl.n_splits == 1) REQUIRE(!two && !meet, "one piece meets nobody");
+  REQUIRE(!(two && meet), "merged twice");
+  if (!pc.two_meet) REQUIRE(!two && !meet, "no counters");
+  const int64_t d4 = cfg.head_dim * 4;
+  if (meet) {  // [piece][token][query head] rows of O, and (m, l); a counter per KV head and number of pieces
+    ++g_met;
+    const int64_t rows = (int64_t)n_tokens * cfg.n_q_heads;
+    REQUIRE(pl.direct && pl.n_splits <= kMaxSplits, "which kernel");
+    REQUIRE(pl.n_splits * rows <= pc.ws_rows && pl.n_splits * rows * d4 < ((int64_t)1 << 32), "partial results");
+    REQUIRE(pl.n_splits < kMeetStride && (int64_t)(cfg.n_kv_heads - 1) * kMeetStride + pl.n_splits < (int64_t)kMeetUnits * kMeetStride, "counter");
+    // a wavefront's lanes hold a row, or two, and every piece of it
+    const int per_wave = (int)((n_tokens * (cfg.n_q_heads / cfg.n_kv_heads) + 3) / 4);
+    REQUIRE(per_wave <= 2 && pl.n_splits <= (per_wave == 2 && cfg.head_dim == 128 ? kMeetSplitsFew : kMeetSplits), "rows and pieces of the last workgroup");
+  }
+  if (two) {  // a wavefront's registers as they lie: 32 rows of O a unit, and 64 lanes' (m, l)
+    ++g_two_met;
+    const int64_t waves = (int64_t)cfg.n_kv_heads * pl.wgs_per_head * kUnitsPerWg, units = 2 * waves * pl.units_per_wave;
+    REQUIRE(!pl.key_waves && waves <= kMergeCounters, "counter");
+    REQUIRE(units * (cfg.head_dim / 32) * 4096 <= pc.ws_rows * d4 && units * 512 <= pc.ws_rows * 8, "partial results");
+    REQUIRE(units * (cfg.head_dim / 32) * 4096 < ((int64_t)1 << 32), "32-bit offset of a partial result");
+  }
+}
+
+static void walk_plan(const PlanCtx& pc, const Plan& pl, int n_tokens, int64_t len_prev, int n_sink, int64_t window, bool rope);
+
+// As the cache would plan it, and where that makes a difference without counters and from the static array.
 static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_t len_prev, int n_sink, int64_t window,
                       int force_splits, int force_upw, bool rope = false, int storage_bits = 0) {
   PlanCtx pc{};
@@ -188,8 +256,31 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   pc.tune_splits = force_splits;
   pc.tune_units_per_wave = force_upw;
   pc.storage_bits = storage_bits;
+  pc.two_meet = cfg.dtype == KVFOLD_BF16 && pc.ws_rows > 0;
+  const Plan pl = make_plan(pc, n_tokens, len_prev + n_tokens, n_sink, window);
+  walk_plan(pc, pl, n_tokens, len_prev, n_sink, window, rope);
+  auto same = [&](const Plan& o) {
+    return o.direct == pl.direct && o.key_waves == pl.key_waves && o.units_per_wave == pl.units_per_wave && o.waves_per_wg == pl.waves_per_wg &&
+           o.n_splits == pl.n_splits && o.tiles_per_split == pl.tiles_per_split && o.pair_units == pl.pair_units && o.pair_order == pl.pair_order;
+  };
+  for (int other = 0; other < 2; ++other) {
+    PlanCtx po = pc;
+    if (other == 0)
+      po.two_meet = false;
+    else
+      po.ws_rows = kStaticScratchRows;
+    if (po.ws_rows < (int64_t)2 * n_tokens * cfg.n_q_heads || (other == 1 && (window > 0 || rope || storage_bits))) continue;
+    const Plan o = make_plan(po, n_tokens, len_prev + n_tokens, n_sink, window);
+    check_pieces(po, o, n_tokens);
+    if (!same(o)) walk_plan(po, o, n_tokens, len_prev, n_sink, window, rope);
+  }
+}
+
+static void walk_plan(const PlanCtx& pc, const Plan& pl, int n_tokens, int64_t len_prev, int n_sink, int64_t window, bool rope) {
+  const kvfold_config_t& cfg = pc.cfg;
   const int64_t len_after = len_prev + n_tokens;
-  const Plan pl = make_plan(pc, n_tokens, len_after, n_sink, window);
+  const int storage_bits = pc.storage_bits, n_cu = pc.n_cu;
+  check_pieces(pc, pl, n_tokens);
   const bool fused = attention_appends(pc, pl, n_tokens, rope), work = attention_works_on_rows(pc, pl, n_tokens, rope);
   REQUIRE(!(fused && work), "appended twice");
   const bool rotates = rope && fused;  // several units read the chunk's rows as handed in, and rotate what they read and append
@@ -205,6 +296,7 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
   if (window > 0) REQUIRE(!pl.pair_units && !pl.pair_order, "pairing under a window");
   REQUIRE(pl.waves_per_wg == kUnitsPerWg || (pl.waves_per_wg == 8 && cfg.dtype == KVFOLD_F32 && pl.units_per_wave == 1), "wavefronts");
   REQUIRE(!pl.few_rows || (cfg.dtype == KVFOLD_BF16 && window <= 0 && pl.units_per_head == 1 && pl.wgs_per_head == 1), "few rows");
+  REQUIRE(!pl.direct || (pl.few_rows && n_tokens * G <= (cfg.head_dim == 64 ? 32 : 16)), "keys straight into registers");
   REQUIRE(pl.key_waves == 0 || pl.key_waves == 8 || (pl.key_waves == 4 && (window <= 0 || cfg.dtype == KVFOLD_F32)), "wavefronts that share a unit's keys");
   REQUIRE(pl.key_waves == 0 || cfg.dtype == KVFOLD_BF16 || pl.key_waves == (cfg.head_dim == 64 ? 8 : 4), "fp32 wavefronts");
   REQUIRE(pl.key_waves == 0 || (pl.wgs_per_head == pl.units_per_head && !pl.pair_units && !pl.pair_order), "one unit a workgroup");
@@ -269,6 +361,8 @@ static void walk_step(const kvfold_config_t& cfg, int n_cu, int n_tokens, int64_
         walk_few_f32(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads);
       else if (cfg.dtype != KVFOLD_BF16)
         walk_halves(rd, tm, kr, len_prev + rr.row_hi + 1);
+      else if (pl.direct)
+        walk_decode(rd, tm, kr, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
       else if (pl.key_waves)
         walk_few(rd, tm, kr, pl.key_waves, len_prev + rr.row_hi + 1, split, (split * 5 + ug) % cfg.n_kv_heads, work, appended);
       else
@@ -318,7 +412,8 @@ static void model_sweep() {
               for (int splits : {0, 2, 5})
                 for (int upw : {0, 1, 2}) {
                   if (splits > 0 && (int64_t)splits * C * h[0] > workspace_rows(&cfg)) continue;
-                  if (d == 64 && (splits > 0 || upw > 0)) continue;  // (the widths differ in the plan's own choice)
+                  // (the widths differ in the plan's own choice, and in the kernel for 17 to 32 rows)
+                  if (d == 64 && (upw > 0 || (splits > 0 && units_of_head(C, h[0] / h[1]) > 1))) continue;
                   walk_step(cfg, 256, C, Lp, (int)w[0], w[1], splits, upw);
                   ++steps;
                   // rows with work on their way: few rows of bf16, several units with the rotary embedding alone, and fp32 behind the append kernel
@@ -330,10 +425,24 @@ static void model_sweep() {
                   }
                 }
             }
+  // decoding: every place of the chunk's rows in their blocks and tiles
+  for (int d : {128, 64})
+    for (auto& h : {std::pair<int, int>{4, 1}, {2, 2}, {9, 1}})
+      for (int C : {1, 2, 4, 7})
+        for (int64_t Lp = 0; Lp < 200; ++Lp)
+          for (int splits : {0, 1, 3})
+            for (int work : {0, 1, 2}) {
+              kvfold_config_t cfg = make_cfg(h.first, h.second, d, C, Lp + C, KVFOLD_BF16);
+              if (splits > 0 && (int64_t)splits * C * h.first > workspace_rows(&cfg)) continue;
+              walk_step(cfg, 256, C, Lp, 0, 0, splits, 0, work == 1, work == 2 ? 4 : 0);
+              ++steps;
+            }
+  REQUIRE(g_met >= 200 && g_two_met >= 200, "%ld and %ld steps meet", g_met, g_two_met);
   REQUIRE(g_rotated >= 50, "%ld steps rotate the chunk's rows where they are read", g_rotated);
   // the benchmark's shapes at their real sizes, plain and with the streaming baseline's window
   struct { int Hq, Hkv, C; int64_t Lp; } big[] = {{32, 8, 2048, 14336}, {32, 8, 256, 130816}, {32, 8, 4096, 126976},
-                                                 {28, 4, 128, 65408}, {28, 4, 8192, 57344}, {32, 8, 16, 131056}, {32, 8, 1, 131071}};
+                                                 {28, 4, 128, 65408}, {28, 4, 8192, 57344}, {32, 8, 16, 131056}, {32, 8, 1, 131071}, {32, 8, 1, 4187},
+                                                 {16, 2, 1, 90509}, {16, 1, 1, 60001}, {32, 8, 2, 30000}, {64, 32, 4, 9001}, {32, 8, 37, 32768}};
   for (auto& b : big)
     for (auto& w : {std::pair<int, int64_t>{0, 0}, {4, 1020}}) {
       kvfold_config_t cfg = make_cfg(b.Hq, b.Hkv, 128, b.C, b.Lp + b.C, KVFOLD_BF16);
