@@ -11,7 +11,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -93,30 +92,18 @@ int static_scratch(int device, unsigned char** out) {
 }
 
 // ---- counters of the caches: zero when the code object is loaded, and as good as zero between steps (AttnParams), so that a cache takes a slot of
-// them, and gives it back, without work on the device (a small cache is created in 10 us; with memory cleared for it 60).  Beyond kCounterSlots caches
+// them, and gives it back, without work on the device (a small cache is created in 10 us; with memory cleared for it 60).  Beyond CounterSlots::kCount caches
 // a GPU, memory of the cache's own.
-constexpr int kCounterSlots = 64;
-static __device__ __align__(256) uint32_t counters[kCounterSlots][kCounterBytes / sizeof(uint32_t)];  // 18 MiB
-std::mutex g_counters_mutex;
-uint64_t g_counters_taken[kMaxDevices] = {};
+static __device__ __align__(256) uint32_t counters[CounterSlots::kCount][kCounterBytes / sizeof(uint32_t)];  // 18 MiB
+CounterSlots g_counter_slots[kMaxDevices];
 
 // A free slot and its address (the device must be current); -1: none.
 int take_counters(int device, uint32_t** out) {
   void* ptr = nullptr;
   if (device < 0 || device >= kMaxDevices || hipGetSymbolAddress(&ptr, HIP_SYMBOL(counters)) != hipSuccess || !ptr) return -1;
-  std::lock_guard<std::mutex> lock(g_counters_mutex);
-  for (int i = 0; i < kCounterSlots; ++i)
-    if (!(g_counters_taken[device] >> i & 1)) {
-      g_counters_taken[device] |= uint64_t{1} << i;
-      *out = static_cast<uint32_t*>(ptr) + (size_t)i * (kCounterBytes / sizeof(uint32_t));
-      return i;
-    }
-  return -1;
-}
-
-void give_counters(int device, int slot) {
-  std::lock_guard<std::mutex> lock(g_counters_mutex);
-  g_counters_taken[device] &= ~(uint64_t{1} << slot);
+  const int slot = g_counter_slots[device].take();
+  if (slot >= 0) *out = static_cast<uint32_t*>(ptr) + (size_t)slot * (kCounterBytes / sizeof(uint32_t));
+  return slot;
 }
 
 // Whether two ranges of memory have no byte in common.
@@ -473,7 +460,7 @@ int kvfold_cache_destroy(kvfold_cache_t* c) {
     if (c->ws_o) (void)hipFree(c->ws_o);
     if (c->ws_ml) (void)hipFree(c->ws_ml);
     if (c->merge_count && c->counter_slot < 0) (void)hipFree(c->merge_count);
-    if (c->counter_slot >= 0 && rc == KVFOLD_OK) give_counters(c->pc.cfg.device, c->counter_slot);  // (all steps have ended)
+    if (c->counter_slot >= 0 && rc == KVFOLD_OK) g_counter_slots[c->pc.cfg.device].give(c->counter_slot);  // (all steps have ended)
   }
   delete c;
   return rc;

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "../../include/kvfold.h"
 #include "kvfold_consts.h"
 
@@ -49,6 +51,26 @@ inline bool pieces_meet(const PlanCtx& c, const Plan& pl, int n_tokens, int64_t 
   return c.two_meet && pl.direct && n_splits > 1 && n_splits <= (rows <= 4 || c.cfg.head_dim == 64 ? kMeetSplits : kMeetSplitsFew) && rows <= 8 &&
          c.cfg.n_kv_heads <= kMeetUnits;
 }
+
+// The caches' places among the static counters of a GPU: each in one cache's hands at a time.
+struct CounterSlots {
+  static constexpr int kCount = 64;
+  std::mutex mutex;
+  uint64_t taken = 0;
+  int take() {  // -1: none is free
+    std::lock_guard<std::mutex> lock(mutex);
+    for (int i = 0; i < kCount; ++i)
+      if (!(taken >> i & 1)) {
+        taken |= uint64_t{1} << i;
+        return i;
+      }
+    return -1;
+  }
+  void give(int i) {
+    std::lock_guard<std::mutex> lock(mutex);
+    taken &= ~(uint64_t{1} << i);
+  }
+};
 
 int elem_size(int dtype);
 int validate_config(const kvfold_config_t* c);

@@ -23,7 +23,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <set>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -534,6 +536,41 @@ static void ring_depths() {
   }
 }
 
+// No slot is in two hands, all are handed out before there is none, and one that was given back goes out again.
+static void counter_slots() {
+  CounterSlots slots;
+  std::set<int> held;
+  for (int i = 0; i < CounterSlots::kCount; ++i) {
+    const int s = slots.take();
+    REQUIRE(s >= 0 && s < CounterSlots::kCount && held.insert(s).second, "slot %d", s);
+  }
+  REQUIRE(slots.take() == -1, "none is free");
+  for (int s : {17, 63, 0}) slots.give(s);
+  for (int want : {0, 17, 63}) REQUIRE(slots.take() == want, "slot %d again", want);
+  REQUIRE(slots.take() == -1, "none is free");
+  for (int s = 0; s < CounterSlots::kCount; ++s) slots.give(s);
+  std::vector<int> in_use(CounterSlots::kCount);
+  std::vector<std::thread> threads;
+  std::mutex m;
+  for (int t = 0; t < 8; ++t)
+    threads.emplace_back([&, t]() {
+      for (int i = 0; i < 2000; ++i) {
+        const int s = slots.take();
+        {
+          std::lock_guard<std::mutex> lock(m);
+          REQUIRE(s >= 0 && in_use[(size_t)s]++ == 0, "slot %d of thread %d", s, t);
+        }
+        {
+          std::lock_guard<std::mutex> lock(m);
+          --in_use[(size_t)s];
+        }
+        slots.give(s);
+      }
+    });
+  for (auto& t : threads) t.join();
+  REQUIRE(slots.taken == 0, "all given back");
+}
+
 static void oracle_tiny() {
   const int64_t Hq = 4, Hkv = 2, d = 8, cap = 40, C = 9, len_prev = 31;
   std::vector<double> K((size_t)Hkv * cap * d), V(K.size()), q((size_t)C * Hq * d);
@@ -573,6 +610,7 @@ int main() {
   model_sweep();
   planner_sweep();
   plans_of_single_heads();
+  counter_slots();
   plans_of_few_rows();
   ring_depths();
   oracle_tiny();

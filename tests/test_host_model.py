@@ -15,7 +15,7 @@ def test_host_model_under_address_and_ub_sanitizers(tmp_path):
     san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-g"]
     subprocess.run(["gcc", "-O1", *san, "-c", os.path.join(ROOT, "oracle", "kvfold_oracle.c"), "-o", obj], check=True)
     subprocess.run(["g++", "-std=c++17", "-O2", *san, os.path.join(ROOT, "tests", "host_model_main.cpp"),
-                    os.path.join(csrc, "kvfold_plan.cpp"), obj, "-lm", "-o", exe], check=True)
+                    os.path.join(csrc, "kvfold_plan.cpp"), obj, "-lm", "-pthread", "-o", exe], check=True)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     env.pop("LD_PRELOAD", None)   # the sanitizer runtime has to come first in the new process
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
