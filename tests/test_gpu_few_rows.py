@@ -117,9 +117,11 @@ def test_graph_replays():
 
 
 def test_cache_created_while_a_stream_is_captured():
-    """Creating a cache touches no other stream: not the legacy one, which a capture in relaxed mode would not survive."""
+    """Creating a cache touches no other stream: not the legacy one, which a capture in relaxed mode would not survive.  With the static
+    counters all taken, so that it clears counters of its own."""
     L = 1000
     cache, args = _filled(8, 2, 128, 1, L)
+    holders = [kv.KvFoldCache(1, 8, 2, 128, 1, L + 1, "bf16") for _ in range(64)]
     want = _step(cache, L, args)
     out = torch.zeros_like(want)
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
@@ -136,12 +138,12 @@ def test_cache_created_while_a_stream_is_captured():
         rows.copy_(filled)
     other.set_length(0, L)
     assert torch.equal(_step(other, L, args), want)
-    other.close()
-    cache.close()
+    for c in [other, cache] + holders:
+        c.close()
 
 
 def test_counters_of_many_caches():
-    """More caches than there are static counters, in turn and given back in between: the same bits from each, the last one's counters its own."""
+    """More caches than there are static counters, some given back in between: the same bits from each.  (Whose counters are whose: the host model.)"""
     L = 1000
     first, args = _filled(8, 2, 128, 1, L)
     want = _step(first, L, args)
@@ -155,16 +157,75 @@ def test_counters_of_many_caches():
         c.close()
 
 
-def _by_merge_kernel(cache, L, args):
+def _by_merge_kernel(cache, L, args, **kw):
     """The step with its pieces merged by the merge kernel: the output's first row lies on the last row's last query."""
     q = args[0]
     both = torch.zeros(2 * q.numel(), device="cuda", dtype=q.dtype)
     out = both[q.numel() - 8:2 * q.numel() - 8].view(q.shape)
     cache.set_length(0, L)
     cache.profile_begin(1)
-    cache.step(0, both[:q.numel()].view(q.shape).copy_(q), *args[1:], out, pos_offset=L)
+    cache.step(0, both[:q.numel()].view(q.shape).copy_(q), *args[1:], out, pos_offset=L, **kw)
     assert cache.profile_end()[3] > 0
     return out.clone()
+
+
+def _in_the_kernel(cache, L, args, **kw):
+    """The step with pieces that meet in the attention kernel, and no append kernel in front."""
+    cache.profile_begin(1)
+    out = _step(cache, L, args, **kw)
+    _, append_ms, _, merge_ms = cache.profile_end()
+    assert append_ms == 0 and merge_ms == 0
+    return out
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,n", [(2, 2, 128, 4), (8, 2, 128, 2), (2, 2, 64, 4), (8, 2, 64, 2)])
+def test_pieces_of_which_a_row_sees_nothing(Hq, Hkv, d, n):
+    """Pieces of a tile each, the chunk's first row the last key of the last but one: the first token sees nothing of the last piece, whose values are NaN
+    and infinite.  One row sees every key of every piece at -inf.  One row of a wavefront and two."""
+    L = 64 * 5 - 1
+    cache, (q, k, v) = _filled(Hq, Hkv, d, n, L)
+    v[1:, 0], v[1:, 1, 5] = math.nan, math.inf
+    for rows in (cache.view(0)[0][-1, :L], k[:, -1]):
+        rows[:, 3] = 3e38
+    q[:, -(Hq // Hkv):, 3] = 0
+    q[0, -1, 3] = -3e38
+    cache.set_tuning(kv.TUNE_SPLITS, 6)
+    assert cache.plan(n, L + n)[1] == 6
+    lse = torch.zeros(Hq, n, device="cuda")
+    got = _in_the_kernel(cache, L, (q, k, v), lse=lse).float()
+    want = _by_merge_kernel(cache, L, (q, k, v)).float()
+    assert torch.isfinite(got[0, :-1]).all() and torch.isnan(got[0, -1]).all()
+    assert torch.isnan(got[1:, :Hq // Hkv]).all() and not torch.isfinite(got[1:, -(Hq // Hkv):, 5]).any()
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    ok = torch.isfinite(want)
+    assert ((got - want)[ok].abs() <= 2.0 ** -7 * want[ok].abs() + 1e-6).all()  # (sums in another order: neighbours at most)
+    assert lse[-1, 0] == -math.inf and torch.isfinite(lse.flatten()[torch.arange(Hq * n) != (Hq - 1) * n]).all()
+    cache.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 128, 2), (4, 4, 64, 4), (16, 2, 64, 1)])
+@pytest.mark.parametrize("bits,rope", [(0, True), (8, False), (4, True)])
+@pytest.mark.parametrize("L", [700, 64 * 11 - 1])
+def test_pieces_that_meet_and_rows_that_their_readers_work_on(Hq, Hkv, d, n, bits, rope, L):
+    """The rotary embedding and the round trip inside a step whose pieces meet: the bits, outputs and cache rows, of the step behind an append kernel, and
+    within rounding those of the merge kernel."""
+    cache, args = _filled(Hq, Hkv, d, n, L)
+    cache.set_storage_roundtrip(bits)
+    cache.set_tuning(kv.TUNE_SPLITS, 6)
+    kw = {"rope": I.rope_tables(d, L, n, device="cuda")} if rope else {}
+    one = _in_the_kernel(cache, L, args, **kw)
+    rows = [t[:, L:L + n].clone() for t in cache.view(0)]
+    for t in cache.view(0):
+        t[:, L:L + n] = 0
+    want = _by_merge_kernel(cache, L, args, **kw).float()
+    assert ((one.float() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-6).all()
+    assert all(torch.equal(t[:, L:L + n], r) for t, r in zip(cache.view(0), rows))
+    cache.set_tuning(kv.TUNE_FUSED_APPEND, 1)
+    for t in cache.view(0):
+        t[:, L:L + n] = 0
+    assert torch.equal(one, _step(cache, L, args, **kw))
+    assert all(torch.equal(t[:, L:L + n], r) for t, r in zip(cache.view(0), rows))
+    cache.close()
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,n", [(32, 8, 128, 1), (8, 2, 64, 1), (3, 3, 128, 4), (2, 2, 64, 1), (10, 2, 128, 1), (8, 1, 64, 1), (7, 1, 128, 1), (9, 1, 64, 1)])
