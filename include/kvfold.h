@@ -84,6 +84,10 @@ size_t kvfold_cache_bytes_required(const kvfold_config_t* cfg /* host */);
  * Layout in HBM: K rows [layer][kv_head][capacity][head_dim], then V rows with
  * the same shape; a row never moves once written.  Also reserves a fixed
  * workspace for split-prefix partial results so that steps allocate nothing.
+ * Pieces of a bf16 step that meet in the attention kernel do so by counters of
+ * the cache: one of 64 places in a static array of the library (18 MiB per GPU,
+ * held until the process ends), given back by kvfold_cache_destroy, or, for
+ * caches beyond 64, 288 KiB of device memory allocated and cleared here.
  * cfg: host.  out_cache: host, receives the handle (NULL on error).
  */
 int kvfold_cache_create(const kvfold_config_t* cfg, kvfold_cache_t** out_cache);
@@ -170,7 +174,8 @@ int kvfold_step_window(kvfold_cache_t* cache, int layer, const void* q, const vo
 /*
  * kvfold_step_ex for callers that can neither allocate device memory nor tolerate a library that does: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, layouts,
- * results and errors as kvfold_step_ex, but the partial results of a split key range go to a fixed array that
+ * results and errors as kvfold_step_ex -- the same bits where the pieces that the planner cuts the keys into fit both places
+ * for their partial results, else equal to the rounding of another order of sums -- but the partial results of a split key range go to a fixed array that
  * is part of the library's code object (65 MiB per GPU, held until the process ends) instead of the cache's
  * workspace; the call allocates nothing and frees nothing.  Limit: n_tokens * n_q_heads <= 65536 (two pieces of
  * the step must fit the array's 131072 (row, piece) slots), else KVFOLD_ERR_SCRATCH and nothing is enqueued;
@@ -253,7 +258,7 @@ int kvfold_cache_set_storage_roundtrip(kvfold_cache_t* cache, int32_t n_bits);
  *                              - neither rotary embedding nor a storage round trip is in play and the chunk's K
  *                                rows (n_tokens * n_kv_heads * head_dim elements) take less than 2^32 bytes (it reads
  *                                the chunk's own rows from k_new / v_new, with 32-bit byte offsets), bf16: unless
- *                                out or lse of an unsplit step lies on these rows (out in their very place may, with
+ *                                out or lse lies on these rows in a step of one piece or of pieces that meet in the attention kernel (out in their very place may, with
  *                                as many KV as query heads and at most 32 tokens); fp32: the kernel for
  *                                few blocks, and workgroups of four wavefronts whose pieces of the key range have fewer than 20 tiles (head_dim 64: 12), and
  *                                rows apart from out, lse and the cache;
@@ -287,7 +292,8 @@ int kvfold_cache_plan(const kvfold_cache_t* cache, int32_t n_tokens, int64_t len
  */
 typedef struct {
   int32_t n_workgroups;    /* workgroups of the attention kernel (fp32: of four or eight wavefronts)     */
-  int32_t n_splits;        /* pieces the key range is cut into (> 1: a merge kernel follows)            */
+  int32_t n_splits;        /* pieces the key range is cut into (> 1: they meet in the attention kernel or */
+                           /* in a merge kernel behind it)                                              */
   int32_t units_per_wave;  /* 32-row query blocks per wavefront (bf16: 1 or 2; fp32, and bf16 steps of few */
                            /* rows, whose kernel has workgroups of one such block: 1)                   */
   int32_t tiles_per_split; /* 64-key tiles per piece                                                    */
@@ -303,8 +309,8 @@ int kvfold_plan_for(const kvfold_config_t* cfg /* host */, int32_t n_compute_uni
  * Per-kernel timing for measurements.  Between _begin and _end every step additionally records
  * HIP events on the step's stream around each of its kernels (append, attention, merge), at most
  * `max_steps` steps (further steps run untimed).  _end synchronises the device, adds up the
- * elapsed times in milliseconds, releases the events and returns to normal operation.  A step
- * whose attention kernel appended by itself counts wholly as attention time.  Any
+ * elapsed times in milliseconds, releases the events and returns to normal operation.  What the
+ * attention kernel does by itself, the append or the merge of pieces that meet in it, counts as attention time.  Any
  * output pointer may be NULL.  Event creation makes _begin the only call besides create/destroy
  * that allocates.
  */
