@@ -37,7 +37,7 @@ PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA (256 CU x 4096 FLOP/clk x 2
 PEAK_F32_MODE_TFLOPS = PEAK_BF16_TFLOPS / 7   # an fp32 product is eight (Q K^T) or six (P V) bf16 products of terms
 PEAK_HBM_GBS = 8000.0
 
-KERNEL_SOURCES = ("attn_bf16.hip", "attn_few.hip", "append_rows.h", "wave_ops.h", "kvfold_internal.h", "kvfold_consts.h", "kvfold_plan.cpp", "kvfold_plan.h")
+KERNEL_SOURCES = ("attn_bf16.hip", "attn_decode.hip", "attn_few.hip", "meet.h", "append_rows.h", "wave_ops.h", "kvfold_internal.h", "kvfold_consts.h", "kvfold_plan.cpp", "kvfold_plan.h")
 
 
 def kernel_source_hash():

@@ -18,8 +18,8 @@
 // token, 32 heads on 8, 128 wide, 93 keys 5.08 -> 3.79 us, 1000 8.34 -> 7.05, 4187 10.75 -> 9.30, 16K 17.8 -> 16.8, 128K 95.1 -> 91.8
 // (5.84 TB/s); 64 wide 4187 keys 9.00 -> 8.13.  Over 116 shapes (1 to 64 heads, 1 to 16 tokens on 64 to 127K keys) 0.92 of the time, each at
 // its plan.  17 to 32 rows of 128 columns stay there: here they take 392 registers, one wavefront per SIMD, and gained nothing (14 shapes 0.99,
-// 8 tokens on 4187 keys, 32 heads on 8, 13.0 / 12.9; 2 on 115K, 32 on 2, 29.9 / 32.4).  (A few workgroups on long caches are a little slower, one
-// token on 88K keys, 32 heads on 2, 128 workgroups, 24.7 -> 25.7.)
+// 8 tokens on 4187 keys, 32 heads on 8, 13.0 / 12.9; 2 on 115K, 32 on 2, 29.9 / 32.4).  Nor do long ranges of one or two KV heads come
+// here, whose pieces leave half the CUs without a workgroup (plan_with(); one token on 88K keys, 32 heads on 2, 128 workgroups, 24.7 / 25.7).
 #include <type_traits>
 
 #include "append_rows.h"

@@ -3,8 +3,8 @@
 // scale * log2(e) and rounded once more, P = 2^(S - m) rounded to bf16 for P V, row sums in fp32 from the unrounded P, the reference
 // m stale by at most 2^16.
 //
-// Two kinds of step are for it.  Few rows (C G <= 32, a few tokens at a time, every key visible up to the row's own position; at most 16 rows,
-// and all of them 64 wide, have a kernel of their own by now, attn_decode.hip; the figures of one token below are from before) read every key once and compute next to nothing: they are bound by memory when the cache is long and by what a launch does
+// Two kinds of step are for it.  Few rows (C G <= 32, a few tokens at a time, every key visible up to the row's own position; at most 16 rows but for
+// long ranges of one or two KV heads, and all of them 64 wide, have a kernel of their own by now, attn_decode.hip; the figures of one token below are from before) read every key once and compute next to nothing: they are bound by memory when the cache is long and by what a launch does
 // once when it is short.  A few units per KV head on not too many keys, or under a window, are bound by the chain of a wavefront: the
 // general kernel walks a piece tile by tile with its four wavefronts side by side on four units, behind a software pipeline whose start
 // and code cost more than a short step's work, and needs a split and its merge to fill the chip.  Here

@@ -91,7 +91,7 @@ struct KernelCost {
   bool two_per_cu;
 };
 KernelCost kernel_cost(int dtype, int head_dim, int upw, int waves, bool few_rows, double with_rows) {
-  if (few_rows) return KernelCost{0.46, 0.46, 0.46, 4.6, true};  // (128 wide; 64 wide: plan_direct())
+  if (few_rows) return KernelCost{0.46, 0.46, 0.46, 4.6, true};  // (128 wide: 17 to 32 rows, and fewer on long ranges of one or two KV heads; the others: plan_direct())
   if (dtype == KVFOLD_BF16) {
     // half the head dim leaves the same vector work per logit
     if (head_dim == 64) return upw == 2 ? KernelCost{0.98, 0.98, 0, 10.0, false} : KernelCost{0.74, 0.78, 1.3, 5.7, true};
@@ -339,7 +339,8 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // -- and bf16's two-unit kernel with 64-wide heads (4045 tokens on 189 keys, 4 heads on 1: 31 us in 320 workgroups, 45 in 448 of
       // which 256 have work; 128 wide it lets others in sooner, 3835 tokens on 425 keys, 8 on 2, 360 of which 256 have work 57, 63 with one unit)
       if ((fp32 || (f.head_dim == 64 && upw == 2)) && (double)w > slots && busy < slots) t *= 1.0 + 1.5 * std::max(0.0, busy / slots - 0.8);
-      // few rows: the blocks of an odd number of tiles do not go round the four wavefronts.  (Over 560 shapes on as many layers as
+      // few rows: the blocks of an odd number of tiles do not go round the four wavefronts.  (The figures here and below are from when every step of one token
+      // came this way.  Over 560 shapes on as many layers as
       // keep the caches out of the chip's own, the choice is 0.8 % above the best with this and 0.9 % without the second
       // term.  A step's two launches follow each other in steps of 0.8 us, which is the scatter: one token on 4187 keys, 2 / 3 / 4 / 5 tiles
       // a piece 12.4 / 11.7 / 10.8 / 11.5 us, on 4538 12.4 / 11.0 / 11.7 / 11.6.)

@@ -27,7 +27,7 @@ struct PlanCtx {
 
 struct Plan {
   bool few_rows;     // a bf16 kernel for at most 32 packed rows per KV head
-  bool direct;       // of these, the one whose keys come straight into registers: at most 16 rows, 32 where heads are 64 wide
+  bool direct;       // of these, the one whose keys come straight into registers: at most 16 rows (not on long ranges of one or two KV heads), 32 where heads are 64 wide
   int key_waves;     // the kernel whose workgroups deal the keys of one unit to their wavefronts: 4 or 8 of them (0: another kernel)
   int waves_per_wg;  // 4, or 8 in the fp32 kernel's large form
   int units_per_wave, units_per_head, wgs_per_head, n_splits, tiles_per_split, n_wgs, pair_order, pair_units;
