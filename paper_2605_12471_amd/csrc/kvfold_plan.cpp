@@ -364,12 +364,14 @@ Plan plan_with(const PlanCtx& c, int n_tokens, int64_t len_after, int upw, int n
       // Two pieces that meet in the attention kernel: no launch, but the later one's way through memory at the end; less where 64-wide workgroups
       // share a CU or have two units a wavefront.  Over 600 shapes, 48 to 4096 tokens on 16 to 127K keys, both kernels, all split counts up to
       // eight and the kernel of one unit a workgroup where it was chosen: 1.3 % above the best on average 128 wide, 1.8 % 64 wide.  Of
-      // these and 1500 others eight are more than 3 % slower than when pieces did not meet (4 heads on 1, 64 wide, 3845 tokens on 1320 keys 37 -> 40.3 us).  (At 1 us and the traffic of the merge kernel 1.5 and 2.0 %, and short steps split
-      // that are faster whole: 286 tokens on 319 keys, 32 heads on 8, 13.05 / 15.4 us; 64 wide 1202 on 1710, 8 on 1, two pieces 27.5, three 22.4.)
-      // Not where the prefix is less than a quarter of the chunk: the later piece is empty for most rows then (2500 tokens on 95 keys, 28 heads on 4).
-      const bool meet = two_pieces_meet(c, pl, (int)cand) && 4 * (len_after - n_tokens) >= n_tokens;
+      // these and 1500 others seven are more than 3 % slower than when pieces did not meet, by up to 3.3 %.  (At 1 us and the traffic of the merge kernel 1.5 and 2.0 %,
+      // and short steps split that are faster whole: 286 tokens on 319 keys, 32 heads on 8, 13.05 / 15.4 us; 64 wide 1202 on 1710, 8 on 1, two pieces
+      // 27.5, three 22.4.)  Not where the prefix is less than half of the chunk (64-wide workgroups that share a CU or have two units a wavefront: a quarter): the later
+      // piece is empty for most rows then (2182 tokens on 631 keys, 32 heads on 2, 97 whole, 102.5 in two; 64 wide 3845 on 1320, 4 on 1, 37 / 40.3).
+      const bool late = f.head_dim == 128 || (upw == 1 && w <= (int64_t)c.n_cu);
+      const bool meet = two_pieces_meet(c, pl, (int)cand) && (late ? 2 : 4) * (len_after - n_tokens) >= n_tokens;
       if (meet)
-        t += f.head_dim == 128 || (upw == 1 && w <= (int64_t)c.n_cu) ? 5.0 : 2.0;
+        t += late ? 5.0 : 2.0;
       else if (cand > 1)
         t += (double)cand * rows * (f.head_dim + 2) * 8.0 / (fp32 ? 5.7e6 : 6.7e6) + (few_rows ? 3.4 : fp32 ? 3.9 : 4.7);
       t = std::max(t, 4.0 + 2.65 * (launches + (cand > 1 && !meet ? 1 : 0))) + 0.1 * t;  // (where the launches decide, the shorter kernel)

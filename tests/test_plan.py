@@ -47,6 +47,8 @@ def test_neither_form_evenly_dealt(d, n, prev):
     (8, 1, 64, 1202, 1710, 3),    # 22.4 / 27.5
     (16, 2, 64, 821, 5170, 4),    # 38.2 / 39.6
     (28, 4, 64, 565, 6793, 4),    # 45 / 49
+    (32, 2, 128, 2182, 631, 1),   # 97 / 102.5
+    (4, 1, 64, 3845, 1320, 4),    # 37 / 40.3
 ])
 def test_pieces_that_meet_are_not_free(hq, hkv, d, n, prev, splits):
     """Two pieces need no merge kernel, but the later one waits for memory at its end."""
